@@ -832,6 +832,478 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
 }
 
 // ------------------------------------------------------------------------------------------------
+// The kernels with 128-row query tiles, 32 rows per wavefront.  Both contractions run on v_mfma_f32_16x16x32, in the transposed form:
+// S^T in blocks of 16 keys x 16 query rows, O^T in blocks of 16 columns of O x 16 query rows.  Lane l holds, for query
+// row l % 16 of a block, keys (columns) 4*(l/16) + r of it in register r.  Two blocks of 16 keys of S^T are, register
+// for register, one B operand of the second product once its contraction index is read as
+//     slot (l/16, 4t + r) <-> key 16t + 4*(l/16) + r,
+// and V^T in the matching A layout is two ds_read_b64_tr_b16.  Every K and V^T fragment read from LDS feeds two MFMAs,
+// one per block of 16 query rows.
+// Why this shape and not 32x32x16: with live operands the chip is at its power limit, and a 16x16x32 reads and writes
+// half as many accumulators per multiply-add.  MFMA-only loops on N(0, 1/4) operands: 1912 against 1671 TFLOP/s.
+template <int D>
+struct NarrowState {
+    u4 qf[D / 32][2];     // Q^T as B operand: lane holds Q[row 16*qt + l%16][32*ks + 8*(l/16) .. +7] in qf[ks][qt]
+    f4 o[D / 16][2];      // O^T accumulators: o[db][qt][r] is column 16*db + 4*(l/16) + r of row 16*qt + l%16
+    float M[2];           // [qt]: reference maximum of score*c (log2 domain), same in the four lanes of a query row
+    f4 L[2];              // [qt]: running sum of the query row, in every element (a product with ones)
+};
+
+// Lane-constant addresses.  A tile is filled as described at Geo, with a permutation of its own: chunk cc of row r sits
+// at chunk position cc ^ swz(r).  V operand: 32 lanes read two neighbouring chunks of 8 rows, so swz / 2 is distinct
+// over rows 0..7 and 8..15.  K operand: a ds_read_b128 is served 16 lanes at a time, 0-3, 12-15, 20-27 together and
+// 4-11, 16-19, 28-31 together (measured; the same 32 on), which are rows 0-3 and 12-15 of one chunk with rows 4-11 of
+// its neighbour and the other way round, so rows r and r + 8 may share a position's upper bits exactly if their last
+// bits agree.  (A map that is only distinct over the 16 rows of one chunk: 14 % of the cycles lost to bank conflicts.)
+template <int D>
+struct NarrowMap {
+    using G = Geo<D>;
+    __device__ static __forceinline__ int swz(int row) {
+        return D == 128 ? (row & 7) << 1 : ((row >> 1) & 3) << 1;
+    }
+    unsigned fill_src;        // source offset of load 0 inside a tile (load l: + 4096 l, the permutation repeats every 16 rows)
+    unsigned fill_dst;        // wave * 1024 (load l: + 4096 l): LDS byte offset inside the tile
+    unsigned k_rd[D / 32];    // byte offset inside a K tile, MFMA step ks, keys l%16 (+16 kb: + 16 kb row_bytes)
+    unsigned v_rd[D / 16];    // byte offset inside a V tile of column block db, keys 4*(l/16) .. (+16: + 16 row_bytes)
+    __device__ __forceinline__ NarrowMap(int wave, int lane) {
+        const int r0 = wave * G::kRowsPerWaveLoad + lane / G::kChunksPerRow;
+        fill_src = r0 * G::kRowBytes + ((lane % G::kChunksPerRow) ^ swz(r0)) * 16;
+        fill_dst = wave * 1024;
+        const int g = lane >> 4, ln = lane & 15;
+#pragma unroll
+        for (int ks = 0; ks < D / 32; ++ks) k_rd[ks] = ln * G::kRowBytes + ((4 * ks + g) ^ swz(ln)) * 16;
+        const int vrow = 4 * g + (ln >> 2);
+#pragma unroll
+        for (int db = 0; db < D / 16; ++db)
+            v_rd[db] = vrow * G::kRowBytes + ((2 * db + ((ln & 3) >> 1)) ^ swz(vrow)) * 16 + (ln & 1) * 8;
+    }
+};
+
+// The values are computed before this point.
+__device__ __forceinline__ void keep_here(float (&x)[32]) {
+#pragma unroll
+    for (int i = 0; i < 32; i += 16)
+        asm volatile("" : "+v"(x[i]), "+v"(x[i + 1]), "+v"(x[i + 2]), "+v"(x[i + 3]), "+v"(x[i + 4]), "+v"(x[i + 5]),
+                     "+v"(x[i + 6]), "+v"(x[i + 7]), "+v"(x[i + 8]), "+v"(x[i + 9]), "+v"(x[i + 10]), "+v"(x[i + 11]),
+                     "+v"(x[i + 12]), "+v"(x[i + 13]), "+v"(x[i + 14]), "+v"(x[i + 15]));
+}
+
+template <bool BF16>
+__device__ __forceinline__ f4 mfma_16x16(u4 a, u4 b, f4 c) {
+    if constexpr (BF16)
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
+}
+
+// Maximum and sum over the four lanes l, l+16, l+32, l+48 that share a query row.  v_permlane16_swap swaps the odd
+// 16-lane rows of its first operand with the even ones of its second (see lane_pair).
+__device__ __forceinline__ void lane_rows(float x, float& even, float& odd) {
+    unsigned a = __builtin_bit_cast(unsigned, x), b = a;
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+    even = __builtin_bit_cast(float, a);
+    odd = __builtin_bit_cast(float, b);
+}
+__device__ __forceinline__ float quad_max(float x) {
+    float e, o;
+    lane_rows(x, e, o);
+    return pair_max(fmaxf(e, o));
+}
+
+// Resource descriptor of a K/V tile: `bytes` of it exist.  Rows past the end of the sequence, and whole tiles past the
+// end of a scan (bytes = 0), read as zeros and cost no memory traffic.
+__device__ __forceinline__ u4 tile_descriptor(const char* tile, unsigned bytes) {
+    u4 r;
+    r[0] = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)tile);
+    r[1] = __builtin_amdgcn_readfirstlane((unsigned)((unsigned long long)tile >> 32) & 0xffffu);
+    r[2] = __builtin_amdgcn_readfirstlane(bytes);
+    r[3] = 0x00020000u;
+    return r;
+}
+// Load l of this wavefront's share of a tile, straight into LDS (see load_to_lds_16B for the inline assembly; rows
+// 4096 bytes apart in the tile are 4096 bytes apart in LDS, and the chunk permutation repeats every 16 rows, so one
+// lane offset serves all loads).
+__device__ __forceinline__ void tile_load_to_lds(u4 descriptor, unsigned voff, unsigned soff, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds_addr), "v"(voff), "s"(descriptor), "s"(soff) : "memory", "m0");
+}
+__device__ __forceinline__ u4 tile_load(u4 d, unsigned voff, unsigned soff) {
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((unsigned long long)d[0] | (unsigned long long)d[1] << 32), 0, (int)d[2], (int)d[3]);
+    return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+}
+// All but the last VM vector-memory loads of this wavefront have landed, its LDS accesses are done, and so it is for
+// every wavefront of the workgroup.
+template <int VM>
+__device__ __forceinline__ void landed_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(VM) : "memory");
+}
+
+// The scan of one query tile over its `nkv` K/V tiles j0, j0 + step, ..., software pipelined across tiles, for the
+// kernels with 32 query rows per wavefront.  While the MFMAs of S(i+1)^T = K(i+1) Q^T run, the exponentials of tile i
+// are issued between them; while the MFMAs of O^T += V(i)^T P(i)^T run, the row maximum of S(i+1), the lazy-rescale
+// check and the (score*c - M) of tile i+1 are issued between them.  Two register sets alternate roles without copies:
+// `A` accumulates the scores of the tile one ahead, `x` holds the shifted scores of the current tile until they have
+// become probabilities.
+//
+// The one barrier of an iteration stands between the two products.  By then nobody reads K(i+1) or V(i-1) any more,
+// so K(i+3) and V(i+1) are fetched into their places right behind it and have a whole iteration to land, although
+// there are only two buffers of each.
+// PHASES: the wavefronts that are in their second product, with its MFMAs and few vector instructions, go before
+// those in their first, with all the exponentials, so that the two share the SIMD's units (see default_phase_priority).
+// (For bfloat16 inputs V travels global -> registers -> binary16 -> LDS: V(i+2) is loaded in the middle of the second
+// product of iteration i and converted in the first half of the second product of iteration i+1.)
+//
+// Tiles that need a mask (they reach past the first row of this wavefront under the causal mask, or past the end of
+// the sequence) take the same way: their scores are set to -inf once they are complete, one comparison and one select
+// each, and the reference maximum starts from a finite value, so that nothing later meets -inf - (-inf).
+template <int D, bool BF16, bool CAUSAL, bool PHASES>
+__device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D>& lm, const char* Kh, const char* Vh, int N,
+                                           float c, int j0, int step, int nkv, int qw0, int qrow, int lane,
+                                           LDS_PTR(char) lds) {
+    using G = Geo<D>;
+    constexpr int KS = D / 32, DB = D / 16;
+    constexpr int NA = 4 * KS;            // K fragments of a tile (two MFMAs each)
+    constexpr int NB = 2 * DB;            // V^T fragments of a tile (two MFMAs each)
+    constexpr int NL = G::kLoadsPerWave;
+    constexpr int TA = 2 * NA, TB = 2 * NB;   // MFMAs of the first and of the second product
+    constexpr int LA = D == 64 ? 2 : 3;   // fragments read ahead of their use
+    const unsigned lds0 = (unsigned)(size_t)lds;
+    const int g = lane >> 4;
+    u4 ones = {0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u};      // binary16 1.0, A operand of the row sums
+    asm volatile("" : "+v"(ones));
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    f4 A[4][2];         // S^T of the tile one ahead: block (kb, qt) = keys 16kb.. x query rows 16qt..
+    float x[32];        // score*c - M of the current tile, index 16*qt + 4*kb + r
+    u4 pf[2][2];        // its probabilities as B operands: pf[kh][qt] = keys 32kh..32kh+31
+    u4 vreg[NL];        // bfloat16 V chunks in flight (BF16 only)
+    float lim[2] = {-INFINITY, -INFINITY};    // [qt]: the raw score above which the reference maximum has to be raised
+
+    // LDS read addresses: K of the tile one ahead, V of the current tile
+    unsigned rk[KS], rv[DB];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) rk[ks] = lds0 + lm.k_rd[ks];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) rv[db] = lds0 + 2 * G::kTile + lm.v_rd[db];
+
+    // The fetches walk the scan position by position.  dk, dv: descriptors of the next K and V tile; rows: rows of the
+    // scan from the next K tile on (the sequence may end inside the last tile, which comes first in a backward scan and
+    // last in a forward one).  V follows K two positions behind (one, if it goes through registers), so its sizes are
+    // K's of before.
+    const int ragged = kTileKV * ((N + kTileKV - 1) / kTileKV) - N;      // rows the last tile of the sequence lacks
+    const int lack = nkv * kTileKV > N ? ragged : 0;                     // ... if the scan includes that tile
+    const long long stride = (long long)step * G::kTile;
+    // (readfirstlane: everything here is uniform, and has to stay in scalar registers)
+    auto size_of = [](int rows) {
+        return (unsigned)__builtin_amdgcn_readfirstlane((rows < 0 ? 0 : rows < kTileKV ? rows : kTileKV) * G::kRowBytes);
+    };
+    auto advance = [&](u4& d) {
+        const unsigned long long at = ((unsigned long long)d[1] << 32 | d[0]) + (unsigned long long)stride;
+        d[0] = __builtin_amdgcn_readfirstlane((unsigned)at);
+        d[1] = __builtin_amdgcn_readfirstlane((unsigned)(at >> 32));
+    };
+    const int first_rows = step < 0 || nkv == 1 ? kTileKV - lack : kTileKV;
+    u4 dk = tile_descriptor(Kh + (long long)j0 * G::kTile, size_of(first_rows));
+    u4 dv = tile_descriptor(Vh + (long long)j0 * G::kTile, size_of(first_rows));
+    int rows = nkv * kTileKV - lack - first_rows;
+    unsigned bytes1 = 0, bytes2 = 0;         // sizes of the K tiles one and two before the one in dk
+    auto next_k = [&]() {
+        bytes2 = bytes1;
+        bytes1 = dk[2];
+        advance(dk);
+        dk[2] = size_of(rows);
+        rows -= kTileKV;
+    };
+    auto next_v = [&]() {
+        advance(dv);
+        dv[2] = BF16 ? bytes1 : bytes2;
+    };
+    auto fetch_burst = [&](u4 d, unsigned dst) {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) tile_load_to_lds(d, lm.fill_src, l * 4096, dst + lm.fill_dst + l * 4096);
+    };
+    auto v_to_regs = [&]() {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) vreg[l] = tile_load(dv, lm.fill_src, l * 4096);
+    };
+    // w-th 32-bit word of the fetched chunks from bfloat16 to binary16; every fourth completes 16 bytes for LDS
+    auto convert_word = [&](int w, unsigned dst) {
+        f2 y;
+        const unsigned word = vreg[w / 4][w % 4];
+        y[0] = __builtin_bit_cast(float, word << 16);
+        y[1] = __builtin_bit_cast(float, word & 0xffff0000u);
+        vreg[w / 4][w % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(y, h2));
+        if (w % 4 == 3) *(LDS_PTR(u4))(size_t)(dst + (w / 4) * 4096 + lane * 16) = vreg[w / 4];
+    };
+    constexpr int CW = NL * 4;     // 32-bit words of bfloat16 V this wavefront converts per tile
+    // fragment m of K: keys 16*(m / KS).., columns 32*(m % KS)..; fragment m of V^T: keys 32*(m / DB).., columns 16*(m % DB)..
+    auto k_read = [&](int m) -> u4 { return *(LDS_PTR(u4))(size_t)(rk[m % KS] + (m / KS) * 16 * G::kRowBytes); };
+    auto v_read = [&](int m) -> u4 {
+        const unsigned at = rv[m % DB] + (m / DB) * 32 * G::kRowBytes;
+        const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s4))(size_t)at);
+        const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s4))(size_t)(at + 16 * G::kRowBytes));
+        return __builtin_bit_cast(u4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto s_mfma = [&](int m, int qt, u4 a) {
+        A[m / KS][qt] = mfma_16x16<BF16>(a, st.qf[m % KS][qt], m % KS == 0 ? zero : A[m / KS][qt]);
+    };
+    auto o_mfma = [&](int m, int qt, u4 a) { st.o[m % DB][qt] = mfma_16x16<false>(a, pf[m / DB][qt], st.o[m % DB][qt]); };
+    // The scores in A: -inf where the key is not visible.  Register r of block kb is key
+    // 16kb + 4g + r of the tile: visible up to the offset `ahead`.
+    const int all_see = CAUSAL ? (qw0 < N - 1 ? qw0 : N - 1) : N - 1;      // last key visible to every row of the wavefront
+    int kv0 = j0 * kTileKV;          // first key of the tile in A
+    const int kv_step = step * kTileKV;
+    auto mask = [&]() {
+        if (kv0 + kTileKV - 1 > all_see) {
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt) {
+                const int last_key = CAUSAL ? (qrow + 16 * qt < N - 1 ? qrow + 16 * qt : N - 1) : N - 1;
+                int ahead = last_key - kv0 - 4 * g;
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        asm volatile("" : "+v"(ahead));     // (separate comparisons: no lane masks kept and combined)
+                        A[kb][qt][r] = 16 * kb + r > ahead ? -INFINITY : A[kb][qt][r];
+                    }
+            }
+        }
+    };
+    // Raises the reference maxima for the tile in x (shifted by the old ones), whose largest raw scores in this lane are
+    // mx (at least lim).  The limit keeps a distance of |M| 2^-21 from M + slack, which covers the rounding of the
+    // division and of the comparison on raw scores.  A row that has met no key yet (L = 0, lim = -inf) takes any maximum, and starts from O = 0 whatever the values behind its
+    // masked keys were (0 times an infinite one is no number).
+    float mx[2];
+    auto max_op = [&](int qt, int op) {     // op-th of the 8 updates of mx[qt]: two scores each
+        const f4& a = A[op / 2][qt];
+        mx[qt] = fmaxf(fmaxf(mx[qt], a[2 * (op & 1)]), a[2 * (op & 1) + 1]);
+    };
+    auto raise_reference = [&]() {
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt) {
+            const float t = quad_max(mx[qt]);           // the lanes of a query row move together
+            const bool up = t > lim[qt];
+            const float Mnew = up ? t * c : st.M[qt];
+            const float d = Mnew - st.M[qt];
+            const bool fresh = st.L[qt][0] == 0.f;
+            const float alpha = up && !fresh ? fast_exp2(-d) : 1.0f;
+            st.M[qt] = Mnew;
+            st.L[qt] *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) st.o[db][qt][r] = fresh ? 0.f : st.o[db][qt][r] * alpha;
+            if (up) lim[qt] = (Mnew + kRescaleSlack - fabsf(Mnew) * 0x1p-21f) / c;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) x[16 * qt + k] -= d;
+        }
+    };
+    auto shift_score = [&](int k) { x[k] = __builtin_fmaf(A[(k >> 2) & 3][k >> 4][k & 3], c, -st.M[k >> 4]); };
+    // Pair u = 0..15 of probabilities is word u % 4 of B operand (kh, qt) = (u / 8, u / 4 % 2): keys
+    // 16 (2 kh + u % 4 / 2) + 4g + 2 (u % 2), + 1.  Its steps: the two exponentials, the convert, the two additions to
+    // the running sum (of the rounded probabilities, the values the second product uses).
+    float e[16][2];
+    auto exp_op = [&](int u, int h) { e[u][h] = fast_exp2(x[16 * (u / 4 % 2) + 4 * (2 * (u / 8) + u % 4 / 2) + 2 * (u % 2) + h]); };
+    auto convert_op = [&](int u) {
+        pf[u / 8][u / 4 % 2][u % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u][0], e[u][1]}, h2));
+    };
+    // (of the rounded probabilities, the values the second product uses)
+    auto sum_mfma = [&](int kh, int qt) { st.L[qt] = mfma_16x16<false>(ones, pf[kh][qt], st.L[qt]); };
+    // What runs under the first product, in order: step k of pair u, the convert one pair behind its exponentials.
+    constexpr int OA = 48;
+    auto op_a = [&](int n) {
+        const int u = n / 3, k = n % 3;
+        if (k < 2) exp_op(u, k);
+        else if (u > 0) convert_op(u - 1);
+    };
+
+    // ---------------------------------------------------------------- prologue: S(0), K(1..2) and V(0) on their way
+    fetch_burst(dk, lds0);
+    next_k();
+    fetch_burst(dk, lds0 + G::kTile);
+    if constexpr (BF16) v_to_regs();
+    else fetch_burst(dv, lds0 + 2 * G::kTile);
+    landed_barrier<NL>();
+    {
+        u4 a[NA];
+#pragma unroll
+        for (int m = 0; m < LA; ++m) a[m] = k_read(m);
+#pragma unroll
+        for (int m = 0; m < NA; ++m) {
+            if (m + LA < NA) a[m + LA] = k_read(m + LA);
+#pragma unroll
+            for (int qt = 0; qt < 2; ++qt) s_mfma(m, qt, a[m]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if constexpr (BF16) {
+#pragma unroll
+        for (int w = 0; w < CW; ++w) convert_word(w, lds0 + 2 * G::kTile + lm.fill_dst);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // K(0) has been read
+    next_k();
+    fetch_burst(dk, lds0);
+    if constexpr (BF16) {
+        next_v();
+        v_to_regs();
+    }
+    mask();
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+        mx[qt] = lim[qt];
+#pragma unroll
+        for (int op = 0; op < 8; ++op) max_op(qt, op);
+    }
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+        const float t = quad_max(mx[qt]);
+        st.M[qt] = t == -INFINITY ? 0.f : t * c;
+        if (t != -INFINITY) lim[qt] = (st.M[qt] + kRescaleSlack - fabsf(st.M[qt]) * 0x1p-21f) / c;
+    }
+#pragma unroll
+    for (int k = 0; k < 32; ++k) shift_score(k);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) rk[ks] += G::kTile;   // K of tile 1 is in buffer 1
+    u4 ak[LA];          // the first K fragments of the tile one ahead, read before the iteration starts
+#pragma unroll
+    for (int m = 0; m < LA; ++m) ak[m] = k_read(m);
+
+    unsigned kdst = lds0 + G::kTile + lm.fill_dst, vdst = lds0 + 3 * G::kTile + lm.fill_dst;      // buffers (i+1)&1
+    int flip = -G::kTile;                                                                         // ... to buffers i&1
+    // ---------------------------------------------------------------- steady state: iteration i
+    // reads K(i+1) from K buffer (i+1)&1 and V(i) from V buffer i&1; fetches K(i+3) and V(i+1) into the buffers (i+1)&1.
+    // Returns whether the reference maximum has to be raised before tile i+1 can be used.
+    auto iteration = [&](int i) -> bool {
+        if constexpr (PHASES) __builtin_amdgcn_s_setprio(1);
+        next_k();     // K(i+3)
+        next_v();     // V(i+1), with V through registers V(i+2)
+        // ---- phase A
+        {
+            u4 a[NA];
+#pragma unroll
+            for (int m = 0; m < LA; ++m) a[m] = ak[m];
+#pragma unroll
+            for (int m = 0; m < NA; ++m) {
+                if (m + LA < NA) a[m + LA] = k_read(m + LA);
+#pragma unroll
+                for (int qt = 0; qt < 2; ++qt) {
+                    const int t = 2 * m + qt;
+                    s_mfma(m, qt, a[m]);
+#pragma unroll
+                    for (int n = t * OA / TA; n < (t + 1) * OA / TA; ++n) op_a(n);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            convert_op(15);
+        }
+        // ---- everything fetched in the iteration before has landed; nobody reads K(i+1) and V(i-1) any more
+        //      (the probabilities pass through the statement, or the compiler moves the exponentials behind it)
+        asm volatile("" : "+v"(pf[0][0]), "+v"(pf[0][1]), "+v"(pf[1][0]), "+v"(pf[1][1]));
+        landed_barrier<0>();
+        if constexpr (PHASES) __builtin_amdgcn_s_setprio(2);
+        kv0 += kv_step;
+        mask();
+        // ---- phase B.  Under its MFMAs, in order: the row maxima of A, the row sums of tile i, the shifted scores of tile
+        //      i+1 -- if the reference maximum has to be raised (need), they follow it after the loop exit.  The direct
+        //      loads of an iteration are spread over it too, V first because it is needed first.
+        //      With V through registers the conversion comes along with the maxima, then the next V loads.  (The V registers
+        //      have landed: the compiler is told so here, or it would wait for them where it uses them, and with them for the
+        //      direct loads issued in between, which it does not know of.)
+        if constexpr (BF16) {
+#pragma unroll
+            for (int l = 0; l < NL; ++l) asm volatile("" : "+v"(vreg[l]));
+        }
+        u4 av[NB];
+#pragma unroll
+        for (int m = 0; m < LA; ++m) av[m] = v_read(m);
+        __builtin_amdgcn_sched_barrier(0);
+        mx[0] = lim[0];
+        mx[1] = lim[1];
+        bool need = false;
+        constexpr int OC = BF16 ? 3 * CW : 0;            // conversions count as three
+        constexpr int OM = 16 + OC, OB = OM + 32;        // maxima (and conversions), all
+        constexpr int T0 = (OM * TB + OB - 1) / OB;      // first MFMA after the conversions
+        constexpr int NV = BF16 ? 0 : NL;
+        constexpr int TL = NV + NL;               // direct loads
+        auto op_b = [&](int n) {
+            if (n < OM) {
+                const int j = n * 16 / OM, done = (n + 1) * 16 / OM;      // maxima begun before and with this step
+                if (j != done) max_op(j & 1, j >> 1);
+                if constexpr (BF16) {
+                    const int w = n * CW / OM;
+                    if (w != (n + 1) * CW / OM) convert_word(w, vdst);
+                }
+            } else {
+                shift_score(n - OM);
+            }
+        };
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            const int m = t / 2;
+            if ((t & 1) == 0 && m + LA < NB) av[m + LA] = v_read(m + LA);
+            if (BF16 && t == T0) v_to_regs();
+            o_mfma(m, t & 1, av[m]);
+            if (t % (TB / 4) == TB / 4 - 1) sum_mfma(t / (TB / 2), t / (TB / 4) & 1);
+#pragma unroll
+            for (int li = t * TL / TB; li < (t + 1) * TL / TB; ++li) {
+                if (li < NV) tile_load_to_lds(dv, lm.fill_src, li * 4096, vdst + li * 4096);
+                else tile_load_to_lds(dk, lm.fill_src, (li - NV) * 4096, kdst + (li - NV) * 4096);
+            }
+#pragma unroll
+            for (int n = t * OB / TB; n < (t + 1) * OB / TB; ++n) {
+                op_b(n);
+                // (mx starts from lim: it exceeds lim exactly when a score does)
+                if (n == OM + 8) need = __builtin_amdgcn_ballot_w64(!(mx[0] <= lim[0]) || !(mx[1] <= lim[1])) != 0;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        keep_here(x);       // (or the compiler moves what no instruction up to here reads behind the loop's branch)
+        // ---- switch buffers: K(i+2) is in buffer i&1, V(i+1) in buffer (i+1)&1
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) rk[ks] += flip;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) rv[db] -= flip;
+        kdst += flip;
+        vdst += flip;
+        flip = -flip;
+#pragma unroll
+        for (int m = 0; m < LA; ++m) ak[m] = k_read(m);
+        return need;
+    };
+    int i = 0;
+    while (i + 1 < nkv) {
+        bool need = false;
+#pragma unroll 1
+        for (; i + 1 < nkv; ++i) {
+            need = iteration(i);
+            if (need) { ++i; break; }
+        }
+        if (need) raise_reference();
+    }
+
+    // ---------------------------------------------------------------- last tile: probabilities, then O^T += V^T P^T
+    if constexpr (PHASES) __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+    for (int n = 0; n < OA; ++n) op_a(n);
+    convert_op(15);
+    landed_barrier<0>();      // also the fetches past the end of the scan, which write zeros into buffers nobody reads
+    if (!CAUSAL || kv0 <= qw0 + 31) {      // (not if every row of the wavefront lies before the tile's first key)
+        u4 av[NB];
+#pragma unroll
+        for (int m = 0; m < LA; ++m) av[m] = v_read(m);
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            const int m = t / 2;
+            if ((t & 1) == 0 && m + LA < NB) av[m + LA] = v_read(m + LA);
+            o_mfma(m, t & 1, av[m]);
+            if (t % (TB / 4) == TB / 4 - 1) sum_mfma(t / (TB / 2), t / (TB / 4) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __syncthreads();   // all reads of the last tile are done before anything refills the buffers
+}
+
+// ------------------------------------------------------------------------------------------------
 // Wide variant (head dimension 128): a wavefront owns 64 query rows as two 32-row
 // halves, a workgroup 256 rows, one workgroup per CU.  Every K and V^T fragment read from LDS feeds
 // two MFMAs, one per half, which halves the LDS operand traffic and the L2 -> LDS traffic per flop.
@@ -1489,6 +1961,144 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
     }
 }
 
+// One query tile (Alg. 1 body) of the kernels with 128-row tiles: rows [t*128, (t+1)*128) of head `hh`,
+// K/V tiles j0, j0+step, ... (nkv of them).
+template <int D, bool BF16, bool CAUSAL, bool PHASES>
+__device__ __forceinline__ void process_q_tile_narrow(const Params& p, const NarrowMap<D>& lm, int hh, int t, int j0, int step,
+                                                      int nkv, int wave, int lane, LDS_PTR(char) lds) {
+    using G = Geo<D>;
+    constexpr int KS = D / 32;    // MFMA steps along d for S^T
+    constexpr int DB = D / 16;    // column blocks of O^T
+    constexpr int TQ = kTileQ;
+    const int N = p.N;
+    const size_t head_off = (size_t)hh * N * G::kRowBytes;
+    const char* Qh = static_cast<const char*>(p.Q) + head_off;
+    const char* Kh = static_cast<const char*>(p.K) + head_off;
+    const char* Vh = static_cast<const char*>(p.V) + head_off;
+
+    const int qw0 = t * TQ + wave * 32;       // first query row of this wavefront
+
+    NarrowState<D> st;
+    // With variant.qo_streaming the rows of Q come in the way K tiles do -- 64 rows at a time straight into LDS, whole
+    // lines per instruction, the four wavefronts together -- but marked non-temporal, and are read from there in the
+    // K operand's pattern, which is also Q's.  The buffers are free: the last range of the previous tile ended with a barrier.
+    unsigned q_at = 0;     // byte offset in LDS of this lane's first fragment
+    if (p.stream_q) {
+        int l2 = lane;
+        asm volatile("" : "+v"(l2));        // (a lane map of its own that does not live on: see the note on registers below)
+        const NarrowMap<D> lq(wave, l2);
+        const unsigned lds0 = (unsigned)(size_t)lds;
+        const int row = lq.fill_src / G::kRowBytes, chunk = lq.fill_src % G::kRowBytes;
+#pragma unroll
+        for (int m = 0; m < TQ / kTileKV; ++m) {
+            const int q0 = t * TQ + m * kTileKV;
+            const int first = q0 < N ? q0 : N - 1;          // rows beyond N repeat row N-1, as below
+            const char* base = Qh + (size_t)first * G::kRowBytes;
+#pragma unroll
+            for (int i = 0; i < G::kLoadsPerWave; ++i) {
+                const int r0 = q0 + row + i * (4096 / G::kRowBytes);
+                const int r = r0 < N ? r0 : N - 1;
+                load_to_lds_16B_nt(base, (unsigned)((r - first) * G::kRowBytes + chunk), lds0 + m * G::kTile + lq.fill_dst + i * 4096);
+            }
+        }
+        q_at = (wave / 2) * G::kTile + (wave & 1) * 32 * G::kRowBytes + lq.k_rd[0];
+        wait_tile_landed();
+        __syncthreads();
+    }
+    int lane_q = lane;
+    asm volatile("" : "+v"(lane_q));      // (addresses used once: built from a copy of the lane index of their own)
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {   // rows beyond N repeat row N-1 (computed, never stored)
+        const int q0 = qw0 + (lane_q & 15) + 16 * qt;
+        const int qr = q0 < N ? q0 : N - 1;
+        const char* qp = Qh + (size_t)qr * G::kRowBytes + (lane_q >> 4) * 16;
+        const unsigned flip = p.negate_q ? 0x80008000u : 0u;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            // (chunk 4 ks + g of a row sits at chunk position (4 ks + g) ^ swz(row): k_rd[ks] = k_rd[0] ^ (64 ks))
+            u4 v = p.stream_q ? *(LDS_PTR(u4))(lds + ((q_at + qt * 16 * G::kRowBytes) ^ (unsigned)(ks * 64)))
+                              : *reinterpret_cast<const u4*>(qp + ks * 64);
+            v[0] ^= flip; v[1] ^= flip; v[2] ^= flip; v[3] ^= flip;
+            st.qf[ks][qt] = v;
+        }
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) st.o[db][qt][r] = 0.f;
+        st.M[qt] = 0.f;
+        st.L[qt] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+    if (p.stream_q) __syncthreads();      // the fragments are in registers before the first K/V fetch overwrites the rows
+
+    scan_tiles<D, BF16, CAUSAL, PHASES>(st, lm, Kh, Vh, N, p.c, j0, step, nkv, qw0, qw0 + (lane & 15), lane, lds);
+
+    // ---- epilogue: O_i = acc / l  (the division Alg. 1 leaves implicit; Eq. 1 fixes it)
+    const float inv[2] = {1.0f / st.L[0][0], 1.0f / st.L[1][0]};
+    if (p.stream_o) {
+        // (the scan ended with a barrier and nothing in flight: the K/V buffers serve as staging area)
+        LDS_PTR(char) stage = lds + wave * 4096;
+        int l2 = lane;
+        asm volatile("" : "+v"(l2));     // lane-derived addresses are built here, not carried across the scan
+        const int g = l2 >> 4, ln = l2 & 15;
+        const int sw = ln & 7;
+        const int rows_left = N - qw0;      // <= 0: all rows lie beyond the sequence
+        if (p.o_dtype == SAWATTN_F32) {
+            constexpr size_t RB = (size_t)D * 4;
+            char* dst = static_cast<char*>(p.O) + ((size_t)hh * N + qw0) * RB;
+#pragma unroll
+            for (int pass = 0; pass < DB / 2; ++pass) {          // 32 columns = 128 bytes per row
+#pragma unroll
+                for (int dbl = 0; dbl < 2; ++dbl)
+#pragma unroll
+                    for (int qt = 0; qt < 2; ++qt) {
+                        const f4 v = st.o[2 * pass + dbl][qt] * inv[qt];
+                        *(LDS_PTR(f4))(stage + (16 * qt + ln) * 128 + (((4 * dbl + g) ^ sw) << 4)) = v;
+                    }
+                drain_stage(stage, dst + pass * 128, RB, rows_left, l2);
+            }
+        } else {
+            constexpr size_t RB = (size_t)D * 2;
+            char* dst = static_cast<char*>(p.O) + ((size_t)hh * N + qw0) * RB;
+#pragma unroll
+            for (int pass = 0; pass < DB / 4; ++pass) {   // 64 columns = 128 bytes per row
+#pragma unroll
+                for (int dbl = 0; dbl < 4; ++dbl)
+#pragma unroll
+                    for (int qt = 0; qt < 2; ++qt) {
+                        const f4 v = st.o[4 * pass + dbl][qt] * inv[qt];
+                        LDS_PTR(char) at = stage + (16 * qt + ln) * 128 + (((2 * dbl + (g >> 1)) ^ sw) << 4) + 8 * (g & 1);
+                        if (p.o_dtype == SAWATTN_F16) *(LDS_PTR(h4))at = __builtin_convertvector(v, h4);
+                        else *(LDS_PTR(b4))at = __builtin_convertvector(v, b4);
+                    }
+                drain_stage(stage, dst + pass * 128, RB, rows_left, l2);
+            }
+        }
+        __syncthreads();          // the staging area is read before the next tile's fetches overwrite it
+        return;
+    }
+    int lane_out = lane;
+    asm volatile("" : "+v"(lane_out));
+    const int g_out = lane_out >> 4, qrow_out = qw0 + (lane_out & 15);
+#pragma unroll
+    for (int qt = 0; qt < 2; ++qt) {
+        if (qrow_out + 16 * qt < N) {
+            const size_t orow = ((size_t)hh * N + qrow_out + 16 * qt) * D;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const f4 v = st.o[db][qt] * inv[qt];
+                const size_t col = 16 * db + 4 * g_out;
+                if (p.o_dtype == SAWATTN_F32) {
+                    *reinterpret_cast<f4*>(static_cast<float*>(p.O) + orow + col) = v;
+                } else if (p.o_dtype == SAWATTN_F16) {
+                    *reinterpret_cast<h4*>(static_cast<_Float16*>(p.O) + orow + col) = __builtin_convertvector(v, h4);
+                } else {
+                    *reinterpret_cast<b4*>(static_cast<__bf16*>(p.O) + orow + col) = __builtin_convertvector(v, b4);
+                }
+            }
+        }
+    }
+}
+
 // bfloat16 -> binary16 copies of K and V for the workspace path (16 bytes per lane and step).
 __global__ __launch_bounds__(256) void bf16_to_f16_kernel(const u4* __restrict__ K, const u4* __restrict__ V,
                                                           u4* __restrict__ K16, u4* __restrict__ V16, size_t chunks) {
@@ -1535,9 +2145,9 @@ __device__ __forceinline__ void domain_sync(int set, int domain, int slots) {
     __syncthreads();
 }
 
-template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false>
-__global__ __launch_bounds__(kThreads, HALVES ? (D == 64 ? 2 : 1) : NH == 2 ? 1 : (D == 64 ? 3 : 2)) void attn_fwd_kernel(Params p) {
-    extern __shared__ __align__(16) char smem[];
+// The outer loop of a workgroup: its query tiles one after the other (Alg. 2, Alg. 3), `tile` computes one.
+template <bool CAUSAL, typename TILE>
+__device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
     const Schedule& s = p.sched;
     const int lane0 = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1556,8 +2166,7 @@ __global__ __launch_bounds__(kThreads, HALVES ? (D == 64 ? 2 : 1) : NH == 2 ? 1 
             // compiler cannot see through, so that they are not kept in registers across the loops.
             int lane = lane0;
             asm volatile("" : "+v"(lane));
-            const LaneMap<D> lm(wave, lane);
-            process_q_tile<D, BF16, CAUSAL, NH, HALVES>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
+            tile(w, j0, step, nkv, wave, lane);
             ++local;
         }
         // Every workgroup of the domain comes here once per head, also those that sat rounds out.
@@ -1566,6 +2175,25 @@ __global__ __launch_bounds__(kThreads, HALVES ? (D == 64 ? 2 : 1) : NH == 2 ? 1 
         if (w.sync_after) domain_sync(p.ticket_set, (int)blockIdx.x % kDomains, s.slots);
     }
     if (p.trace_count && threadIdx.x == 0) p.trace_count[blockIdx.x] = local;
+}
+
+template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false>
+__global__ __launch_bounds__(kThreads, HALVES ? (D == 64 ? 2 : 1) : NH == 2 ? 1 : (D == 64 ? 3 : 2)) void attn_fwd_kernel(Params p) {
+    extern __shared__ __align__(16) char smem[];
+    for_each_q_tile<CAUSAL>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
+        const LaneMap<D> lm(wave, lane);
+        process_q_tile<D, BF16, CAUSAL, NH, HALVES>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
+    });
+}
+
+// 128-row tiles where workgroups share the compute units (see default_shared_kernel, default_phase_priority).
+template <int D, bool BF16, bool CAUSAL, bool PHASES>
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_shared_kernel(Params p) {
+    extern __shared__ __align__(16) char smem[];
+    for_each_q_tile<CAUSAL>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
+        const NarrowMap<D> lm(wave, lane);
+        process_q_tile_narrow<D, BF16, CAUSAL, PHASES>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
+    });
 }
 
 
@@ -1608,10 +2236,10 @@ void fill_info(const Schedule& s, int d, sawattn_launch_info* out) {
 
 std::atomic<unsigned> g_ticket_turn{0};
 
-template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false>
-int launch(Params& p, int grid, hipStream_t stream) {
-    auto kern = attn_fwd_kernel<D, BF16, CAUSAL, NH, HALVES>;
-    constexpr int lds_bytes = NH == 2 ? kWideLdsBytes : (HALVES ? 2 : 1) * Geo<D>::kLdsBytes;
+// (KERNEL a template argument: the state below is kept per kernel)
+template <void (*KERNEL)(Params)>
+int launch_kernel(Params& p, int grid, int lds_bytes, hipStream_t stream) {
+    auto kern = KERNEL;
     // The LDS size a kernel may ask for is a per-device attribute of the function: set once per device (bit = device).
     static std::atomic<unsigned long long> configured{0};
     int dev = 0;
@@ -1640,6 +2268,23 @@ int launch(Params& p, int grid, hipStream_t stream) {
         return fail(SAWATTN_ERR_RUNTIME, msg);
     }
     return SAWATTN_OK;
+}
+
+template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false>
+int launch(Params& p, int grid, hipStream_t stream) {
+    return launch_kernel<attn_fwd_kernel<D, BF16, CAUSAL, NH, HALVES>>(
+        p, grid, NH == 2 ? kWideLdsBytes : (HALVES ? 2 : 1) * Geo<D>::kLdsBytes, stream);
+}
+
+// 128-row tiles: the kernel for shared compute units or the one for workgroups that have theirs to themselves.
+template <int D, bool BF16, bool CAUSAL>
+int launch_128(Params& p, int grid, hipStream_t stream) {
+    if (default_shared_kernel(p.sched, D, CAUSAL)) {
+        if (!CAUSAL || default_phase_priority(p.sched, D, CAUSAL))
+            return launch_kernel<attn_fwd_shared_kernel<D, BF16, CAUSAL, true>>(p, grid, Geo<D>::kLdsBytes, stream);
+        return launch_kernel<attn_fwd_shared_kernel<D, BF16, CAUSAL, !CAUSAL>>(p, grid, Geo<D>::kLdsBytes, stream);
+    }
+    return launch<D, BF16, CAUSAL, 1>(p, grid, stream);
 }
 
 // Validates a variant description (NULL = the default schedule) and builds its schedule.
@@ -1805,11 +2450,11 @@ int run(const void* Q, const void* K, const void* V, void* O, int B, int H, int 
         return ca ? launch<64, false, true, 1, true>(p, grid, stream) : launch<64, false, false, 1, true>(p, grid, stream);
     }
     if (d == 128) {
-        if (bf) return ca ? launch<128, true, true, 1>(p, grid, stream) : launch<128, true, false, 1>(p, grid, stream);
-        return ca ? launch<128, false, true, 1>(p, grid, stream) : launch<128, false, false, 1>(p, grid, stream);
+        if (bf) return ca ? launch_128<128, true, true>(p, grid, stream) : launch_128<128, true, false>(p, grid, stream);
+        return ca ? launch_128<128, false, true>(p, grid, stream) : launch_128<128, false, false>(p, grid, stream);
     }
-    if (bf) return ca ? launch<64, true, true, 1>(p, grid, stream) : launch<64, true, false, 1>(p, grid, stream);
-    return ca ? launch<64, false, true, 1>(p, grid, stream) : launch<64, false, false, 1>(p, grid, stream);
+    if (bf) return ca ? launch_128<64, true, true>(p, grid, stream) : launch_128<64, true, false>(p, grid, stream);
+    return ca ? launch_128<64, false, true>(p, grid, stream) : launch_128<64, false, false>(p, grid, stream);
 }
 
 // ---- scratch memory of attn_fwd_static: a fixed array in device memory instead of a caller's workspace.

@@ -200,6 +200,40 @@ SAW_HD Schedule make_schedule(int heads, int N, bool causal, int launch, int dec
     return s;
 }
 
+// Which kernel computes 128-row tiles: the one with 16x16x32 MFMAs (attn_fwd_shared_kernel) where workgroups share the
+// compute units, the one with 32x32x16 MFMAs where a workgroup has one to itself.  The smaller MFMA switches less
+// current per multiply-add, which is worth more clock once the chip is at its power limit, but takes twice the issue
+// slots; a wavefront alone on its SIMD is bound by those.  Measured, 32x32 -> 16x16, d = 128: 32 heads x 4096: 255 ->
+// 240 us, 8 x 6000 (376 workgroups): 156 -> 146 us, but 8 x 4096 (256): 69 -> 71 us, 1 x 20000 (157): 244 -> 321 us; d =
+// 64: 1 x 65536: 1216 -> 1094 us, 100 x 300 causal (300): 10.6 -> 9.8 us, but 32 x 1024 (256): 14.8 -> 15.4 us.  At d =
+// 128 a causal launch with a single round is as long as its longest tile, which runs alone for half its time: 8 x 8192:
+// 153 -> 163 us, 1 x 40000: 559 -> 648 us.  (At d = 64 three workgroups share a compute unit then: 8 x 10000: 141 -> 134 us.)
+SAW_HD bool default_shared_kernel(const Schedule& s, int d, bool causal) {
+    if (s.slots <= 32) return false;
+    return !(d == 128 && causal && s.launch == kLaunchPersistent && s.local_iters == 1);
+}
+
+// Whether that kernel gives the wavefronts in their second product precedence on their SIMD (scan_tiles).  By
+// itself the hardware prefers the oldest wavefront, so of the workgroups that share a compute unit one runs ahead and
+// the other finishes alone, without anybody to share the units with.  With precedence by phase they advance alike:
+// 12 heads x 5000, d = 128, bfloat16: 156 -> 151 us; causal, several rounds: 32 heads x 5000, d = 128: 260 -> 246 us,
+// 16 x 8192, d = 64: 152 -> 146 us.  Some causal launches are better off with one ahead: a persistent one with a single
+// round, whose time is that of the longest tile (8 heads x 10000, d = 64: 137 us against 150), or with some compute units
+// shared and some not (24 x 6000, d = 128, 47 workgroups per XCD: 262 against 283 us); and direct launches
+// in which co-resident workgroups would free their places all together: more workgroups than fit at once whose heads'
+// tiles divide the 32 compute units evenly, so that those of one compute unit are equally long (32 x 4096, d = 128: 156
+// against 164 us; 64 x 2048, d = 64: 53 against 58 us), or about two rounds of workgroups (21 x 6000, d = 128: 262
+// against 267 us; at 1.5, 2.5 and 6 rounds precedence gains 1 to 6 %).
+SAW_HD bool default_phase_priority(const Schedule& s, int d, bool causal) {
+    if (!causal) return true;
+    if (s.launch == kLaunchPersistent) return s.local_iters > 1 && s.slots % 32 == 0;
+    const long long resident = resident_slots(d);
+    if (s.slots <= resident) return true;
+    const int per_part = (s.q_tiles + s.parts - 1) / s.parts;
+    if (per_part <= 32 ? 32 % per_part == 0 : per_part % 32 == 0) return false;
+    return 10LL * s.slots < 19 * resident || 10LL * s.slots > 23 * resident;
+}
+
 // What workgroup `wg` does in its local iteration `it` (0 <= it < local_iters).
 SAW_HD Work decode_work(const Schedule& s, int wg, int it, bool causal, bool sawtooth) {
     Work w;

@@ -756,3 +756,69 @@ def test_static_entry_point_replays_from_a_graph(sa, oracle, B, H, N, d, dtype, 
             rows = list(range(0, N, 97)) + [N - 1]
             ref = oracle.attention(fresh[0].cpu(), fresh[1].cpu(), fresh[2].cpu(), scale, causal=causal, rows=rows)
             assert_close(got.double().cpu().numpy()[:, :, rows], ref, f"graph replay {B},{H},{N},{d} {dtype}")
+
+
+# ------------------------------------------------------------------ 128-row tiles on shared compute units
+SHARED_HEADS = 264     # 33 workgroups and more per XCD, none of them with a compute unit to itself; too many for a halved scan
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "f16"), (128, "bf16")])
+def test_shared_compute_units_at_tile_edges(sa, oracle, d, dtype, causal):
+    """The kernel of launches whose workgroups share the compute units, over the lengths where a scan begins, ends or is
+    masked differently: one key, one row more or less than a tile, a ragged tile last (forward) and first (backward: two
+    tiles per workgroup, the second walked down), rows that meet no key in the first tile they walk."""
+    two = sa.variant(launch="grid", tiles_per_workgroup=2)
+    for k, N in enumerate([1, 63, 64, 65, 128, 129, 200, 321]):
+        Q, K, V = workloads.make_random(1, SHARED_HEADS, N, d, dtype, seed=6000 + N)
+        assert sa.attn_fwd_variant_launch_info(1, SHARED_HEADS, N, d, causal, two, dtype)["slots"] > 32
+        scale = 1.0 / math.sqrt(d) * (-1 if k % 3 == 2 else 1)
+        want = oracle.attention(Q, K, V, scale, causal=causal)
+        Qd, Kd, Vd = Q.cuda(), K.cuda(), V.cuda()
+        for var, order, qo in ((None, "cyclic", 0), (two, "sawtooth", 0), (two, "sawtooth", 3), (two, "sawtooth", 4)):
+            v = var if var is None else sa.variant(launch="grid", tiles_per_workgroup=2, qo_streaming=qo)
+            O = sa.attn_fwd_variant(Qd, Kd, Vd, scale=scale, causal=causal, scan_order=order, o_dtype=torch.float32, variant=v)
+            torch.cuda.synchronize()
+            assert_close(O.double().cpu().numpy(), want, f"shared N={N} d={d} {dtype} causal={causal} {order} qo={qo}")
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_shared_compute_units_moving_maximum_and_bad_rows(sa, oracle, d, causal):
+    """Score levels that jump by up to 60 from tile to tile, up and down, walked in both directions (the reference maximum
+    is raised in mid scan, over several tiles); and a query row of NaN, an infinite key and an infinite value, which may
+    spoil the rows that meet them and no other row of the wavefront."""
+    N = 449
+    g = torch.Generator("cpu").manual_seed(77 + d)
+    K = torch.randn(1, SHARED_HEADS, N, d, generator=g)
+    level = 60.0 * torch.rand(SHARED_HEADS, (N + 63) // 64, generator=g)
+    K[0, :, :, 0] = level.repeat_interleave(64, dim=1)[:, :N]
+    Q = 0.3 * torch.randn(1, SHARED_HEADS, N, d, generator=g)
+    Q[0, :, :, 0] = 1.0
+    V = torch.randn(1, SHARED_HEADS, N, d, generator=g)
+    Q, K, V = Q.half(), K.half(), V.half()
+    two = sa.variant(launch="grid", tiles_per_workgroup=2)
+    want = oracle.attention(Q, K, V, 1.0, causal=causal)
+    outs = {}
+    for order in ORDERS:
+        outs[order] = sa.attn_fwd_variant(Q.cuda(), K.cuda(), V.cuda(), scale=1.0, causal=causal, scan_order=order,
+                                          o_dtype=torch.float32, variant=two)
+        torch.cuda.synchronize()
+        assert_close(outs[order].double().cpu().numpy(), want, f"shared moving maximum d={d} causal={causal} {order}")
+    Qb = Q.clone()
+    Qb[0, :, 17] = float("nan")
+    for order in ORDERS:
+        O = sa.attn_fwd_variant(Qb.cuda(), K.cuda(), V.cuda(), scale=1.0, causal=causal, scan_order=order,
+                                o_dtype=torch.float32, variant=two)
+        torch.cuda.synchronize()
+        rest = [r for r in range(N) if r != 17]
+        assert torch.isnan(O[0, :, 17]).all() and torch.equal(O[:, :, rest], outs[order][:, :, rest])
+    if causal:      # rows above the bad key and value never meet them
+        Kb, Vb = K.clone(), V.clone()
+        Kb[0, :, 300, 0] = float("inf")
+        Vb[0, :, 310] = float("inf")
+        O = sa.attn_fwd_variant(Q.cuda(), Kb.cuda(), Vb.cuda(), scale=1.0, causal=True, scan_order="cyclic",
+                                o_dtype=torch.float32, variant=two)
+        torch.cuda.synchronize()
+        # (a masked key's probability is 0, and 0 times an infinite value is no number: whole tiles above the bad rows)
+        assert torch.equal(O[:, :, :256], outs["cyclic"][:, :, :256])
