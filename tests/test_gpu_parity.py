@@ -822,3 +822,41 @@ def test_shared_compute_units_moving_maximum_and_bad_rows(sa, oracle, d, causal)
         torch.cuda.synchronize()
         # (a masked key's probability is 0, and 0 times an infinite value is no number: whole tiles above the bad rows)
         assert torch.equal(O[:, :, :256], outs["cyclic"][:, :, :256])
+
+
+# ------------------------------------------------------------------ what the binding refuses, and the stream it takes
+@pytest.mark.parametrize("which", ["K on the host", "Q transposed", "V of rank 3", "K longer", "V in bfloat16",
+                                   "all float32", "O too short", "O of integers", "O on the host"])
+def test_binding_refuses(sa, which):
+    shape = (1, 2, 64, 64)
+    t = {n: torch.zeros(shape, dtype=torch.float16, device="cuda") for n in "QKVO"}
+    want = {"K on the host": ("K", lambda x: x.cpu(), "K must be a contiguous"),
+            "Q transposed": ("Q", lambda x: x.transpose(1, 2), "Q must be a contiguous"),
+            "V of rank 3": ("V", lambda x: x[0], "V must be a contiguous"),
+            "K longer": ("K", lambda x: torch.cat([x, x], 2), "share shape and dtype"),
+            "V in bfloat16": ("V", lambda x: x.bfloat16(), "share shape and dtype"),
+            "all float32": ("QKV", lambda x: x.float(), "float16 or bfloat16"),
+            "O too short": ("O", lambda x: x[:, :, :32].contiguous(), "O must be"),
+            "O of integers": ("O", lambda x: x.int(), "O must be"),
+            "O on the host": ("O", lambda x: x.cpu(), "O must be")}[which]
+    for n in want[0]:
+        t[n] = want[1](t[n])
+    with pytest.raises(ValueError, match=want[2]):
+        sa.attn_fwd(t["Q"], t["K"], t["V"], t["O"], scale=0.125)
+
+
+def test_binding_takes_the_current_stream_of_the_thread(sa):
+    q = torch.randn(1, 2, 192, 64, dtype=torch.float16, device="cuda")
+    want = sa.attn_fwd(q, q, q, scale=0.125)
+    torch.cuda.synchronize()
+    side, got = torch.cuda.Stream(), torch.empty_like(q)
+    x = torch.zeros_like(q)
+    with torch.cuda.stream(side):
+        # on the side stream the inputs are written only after a long product: a call on another stream reads zeros
+        a = torch.randn(4096, 4096, device="cuda")
+        for _ in range(4):
+            a = (a @ a).clamp(-1, 1)
+        x.copy_(q + 0 * a[0, 0].half())
+        sa.attn_fwd(x, x, x, got, scale=0.125)
+    side.synchronize()
+    assert torch.equal(got, want)
