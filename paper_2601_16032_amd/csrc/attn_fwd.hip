@@ -2146,14 +2146,14 @@ __device__ __forceinline__ void domain_sync(int set, int domain, int slots) {
 }
 
 // The outer loop of a workgroup: its query tiles one after the other (Alg. 2, Alg. 3), `tile` computes one.
-template <bool CAUSAL, typename TILE>
+template <bool CAUSAL, bool LATE, typename TILE>
 __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
     const Schedule& s = p.sched;
     const int lane0 = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int local = 0;           // query tiles this workgroup has processed
     for (int it = 0; it < s.local_iters; ++it) {
-        const Work w = decode_work(s, (int)blockIdx.x, it, CAUSAL, p.sawtooth != 0);
+        const Work w = decode_work<LATE>(s, (int)blockIdx.x, it, CAUSAL, p.sawtooth != 0);
         if (w.tile >= 0) {
             const int nkv = visible_kv_tiles(s, w.tile, p.N, CAUSAL);
             const int j0 = w.backward ? nkv - 1 : 0;
@@ -2180,7 +2180,7 @@ __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
 template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false>
 __global__ __launch_bounds__(kThreads, HALVES ? (D == 64 ? 2 : 1) : NH == 2 ? 1 : (D == 64 ? 3 : 2)) void attn_fwd_kernel(Params p) {
     extern __shared__ __align__(16) char smem[];
-    for_each_q_tile<CAUSAL>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
+    for_each_q_tile<CAUSAL, NH == 1>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
         const LaneMap<D> lm(wave, lane);
         process_q_tile<D, BF16, CAUSAL, NH, HALVES>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
     });
@@ -2190,7 +2190,7 @@ __global__ __launch_bounds__(kThreads, HALVES ? (D == 64 ? 2 : 1) : NH == 2 ? 1 
 template <int D, bool BF16, bool CAUSAL, bool PHASES>
 __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_shared_kernel(Params p) {
     extern __shared__ __align__(16) char smem[];
-    for_each_q_tile<CAUSAL>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
+    for_each_q_tile<CAUSAL, true>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
         const NarrowMap<D> lm(wave, lane);
         process_q_tile_narrow<D, BF16, CAUSAL, PHASES>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
     });

@@ -234,7 +234,25 @@ SAW_HD bool default_phase_priority(const Schedule& s, int d, bool causal) {
     return 10LL * s.slots < 19 * resident || 10LL * s.slots > 23 * resident;
 }
 
+// a / b for a >= 0, b > 0.  On the GPU a division is some 40 dependent scalar and vector instructions, and the part of it
+// that depends on b alone would be computed ahead of the loop over the tiles, also where no quotient is needed: most
+// workgroups only ever see the first chunk (a < b).  With LATE nothing is computed ahead, because with short sequences
+// the time up to the first fetch counts (one head of 256 rows, d = 64: 6.5 -> 6.2 us on the GPU; 8 heads x 2048, d = 64:
+// 16.5 -> 16.2 us).  The kernel with 256-row tiles, whose scans are long, keeps the plain division: the change moves its
+// registers and costs it time (128 heads x 32768, bfloat16, causal: 30.9 -> 31.4 ms).
+template <bool LATE, typename T>
+SAW_HD T quotient(T a, T b) {
+    if constexpr (LATE) {
+        if (a < b) return 0;
+#ifdef __HIP_DEVICE_COMPILE__
+        asm volatile("" : "+s"(b));
+#endif
+    }
+    return a / b;
+}
+
 // What workgroup `wg` does in its local iteration `it` (0 <= it < local_iters).
+template <bool LATE = false>
 SAW_HD Work decode_work(const Schedule& s, int wg, int it, bool causal, bool sawtooth) {
     Work w;
     w.head = 0;
@@ -246,8 +264,9 @@ SAW_HD Work decode_work(const Schedule& s, int wg, int it, bool causal, bool saw
         const long long k = s.launch == kLaunchPersistent ? (long long)wg + (long long)it * s.grid
                                                           : (long long)wg * s.tiles_per_wg + it;
         if (k < (long long)s.heads * s.q_tiles) {
-            w.head = (int)(k / s.q_tiles);
-            w.tile = (int)(k % s.q_tiles);
+            // (k is below 2^32 here: at most 2^31 tiles of 128 rows; a 64-bit division is several times longer)
+            w.head = LATE ? (int)quotient<LATE>((unsigned)k, (unsigned)s.q_tiles) : (int)(k / s.q_tiles);
+            w.tile = (int)(k - (long long)w.head * s.q_tiles);
         }
         w.backward = sawtooth && (it & 1);
         return w;
@@ -255,14 +274,14 @@ SAW_HD Work decode_work(const Schedule& s, int wg, int it, bool causal, bool saw
     const int domain = wg % kDomains, slot = wg / kDomains;
     int cs, u;
     if (s.launch == kLaunchPersistent) {
-        cs = it / s.rounds_per_chunk;
+        cs = quotient<LATE>(it, s.rounds_per_chunk);
         const int r = it - cs * s.rounds_per_chunk;
         u = r * s.slots + ((it & 1) ? s.slots - 1 - slot : slot);
         w.backward = sawtooth && (r & 1);
         w.sync_after = (s.sync_heads && r + 1 == s.rounds_per_chunk && cs + 1 < s.chunks_per_domain) ||
                        (s.sync_rounds && it + 1 < s.local_iters);
     } else {
-        cs = slot / s.units_per_chunk;
+        cs = quotient<LATE>(slot, s.units_per_chunk);
         u = (slot - cs * s.units_per_chunk) * s.tiles_per_wg + it;
         w.backward = sawtooth && (it & 1);
     }
