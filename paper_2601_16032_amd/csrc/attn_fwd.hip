@@ -920,17 +920,18 @@ __device__ __forceinline__ u4 tile_descriptor(const char* tile, unsigned bytes) 
     r[3] = 0x00020000u;
     return r;
 }
-// Load l of this wavefront's share of a tile, straight into LDS (see load_to_lds_16B for the inline assembly; rows
-// 4096 bytes apart in the tile are 4096 bytes apart in LDS, and the chunk permutation repeats every 16 rows, so one
-// lane offset serves all loads).
-__device__ __forceinline__ void tile_load_to_lds(u4 descriptor, unsigned voff, unsigned soff, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds_addr), "v"(voff), "s"(descriptor), "s"(soff) : "memory", "m0");
+// One load of this wavefront's share of a tile, straight into LDS (see load_to_lds_16B for the inline assembly).  The
+// whole offset inside the tile is in `voff`, the vector offset: that is the part that the range check compares with the
+// descriptor's size.  A scalar offset is not: the check takes it off the size, which may be smaller here (0 behind a
+// scan, a single row in a ragged tile), or leaves it out.
+__device__ __forceinline__ void tile_load_to_lds(u4 descriptor, unsigned voff, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :: "s"(lds_addr), "v"(voff), "s"(descriptor) : "memory", "m0");
 }
-__device__ __forceinline__ u4 tile_load(u4 d, unsigned voff, unsigned soff) {
+__device__ __forceinline__ u4 tile_load(u4 d, unsigned voff) {
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
         (void*)((unsigned long long)d[0] | (unsigned long long)d[1] << 32), 0, (int)d[2], (int)d[3]);
-    return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+    return __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0);
 }
 // All but the last VM vector-memory loads of this wavefront have landed, its LDS accesses are done, and so it is for
 // every wavefront of the workgroup.
@@ -1020,11 +1021,11 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
     };
     auto fetch_burst = [&](u4 d, unsigned dst) {
 #pragma unroll
-        for (int l = 0; l < NL; ++l) tile_load_to_lds(d, lm.fill_src, l * 4096, dst + lm.fill_dst + l * 4096);
+        for (int l = 0; l < NL; ++l) tile_load_to_lds(d, lm.fill_src + l * 4096, dst + lm.fill_dst + l * 4096);
     };
     auto v_to_regs = [&]() {
 #pragma unroll
-        for (int l = 0; l < NL; ++l) vreg[l] = tile_load(dv, lm.fill_src, l * 4096);
+        for (int l = 0; l < NL; ++l) vreg[l] = tile_load(dv, lm.fill_src + l * 4096);
     };
     // w-th 32-bit word of the fetched chunks from bfloat16 to binary16; every fourth completes 16 bytes for LDS
     auto convert_word = [&](int w, unsigned dst) {
@@ -1246,8 +1247,8 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
             if (t % (TB / 4) == TB / 4 - 1) sum_mfma(t / (TB / 2), t / (TB / 4) & 1);
 #pragma unroll
             for (int li = t * TL / TB; li < (t + 1) * TL / TB; ++li) {
-                if (li < NV) tile_load_to_lds(dv, lm.fill_src, li * 4096, vdst + li * 4096);
-                else tile_load_to_lds(dk, lm.fill_src, (li - NV) * 4096, kdst + (li - NV) * 4096);
+                if (li < NV) tile_load_to_lds(dv, lm.fill_src + li * 4096, vdst + li * 4096);
+                else tile_load_to_lds(dk, lm.fill_src + (li - NV) * 4096, kdst + (li - NV) * 4096);
             }
 #pragma unroll
             for (int n = t * OB / TB; n < (t + 1) * OB / TB; ++n) {

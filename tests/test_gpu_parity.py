@@ -824,6 +824,40 @@ def test_shared_compute_units_moving_maximum_and_bad_rows(sa, oracle, d, causal)
         assert torch.equal(O[:, :, :256], outs["cyclic"][:, :, :256])
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "f16"), (128, "bf16")])
+def test_shared_compute_units_read_no_other_rows(sa, d, dtype, causal):
+    """Rows outside a head never reach its output: K and V of every other head, and of 256 rows before the first and
+    behind the last one, once hold ordinary values and once NaN (K) and infinities (V), and the outputs of the heads in
+    between are the same bit for bit.  The bad heads are neighbours of the checked ones in memory, and on an XCD they
+    are computed before and beside them, so that what is left in LDS is theirs.  Lengths with a last tile of one row and
+    of more, one tile and several, walked up and down, one tile per workgroup and several heads per workgroup."""
+    guard = 256
+    head = torch.arange(SHARED_HEADS)
+    bad = ((head % 2) ^ (head // 8 % 2)).bool().cuda()
+    launches = [(None, "cyclic"), (sa.variant(launch="grid", tiles_per_workgroup=2), "sawtooth"),
+                (sa.variant(launch="persistent", decode="linear"), "sawtooth")]
+    for N in (1, 65, 129, 449):
+        for v, _ in launches:
+            info = sa.attn_fwd_variant_launch_info(1, SHARED_HEADS, N, d, causal, v, dtype)
+            assert info["tile_q"] == 128 and info["slots"] > 32
+        Q, K, V = (t.cuda() for t in workloads.make_random(1, SHARED_HEADS, N, d, dtype, seed=7000 + N))
+        def inside(t, fill):
+            room = torch.full((guard + SHARED_HEADS * N + guard, d), fill, dtype=t.dtype, device="cuda")
+            room[guard:-guard] = t.reshape(-1, d)
+            return room[guard:-guard].view(t.shape)
+        outs = []
+        for k_fill, v_fill in ((0.0, 0.0), (float("nan"), float("inf"))):
+            Kg, Vg = inside(K, k_fill), inside(V, v_fill)
+            if k_fill != 0.0:
+                Kg[:, bad], Vg[:, bad] = k_fill, v_fill
+            outs.append([sa.attn_fwd_variant(Q, Kg, Vg, scale=1.0 / math.sqrt(d), causal=causal, scan_order=order,
+                                             o_dtype=torch.float32, variant=v) for v, order in launches])
+            torch.cuda.synchronize()
+        for i, (clean, mixed) in enumerate(zip(*outs)):
+            assert torch.isfinite(clean).all() and torch.equal(clean[:, ~bad], mixed[:, ~bad]), f"N={N} launch {i}"
+
+
 # ------------------------------------------------------------------ what the binding refuses, and the stream it takes
 @pytest.mark.parametrize("which", ["K on the host", "Q transposed", "V of rank 3", "K longer", "V in bfloat16",
                                    "all float32", "O too short", "O of integers", "O on the host"])

@@ -549,3 +549,28 @@ def test_header_is_plain_c_and_the_binding_mirrors_its_structs(tmp_path):
         assert int(got[cname]) == ctypes.sizeof(mirror)
         for n, _ in mirror._fields_:
             assert int(got[f"{cname}.{n}"]) == getattr(mirror, n).offset
+
+
+def test_range_checked_loads_carry_no_scalar_offset(tmp_path):
+    """The kernels that fetch K and V through buffer descriptors rely on the range check for the rows past the end of a
+    sequence and the tiles past the end of a scan, whose descriptors are smaller than a tile or empty.  The check holds
+    for the vector offset; so no buffer load of the built library may carry part of its offset in the scalar one."""
+    import shutil
+    import subprocess
+    from paper_2601_16032_amd import build as hip_build
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    shutil.copy(hip_build.LIB_PATH, tmp_path / "lib.so")
+    subprocess.run([objdump, "--offloading", "lib.so"], cwd=tmp_path, check=True, capture_output=True)
+    device, = tmp_path.glob("lib.so.*gfx950")
+    listing = subprocess.run([objdump, "-d", "--mcpu=gfx950", str(device)], check=True, capture_output=True, text=True).stdout
+    loads, kernel = {}, None
+    for line in listing.splitlines():
+        head = re.match(r"[0-9a-f]+ <(\w+)>:", line)
+        if head:
+            kernel = head.group(1)
+        elif re.match(r"\s*buffer_load", line):
+            offsets = re.match(r"\s*buffer_load_\w+ (?:v\[[0-9:]+\]|v\d+)(?:, (?:v\[[0-9:]+\]|v\d+))?, s\[[0-9:]+\], (\S+) offen", line)
+            assert offsets, line
+            loads.setdefault(kernel, set()).add(offsets.group(1))
+    assert len(loads) == 12 and all("attn_fwd_shared_kernel" in k for k in loads)
+    assert all(v == {"0"} for v in loads.values()), loads
