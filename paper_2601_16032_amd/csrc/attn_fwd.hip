@@ -39,6 +39,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "running_max.h"
 #include "sawattn.h"
 #include "schedule.h"
 
@@ -282,12 +283,6 @@ __device__ __forceinline__ void add_pair(float& sum_lo, float& sum_hi, h2 ph, _F
     sum_lo = __builtin_fmaf((float)ph[0], (float)one, sum_lo);
     sum_hi = __builtin_fmaf((float)ph[1], (float)one, sum_hi);
 }
-
-// The running maximum is only raised when a tile's maximum exceeds it by more than this many
-// binades; until then probabilities are taken relative to the older, smaller reference and may be
-// as large as 2^kRescaleSlack.  O and the running sum stay consistent, so the result is unchanged;
-// it saves rescaling the whole accumulator on almost every tile.
-constexpr float kRescaleSlack = 8.0f;
 
 // Per-wavefront state of one query tile that the K/V loop carries along.
 template <int D>
@@ -1071,9 +1066,8 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
         }
     };
     // Raises the reference maxima for the tile in x (shifted by the old ones), whose largest raw scores in this lane are
-    // mx (at least lim).  The limit keeps a distance of |M| 2^-21 from M + slack, which covers the rounding of the
-    // division and of the comparison on raw scores.  A row that has met no key yet (L = 0, lim = -inf) takes any maximum, and starts from O = 0 whatever the values behind its
-    // masked keys were (0 times an infinite one is no number).
+    // mx (at least lim, see score_limit).  A row that has met no key yet (L = 0, lim = -inf) takes any maximum, and starts
+    // from O = 0 whatever the values behind its masked keys were (0 times an infinite one is no number).
     float mx[2];
     auto max_op = [&](int qt, int op) {     // op-th of the 8 updates of mx[qt]: two scores each
         const f4& a = A[op / 2][qt];
@@ -1094,7 +1088,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
             for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) st.o[db][qt][r] = fresh ? 0.f : st.o[db][qt][r] * alpha;
-            if (up) lim[qt] = (Mnew + kRescaleSlack - fabsf(Mnew) * 0x1p-21f) / c;
+            if (up) lim[qt] = score_limit(t, Mnew, c);
 #pragma unroll
             for (int k = 0; k < 16; ++k) x[16 * qt + k] -= d;
         }
@@ -1159,7 +1153,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
     for (int qt = 0; qt < 2; ++qt) {
         const float t = quad_max(mx[qt]);
         st.M[qt] = t == -INFINITY ? 0.f : t * c;
-        if (t != -INFINITY) lim[qt] = (st.M[qt] + kRescaleSlack - fabsf(st.M[qt]) * 0x1p-21f) / c;
+        if (t != -INFINITY) lim[qt] = score_limit(t, st.M[qt], c);
     }
 #pragma unroll
     for (int k = 0; k < 32; ++k) shift_score(k);

@@ -858,6 +858,27 @@ def test_shared_compute_units_read_no_other_rows(sa, d, dtype, causal):
             assert torch.isfinite(clean).all() and torch.equal(clean[:, ~bad], mixed[:, ~bad]), f"N={N} launch {i}"
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("level", [2048.0, 8192.0])
+@pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "f16"), (128, "bf16")])
+def test_shared_compute_units_large_scores_that_fall_and_rise(sa, oracle, d, dtype, level, causal):
+    """Scores of 2^22 and 2^26 that differ from tile to tile by 16, walked down (falling) and up: the maximum of a row
+    lies so high that rounding it costs more than the slack of the running maximum, and may still not come down."""
+    N = 449
+    Q, K = torch.zeros(1, SHARED_HEADS, N, d), torch.zeros(1, SHARED_HEADS, N, d)
+    Q[..., 0], Q[..., 1], K[..., 0] = level, 1.0, level
+    K[..., 1] = -16.0 * torch.div(torch.arange(N), 64, rounding_mode="floor")      # (exact in both types)
+    V = torch.randn(1, SHARED_HEADS, N, d, generator=torch.Generator("cpu").manual_seed(5 + d))
+    Q, K, V = (t.half() if dtype == "f16" else t.bfloat16() for t in (Q, K, V))
+    two = sa.variant(launch="grid", tiles_per_workgroup=2)
+    want = oracle.attention(Q, K, V, 1.0, causal=causal)
+    for order in ORDERS:
+        O = sa.attn_fwd_variant(Q.cuda(), K.cuda(), V.cuda(), scale=1.0, causal=causal, scan_order=order,
+                                o_dtype=torch.float32, variant=two)
+        torch.cuda.synchronize()
+        assert_close(O.double().cpu().numpy(), want, f"large scores d={d} {dtype} level={level} causal={causal} {order}")
+
+
 # ------------------------------------------------------------------ what the binding refuses, and the stream it takes
 @pytest.mark.parametrize("which", ["K on the host", "Q transposed", "V of rank 3", "K longer", "V in bfloat16",
                                    "all float32", "O too short", "O of integers", "O on the host"])

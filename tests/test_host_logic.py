@@ -574,3 +574,31 @@ def test_range_checked_loads_carry_no_scalar_offset(tmp_path):
             loads.setdefault(kernel, set()).add(offsets.group(1))
     assert len(loads) == 12 and all("attn_fwd_shared_kernel" in k for k in loads)
     assert all(v == {"0"} for v in loads.values()), loads
+
+
+def test_score_limit_never_lies_below_the_maximum_it_comes_from(tmp_path):
+    """The limit on raw scores above which the shared-unit kernel raises its reference M = t * c: never below t (a
+    smaller maximum would lower the reference and let O and the sum grow without bound), never NaN (an infinite score
+    would ask for a raise in every tile that follows), and one slack of 8 binades above t, less 2^-21 of |M|, wherever
+    that is larger."""
+    import subprocess
+    src = tmp_path / "limit.cpp"
+    src.write_text('#include <stdio.h>\n#include "running_max.h"\nint main() {\n    float t, c;\n'
+                   '    while (scanf("%a %a", &t, &c) == 2) { const volatile float M = t * c; printf("%a\\n", sawattn::score_limit(t, M, c)); }\n}\n')
+    exe = tmp_path / "limit"
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-ffp-contract=off", "-I",
+                    os.path.join(ROOT, "paper_2601_16032_amd", "csrc"), str(src), "-o", str(exe)], check=True, capture_output=True)
+    rng = np.random.default_rng(3)
+    t = np.concatenate([np.float32(10.0) ** rng.uniform(-6, 12, 4000) * rng.choice([-1, 1], 4000), [0.0, 8192.0 ** 2, 8192.0 ** 2 - 16]])
+    c = np.concatenate([10.0 ** rng.uniform(-3, 1, 4000), [1.0, math.log2(math.e), math.log2(math.e)]])
+    t, c = np.append(t, [0.0, 1e9, np.inf, np.inf]).astype(np.float32), np.append(c, [1e-30, 1e-30, 1.0, 1e-30]).astype(np.float32)
+    text = "\n".join(f"{float(a).hex()} {float(b).hex()}" for a, b in zip(t, c))
+    out = subprocess.run([str(exe)], input=text, check=True, capture_output=True, text=True).stdout.split()
+    lim = np.array([float.fromhex(x) for x in out], dtype=np.float64)
+    assert lim.shape == t.shape and not np.isnan(lim).any() and (lim >= t).all()
+    assert np.isinf(lim[-2:]).all() and np.isfinite(lim[:-2]).all()
+    M = t[:-2].astype(np.float64) * c[:-2]
+    above = (lim[:-2] * c[:-2] - M)                      # binades between the reference and the limit
+    want = np.maximum(8.0 - np.abs(M) * 2.0 ** -21, 0.0)
+    # M is rounded (2^-24 |M|), then the sum, the quotient and the product: together below 4 * 2^-24 (|M| + 8)
+    assert (np.abs(above - want) <= 4 * 2.0 ** -24 * (np.abs(M) + 8)).all()
