@@ -966,8 +966,16 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
     constexpr int LA = D == 64 ? 2 : 3;   // fragments read ahead of their use
     const unsigned lds0 = (unsigned)(size_t)lds;
     const int g = lane >> 4;
-    u4 ones = {0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u};      // binary16 1.0, A operand of the row sums
-    asm volatile("" : "+v"(ones));
+    // Binary16 1.0, A operand of the row sums.  Made where it is used, from a scalar register: a constant that the compiler
+    // sees through is kept in vector registers over the whole kernel, and d = 64 has none to spare (20 to 32 bytes of scratch).
+    auto make_ones = []() {
+        unsigned one = 0x3c003c00u;
+        asm volatile("" : "+s"(one));
+        u4 v = {one, one, one, one};
+        asm volatile("" : "+v"(v));
+        return v;
+    };
+    u4 ones = make_ones();
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
     f4 A[4][2];         // S^T of the tile one ahead: block (kb, qt) = keys 16kb.. x query rows 16qt..
     float x[32];        // score*c - M of the current tile, index 16*qt + 4*kb + r
@@ -1065,9 +1073,11 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
             }
         }
     };
-    // Raises the reference maxima for the tile in x (shifted by the old ones), whose largest raw scores in this lane are
-    // mx (at least lim, see score_limit).  A row that has met no key yet (L = 0, lim = -inf) takes any maximum, and starts
-    // from O = 0 whatever the values behind its masked keys were (0 times an infinite one is no number).
+    auto shift_score = [&](int k) { x[k] = __builtin_fmaf(A[(k >> 2) & 3][k >> 4][k & 3], c, -st.M[k >> 4]); };
+    // Raises the reference maxima for the tile in A, whose largest raw scores in this lane are mx (at least lim, see
+    // score_limit), and takes its shifted scores again from the scores themselves: a difference of shifted scores would
+    // carry the rounding at the distance from the old reference.  A row that has met no key yet (L = 0, lim = -inf) takes
+    // any maximum, and starts from O = 0 whatever the values behind its masked keys were (0 times an infinite one is no number).
     float mx[2];
     auto max_op = [&](int qt, int op) {     // op-th of the 8 updates of mx[qt]: two scores each
         const f4& a = A[op / 2][qt];
@@ -1079,9 +1089,8 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
             const float t = quad_max(mx[qt]);           // the lanes of a query row move together
             const bool up = t > lim[qt];
             const float Mnew = up ? t * c : st.M[qt];
-            const float d = Mnew - st.M[qt];
             const bool fresh = st.L[qt][0] == 0.f;
-            const float alpha = up && !fresh ? fast_exp2(-d) : 1.0f;
+            const float alpha = up && !fresh ? fast_exp2(st.M[qt] - Mnew) : 1.0f;
             st.M[qt] = Mnew;
             st.L[qt] *= alpha;
 #pragma unroll
@@ -1090,10 +1099,9 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
                 for (int r = 0; r < 4; ++r) st.o[db][qt][r] = fresh ? 0.f : st.o[db][qt][r] * alpha;
             if (up) lim[qt] = score_limit(t, Mnew, c);
 #pragma unroll
-            for (int k = 0; k < 16; ++k) x[16 * qt + k] -= d;
+            for (int k = 16 * qt; k < 16 * qt + 16; ++k) shift_score(k);
         }
     };
-    auto shift_score = [&](int k) { x[k] = __builtin_fmaf(A[(k >> 2) & 3][k >> 4][k & 3], c, -st.M[k >> 4]); };
     // Pair u = 0..15 of probabilities is word u % 4 of B operand (kh, qt) = (u / 8, u / 4 % 2): keys
     // 16 (2 kh + u % 4 / 2) + 4g + 2 (u % 2), + 1.  Its steps: the two exponentials, the convert, the two additions to
     // the running sum (of the rounded probabilities, the values the second product uses).
@@ -1199,7 +1207,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
         kv0 += kv_step;
         mask();
         // ---- phase B.  Under its MFMAs, in order: the row maxima of A, the row sums of tile i, the shifted scores of tile
-        //      i+1 -- if the reference maximum has to be raised (need), they follow it after the loop exit.  The direct
+        //      i+1 -- if the reference maximum has to be raised (need), they are taken again behind the iteration.  The direct
         //      loads of an iteration are spread over it too, V first because it is needed first.
         //      With V through registers the conversion comes along with the maxima, then the next V loads.  (The V registers
         //      have landed: the compiler is told so here, or it would wait for them where it uses them, and with them for the
@@ -1261,19 +1269,18 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
         kdst += flip;
         vdst += flip;
         flip = -flip;
-#pragma unroll
-        for (int m = 0; m < LA; ++m) ak[m] = k_read(m);
         return need;
     };
+    // (behind a raise, so that these fragments and the scores in A, which only a raise still reads, do not both take registers)
+    auto read_ahead = [&]() {
+#pragma unroll
+        for (int m = 0; m < LA; ++m) ak[m] = k_read(m);
+    };
     int i = 0;
-    while (i + 1 < nkv) {
-        bool need = false;
 #pragma unroll 1
-        for (; i + 1 < nkv; ++i) {
-            need = iteration(i);
-            if (need) { ++i; break; }
-        }
-        if (need) raise_reference();
+    for (; i + 1 < nkv; ++i) {
+        if (iteration(i)) raise_reference();
+        read_ahead();
     }
 
     // ---------------------------------------------------------------- last tile: probabilities, then O^T += V^T P^T
@@ -1281,6 +1288,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
 #pragma unroll
     for (int n = 0; n < OA; ++n) op_a(n);
     convert_op(15);
+    ones = make_ones();
     landed_barrier<0>();      // also the fetches past the end of the scan, which write zeros into buffers nobody reads
     if (!CAUSAL || kv0 <= qw0 + 31) {      // (not if every row of the wavefront lies before the tile's first key)
         u4 av[NB];

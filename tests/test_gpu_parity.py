@@ -879,6 +879,26 @@ def test_shared_compute_units_large_scores_that_fall_and_rise(sa, oracle, d, dty
         assert_close(O.double().cpu().numpy(), want, f"large scores d={d} {dtype} level={level} causal={causal} {order}")
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "f16"), (128, "bf16")])
+def test_shared_compute_units_exact_behind_a_jump_of_the_maximum(sa, oracle, d, dtype, causal):
+    """The first 64 keys score about -2^20, all others what their own values give.  The maximum rises by 2^20 in the
+    second tile, and that tile's probabilities, half of the result and more, are to be as exact as if it came first: at
+    the distance from the old maximum the scores' last bit would be worth 1/16.  (Rows below 64 are left out under the
+    mask: their scores really are that coarse.)"""
+    N = 200
+    g = torch.Generator("cpu").manual_seed(91 + d)
+    Q = 0.3 * torch.randn(1, SHARED_HEADS, N, d, generator=g)
+    K = torch.randn(1, SHARED_HEADS, N, d, generator=g)
+    V = torch.randn(1, SHARED_HEADS, N, d, generator=g)
+    Q[..., 0], K[..., 0], K[:, :, :64, 0] = 1024.0, 0.0, -1024.0
+    Q, K, V = (t.half() if dtype == "f16" else t.bfloat16() for t in (Q, K, V))
+    want = oracle.attention(Q, K, V, 1.0, causal=causal)
+    O = sa.attn_fwd(Q.cuda(), K.cuda(), V.cuda(), scale=1.0, causal=causal, scan_order="cyclic", o_dtype=torch.float32)
+    torch.cuda.synchronize()
+    assert_close(O.double().cpu().numpy()[:, :, 64:], want[:, :, 64:], f"jump d={d} {dtype} causal={causal}")
+
+
 # ------------------------------------------------------------------ what the binding refuses, and the stream it takes
 @pytest.mark.parametrize("which", ["K on the host", "Q transposed", "V of rank 3", "K longer", "V in bfloat16",
                                    "all float32", "O too short", "O of integers", "O on the host"])
