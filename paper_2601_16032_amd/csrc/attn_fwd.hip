@@ -2312,12 +2312,12 @@ int launch(Params& p, int grid, hipStream_t stream) {
 // 128-row tiles: the kernel for shared compute units or the one for workgroups that have theirs to themselves.
 template <int D, bool BF16, bool CAUSAL>
 int launch_128(Params& p, int grid, hipStream_t stream) {
-    if (default_shared_kernel(p.sched, D, CAUSAL)) {
-        if (!CAUSAL || default_phase_priority(p.sched, D, CAUSAL))
-            return launch_kernel<attn_fwd_shared_kernel<D, BF16, CAUSAL, true>>(p, grid, Geo<D>::kLdsBytes, stream);
-        return launch_kernel<attn_fwd_shared_kernel<D, BF16, CAUSAL, !CAUSAL>>(p, grid, Geo<D>::kLdsBytes, stream);
+    if (!default_shared_kernel(p.sched, D, CAUSAL, BF16)) return launch<D, BF16, CAUSAL, 1>(p, grid, stream);
+    if constexpr (CAUSAL) {      // (without a mask always with precedence: the other kernel is not built)
+        if (!default_phase_priority(p.sched, D, CAUSAL))
+            return launch_kernel<attn_fwd_shared_kernel<D, BF16, CAUSAL, false>>(p, grid, Geo<D>::kLdsBytes, stream);
     }
-    return launch<D, BF16, CAUSAL, 1>(p, grid, stream);
+    return launch_kernel<attn_fwd_shared_kernel<D, BF16, CAUSAL, true>>(p, grid, Geo<D>::kLdsBytes, stream);
 }
 
 // Validates a variant description (NULL = the default schedule) and builds its schedule.

@@ -200,38 +200,83 @@ SAW_HD Schedule make_schedule(int heads, int N, bool causal, int launch, int dec
     return s;
 }
 
+// Workgroups of a chunk (domain decode) or of a head (linear decode) in a direct launch, tiles of a chunk otherwise.
+SAW_HD int per_chunk(const Schedule& s) {
+    if (s.decode == kDecodeLinear) return ceil_div_i(s.q_tiles, s.tiles_per_wg);
+    return s.launch == kLaunchGrid ? s.units_per_chunk : ceil_div_i(s.q_tiles, s.parts);
+}
+
 // Which kernel computes 128-row tiles: the one with 16x16x32 MFMAs (attn_fwd_shared_kernel) where workgroups share the
 // compute units, the one with 32x32x16 MFMAs where a workgroup has one to itself.  The smaller MFMA switches less
 // current per multiply-add, which is worth more clock once the chip is at its power limit, but takes twice the issue
-// slots; a wavefront alone on its SIMD is bound by those.  Measured, 32x32 -> 16x16, d = 128: 32 heads x 4096: 255 ->
-// 240 us, 8 x 6000 (376 workgroups): 156 -> 146 us, but 8 x 4096 (256): 69 -> 71 us, 1 x 20000 (157): 244 -> 321 us; d =
-// 64: 1 x 65536: 1216 -> 1094 us, 100 x 300 causal (300): 10.6 -> 9.8 us, but 32 x 1024 (256): 14.8 -> 15.4 us.  At d =
-// 128 a causal launch with a single round is as long as its longest tile, which runs alone for half its time: 8 x 8192:
-// 153 -> 163 us, 1 x 40000: 559 -> 648 us.  (At d = 64 three workgroups share a compute unit then: 8 x 10000: 141 -> 134 us.)
-SAW_HD bool default_shared_kernel(const Schedule& s, int d, bool causal) {
+// slots; a wavefront alone on its SIMD is bound by those.  What follows is the change of the time from 32x32 to 16x16
+// over 1358 launches (profiles/shared_kernel_rules.txt).  With 32 workgroups per XCD and fewer 0 to +32 % (1 x 20000, d =
+// 128, 20 workgroups: 244 -> 321 us).  From 33 on -12 to +2 % at d = 64, where three share a compute unit (132 heads x 256:
+// 9.4 -> 8.9 us; 1 x 131072, causal: 2520 -> 2310 us).  At d = 128 it loses where workgroups run alone for a good part of the
+// launch:
+//   * without a mask, where the last workgroups have a compute unit each (1 to 32 left over by whole loads of 64 per XCD).
+//     bfloat16: one load and up to 32 more +7.5 % in the mean (24 x 4096: 204 -> 238 us), two and three loads +3 %, a second
+//     round of a persistent launch 0 to +2 %, from four loads on 0.  Binary16: one load and up to 32 more +1.8 % (3 x 28077:
+//     1212 -> 1318 us), then -1 to -3 %.  (One tile per head and XCD, one load and more: -10 to +3 %.)  Elsewhere -3 % in the
+//     mean for bfloat16 and -7 % for binary16;
+//   * under the mask, a persistent launch of a single round, as long as its longest tile: +2 to +16 %; two rounds of which
+//     the second is less than 1/8 full: +1.5 to +5 %;
+//   * under the mask, few compute units shared and workgroups of unequal length: direct launches of 33 to 47 workgroups per
+//     XCD, 3 and more to a chunk: -2 to +18 % (+3.7 % in the mean; 48 and more: -7 to +3 %), persistent ones of three
+//     rounds of 33 and 35: +8 and +4 %.  (With the lengths evened out by a second round 33 to 39 workgroups gain 4 to 9 %, and
+//     33 to 47 with one or two short tiles to a chunk gain 2 to 11 %.)
+//   * under the mask, a direct launch of more workgroups than fit at once, with 2, 4 or 8 of them to a chunk: those of a
+//     compute unit are then equally long and make room all together.  89 of 106 of these lose, up to 10 % (2.7 % in the
+//     mean); with 16 and 32 to a chunk -9 to +4 % (-0.6 %), with 1 -7 to +3 % (-1.4 %), with others -7 to +4 % (-1.3 %).
+SAW_HD bool default_shared_kernel(const Schedule& s, int d, bool causal, bool bf16) {
     if (s.slots <= 32) return false;
-    return !(d == 128 && causal && s.launch == kLaunchPersistent && s.local_iters == 1);
+    if (d == 64) return true;
+    const int n = per_chunk(s), resident = resident_slots(d);
+    if (!causal) {
+        const int wgs = s.launch == kLaunchGrid ? s.slots : n;     // (persistent: what the last round of a chunk leaves)
+        if (wgs <= resident || (wgs - 1) % resident >= 32) return true;
+        if (s.launch == kLaunchGrid && wgs < 2 * resident) return n == 1;
+        return !bf16 || wgs > 4 * resident;
+    }
+    if (s.launch == kLaunchPersistent) {
+        if (s.local_iters == 1) return false;
+        if (s.decode == kDecodeLinear) return true;
+        if (s.rounds_per_chunk == 1) return s.local_iters != 3 || s.slots >= 40;
+        return s.rounds_per_chunk > 2 || 8 * (n - s.slots) >= s.slots;
+    }
+    if (s.slots <= resident) return s.slots >= 48 || n <= 2;
+    return n == 1 || n >= 16 || 32 % n != 0;
 }
 
 // Whether that kernel gives the wavefronts in their second product precedence on their SIMD (scan_tiles).  By
 // itself the hardware prefers the oldest wavefront, so of the workgroups that share a compute unit one runs ahead and
-// the other finishes alone, without anybody to share the units with.  With precedence by phase they advance alike:
-// 12 heads x 5000, d = 128, bfloat16: 156 -> 151 us; causal, several rounds: 32 heads x 5000, d = 128: 260 -> 246 us,
-// 16 x 8192, d = 64: 152 -> 146 us.  Some causal launches are better off with one ahead: a persistent one with a single
-// round, whose time is that of the longest tile (8 heads x 10000, d = 64: 137 us against 150), or with some compute units
-// shared and some not (24 x 6000, d = 128, 47 workgroups per XCD: 262 against 283 us); and direct launches
-// in which co-resident workgroups would free their places all together: more workgroups than fit at once whose heads'
-// tiles divide the 32 compute units evenly, so that those of one compute unit are equally long (32 x 4096, d = 128: 156
-// against 164 us; 64 x 2048, d = 64: 53 against 58 us), or about two rounds of workgroups (21 x 6000, d = 128: 262
-// against 267 us; at 1.5, 2.5 and 6 rounds precedence gains 1 to 6 %).
+// the other finishes alone, without anybody to share the units with.  With precedence by phase they advance alike, which
+// is better where they also have equally much to do (12 heads x 5000, d = 128, bfloat16: 156 -> 151 us) and worse where the
+// launch waits for the one with the most.  Measured under the causal mask, without -> with precedence:
+//   * persistent, one round per chunk: an even number of rounds gives every workgroup the same length, -9 to -1 %; an odd
+//     number leaves the longest one 1/rounds above the mean: d = 128, 3 and 5 rounds: +2 to +11 %, 7 and 9: 0 to +4 %, more:
+//     -3 to 0 %; d = 64, one round: +5 to +12 %, three: -1 to +5 % up to 64 workgroups per XCD, -6 to -2 % above, five and
+//     more: -6 to -1 %;
+//   * persistent, two rounds per chunk, the second to a share f: the longest one is 2/(1+f) of the mean.  d = 128 (f up to
+//     0.7; longer heads run 256-row tiles): +2 to +10 %; d = 64: f below 1/4: 0 to +8 %, above: -5 to -1 %.  Three rounds
+//     and more: -5 to +1 %;
+//   * direct launch, all workgroups at once: -6 to +1 % (one of 86: +5 %).
+//   * direct launch of more than fit.  d = 64: -5 to +2 % (-0.9 % in the mean) from twice as many on; fewer: -5 to +1 % (-1.4
+//     %) where a head is spread over 4 or 8 XCDs, two tiles and more to a chunk, -4 to +10 % (+2.2 %) otherwise (64 heads x
+//     2048: 54 against 59 us, 40 x 3968: 104 against 114 us).  d = 128: -7 to +7 % (+0.7 %); -10 to +2 % (-2.6 %) for 4/3 to
+//     twice as many, a head over 4 or 8 XCDs and five tiles and more to a chunk (5 x 23936: 844 -> 793 us).
 SAW_HD bool default_phase_priority(const Schedule& s, int d, bool causal) {
     if (!causal) return true;
-    if (s.launch == kLaunchPersistent) return s.local_iters > 1 && s.slots % 32 == 0;
-    const long long resident = resident_slots(d);
-    if (s.slots <= resident) return true;
-    const int per_part = (s.q_tiles + s.parts - 1) / s.parts;
-    if (per_part <= 32 ? 32 % per_part == 0 : per_part % 32 == 0) return false;
-    return 10LL * s.slots < 19 * resident || 10LL * s.slots > 23 * resident;
+    const int rounds = s.local_iters, resident = resident_slots(d), n = per_chunk(s);
+    if (s.launch == kLaunchGrid) {
+        if (s.slots <= resident) return true;
+        if (d == 64) return s.slots >= 2 * resident || (s.parts >= 4 && n > 1);
+        return s.parts >= 4 && n >= 5 && 3 * s.slots >= 4 * resident && s.slots < 2 * resident;
+    }
+    if (s.decode == kDecodeLinear) return rounds > 1 && s.slots % 32 == 0;
+    if (s.rounds_per_chunk == 1)
+        return rounds % 2 == 0 || (d == 64 ? rounds >= 5 || (rounds == 3 && s.slots > 64) : rounds > 10);
+    return s.rounds_per_chunk > 2 || (d == 64 && 4 * (n - s.slots) >= s.slots);
 }
 
 // a / b for a >= 0, b > 0.  On the GPU a division is some 40 dependent scalar and vector instructions, and the part of it

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from paper_2601_16032_amd import binding, workloads
-from tests.util import assert_close, errors, oracle_inputs
+from tests.util import SHARED_HEADS, SHARED_LENGTHS, assert_close, errors, oracle_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -759,8 +759,6 @@ def test_static_entry_point_replays_from_a_graph(sa, oracle, B, H, N, d, dtype, 
 
 
 # ------------------------------------------------------------------ 128-row tiles on shared compute units
-SHARED_HEADS = 264     # 33 workgroups and more per XCD, none of them with a compute unit to itself; too many for a halved scan
-
 
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "f16"), (128, "bf16")])
@@ -769,7 +767,7 @@ def test_shared_compute_units_at_tile_edges(sa, oracle, d, dtype, causal):
     masked differently: one key, one row more or less than a tile, a ragged tile last (forward) and first (backward: two
     tiles per workgroup, the second walked down), rows that meet no key in the first tile they walk."""
     two = sa.variant(launch="grid", tiles_per_workgroup=2)
-    for k, N in enumerate([1, 63, 64, 65, 128, 129, 200, 321]):
+    for k, N in enumerate(SHARED_LENGTHS):
         Q, K, V = workloads.make_random(1, SHARED_HEADS, N, d, dtype, seed=6000 + N)
         assert sa.attn_fwd_variant_launch_info(1, SHARED_HEADS, N, d, causal, two, dtype)["slots"] > 32
         scale = 1.0 / math.sqrt(d) * (-1 if k % 3 == 2 else 1)
@@ -787,8 +785,9 @@ def test_shared_compute_units_at_tile_edges(sa, oracle, d, dtype, causal):
 def test_shared_compute_units_moving_maximum_and_bad_rows(sa, oracle, d, causal):
     """Score levels that jump by up to 60 from tile to tile, up and down, walked in both directions (the reference maximum
     is raised in mid scan, over several tiles); and a query row of NaN, an infinite key and an infinite value, which may
-    spoil the rows that meet them and no other row of the wavefront."""
-    N = 449
+    spoil the rows that meet them and no other row of the wavefront (behind a masked infinite value, no other row but
+    those above it in its 64-row tile: the masked probability is 0, and 0 times an infinite value is no number)."""
+    N = 577
     g = torch.Generator("cpu").manual_seed(77 + d)
     K = torch.randn(1, SHARED_HEADS, N, d, generator=g)
     level = 60.0 * torch.rand(SHARED_HEADS, (N + 63) // 64, generator=g)
@@ -813,15 +812,43 @@ def test_shared_compute_units_moving_maximum_and_bad_rows(sa, oracle, d, causal)
         torch.cuda.synchronize()
         rest = [r for r in range(N) if r != 17]
         assert torch.isnan(O[0, :, 17]).all() and torch.equal(O[:, :, rest], outs[order][:, :, rest])
-    if causal:      # rows above the bad key and value never meet them
-        Kb, Vb = K.clone(), V.clone()
-        Kb[0, :, 300, 0] = float("inf")
-        Vb[0, :, 310] = float("inf")
-        O = sa.attn_fwd_variant(Q.cuda(), Kb.cuda(), Vb.cuda(), scale=1.0, causal=True, scan_order="cyclic",
-                                o_dtype=torch.float32, variant=two)
-        torch.cuda.synchronize()
-        # (a masked key's probability is 0, and 0 times an infinite value is no number: whole tiles above the bad rows)
-        assert torch.equal(O[:, :, :256], outs["cyclic"][:, :, :256])
+    if causal:
+        def run(K, V, order):
+            O = sa.attn_fwd_variant(Q.cuda(), K.cuda(), V.cuda(), scale=1.0, causal=True, scan_order=order,
+                                    o_dtype=torch.float32, variant=two)
+            torch.cuda.synchronize()
+            return O
+        # an infinite key: rows above it in its own tile and wavefront mask it, in a scan up (300) and down (200)
+        for order in ORDERS:
+            for bad in (200, 300):
+                Kb = K.clone()
+                Kb[0, :, bad, 0] = float("inf")
+                assert torch.equal(run(Kb, V, order)[:, :, :bad], outs[order][:, :, :bad])
+        # an infinite value.  Of the five query tiles of a head, two to a workgroup, the longest first, tiles 3 and 1 are
+        # walked down: rows 128..191 and 384..447 meet the tile with the bad value first, wholly masked, before any key of
+        # their own.  Walked up, it is the last tile of their scan, which they leave out.
+        for order in ORDERS:
+            for bad in (200, 460):
+                Vb = V.clone()
+                Vb[0, :, bad] = float("inf")
+                above = bad // 64 * 64
+                assert torch.equal(run(K, Vb, order)[:, :, :above], outs[order][:, :, :above])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,dtype", [(64, "f16"), (64, "bf16"), (128, "f16"), (128, "bf16")])
+def test_shared_compute_units_scale_zero_and_tiny(sa, oracle, d, dtype, causal):
+    """Scale 0 and one below the floor on scale * log2(e) give uniform attention over the visible keys, a negative one its
+    mirror image: the limit on raw scores is (M + slack) / c, with c at its smallest."""
+    N = 577
+    Q, K, V = workloads.make_random(1, SHARED_HEADS, N, d, dtype, seed=61)
+    for scale in (0.0, 1e-36, -0.09):
+        want = oracle.attention(Q, K, V, scale, causal=causal)
+        for order in ORDERS:
+            O = sa.attn_fwd_variant(Q.cuda(), K.cuda(), V.cuda(), scale=scale, causal=causal, scan_order=order,
+                                    o_dtype=torch.float32, variant=sa.variant(launch="grid", tiles_per_workgroup=2))
+            torch.cuda.synchronize()
+            assert_close(O.double().cpu().numpy(), want, f"shared scale={scale} d={d} {dtype} causal={causal} {order}")
 
 
 @pytest.mark.parametrize("causal", [False, True])
@@ -837,7 +864,7 @@ def test_shared_compute_units_read_no_other_rows(sa, d, dtype, causal):
     bad = ((head % 2) ^ (head // 8 % 2)).bool().cuda()
     launches = [(None, "cyclic"), (sa.variant(launch="grid", tiles_per_workgroup=2), "sawtooth"),
                 (sa.variant(launch="persistent", decode="linear"), "sawtooth")]
-    for N in (1, 65, 129, 449):
+    for N in (1, 65, 129, 577):
         for v, _ in launches:
             info = sa.attn_fwd_variant_launch_info(1, SHARED_HEADS, N, d, causal, v, dtype)
             assert info["tile_q"] == 128 and info["slots"] > 32
@@ -864,7 +891,7 @@ def test_shared_compute_units_read_no_other_rows(sa, d, dtype, causal):
 def test_shared_compute_units_large_scores_that_fall_and_rise(sa, oracle, d, dtype, level, causal):
     """Scores of 2^22 and 2^26 that differ from tile to tile by 16, walked down (falling) and up: the maximum of a row
     lies so high that rounding it costs more than the slack of the running maximum, and may still not come down."""
-    N = 449
+    N = 577
     Q, K = torch.zeros(1, SHARED_HEADS, N, d), torch.zeros(1, SHARED_HEADS, N, d)
     Q[..., 0], Q[..., 1], K[..., 0] = level, 1.0, level
     K[..., 1] = -16.0 * torch.div(torch.arange(N), 64, rounding_mode="floor")      # (exact in both types)
@@ -886,7 +913,7 @@ def test_shared_compute_units_exact_behind_a_jump_of_the_maximum(sa, oracle, d, 
     second tile, and that tile's probabilities, half of the result and more, are to be as exact as if it came first: at
     the distance from the old maximum the scores' last bit would be worth 1/16.  (Rows below 64 are left out under the
     mask: their scores really are that coarse.)"""
-    N = 200
+    N = 300
     g = torch.Generator("cpu").manual_seed(91 + d)
     Q = 0.3 * torch.randn(1, SHARED_HEADS, N, d, generator=g)
     K = torch.randn(1, SHARED_HEADS, N, d, generator=g)

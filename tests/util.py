@@ -45,3 +45,11 @@ def oracle_inputs(info, d, variant_kw=None):
     out["tile_q"] = info["tile_q"]
     out["resident"] = kw.get("slots_per_domain") or RESIDENT_PER_XCD[(d, info["tile_q"])]
     return out
+
+
+# Short heads that make the kernel for compute units shared by workgroups run (33 workgroups and more per XCD; too many heads
+# for a halved scan), and lengths at which, launched one or two tiles per workgroup, they reach every build of it: both head
+# dimensions and input types, without a mask, and under the mask with and without precedence by phase (d = 128 with 2, 4 or
+# 8 workgroups per head, as at 129..256 and 385..512 rows, is left to the other kernel there).
+SHARED_HEADS = 264
+SHARED_LENGTHS = [1, 63, 64, 65, 128, 129, 200, 321, 577]
