@@ -4,28 +4,30 @@
 // query rows 32w..32w+31 of the tile and keeps them in registers for the whole inner loop.  K and V
 // are streamed in 64-row tiles through two LDS buffers each, filled by direct global->LDS loads.
 //
-// Both contractions run on v_mfma_f32_32x32x16 in the transposed form
+// Three kernels do this.  They share the transposed form of both contractions
 //     S^T (kv x q) = K_j   (kv x d) . Q_i^T (d x q)
 //     O^T (d  x q) = V_j^T (d x kv) . P^T   (kv x q)
-// because the accumulator layout of S^T (a lane holds, for its query column lane%32, the kv rows
-// 8*(r/4) + 4*(lane/32) + r%4 of a 32-row block in register r) is, register for register, the
-// B-operand layout of the second product once the contraction index of each 16-wide MFMA step is
-// read as  slot (lane/32, e) <-> kv = 16*step + 8*(e/4) + 4*(lane/32) + e%4.  So P never leaves
-// registers.  V^T in the matching A-operand layout comes from ds_read_b64_tr_b16, which hands lane
-// i of a 16-lane group the column i of a 4 x 16 block whose four row addresses are supplied by
-// lanes 4e + c (row e, 8-byte column chunk c) of that group.
+// because the accumulator layout of S^T is then, register for register, the B-operand layout of the second
+// product, so P never leaves registers.  V^T in the matching A-operand layout comes from ds_read_b64_tr_b16, which
+// hands lane i of a 16-lane group the column i of a 4 x 16 block whose four row addresses are supplied by lanes
+// 4e + c (row e, 8-byte column chunk c) of that group.  The workgroups of one XCD walk the same head together and
+// re-align between heads (domain_sync).
 //
-// Softmax statistics live per lane: lanes l and l+32 share a query row and hold disjoint key
-// subsets, so the running maximum is merged across the pair every tile while the running sum stays
-// a per-lane partial (it is linear) and is merged once in the epilogue.
+// attn_fwd_kernel (pipelined_range, general_range), for workgroups that have a compute unit to themselves: both
+// contractions on v_mfma_f32_32x32x16.  A lane holds, for its query column lane%32, the kv rows
+// 8*(r/4) + 4*(lane/32) + r%4 of a 32-row block in register r; the contraction index of each 16-wide step of the second
+// product is read as  slot (lane/32, e) <-> kv = 16*step + 8*(e/4) + 4*(lane/32) + e%4.  Softmax statistics live per
+// lane: lanes l and l+32 share a query row and hold disjoint key subsets, so the running maximum is merged across the
+// pair every tile while the running sum stays a per-lane partial (it is linear) and is merged once in the epilogue.  A
+// query tile's scan is a software-pipelined run of full, unmasked K/V tiles (pipelined_range) plus, at one end, a short
+// run of masked tiles (general_range).  With 64-row tiles it walks the two halves of a scan at once (HALVES).
 //
-// A query tile's scan is a software-pipelined run of full, unmasked K/V tiles (pipelined_range)
-// plus, at one end, a short run of masked tiles (general_range).  The workgroups of one XCD walk
-// the same head together and re-align between heads (domain_sync).
+// The same with 256-row tiles, head dimension 128 (NH = 2 in the templates, pipelined_range_wide): a wavefront owns two
+// 32-row halves, one workgroup per CU, and every K / V^T fragment read from LDS feeds one MFMA per half.
 //
-// For head dimension 128 there is a second tile shape (NH = 2 in the templates, pipelined_range_wide):
-// a wavefront owns two such 32-row halves, a workgroup 256 query rows, one workgroup per CU, and every
-// K / V^T fragment read from LDS feeds one MFMA per half.
+// attn_fwd_shared_kernel (scan_tiles), 128-row tiles where workgroups share the compute units: both contractions on
+// v_mfma_f32_16x16x32, layouts as described there.  Four lanes share a query row, row sums are a product with ones,
+// the running maximum is compared on raw scores, and masked tiles stay in the pipeline.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -827,10 +829,12 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
 }
 
 // ------------------------------------------------------------------------------------------------
-// The kernels with 128-row query tiles, 32 rows per wavefront.  Both contractions run on v_mfma_f32_16x16x32, in the transposed form:
-// S^T in blocks of 16 keys x 16 query rows, O^T in blocks of 16 columns of O x 16 query rows.  Lane l holds, for query
-// row l % 16 of a block, keys (columns) 4*(l/16) + r of it in register r.  Two blocks of 16 keys of S^T are, register
-// for register, one B operand of the second product once its contraction index is read as
+// The scan of attn_fwd_shared_kernel: 128-row query tiles, 32 rows per wavefront, compute units shared by workgroups (the
+// kernel for 128-row tiles that have a compute unit to themselves is attn_fwd_kernel, above).  Both contractions run on
+// v_mfma_f32_16x16x32, in the transposed form: S^T in blocks of 16 keys x 16 query rows, O^T in blocks of 16 columns of
+// O x 16 query rows.  Lane l holds, for query row l % 16 of a block, keys (columns) 4*(l/16) + r of it in register r.
+// Two blocks of 16 keys of S^T are, register for register, one B operand of the second product once its contraction
+// index is read as
 //     slot (l/16, 4t + r) <-> key 16t + 4*(l/16) + r,
 // and V^T in the matching A layout is two ds_read_b64_tr_b16.  Every K and V^T fragment read from LDS feeds two MFMAs,
 // one per block of 16 query rows.
@@ -935,8 +939,7 @@ __device__ __forceinline__ void landed_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(VM) : "memory");
 }
 
-// The scan of one query tile over its `nkv` K/V tiles j0, j0 + step, ..., software pipelined across tiles, for the
-// kernels with 32 query rows per wavefront.  While the MFMAs of S(i+1)^T = K(i+1) Q^T run, the exponentials of tile i
+// The scan of one query tile over its `nkv` K/V tiles j0, j0 + step, ..., software pipelined across tiles.  While the MFMAs of S(i+1)^T = K(i+1) Q^T run, the exponentials of tile i
 // are issued between them; while the MFMAs of O^T += V(i)^T P(i)^T run, the row maximum of S(i+1), the lazy-rescale
 // check and the (score*c - M) of tile i+1 are issued between them.  Two register sets alternate roles without copies:
 // `A` accumulates the scores of the tile one ahead, `x` holds the shifted scores of the current tile until they have
@@ -1103,14 +1106,13 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
         }
     };
     // Pair u = 0..15 of probabilities is word u % 4 of B operand (kh, qt) = (u / 8, u / 4 % 2): keys
-    // 16 (2 kh + u % 4 / 2) + 4g + 2 (u % 2), + 1.  Its steps: the two exponentials, the convert, the two additions to
-    // the running sum (of the rounded probabilities, the values the second product uses).
+    // 16 (2 kh + u % 4 / 2) + 4g + 2 (u % 2), + 1.  Its steps: the two exponentials and the convert.
     float e[16][2];
     auto exp_op = [&](int u, int h) { e[u][h] = fast_exp2(x[16 * (u / 4 % 2) + 4 * (2 * (u / 8) + u % 4 / 2) + 2 * (u % 2) + h]); };
     auto convert_op = [&](int u) {
         pf[u / 8][u / 4 % 2][u % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u][0], e[u][1]}, h2));
     };
-    // (of the rounded probabilities, the values the second product uses)
+    // Row sums of the rounded probabilities, the values the second product uses.
     auto sum_mfma = [&](int kh, int qt) { st.L[qt] = mfma_16x16<false>(ones, pf[kh][qt], st.L[qt]); };
     // What runs under the first product, in order: step k of pair u, the convert one pair behind its exponentials.
     constexpr int OA = 48;
@@ -1968,7 +1970,7 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
     }
 }
 
-// One query tile (Alg. 1 body) of the kernels with 128-row tiles: rows [t*128, (t+1)*128) of head `hh`,
+// One query tile (Alg. 1 body) of attn_fwd_shared_kernel: rows [t*128, (t+1)*128) of head `hh`,
 // K/V tiles j0, j0+step, ... (nkv of them).
 template <int D, bool BF16, bool CAUSAL, bool PHASES>
 __device__ __forceinline__ void process_q_tile_narrow(const Params& p, const NarrowMap<D>& lm, int hh, int t, int j0, int step,

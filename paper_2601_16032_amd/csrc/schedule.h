@@ -45,10 +45,12 @@ SAW_HD int ceil_div_i(long long a, long long b) { return (int)((a + b - 1) / b);
 // workgroup tiles) for head dimension 128 (either input type) once the steady state dominates, i.e.
 // every resident workgroup of a domain gets at least one full-length tile of a head (nearly two under the
 // causal mask, where a tile walks half the keys on average), and only if the rounds of 32 tiles are well
-// filled: a last round with a few tiles costs this kernel a full round, while the 32-row kernel's workgroups
-// run faster when they have their compute unit to themselves.  Measured, 256-row tiles per head and XCD against
-// the gain over the 32-row kernel: plain 32: +9 %, 36: -10 %, 40: -9 %, 48: 0, 56: +11 %, 64: +9 %, 72: -5 %,
-// 80: +1 %, 88: +12 %, 96: +10 %; causal 48: -4 %, 56: +4 %, 64: +7 %, 72: +2 %, 88: +4 %, 96: +5 %.
+// filled: a last round with a few tiles costs this kernel a full round, while the workgroups of 128-row tiles run faster when
+// they have their compute unit to themselves.  The lines were drawn against the 32x32x16 kernel for 128-row tiles, over which
+// the wide one gains up to 12 %.  Against 128-row tiles as they run now (default_shared_kernel), by 256-row tiles per head and XCD,
+// binary16 / bfloat16, 8 heads, change of the rate: plain 32: -1 / +2 %, 36: -11 / -13, 40: -11 / -13, 48: -8 / -8, 56: +1 / +4,
+// 64: 0 / +3, 72: -6 / -9, 80: -4 / -5, 88: +1 / +4, 96: +1 / +3; causal 48: -13 / -11, 56: -3 / -1, 64: 0 / +3, 72: -5 / -4,
+// 80: -5 / -4, 88: -4 / -3, 96: -3 / -2.
 SAW_HD int default_rows_per_wavefront(int heads, int N, int d, bool causal, bool bf16) {
     (void)bf16;
     if (d != 128) return 32;
@@ -75,10 +77,13 @@ SAW_HD int resident_slots(int d, int tile_q = kTileQ) {
 // the launch takes as long as one wavefront needs to walk all K/V tiles of a head.  Then a workgroup takes 64 rows
 // instead and walks the two halves of the scan at once, two wavefronts each.  At d = 64, where two such workgroups
 // fit a compute unit (512 on the chip), it goes on paying for somewhat larger problems, most under the causal mask,
-// where the longest tile of a head sets the pace and is the one cut in two.  Measured limits, in 128-row tiles of the
-// whole problem: d = 128: 128 (beyond, the 64-row workgroups, one per compute unit, no longer run all at once: up to
-// 1.5x slower at 256); d = 64: 384 plain, 512 causal (gains of 3-10 % there, none at 768), and beyond 128 only for
-// N >= 2048: a scan of 16 tiles or fewer is too short for its halves to pay for the merge (N = 512: 25 % slower).
+// where the longest tile of a head sets the pace and is the one cut in two.  Limits, in 128-row tiles of the whole problem:
+// d = 128: 128 (beyond, the 64-row workgroups, one per compute unit, no longer run all at once: up to 1.5x slower at 256);
+// d = 64: 384 plain, 512 causal, and beyond 128 only for N >= 2048: a scan of 16 tiles or fewer is too short for its halves to
+// pay for the merge (N = 512: 25 % slower).  They were drawn against the 32x32x16 kernel (gains of 3-10 % there, none at 768).
+// Time against 128-row tiles as they run now (default_shared_kernel), binary16 and bfloat16: d = 128, 128 tiles: -4 to -32 %;
+// d = 64, plain, 128 tiles: -29 to -40 %, 256: -7 to 0 %, 384: +8 to +11 %; causal, 128: -27 to -43 %, 256: -14 to -36 %, 384:
+// -6 to -16 %, 512: 0 to +4 %.
 // 1 = one scan per workgroup, 2 = two halves.
 SAW_HD int default_kv_halves(int heads, int N, int d, bool causal, bool bf16) {
     (void)bf16;
@@ -282,9 +287,10 @@ SAW_HD bool default_phase_priority(const Schedule& s, int d, bool causal) {
 // a / b for a >= 0, b > 0.  On the GPU a division is some 40 dependent scalar and vector instructions, and the part of it
 // that depends on b alone would be computed ahead of the loop over the tiles, also where no quotient is needed: most
 // workgroups only ever see the first chunk (a < b).  With LATE nothing is computed ahead, because with short sequences
-// the time up to the first fetch counts (one head of 256 rows, d = 64: 6.5 -> 6.2 us on the GPU; 8 heads x 2048, d = 64:
-// 16.5 -> 16.2 us).  The kernel with 256-row tiles, whose scans are long, keeps the plain division: the change moves its
-// registers and costs it time (128 heads x 32768, bfloat16, causal: 30.9 -> 31.4 ms).
+// the time up to the first fetch counts: 0.2 to 0.3 us of a kernel's duration (kernel trace, a launch at a time: one head of
+// 256 rows, d = 64: 6.64 -> 6.36 us; 8 heads x 2048: 18.68 -> 18.36 us; 128 x 512, d = 128: 22.3 -> 22.1 us.  Calls in a row hide
+// most of it: 8 x 2048 takes 16.3 us either way).  The kernel with 256-row tiles, whose scans are long, keeps the plain
+// division: the change moves its registers and costs it time (128 heads x 32768, bfloat16, causal: 30.9 -> 31.4 ms).
 template <bool LATE, typename T>
 SAW_HD T quotient(T a, T b) {
     if constexpr (LATE) {
