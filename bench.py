@@ -229,7 +229,8 @@ def main():
     head = orders[0]
     r = res[head]
     traffic, misses, profile = profiled_counters(w.name, bool(ws_bytes)) if var is None else ({}, {}, None)
-    kernel = f"attn_fwd_kernel<d={w.d}, {w.dtype if not ws_bytes else 'f16 copies'}, {'causal' if w.causal else 'full'}, " \
+    # (which of the two kernels computes 128-row tiles is the library's choice and not reported: the profile named below shows it)
+    kernel = f"attn_fwd<d={w.d}, {w.dtype if not ws_bytes else 'f16 copies'}, {'causal' if w.causal else 'full'}, " \
              + ("32 rows per wavefront, the two halves of the scan at once>" if info["tile_q"] == 64
                 else f"{info['tile_q'] // 4} rows per wavefront>")
     out = {
