@@ -2160,15 +2160,16 @@ __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
     const Schedule& s = p.sched;
     const int lane0 = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wg = CAUSAL && LATE ? workgroup_of_block(s, (int)blockIdx.x) : (int)blockIdx.x;      // (LATE: 128-row tiles and shorter)
     int local = 0;           // query tiles this workgroup has processed
     for (int it = 0; it < s.local_iters; ++it) {
-        const Work w = decode_work<LATE>(s, (int)blockIdx.x, it, CAUSAL, p.sawtooth != 0);
+        const Work w = decode_work<LATE>(s, wg, it, CAUSAL, p.sawtooth != 0);
         if (w.tile >= 0) {
             const int nkv = visible_kv_tiles(s, w.tile, p.N, CAUSAL);
             const int j0 = w.backward ? nkv - 1 : 0;
             const int step = w.backward ? -1 : 1;
             if (p.trace && threadIdx.x == 0) {
-                int32_t* rec = p.trace + ((size_t)blockIdx.x * p.max_local + local) * 4;
+                int32_t* rec = p.trace + ((size_t)wg * p.max_local + local) * 4;
                 rec[0] = w.head; rec[1] = w.tile; rec[2] = j0; rec[3] = j0 + (nkv - 1) * step;
             }
             // The per-lane address tables are rebuilt for every query tile from a lane index the
@@ -2183,7 +2184,7 @@ __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
         // nor the time of the kernel with 64 rows per wavefront, whose workgroups stay in step by themselves.)
         if (w.sync_after) domain_sync(p.ticket_set, (int)blockIdx.x % kDomains, s.slots);
     }
-    if (p.trace_count && threadIdx.x == 0) p.trace_count[blockIdx.x] = local;
+    if (p.trace_count && threadIdx.x == 0) p.trace_count[wg] = local;
 }
 
 template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false>
@@ -2380,6 +2381,7 @@ int schedule_for(int B, int H, int N, int d, bool causal, bool bf16, const sawat
     if (tiles_per_wg == 0) tiles_per_wg = 2;
     if (max_slots == 0) max_slots = resident_slots(d, tile_q);
     *out = make_schedule(B * H, N, causal, launch, decode, max_slots, tiles_per_wg, tile_q, align_rounds);
+    start_longest_first(*out, d, causal);
     out->qo_streaming = v && v->qo_streaming ? v->qo_streaming : default_qo_streaming(N, d);
     return SAWATTN_OK;
 }

@@ -21,7 +21,9 @@
 //     walk the same K/V, which is where reversing the direction shortens the reuse distance; the
 //     first round of a new chunk meets cold K/V whichever way it walks, and walks forward so that
 //     causal tiles all start from key 0 together.  Taking the round index rather than a per-
-//     workgroup count keeps the whole domain walking one way when a workgroup sits a round out.
+//     workgroup count keeps the whole domain walking one way when a workgroup sits a round out;
+//   * a direct launch has one workgroup per tile, numbered chunk after chunk.  Under the causal mask they start in
+//     another order than that of their numbers, the longest of several chunks first (start_longest_first).
 #pragma once
 
 #if defined(__HIPCC__)
@@ -146,6 +148,7 @@ struct Schedule {
     int local_iters;        // local iterations every workgroup runs through (some may be idle)
     int sync_heads;         // persistent, domain decode: the workgroups of a domain wait for each other between heads
     int sync_rounds;        // ... and after every round as well (a study of Sec. 3.4's lockstep; costs time)
+    int chunks_abreast;     // direct launch: chunks whose workgroups start together, longest first (1: in the order of their numbers)
     int qo_streaming;       // 1: O tiles leave through LDS as whole non-temporal lines; 2: Q tiles arrive that way; 3: both; 4: neither
 };
 
@@ -176,6 +179,7 @@ SAW_HD Schedule make_schedule(int heads, int N, bool causal, int launch, int dec
     s.units_per_chunk = 0;
     s.sync_heads = 0;
     s.sync_rounds = 0;
+    s.chunks_abreast = 1;   // start_longest_first
     const long long total = (long long)heads * s.q_tiles;
     if (launch == kLaunchPersistent) {
         if (decode == kDecodeDomain) {
@@ -203,6 +207,41 @@ SAW_HD Schedule make_schedule(int heads, int N, bool causal, int launch, int dec
     }
     s.grid = kDomains * s.slots;
     return s;
+}
+
+// Direct launches under the causal mask: which workgroups start first.  The hardware starts them in the order of their block numbers and
+// a new one wherever one has finished.  In the order of their own numbers, chunk after chunk, the last chunk's longest
+// workgroups start when most of the work is done and finish alone: 4 chunks of 32 tiles on 64 places take 49 steps of the longest
+// tile's 32 where 33 would do.  So the workgroups of several chunks start together, longest first, and the short ones
+// fill up the end.  Not of all chunks: those of one chunk then start far apart and share less of its K and V in the
+// L2.  Time against chunk after chunk, abreast as many chunks as make 1, 3/2, 2, 3, 4 loads of the XCD, and all of them: 128 heads x 4096, d = 128:
+// -2.4, -4.7, -4.7, -4.4, -3.9, -2.0 %; 48 x 4096, d = 64: -15, -20, -20, -21, -21, -21 %; 126 x 3500, d = 128: +0.9, -0.3,
+// +0.8, +7, +10, +10 %.  At 3/2 loads, over 155 launches that were direct before: -38 to +1 %, -11 % in the mean (32 x 4096, d =
+// 128: 151 -> 130 us; 64 x 2048, d = 64: 52.7 -> 43 us).  Who computes what, and the recorded schedule, stay as they are.
+// Not at d = 128 with 3, 5 or 6 workgroups to a chunk and 2.7 loads and more: the end counts for less there than what the few workgroups
+// of a chunk share when they start together (107 heads x 2880: +9 %, 127 x 5000: +5 %, 63 x 3000: +3 %, 75 x 5000: -1 %).  Chunks of
+// 2, 4 and 8 gain all the same (111 x 3097: -22 %), as workgroups of one length would meet on the compute units otherwise.
+SAW_HD void start_longest_first(Schedule& s, int d, bool causal) {
+    if (!causal || s.launch != kLaunchGrid || s.decode != kDecodeDomain || s.tiles_per_wg != 1 || s.tile_q > kTileQ) return;
+    const int n = s.units_per_chunk, resident = resident_slots(d, s.tile_q);
+    if (n < 2 || (d == 128 && (n == 3 || n == 5 || n == 6) && 10ll * s.slots >= 27 * resident)) return;
+    const int least = (3 * resident + 2 * n - 1) / (2 * n);
+    const int groups = s.chunks_per_domain / least;
+    s.chunks_abreast = groups > 1 ? (s.chunks_per_domain + groups - 1) / groups : s.chunks_per_domain;
+}
+
+// The workgroup that the hardware's block `block` is.
+SAW_HD int workgroup_of_block(const Schedule& s, int block) {
+    if (s.chunks_abreast <= 1) return block;
+    int at = block / kDomains, first = 0, abreast = s.chunks_abreast;      // place in the group, its first chunk, its chunks
+    if (abreast < s.chunks_per_domain) {
+        const int group = at / (abreast * s.units_per_chunk);
+        first = group * abreast;
+        at -= first * s.units_per_chunk;
+        if (s.chunks_per_domain - first < abreast) abreast = s.chunks_per_domain - first;
+    }
+    const int u = at / abreast;
+    return ((first + at - u * abreast) * s.units_per_chunk + u) * kDomains + block % kDomains;
 }
 
 // Workgroups of a chunk (domain decode) or of a head (linear decode) in a direct launch, tiles of a chunk otherwise.
@@ -233,10 +272,14 @@ SAW_HD int per_chunk(const Schedule& s) {
 //   * under the mask, a direct launch of more workgroups than fit at once, with 2, 4 or 8 of them to a chunk: those of a
 //     compute unit are then equally long and make room all together.  89 of 106 of these lose, up to 10 % (2.7 % in the
 //     mean); with 16 and 32 to a chunk -9 to +4 % (-0.6 %), with 1 -7 to +3 % (-1.4 %), with others -7 to +4 % (-1.3 %).
+// Direct launches whose longest workgroups start first (start_longest_first; the last two lines hold for those in the order of their
+// numbers), d = 128: up to 47 workgroups per XCD +4 to +12 %; 48 to 64, 8 and more to a chunk: +2 to +4 %, fewer: -7 to +2 %; more than fit:
+// -14 to +2 % (the better of the two with and without precedence).
 SAW_HD bool default_shared_kernel(const Schedule& s, int d, bool causal, bool bf16) {
     if (s.slots <= 32) return false;
     if (d == 64) return true;
     const int n = per_chunk(s), resident = resident_slots(d);
+    if (s.chunks_abreast > 1) return s.slots >= 48 && (s.slots > resident || n < 8);
     if (!causal) {
         const int wgs = s.launch == kLaunchGrid ? s.slots : n;     // (persistent: what the last round of a chunk leaves)
         if (wgs <= resident || (wgs - 1) % resident >= 32) return true;
@@ -269,10 +312,21 @@ SAW_HD bool default_shared_kernel(const Schedule& s, int d, bool causal, bool bf
 //   * direct launch of more than fit.  d = 64: -5 to +2 % (-0.9 % in the mean) from twice as many on; fewer: -5 to +1 % (-1.4
 //     %) where a head is spread over 4 or 8 XCDs, two tiles and more to a chunk, -4 to +10 % (+2.2 %) otherwise (64 heads x
 //     2048: 54 against 59 us, 40 x 3968: 104 against 114 us).  d = 128: -7 to +7 % (+0.7 %); -10 to +2 % (-2.6 %) for 4/3 to
-//     twice as many, a head over 4 or 8 XCDs and five tiles and more to a chunk (5 x 23936: 844 -> 793 us).
+//     twice as many, a head over 4 or 8 XCDs and five tiles and more to a chunk (5 x 23936: 844 -> 793 us);
+//   * direct launch, longest workgroups first (the two lines above hold for the order of their numbers).  d = 64, all at once: 8 and more to
+//     a chunk, or up to 64 per XCD: 0 to +9 %, else -5 to 0 %; more than fit: -5 to +2 %, but +2 to +8 % for up to twice as many of
+//     16 and more to a chunk, a head on one XCD.  d = 128, all at once: +1 to +5 %; up to 1.6 times as many as fit: 2 or 3 to a
+//     chunk -5 to +2 %, more 0 to +6 %; 1.6 to 2.2 times: -10 to -1 % (32 x 4096: 137 -> 130 us); more: -8 to +3 % up to 32 to a
+//     chunk, -3 to +4 % above.
 SAW_HD bool default_phase_priority(const Schedule& s, int d, bool causal) {
     if (!causal) return true;
     const int rounds = s.local_iters, resident = resident_slots(d), n = per_chunk(s);
+    if (s.chunks_abreast > 1) {
+        if (d == 64) return s.slots <= resident ? n < 8 && s.slots > 64 : s.slots > 2 * resident || n < 16 || s.parts > 1;
+        if (s.slots <= resident) return false;
+        if (10ll * s.slots < 16 * resident) return n <= 3;
+        return 10ll * s.slots <= 22 * resident || n <= 32;
+    }
     if (s.launch == kLaunchGrid) {
         if (s.slots <= resident) return true;
         if (d == 64) return s.slots >= 2 * resident || (s.parts >= 4 && n > 1);
