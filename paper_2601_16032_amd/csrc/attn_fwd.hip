@@ -2374,8 +2374,11 @@ int schedule_for(int B, int H, int N, int d, bool causal, bool bf16, const sawat
     if (rows == 0) rows = default_rows_per_wavefront(B * H, N, d, causal, bf16);
     const int tile_q = rows == 64 ? 2 * kTileQ : (halves == 2 ? kTileQ / 2 : kTileQ);
     if (launch < 0) {
-        // the caller leaves the launch open: persistent, or for short heads the direct launch with one tile each
+        // the caller leaves the launch open: persistent, or for short heads and uneven rounds the direct launch with one tile each
         launch = decode == kDecodeDomain && max_slots == 0 ? default_launch(B * H, N, d, causal, tile_q) : kLaunchPersistent;
+        if (launch == kLaunchPersistent && decode == kDecodeDomain && max_slots == 0 && tiles_per_wg < 2 && !align_rounds &&
+            direct_instead(B * H, N, d, causal, tile_q))
+            launch = kLaunchGrid;
         if (launch == kLaunchGrid && tiles_per_wg == 0) tiles_per_wg = 1;
     }
     if (tiles_per_wg == 0) tiles_per_wg = 2;

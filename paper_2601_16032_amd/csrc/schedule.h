@@ -131,6 +131,56 @@ SAW_HD int default_launch(int heads, int N, int d, bool causal, int tile_q) {
 }
 enum { kDecodeDomain = 0, kDecodeLinear = 1 };
 
+// K/V tiles of the busiest workgroup of a persistent hand-out over what an even share would be (the longest tile of a chunk, if that
+// is more).  `n` tiles per chunk, under the causal mask of 1 .. n parts, otherwise of one; rounds as in decode_work.
+SAW_HD float persistent_imbalance(int n, long long chunks, int resident, bool causal) {
+    const int slots = n < resident ? n : resident, rounds = (n + slots - 1) / slots;
+    double most = 0;
+    for (int slot = 0; slot < slots; ++slot) {
+        double in_chunk[2] = {0, 0};                  // the rounds of a chunk that begins with an even / odd one
+        for (int first = 0; first < 2; ++first)
+            for (int r = 0; r < rounds; ++r) {
+                const int u = r * slots + ((r + first) & 1 ? slots - 1 - slot : slot);
+                if (u < n) in_chunk[first] += causal ? n - u : 1;
+            }
+        const double all = rounds % 2 == 0 ? chunks * in_chunk[0] : (chunks + 1) / 2 * in_chunk[0] + chunks / 2 * in_chunk[1];
+        if (all > most) most = all;
+    }
+    const double longest = causal ? n : 1, share = (causal ? n * (n + 1.0) / 2 : n) * chunks / resident;
+    return (float)(most / (share > longest ? share : longest));
+}
+
+// Whether a launch that default_launch leaves persistent is faster as a direct one (under the mask with its longest workgroups first): the
+// dispatcher evens out what a fixed hand-out leaves uneven.  What is given up is the turn-around of the sawtooth order, which
+// exists only where a chunk takes several rounds.  Change of the time from persistent to direct, n tiles per chunk on C chunks per XCD:
+//   * causal, one round per chunk.  An odd number of rounds leaves somebody with an unpaired one: -6 to -38 % at C = 3, 5, -4 to
+//     -37 % at 7 and more.  With an even number all workgroups have the same, but n of them fill the compute units evenly only where
+//     n is a multiple of 32: d = 128, n = 34 to 56: -35 to -3 %, 60: -2 to -1 %, 64: +1 to +2 %; d = 64, n = 34 to 52: -22 to 0 %,
+//     60: -6 to +2 %, 64: -6 to +1 %, 72 to 88: -22 to -6 %, 96: -4 to -2 %;
+//   * several rounds per chunk, by the imbalance above.  Causal, d = 64: 1.1 to 1.2: -3 to -6 %, 1.3 to 1.8: -3 to -16 %; d = 128: 1.17: -3 %,
+//     1.3 to 1.8: -1 to -17 %.  No mask, two chunks and more: 1.3 and 1.5: -6 to -9 %, 1.7 and more: -18 to -27 % (40 heads x 8320, d =
+//     128, bfloat16: 2002 -> 1466 us); one chunk, d = 64: 1.1 and 1.3: -1 to -2 %, 1.5 and more: -5 to -9 %; d = 128: 1.75 and more: -5 %, else 0.
+//     Below that the persistent launch stays, although at d = 64 under the mask it is 2 to 9 % slower: it has the turn-around;
+//   * 64-row tiles: causal, one round per chunk, C = 3 and more, odd: -16 to -21 %; C = 2, n = 47: -10 %, 61: +2 %.
+SAW_HD bool direct_instead(int heads, int N, int d, bool causal, int tile_q) {
+    if (tile_q > kTileQ) return false;
+    const int parts = kDomains / gcd_i(heads, kDomains);
+    const int q_tiles = (N + tile_q - 1) / tile_q;
+    const int n = (q_tiles + parts - 1) / parts, resident = resident_slots(d, tile_q);
+    const long long chunks = ((long long)heads * parts) / kDomains;
+    if (n <= resident) {
+        if (!causal || chunks < 2) return false;
+        if (tile_q < kTileQ) return chunks == 2 ? n > 32 && n < 56 : chunks % 2 != 0;
+        if (d == 128) return chunks == 2 ? n > 32 && n < 64 : n <= 60 || (chunks % 2 != 0 && chunks < 7);
+        if (chunks == 2) return (n > 32 && n <= 48) || (n > 64 && n < 96);
+        return chunks % 2 != 0 || n % 32 != 0;
+    }
+    if (tile_q < kTileQ) return false;
+    const float imbalance = persistent_imbalance(n, chunks, resident, causal);
+    if (causal) return d == 64 ? imbalance >= 1.1f : chunks > 1 && imbalance >= 1.15f;
+    return chunks > 1 ? imbalance >= 1.1f : d == 64 && imbalance >= 1.4f;
+}
+
 struct Schedule {
     int heads;              // B*H
     int tile_q;             // query rows per workgroup tile: kTileQ, or 2*kTileQ in the wide variant

@@ -1,4 +1,4 @@
-"""Which workgroups of a direct causal launch start first, and what computes them.
+"""Which workgroups of a direct causal launch start first, which launches are direct, and what computes them.
 
 The order in which workgroups start is no part of the schedule: every workgroup computes and records what the schedule oracle lists for
 its number.  The CPU tests compile schedule.h, the header that the library is built from."""
@@ -94,11 +94,36 @@ def test_what_computes_a_launch_whose_longest_workgroups_start_first(ask):
     assert not wrong, wrong
 
 
-# Causal launches of every kernel and of one and two groups of chunks.
+DIRECT = [     # (B, H, N, d, causal): the launch that attn_fwd picks
+    # causal, one round per chunk: an odd number of rounds, an even one that does not fill the compute units evenly
+    ((1, 24, 5000, 128, True), "grid"), ((1, 6, 16667, 128, True), "grid"), ((1, 24, 8192, 128, True), "grid"), ((1, 56, 8192, 128, True), "persistent"),
+    ((1, 16, 4352, 128, True), "grid"), ((1, 16, 8000, 128, True), "grid"), ((1, 16, 8192, 128, True), "persistent"), ((1, 32, 7680, 128, True), "grid"),
+    ((1, 32, 7808, 128, True), "persistent"), ((1, 16, 6144, 64, True), "grid"), ((1, 16, 7680, 64, True), "persistent"), ((1, 16, 9216, 64, True), "grid"),
+    ((1, 16, 12288, 64, True), "persistent"), ((1, 32, 7680, 64, True), "grid"), ((1, 32, 8192, 64, True), "persistent"), ((1, 8, 10000, 64, True), "persistent"),
+    # several rounds per chunk
+    ((1, 16, 13440, 64, True), "grid"), ((1, 16, 23296, 64, True), "persistent"), ((8, 1, 32768, 64, True), "grid"), ((1, 8, 27008, 64, True), "persistent"),
+    ((1, 16, 8960, 128, True), "grid"), ((1, 16, 14720, 128, True), "persistent"), ((1, 8, 17920, 128, True), "persistent"),
+    ((1, 16, 8320, 128, False), "grid"), ((1, 8, 8320, 128, False), "persistent"), ((1, 16, 12544, 64, False), "grid"), ((1, 16, 24576, 64, False), "persistent"),
+    ((1, 1, 131072, 64, False), "grid"), ((1, 8, 18432, 64, False), "persistent"), ((1, 8, 24576, 64, False), "persistent"),
+    # 64-row tiles
+    ((1, 24, 2600, 64, True), "grid"), ((1, 16, 3000, 64, True), "grid"), ((1, 16, 3900, 64, True), "persistent"), ((1, 16, 2048, 64, True), "persistent"),
+]
+
+
+@pytest.mark.parametrize("shape,want", DIRECT)
+def test_which_launches_are_direct(shape, want):
+    info = binding.attn_fwd_launch_info(*shape)
+    assert ["persistent", "grid"][info["launch"]] == want and info["tiles_per_workgroup"] == 1
+    # a variant that names the launch, or the number of workgroups, gets what it names
+    assert binding.attn_fwd_variant_launch_info(*shape, binding.variant(launch="persistent"))["launch"] == binding.LAUNCH_PERSISTENT
+    assert binding.attn_fwd_variant_launch_info(*shape, binding.variant(launch="auto", slots_per_domain=7))["launch"] == binding.LAUNCH_PERSISTENT
+
+
+# Causal launches of every kernel and of one and two groups of chunks, and the plain ones that are direct now.
 GPU_CASES = [
     (17, 2048, 128, "f16", True, "A"), (25, 1800, 128, "bf16", True, "S"), (35, 2100, 128, "f16", True, "P"), (97, 1100, 128, "bf16", True, "P"),
     (17, 3100, 128, "f16", True, "S"), (17, 2040, 64, "bf16", True, "S"), (49, 1100, 64, "f16", True, "P"), (64, 2000, 64, "bf16", True, "S"),
-    (11, 1400, 128, "bf16", True, None),
+    (24, 2600, 64, "f16", True, None), (11, 1400, 128, "bf16", True, None), (24, 5000, 128, "f16", True, None), (16, 8300, 128, "bf16", False, None),
 ]
 
 
