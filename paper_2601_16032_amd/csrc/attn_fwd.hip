@@ -22,12 +22,12 @@
 // query tile's scan is a software-pipelined run of full, unmasked K/V tiles (pipelined_range) plus, at one end, a short
 // run of masked tiles (general_range).  With 64-row tiles it walks the two halves of a scan at once (HALVES).
 //
-// The same with 256-row tiles, head dimension 128 (NH = 2 in the templates, pipelined_range_wide): a wavefront owns two
-// 32-row halves, one workgroup per CU, and every K / V^T fragment read from LDS feeds one MFMA per half.
-//
 // attn_fwd_shared_kernel (scan_tiles), 128-row tiles where workgroups share the compute units: both contractions on
 // v_mfma_f32_16x16x32, layouts as described there.  Four lanes share a query row, row sums are a product with ones,
 // the running maximum is compared on raw scores, and masked tiles stay in the pipeline.
+//
+// attn_fwd_kernel with 256-row tiles, head dimension 128 (NH = 2 in its template, scan_tiles_wide): the same with 64 query rows per
+// wavefront and one workgroup per CU, so that every K / V^T fragment read from LDS feeds four MFMAs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -309,53 +309,9 @@ struct ReadAddr {
     }
 };
 
-// MFMAs of the wide variant, written out so that the register file of every operand is fixed: with
-// more than 256 registers per wavefront the accumulation registers (AccVGPRs) have to hold what only
-// the matrix pipe touches -- the O^T accumulators and the Q^T fragments -- and nothing the vector ALU
-// reads, or every use costs a copy.  The compiler does not see these as MFMAs and inserts no wait
-// states for them; mfma_settle_*() is placed wherever the vector ALU reads an accumulator that the
-// few preceding instructions may still be writing (8 passes + 3 wait states).
-template <bool BF16>
-__device__ __forceinline__ void mfma_s_first(f16v& acc, u4 k_frag, const u4& q_frag) {
-    if constexpr (BF16) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(k_frag), "a"(q_frag));
-    else asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, 0" : "=&v"(acc) : "v"(k_frag), "a"(q_frag));
-}
-template <bool BF16>
-__device__ __forceinline__ void mfma_s(f16v& acc, u4 k_frag, const u4& q_frag) {
-    if constexpr (BF16) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(k_frag), "a"(q_frag));
-    else asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(k_frag), "a"(q_frag));
-}
-__device__ __forceinline__ void mfma_o(f16v& acc, s8 v_frag, const u4& p_frag) {
-    asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(v_frag), "v"(p_frag));
-}
-// The accumulators pass through the statement, so that no use of them can be scheduled ahead of it.
-__device__ __forceinline__ void mfma_settle_v(f16v& a0, f16v& a1, f16v& a2, f16v& a3) {
-    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3));
-}
-__device__ __forceinline__ void mfma_settle_v(f16v& a0, f16v& a1) {
-    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(a0), "+v"(a1));
-}
-template <int NACC>
-__device__ __forceinline__ void mfma_settle_a(f16v (&acc)[NACC]) {
-    asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
-#pragma unroll
-    for (int i = 0; i < NACC; ++i) asm volatile("" : "+a"(acc[i]));
-}
-// The other direction: accumulators that vector instructions (or the compiler's copies into accumulation
-// registers) may just have written are placed in their register file here, and the MFMAs that read them
-// start a few wait states later.
-template <int NACC>
-__device__ __forceinline__ void mfma_guard(f16v (&acc)[NACC]) {
-#pragma unroll
-    for (int i = 0; i < NACC; ++i) asm volatile("" : "+a"(acc[i]));
-    asm volatile("s_nop 7" ::: "memory");
-}
-
 // One K/V tile for one wavefront out of the LDS buffers `ra` points at: S^T = K Q^T, softmax
 // update, O^T += V^T P^T.
-// WIDE: the tile state is the wide variant's -- Q^T fragments and O^T accumulators live in accumulation
-// registers and the MFMAs are the written-out ones.
-template <int D, bool BF16, bool CAUSAL, bool MASKED, bool WIDE = false>
+template <int D, bool BF16, bool CAUSAL, bool MASKED>
 __device__ __forceinline__ void compute_tile(TileState<D>& st, const ReadAddr<D>& ra, float c, int kv0, int qrow, int lane,
                                              int N) {
     using G = Geo<D>;
@@ -378,21 +334,10 @@ __device__ __forceinline__ void compute_tile(TileState<D>& st, const ReadAddr<D>
                 a[ks + 2][0] = *(LDS_PTR(u4))(size_t)(ra.k[ks + 2]);
                 a[ks + 2][1] = *(LDS_PTR(u4))(size_t)(ra.k[ks + 2] + 32 * G::kRowBytes);
             }
-            if constexpr (WIDE) {
-                if (ks == 0) {
-                    mfma_s_first<BF16>(s[0], a[ks][0], st.qf[ks]);
-                    mfma_s_first<BF16>(s[1], a[ks][1], st.qf[ks]);
-                } else {
-                    mfma_s<BF16>(s[0], a[ks][0], st.qf[ks]);
-                    mfma_s<BF16>(s[1], a[ks][1], st.qf[ks]);
-                }
-            } else {
-                s[0] = mfma_16bit<BF16>(a[ks][0], st.qf[ks], s[0]);
-                s[1] = mfma_16bit<BF16>(a[ks][1], st.qf[ks], s[1]);
-            }
+            s[0] = mfma_16bit<BF16>(a[ks][0], st.qf[ks], s[0]);
+            s[1] = mfma_16bit<BF16>(a[ks][1], st.qf[ks], s[1]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (WIDE) mfma_settle_v(s[0], s[1]);
     }
     // ---- mask: keys at or beyond N, and keys after the query under the causal mask, get the score -inf, which
     //      c > 0 turns into the probability 0.  Register r of block b is key 32b + 8(r/4) + 4g + r%4 of the tile:
@@ -457,19 +402,16 @@ __device__ __forceinline__ void compute_tile(TileState<D>& st, const ReadAddr<D>
         };
         s8 av[NSTEP];
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (WIDE) mfma_guard(st.o);
 #pragma unroll
         for (int idx = 0; idx < AHEAD; ++idx) av[idx] = read_a(idx);
 #pragma unroll
         for (int idx = 0; idx < NSTEP; ++idx) {
             if (idx + AHEAD < NSTEP) av[idx + AHEAD] = read_a(idx + AHEAD);
             const int ks = idx / DB, db = idx % DB;
-            if constexpr (WIDE) mfma_o(st.o[db], av[idx], pf[ks]);
-            else st.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, pf[ks]),
-                                                                   st.o[db], 0, 0, 0);
+            st.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, pf[ks]),
+                                                              st.o[db], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (WIDE) mfma_settle_a(st.o);
     }
 }
 
@@ -477,8 +419,8 @@ __device__ __forceinline__ void compute_tile(TileState<D>& st, const ReadAddr<D>
 // all without the mask code).  Self-contained: fetches its first tile itself and leaves with every
 // wavefront past the barrier that follows its last tile.  Iteration `it` uses LDS buffer pair it & 1
 // and, while computing, fetches the tile of iteration it+1 into the other pair.
-template <int D, bool BF16, bool CAUSAL, bool MASKED, int NH>
-__device__ __forceinline__ void general_range(TileState<D> (&st)[NH], const LaneMap<D>& lm, const char* Kh, const char* Vh, int N,
+template <int D, bool BF16, bool CAUSAL, bool MASKED>
+__device__ __forceinline__ void general_range(TileState<D>& st, const LaneMap<D>& lm, const char* Kh, const char* Vh, int N,
                                               float c, int j_first, int step, int count, int qw0, int qrow, int lane,
                                               LDS_PTR(char) lds, bool idle = false) {
     // idle: this wavefront fetches and keeps the barriers like the others but computes nothing (its rows are another
@@ -519,11 +461,8 @@ __device__ __forceinline__ void general_range(TileState<D> (&st)[NH], const Lane
             else tile_to_lds<D>(Vh, j + step, off, lm, lds0 + (2 + (cur ^ 1)) * G::kTile);
         }
         const int kv0 = j * kTileKV;
-#pragma unroll
-        for (int h = 0; h < NH; ++h) {   // half h: query rows qw0 + 32h .. +31 (this lane: qrow + 32h)
-            const bool active = !idle && qw0 + 32 * h < N && (!CAUSAL || kv0 <= qw0 + 32 * h + 31);
-            if (active) compute_tile<D, BF16, CAUSAL, MASKED, NH == 2>(st[h], ra, c, kv0, qrow + 32 * h, lane, N);
-        }
+        const bool active = !idle && qw0 < N && (!CAUSAL || kv0 <= qw0 + 31);
+        if (active) compute_tile<D, BF16, CAUSAL, MASKED>(st, ra, c, kv0, qrow, lane, N);
         ra.flip(cur ? -G::kTile : G::kTile);
         if (more) {
             if constexpr (BF16) regs_to_lds_f16<D>(vreg, lm, lane, lds + (2 + (cur ^ 1)) * G::kTile);
@@ -840,12 +779,13 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
 // one per block of 16 query rows.
 // Why this shape and not 32x32x16: with live operands the chip is at its power limit, and a 16x16x32 reads and writes
 // half as many accumulators per multiply-add.  MFMA-only loops on N(0, 1/4) operands: 1912 against 1671 TFLOP/s.
-template <int D>
+template <int D, int QT = 2>
 struct NarrowState {
-    u4 qf[D / 32][2];     // Q^T as B operand: lane holds Q[row 16*qt + l%16][32*ks + 8*(l/16) .. +7] in qf[ks][qt]
-    f4 o[D / 16][2];      // O^T accumulators: o[db][qt][r] is column 16*db + 4*(l/16) + r of row 16*qt + l%16
-    float M[2];           // [qt]: reference maximum of score*c (log2 domain), same in the four lanes of a query row
-    f4 L[2];              // [qt]: running sum of the query row, in every element (a product with ones)
+    u4 qf[D / 32][QT];    // Q^T as B operand: lane holds Q[row 16*qt + l%16][32*ks + 8*(l/16) .. +7] in qf[ks][qt]
+    f4 o[D / 16][QT];     // O^T accumulators: o[db][qt][r] is column 16*db + 4*(l/16) + r of row 16*qt + l%16
+    float M[QT];          // [qt]: reference maximum of score*c (log2 domain), same in the four lanes of a query row
+    f4 L[QT];             // [qt]: running sum of the query row, a product with ones: in every element (QT = 4: in element 0 of lanes
+                          // 0..15, zeros elsewhere)
 };
 
 // Lane-constant addresses.  A tile is filled as described at Geo, with a permutation of its own: chunk cc of row r sits
@@ -907,6 +847,11 @@ __device__ __forceinline__ float quad_max(float x) {
     float e, o;
     lane_rows(x, e, o);
     return pair_max(fmaxf(e, o));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+    float e, o;
+    lane_rows(x, e, o);
+    return pair_sum(e + o);
 }
 
 // Resource descriptor of a K/V tile: `bytes` of it exist.  Rows past the end of the sequence, and whole tiles past the
@@ -1313,397 +1258,437 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
 }
 
 // ------------------------------------------------------------------------------------------------
-// Wide variant (head dimension 128): a wavefront owns 64 query rows as two 32-row
-// halves, a workgroup 256 rows, one workgroup per CU.  Every K and V^T fragment read from LDS feeds
-// two MFMAs, one per half, which halves the LDS operand traffic and the L2 -> LDS traffic per flop.
+// 256-row tiles (head dimension 128): a wavefront owns 64 query rows, as four blocks of 16, and a workgroup has the compute
+// unit to itself.  Products, layouts, masks, row sums and the running maximum are those of scan_tiles; every K and V^T
+// fragment read from LDS feeds four MFMAs instead of two, which halves the operand traffic from LDS and the L2 -> LDS
+// traffic per multiply-add.
 //
-// With one wavefront per SIMD the instruction stream of that wavefront is all the SIMD has: an MFMA
-// occupies the matrix pipe for 32 cycles, and whatever the wavefront issues between two MFMAs
-// (about 5 cycles per vector instruction, 9 per exponential) has to fit under those 32 cycles or the
-// pipe idles.  So the vector work per score is cut to the exponential, half a convert, half a
-// maximum and the row sum, and spread evenly over the MFMAs:
-//   * one FMA per score (score * c - M, c = scale*log2(e) applied to the fp32 score as everywhere else); the
-//     row maximum is tracked on the raw scores against the per-row limit (M + slack) / c, so that the test
-//     "some score exceeds the slack" costs no multiply;
-//   * S^T is computed block by block (kv rows 0..31 of the tile, then 32..63): the exponentials of
-//     the second block of tile i run under the first-block MFMAs of S(i+1)^T, which do not touch it,
-//     the row sums of tile i under the second-block MFMAs; under the MFMAs of O^T += V(i)^T P(i)^T
-//     come the maxima of S(i+1) and the exponentials of its first block, which go into the operand
-//     registers of P as the second product releases them.  Those exponentials are taken before the
-//     maxima are all known; when a maximum exceeds the slack they are redone (rarely).
-// K and V are fetched three and two tiles ahead into four LDS buffers each, so that a fetch has two
-// whole iterations to land.
+// What bounds it: with live operands the power limit, then the issue of its one wavefront per SIMD.  Per tile 136 MFMAs of 16
+// cycles (128 for the products, 8 for the row sums), 64 exponentials, 128 other vector instructions of the softmax and 48 LDS
+// reads: about 3400 cycles against 2176 of MFMA time.  Its predecessor on 32x32x16 MFMAs (half as many, row sums by 64 vector
+// additions) took 3130 with all operands zero, where the clock plays no part, but with live ones the chip took more clock from it
+// than that: 16x16x32 reads and writes half as many accumulators per multiply-add.  32 heads x 16384, from 32x32x16 to this: binary16
+// 3592 -> 3403 us, causal 1874 -> 1776 us, bfloat16 3785 -> 3445 us, causal 1960 -> 1810 us; 128 heads x 32768, bfloat16, causal: 30.5
+// -> 28.7 ms.  (Left out, binary16, no mask: exponentials -8 %, fetches -8 %, row sums -3 %, maxima and shifts -4 %.)
+//
+// What is spread how: exponentials and converts of tile i under the MFMAs of S(i+1)^T, maxima and shifted scores of tile i+1 under
+// those of O^T += V(i)^T P(i)^T, one to two vector instructions per MFMA.  K(i+4) and V(i+2) are fetched at the start of iteration
+// i, one load behind every other MFMA, into four buffers each, and have until the barrier of iteration i+1 (spread over the
+// second product, with half an iteration less: +4 %).  By then V(i+1) is needed, whose first fragments are read ahead of the barrier of
+// iteration i+1 like K's first ones ahead of the loop's branch (first V fragments behind the barrier: +2 %).  Fragments are
+// read two at a time, one pair ahead, and used in the order second, first: one wait covers both.
+//
+// MFMAs are inline assembly with the register file of every operand fixed: with more than 256 registers per wavefront the accumulation
+// registers have to hold what only the matrix pipe touches (O^T, Q^T, the row sums) and nothing the vector ALU reads, or every use
+// costs a copy.  The compiler does not see them as MFMAs and inserts no wait states; wide_settle_*() stands wherever vector
+// instructions read what the last few MFMAs may still be writing (4 passes + 3 wait states), wide_guard() where MFMAs read
+// accumulators that vector instructions have just written.  In the loop the distance is kept by the order: the first maximum reads
+// the first block of scores, 48 MFMAs old, and the last block is read 16 MFMAs after its last one.
 constexpr int kWideBuffers = 4;
 constexpr int kWideLdsBytes = 2 * kWideBuffers * Geo<128>::kTile;
 
 template <bool BF16>
-__device__ __forceinline__ void pipelined_range_wide(TileState<128> (&st)[2], const LaneMap<128>& lm, const char* Kh,
-                                                     const char* Vh, float c, int j_first, int step, int count, int lane,
-                                                     LDS_PTR(char) lds) {
-    constexpr int D = 128;
+__device__ __forceinline__ void wide_s_first(f4& acc, const u4& k, const u4& q) {
+    if constexpr (BF16) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(k), "a"(q));
+    else asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=&v"(acc) : "v"(k), "a"(q));
+}
+template <bool BF16>
+__device__ __forceinline__ void wide_s(f4& acc, const u4& k, const u4& q) {
+    if constexpr (BF16) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(k), "a"(q));
+    else asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(k), "a"(q));
+}
+__device__ __forceinline__ void wide_o(f4& acc, const u4& v, const u4& p) {
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(v), "v"(p));
+}
+__device__ __forceinline__ void wide_sum(f4& acc, const u4& ones, const u4& p) {
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "a"(ones), "v"(p));
+}
+// The accumulators pass through these statements, so that no use of them can be scheduled ahead of the wait (or, wide_guard, behind it).
+__device__ __forceinline__ void wide_settle_s(f4 (&A)[4][4]) {
+    asm volatile("s_nop 15" ::: "memory");
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) asm volatile("" : "+v"(A[kb][0]), "+v"(A[kb][1]), "+v"(A[kb][2]), "+v"(A[kb][3]));
+}
+__device__ __forceinline__ void wide_hold_o(NarrowState<128, 4>& st) {
+#pragma unroll
+    for (int db = 0; db < 8; ++db) asm volatile("" : "+a"(st.o[db][0]), "+a"(st.o[db][1]), "+a"(st.o[db][2]), "+a"(st.o[db][3]));
+    asm volatile("" : "+a"(st.L[0]), "+a"(st.L[1]), "+a"(st.L[2]), "+a"(st.L[3]));
+}
+__device__ __forceinline__ void wide_settle_o(NarrowState<128, 4>& st) {
+    asm volatile("s_nop 15" ::: "memory");
+    wide_hold_o(st);
+}
+__device__ __forceinline__ void wide_guard_o(NarrowState<128, 4>& st) {
+    wide_hold_o(st);
+    asm volatile("s_nop 7" ::: "memory");
+}
+
+template <bool BF16, bool CAUSAL>
+__device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const NarrowMap<128>& lm, const char* Kh, const char* Vh, int N, float c,
+                                                int j0, int step, int nkv, int qw0, int lane, LDS_PTR(char) lds) {
+    constexpr int D = 128, QT = 4;
     using G = Geo<D>;
-    constexpr int KS = D / 16, DB = D / 32;
-    constexpr int NA = 2 * KS;            // K fragments of one tile (each feeds two MFMAs)
-    constexpr int NB = 4 * DB;            // V^T fragments of one tile (each feeds two MFMAs)
-    constexpr int NL = G::kLoadsPerWave;
+    constexpr int KS = 4, DB = 8, NA = 16, NB = 16, NL = G::kLoadsPerWave, TA = 64, TB = 64;
+    constexpr int LA = 2;                              // fragments read ahead of their use
     constexpr unsigned VB = kWideBuffers * G::kTile;   // V buffers follow the K buffers
-    constexpr int RA = 2;                 // fragments read ahead where fragments are read one by one (first and last tile)
-    if (count <= 0) return;
     const unsigned lds0 = (unsigned)(size_t)lds;
-    float L_hi[2] = {0.f, 0.f};   // second partials of the running sums, folded into st[h].L
-    const _Float16 one = opaque_one();
-    f16v S[2][2];                 // [half][block]: raw scores; pair u = 0..15 of a half is S[h][u / 8][2 * (u % 8) .. + 1]
-    float nM[2], lim[2];          // [half]: -M (log2 domain), and the raw score above which M has to be raised
-    u4 pf[2][4];                  // [half][contraction step]: probabilities as B operands; pair u is pf[h][u / 4][u % 4]
-    float e0[2][16], e1[2][16];
-    float tmax_ahead[2] = {0.f, 0.f};   // this lane's maximum of the raw scores of the tile one ahead (never below lim)
-    // bfloat16 inputs: K stays bfloat16 (direct loads, bfloat16 MFMAs for S^T); V travels global -> registers ->
-    // binary16 -> LDS, because the probabilities are binary16.  vreg holds this wavefront's share of the V tile one
-    // ahead between its load (end of an iteration) and its conversion (under the second-block MFMAs of the next).
-    u4 vreg[NL];
-    const unsigned v_store = lds0 + VB + lm.fill_dst + lane * 16;   // this lane's 16 bytes of load 0 in V buffer 0
-    mfma_guard(st[0].o);
-    mfma_guard(st[1].o);
+    const int g = lane >> 4;
+    // A operand of the row sums: binary16 ones in its first row, zeros in the others (all ones: +0.7 %, the zeros switch nothing)
+    const unsigned one = (lane & 15) != 0 ? 0u : 0x3c003c00u;
+    u4 ones = {one, one, one, one};
+    asm volatile("" : "+a"(ones));
+    f4 A[4][QT];        // S^T of the tile one ahead: block (kb, qt) = keys 16kb.. x query rows 16qt..
+    float x[16 * QT];   // score*c - M of the current tile, index 16*qt + 4*kb + r
+    u4 pf[2][QT];       // its probabilities as B operands: pf[kh][qt] = keys 32kh..32kh+31
+    u4 vreg[NL];        // bfloat16 V chunks in flight (BF16 only)
+    float lim[QT], mx[QT];
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) lim[qt] = -INFINITY;
 
-    // Tile i of the range lives in K buffer i & 3 and V buffer i & 3.  Fetches beyond the range re-fetch its
-    // last tile into a buffer nobody reads, which keeps the loop free of special cases.
-    auto tile_base = [&](const char* head, int i) {
-        const int ic = i < count ? i : count - 1;
-        return head + (size_t)(j_first + ic * step) * kTileKV * G::kRowBytes;
-    };
-    auto fetch_k = [&](int i, int l) { load_to_lds_16B(tile_base(Kh, i), lm.fill_src[l], lds0 + (i & 3) * G::kTile + lm.fill_dst + l * 4096); };
-    auto fetch_v = [&](int i, int l) { load_to_lds_16B(tile_base(Vh, i), lm.fill_src[l], lds0 + VB + (i & 3) * G::kTile + lm.fill_dst + l * 4096); };
-    // LDS read addresses of this lane: K of the tile one ahead (buffer 1 at the start), V of the current tile
-    unsigned rk[KS], rv[DB][2];
+    unsigned rk[KS], rv[DB];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) rk[ks] = lds0 + G::kTile + lm.k_rd[ks];
+    for (int ks = 0; ks < KS; ++ks) rk[ks] = lds0 + lm.k_rd[ks];
 #pragma unroll
-    for (int db = 0; db < DB; ++db) { rv[db][0] = lds0 + VB + lm.v_rd[db][0]; rv[db][1] = lds0 + VB + lm.v_rd[db][1]; }
-    // K fragment (ks, b): contraction step ks, kv rows 32b .. 32b+31
-    auto k_read = [&](int ks, int b) -> u4 { return *(LDS_PTR(u4))(size_t)(rk[ks] + b * 32 * G::kRowBytes); };
-    auto v_read = [&](int idx) -> s8 {
-        const int ks = idx / DB, db = idx % DB;
-        const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s4))(size_t)(rv[db][0] + ks * 16 * G::kRowBytes));
-        const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s4))(size_t)(rv[db][1] + ks * 16 * G::kRowBytes));
-        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    };
-    // Softmax work items of half h, pair u = 0..15: the two exponentials, the convert into the B operand,
-    // the addition to the running sum.
-    auto exp2_pair = [&](int h, int u) {
-        const float x0 = __builtin_fmaf(S[h][u / 8][2 * (u % 8)], c, nM[h]);
-        const float x1 = __builtin_fmaf(S[h][u / 8][2 * (u % 8) + 1], c, nM[h]);
-        e0[h][u] = fast_exp2(x0);
-        e1[h][u] = fast_exp2(x1);
-    };
-    auto convert_pair = [&](int h, int u) {
-        pf[h][u / 4][u % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e0[h][u], e1[h][u]}, h2));
-    };
-    auto sum_pair = [&](int h, int u) {
-        const unsigned word = pf[h][u / 4][u % 4];   // (a copy: bit casts of a vector element do not read that element)
-        add_pair(st[h].L, L_hi[h], __builtin_bit_cast(h2, word), one);
-    };
-    auto first_block_probabilities = [&](int h) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) { exp2_pair(h, u); convert_pair(h, u); }
-    };
-    auto set_reference = [&](int h) {
-        nM[h] = -st[h].M;
-        // (c is never zero.  The select stays all the same: without it the compiler allocates this kernel's
-        // registers differently and spills around the hand-placed MFMAs.)
-        lim[h] = c > 0.f ? (st[h].M + kRescaleSlack) / c : INFINITY;
-    };
+    for (int db = 0; db < DB; ++db) rv[db] = lds0 + VB + lm.v_rd[db];
 
-    // ---------------------------------------------------------------- prologue: K(0..2), V(0..1) on their way, S(0)
+    // Position p of the scan lives in K buffer p & 3 and V buffer p & 3.  Fetches beyond the scan re-fetch its last tile into a buffer
+    // nobody reads.  The rows that the last tile of the sequence lacks repeat row N-1: masked before use.
+    auto tile_of = [&](int p) { return j0 + (p < nkv ? p : nkv - 1) * step; };
+    auto offsets = [&](int j, unsigned (&off)[NL]) {
+        const int left = N - j * kTileKV;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+        for (int l = 0; l < NL; ++l) off[l] = lm.fill_src + l * 4096;
+        if (left < kTileKV) {
 #pragma unroll
-        for (int l = 0; l < NL; ++l) fetch_k(i, l);
-        if constexpr (!BF16) {
-            if (i < 2) {
-#pragma unroll
-                for (int l = 0; l < NL; ++l) fetch_v(i, l);
+            for (int l = 0; l < NL; ++l) {
+                const unsigned row = off[l] / G::kRowBytes;
+                off[l] = (row < (unsigned)left ? row : (unsigned)left - 1) * G::kRowBytes + off[l] % G::kRowBytes;
             }
         }
-    }
+    };
+    unsigned off_k[NL], off_v[NL];
+    auto base_of = [&](const char* head, int j) { return head + (size_t)j * G::kTile; };
+    auto fetch = [&](const char* head, int p, unsigned buffers, unsigned (&off)[NL]) {
+        const int j = tile_of(p);
+        offsets(j, off);
+#pragma unroll
+        for (int l = 0; l < NL; ++l) load_to_lds_16B(base_of(head, j), off[l], buffers + (p & 3) * G::kTile + lm.fill_dst + l * 4096);
+    };
+    auto v_to_regs = [&](const char* base) {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) vreg[l] = *reinterpret_cast<const u4*>(base + off_v[l]);
+    };
+    auto convert_word = [&](int w, unsigned dst) {
+        f2 y;
+        const unsigned word = vreg[w / 4][w % 4];
+        y[0] = __builtin_bit_cast(float, word << 16);
+        y[1] = __builtin_bit_cast(float, word & 0xffff0000u);
+        vreg[w / 4][w % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(y, h2));
+        if (w % 4 == 3) *(LDS_PTR(u4))(size_t)(dst + (w / 4) * 4096 + lane * 16) = vreg[w / 4];
+    };
+    constexpr int CW = NL * 4;
+    auto k_read = [&](int m) -> u4 { return *(LDS_PTR(u4))(size_t)(rk[m % KS] + (m / KS) * 16 * G::kRowBytes); };
+    auto v_read = [&](int m) -> u4 {
+        const unsigned at = rv[m % DB] + (m / DB) * 32 * G::kRowBytes;
+        const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s4))(size_t)at);
+        const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s4))(size_t)(at + 16 * G::kRowBytes));
+        return __builtin_bit_cast(u4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    auto s_mfma = [&](int m, int qt, const u4& a, bool first) {
+        if (first) wide_s_first<BF16>(A[m / KS][qt], a, st.qf[m % KS][qt]);
+        else wide_s<BF16>(A[m / KS][qt], a, st.qf[m % KS][qt]);
+    };
+    auto o_mfma = [&](int m, int qt, const u4& a) {
+        wide_o(st.o[m % DB][qt], a, pf[m / DB][qt]);
+    };
+    auto sum_mfma = [&](int kh, int qt) {
+        wide_sum(st.L[qt], ones, pf[kh][qt]);
+    };
+    // Masks, maxima, shifted scores and raises as in scan_tiles.
+    const int all_see = CAUSAL ? (qw0 < N - 1 ? qw0 : N - 1) : N - 1;
+    int kv0 = j0 * kTileKV;
+    const int kv_step = step * kTileKV;
+    auto mask = [&]() {
+        if (__builtin_expect(kv0 + kTileKV - 1 > all_see, 0)) {
+            wide_settle_s(A);
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt) {
+                const int row = qw0 + (lane & 15) + 16 * qt;
+                const int last_key = CAUSAL ? (row < N - 1 ? row : N - 1) : N - 1;
+                int ahead = last_key - kv0 - 4 * g;
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        asm volatile("" : "+v"(ahead));     // (separate comparisons: no lane masks kept and combined)
+                        A[kb][qt][r] = 16 * kb + r > ahead ? -INFINITY : A[kb][qt][r];
+                    }
+            }
+        }
+    };
+    auto shift_score = [&](int k) { x[k] = __builtin_fmaf(A[(k >> 2) & 3][k >> 4][k & 3], c, -st.M[k >> 4]); };
+    auto max_op = [&](int qt, int op) {
+        const f4& a = A[op / 2][qt];
+        mx[qt] = fmaxf(fmaxf(mx[qt], a[2 * (op & 1)]), a[2 * (op & 1) + 1]);
+    };
+    auto raise_reference = [&]() {
+        wide_settle_s(A);
+        wide_settle_o(st);
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) {
+            float t = mx[qt];
+            asm volatile("" : "+v"(t));
+            t = quad_max(t);
+            const bool up = t > lim[qt];
+            const float Mnew = up ? t * c : st.M[qt];
+            const bool fresh = quad_sum(st.L[qt][0]) == 0.f;
+            const float alpha = up && !fresh ? fast_exp2(st.M[qt] - Mnew) : 1.0f;
+            st.M[qt] = Mnew;
+            st.L[qt] *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) st.o[db][qt][r] = fresh ? 0.f : st.o[db][qt][r] * alpha;
+            if (up) lim[qt] = score_limit(t, Mnew, c);
+#pragma unroll
+            for (int k = 16 * qt; k < 16 * qt + 16; ++k) shift_score(k);
+        }
+        wide_guard_o(st);
+    };
+    // Pair u = 0..31 of probabilities is word u % 4 of B operand (kh, qt) = (u / 16, u / 4 % 4)
+    float e[32][2];
+    auto exp_op = [&](int u, int h) { e[u][h] = fast_exp2(x[16 * (u / 4 % 4) + 4 * (2 * (u / 16) + u % 4 / 2) + 2 * (u % 2) + h]); };
+    auto convert_op = [&](int u) {
+        pf[u / 16][u / 4 % 4][u % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u][0], e[u][1]}, h2));
+    };
+    constexpr int OA = 96;
+    auto op_a = [&](int n) {
+        const int u = n / 3, k = n % 3;
+        if (k < 2) exp_op(u, k);
+        else if (u > 0) convert_op(u - 1);
+    };
+    auto pin_p = [&]() {
+        asm volatile("" : "+v"(pf[0][0]), "+v"(pf[0][1]), "+v"(pf[0][2]), "+v"(pf[0][3]), "+v"(pf[1][0]), "+v"(pf[1][1]), "+v"(pf[1][2]), "+v"(pf[1][3]));
+    };
+    wide_guard_o(st);
+
+    // ---------------------------------------------------------------- prologue: K(0..3) and V(0..1) on their way, S(0)
+    fetch(Kh, 0, lds0, off_k);
+    fetch(Kh, 1, lds0, off_k);
+    if constexpr (!BF16) fetch(Vh, 0, lds0 + VB, off_v);
+    fetch(Kh, 2, lds0, off_k);
+    if constexpr (!BF16) fetch(Vh, 1, lds0 + VB, off_v);
+    fetch(Kh, 3, lds0, off_k);
     if constexpr (BF16) {
-        // V(0) goes through registers into buffer 0 now, V(1) waits in vreg for the first iteration
-        u4 v0[NL];
+        // V(0) and V(1) go through registers into their buffers, V(2) waits in vreg
+#pragma unroll 1
+        for (int i = 0; i < 2; ++i) {
+            offsets(tile_of(i), off_v);
+            v_to_regs(base_of(Vh, tile_of(i)));
 #pragma unroll
-        for (int l = 0; l < NL; ++l) v0[l] = *reinterpret_cast<const u4*>(tile_base(Vh, 0) + lm.fill_src[l]);
-#pragma unroll
-        for (int l = 0; l < NL; ++l) vreg[l] = *reinterpret_cast<const u4*>(tile_base(Vh, 1) + lm.fill_src[l]);
-#pragma unroll
-        for (int l = 0; l < NL; ++l) *(LDS_PTR(u4))(size_t)(v_store + l * 4096) = bf16x8_to_f16x8(v0[l]);
+            for (int w = 0; w < CW; ++w) convert_word(w, lds0 + VB + i * G::kTile + lm.fill_dst);
+        }
+        offsets(tile_of(2), off_v);
+        v_to_regs(base_of(Vh, tile_of(2)));
+        landed_barrier<0>();
+    } else {
+        landed_barrier<12>();
     }
-    wait_tile_landed();
-    __syncthreads();
-    u4 ak[RA];          // the first K fragments of the tile one ahead, read before the iteration starts
     {
-        u4 a[NA];       // a[m]: fragment (ks, b) = (m / 2, m % 2) of tile 0 (buffer 0)
-        auto k0_read = [&](int m) -> u4 { return *(LDS_PTR(u4))(size_t)(rk[m / 2] - G::kTile + (m & 1) * 32 * G::kRowBytes); };
+        u4 a[NA];
 #pragma unroll
-        for (int m = 0; m < RA; ++m) a[m] = k0_read(m);
-#pragma unroll
-        for (int m = 0; m < NA; ++m) {
-            if (m + RA < NA) a[m + RA] = k0_read(m + RA);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (m < 2) mfma_s_first<BF16>(S[h][m & 1], a[m], st[h].qf[m / 2]);
-                else mfma_s<BF16>(S[h][m & 1], a[m], st[h].qf[m / 2]);
-            }
+        for (int m = 0; m < LA; ++m) a[m] = k_read(m);
+        static_for<NA>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            if constexpr (m + LA < NA) a[m + LA] = k_read(m + LA);
+            static_for<QT>([&](auto q) { s_mfma(m, decltype(q)::value, a[m], m % KS == 0); });
             __builtin_amdgcn_sched_barrier(0);
-        }
-        ak[0] = k_read(0, 0);
-        ak[1] = k_read(1, 0);
-        mfma_settle_v(S[0][0], S[0][1], S[1][0], S[1][1]);
-        mfma_settle_a(st[0].o);
-        mfma_settle_a(st[1].o);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            float mx = fmaxf(S[h][0][0], S[h][0][1]);
-#pragma unroll
-            for (int r = 2; r < 32; r += 2) mx = fmaxf(fmaxf(mx, S[h][r >> 4][r & 15]), S[h][r >> 4][(r & 15) + 1]);
-            const float tmax = pair_max(mx) * c;
-            // the first tile of a query tile finds M = -inf and takes its own maximum as the reference
-            if (__builtin_amdgcn_ballot_w64(!(tmax <= st[h].M + kRescaleSlack)) != 0) {
-                st[h].L += L_hi[h];
-                L_hi[h] = 0.f;
-                const float Mnew = fmaxf(st[h].M, tmax);
-                const float alpha = (Mnew == -INFINITY) ? 1.0f : fast_exp2(st[h].M - Mnew);
-                st[h].M = Mnew;
-                st[h].L *= alpha;
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) st[h].o[db][r] *= alpha;
-            }
-            set_reference(h);
-            first_block_probabilities(h);
-        }
-        mfma_guard(st[0].o);
-        mfma_guard(st[1].o);
+        });
     }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // K(0) has been read: iteration 0 fetches K(4) into its place
+    wide_settle_s(A);
+    mask();
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+        mx[qt] = lim[qt];
+#pragma unroll
+        for (int op = 0; op < 8; ++op) max_op(qt, op);
+        const float t = quad_max(mx[qt]);
+        st.M[qt] = t == -INFINITY ? 0.f : t * c;
+        if (t != -INFINITY) lim[qt] = score_limit(t, st.M[qt], c);
+#pragma unroll
+        for (int k = 16 * qt; k < 16 * qt + 16; ++k) shift_score(k);
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) rk[ks] += G::kTile;
+    u4 ak[LA];
+#pragma unroll
+    for (int m = 0; m < LA; ++m) ak[m] = k_read(m);
+    offsets(tile_of(4), off_k);
+    offsets(tile_of(BF16 ? 3 : 2), off_v);
 
     // ---------------------------------------------------------------- steady state: iteration i
-    // enters with the scores of tile i in S and the probabilities of its first block in pf[.][0..1];
-    // computes S(i+1)^T from K buffer (i+1)&3 and adds V(i)^T P(i)^T from V buffer i&3; fetches K(i+3) and V(i+2).
-    // Its barrier sits in the middle of the second product: by then everything fetched before this
-    // iteration (K(i+2), V(i+1) among it) has landed, so the first fragments of the next iteration can be read
-    // before this one ends, and the buffers this iteration's fetches overwrite (of K(i-1), V(i-2)) were last
-    // read before the previous barrier.  Returns whether a reference maximum has to be raised before
-    // tile i+1 can be used.
+    // reads K(i+1) and V(i), fetches K(i+4) into the place of K(i), which was read before the barrier of iteration i-1, and V(i+2) into that
+    // of V(i-2), read before it too.  Behind its barrier K(i+2) and V(i+1) have landed (all but the eight loads of its own).
+    // bfloat16: V(i+2) goes from registers into its place in the second product, then V(i+3) is loaded; K(i+4) is fetched there too, as the
+    // compiler waits for all loads where it uses those registers.
+    // Returns whether the reference maximum has to be raised before tile i+1 can be used.
+    struct Fetch {       // what an iteration fetches, and where to
+        const char *kbase, *vbase;
+        unsigned kdst, vdst;
+    };
+    constexpr int NV = BF16 ? 0 : NL, TL = NV + NL;
+    auto aim = [&](int i) {
+        const int jk = tile_of(i + 4), jv = tile_of(BF16 ? i + 3 : i + 2);
+        if (N % kTileKV) {      // (uniform; only the last tile of a sequence that ends inside it has offsets of its own)
+            offsets(jk, off_k);
+            offsets(jv, off_v);
+        }
+        return Fetch{base_of(Kh, jk), base_of(Vh, jv), (unsigned)__builtin_amdgcn_readfirstlane(lds0 + (i & 3) * G::kTile + lm.fill_dst),
+                     (unsigned)__builtin_amdgcn_readfirstlane(lds0 + VB + ((i + 2) & 3) * G::kTile + lm.fill_dst)};
+    };
+    auto load = [&](const Fetch& f, int li) {
+        if (li < NV) load_to_lds_16B(f.vbase, off_v[li], f.vdst + li * 4096);
+        else load_to_lds_16B(f.kbase, off_k[li - NV], f.kdst + (li - NV) * 4096);
+    };
     auto iteration = [&](int i) -> bool {
-        // this iteration's fetches: K(i+3) and V(i+2), source tile bases and LDS destinations of this wavefront
-        const char* kbase = tile_base(Kh, i + 3);
-        const char* vbase = tile_base(Vh, i + 2);
-        const unsigned kdst_s = __builtin_amdgcn_readfirstlane(lds0 + ((i + 3) & 3) * G::kTile + lm.fill_dst);
-        const unsigned vdst_s = __builtin_amdgcn_readfirstlane(lds0 + VB + ((i + 2) & 3) * G::kTile + lm.fill_dst);
-        s8 av[NB];
-        // ---- phase A: S(i+1)^T, block 0 (kv rows 0..31) for both halves, then block 1.
-        //      Slot t = 0..31 is the t-th MFMA; fragment n = t / 2 of the block-major order is (ks, b) = (n % 8, n / 8).
+        const Fetch f = aim(i);
+        const int dk = ((i + 2) & 3) ? G::kTile : -3 * G::kTile, dv = ((i + 1) & 3) ? G::kTile : -3 * G::kTile;
+        u4 av[NB];
         {
-            u4 a[NA];   // indexed by n
-            a[0] = ak[0];
-            a[1] = ak[1];
-            // Fragments are read from LDS two at a time, one pair ahead, and used in the order second, first:
-            // the one wait for the later read covers both (half as many waits in the instruction stream).
+            u4 a[NA];
 #pragma unroll
-            for (int q = 0; q < NA; ++q) {
-                if ((q & 1) == 0) {
-                    if (q + 2 < NA) { a[q + 2] = k_read((q + 2) % 8, (q + 2) / 8); a[q + 3] = k_read((q + 3) % 8, (q + 3) / 8); }
-                    else { av[0] = v_read(0); av[1] = v_read(1); }   // the first V^T fragments of the second product
+            for (int m = 0; m < LA; ++m) a[m] = ak[m];
+            // Fragments are read two at a time and used in the order second, first: the one wait for the later read covers both.
+            static_for<TA>([&](auto tc) {
+                constexpr int t = decltype(tc)::value, q = t / QT, m = q ^ 1, qt = t % QT;
+                if constexpr (qt == 0 && q % 2 == 0) {
+                    if constexpr (q + LA < NA) { a[q + LA] = k_read(q + LA); a[q + LA + 1] = k_read(q + LA + 1); }
+                    else { av[q + LA - NA] = v_read(q + LA - NA); av[q + LA - NA + 1] = v_read(q + LA - NA + 1); }
                 }
-                const int n = q ^ 1, ks = n % 8, b = n / 8;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int t = 2 * q + h;
-                    if (q % 8 == 0) mfma_s_first<BF16>(S[h][b], a[n], st[h].qf[ks]);   // the block's first MFMA
-                    else mfma_s<BF16>(S[h][b], a[n], st[h].qf[ks]);
-                    if (t < 16) {
-                        // exponentials of the second block of tile i: pair 8 + t/2 of half t%2, convert of the one before
-                        const int hh = t & 1, u = 8 + t / 2;
-                        if (u > 8) convert_pair(hh, u - 1);
-                        __builtin_amdgcn_sched_barrier(0);
-                        exp2_pair(hh, u);
-                    } else {
-                        if (t == 16) convert_pair(0, 15);
-                        if (t == 17) convert_pair(1, 15);
-                        __builtin_amdgcn_sched_barrier(0);
-                        // row sums of tile i: words 2(t-16), 2(t-16)+1 of the 32
-                        const int w0 = 2 * (t - 16);
-                        sum_pair(w0 & 1, w0 >> 1);
-                        sum_pair((w0 + 1) & 1, (w0 + 1) >> 1);
-                        if constexpr (BF16) {
-                            // one word of V(i+1) from bfloat16 to binary16; every fourth completes 16 bytes for LDS
-                            const int w = t - 16;
-                            const unsigned word = vreg[w / 4][w % 4];
-                            f2 y;
-                            y[0] = __builtin_bit_cast(float, word << 16);
-                            y[1] = __builtin_bit_cast(float, word & 0xffff0000u);
-                            vreg[w / 4][w % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(y, h2));
-                            if (w % 4 == 3)
-                                *(LDS_PTR(u4))(size_t)(v_store + ((i + 1) & 3) * G::kTile + (w / 4) * 4096) = vreg[w / 4];
-                        }
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
+                s_mfma(m, qt, a[m], q % KS == 0);
+                if constexpr (!BF16 && t >= 2 && t < 2 + 2 * TL && t % 2 == 0) load(f, (t - 2) / 2);
+                static_for<(t + 1) * OA / TA - t * OA / TA>([&](auto k) { op_a(t * OA / TA + decltype(k)::value); });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            convert_op(31);
         }
-        // K read addresses move on to tile i+2
-        {
-            const int dk = ((i + 2) & 3) ? G::kTile : -3 * G::kTile;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) rk[ks] += dk;
+        for (int ks = 0; ks < KS; ++ks) rk[ks] += dk;
+        // (the probabilities pass through the statement, or the compiler moves the exponentials behind the barrier)
+        pin_p();
+        if constexpr (BF16) landed_barrier<0>();
+        else landed_barrier<8>();
+        kv0 += kv_step;
+        mask();
+        if constexpr (BF16) {      // (the V registers have landed: the compiler is told so here, see scan_tiles)
+#pragma unroll
+            for (int l = 0; l < NL; ++l) asm volatile("" : "+v"(vreg[l]));
         }
-        // ---- phase B: O^T += V(i)^T P(i)^T.  Under its MFMAs (slot t = 0..31): the row maxima of S(i+1) and
-        //      their check against the slack (slots 2..9), then the first-block exponentials of tile i+1, whose
-        //      converts overwrite pf[.][0] (free after slot 7) and pf[.][1] (free after slot 15).
-        float mx[2] = {0.f, 0.f};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) mx[qt] = lim[qt];
         bool need = false;
-        auto constexpr_fetch = [&](int li) {
-            if (li == 0) load_to_lds_16B_at<0>(kbase, lm.fill_src[0], kdst_s);
-            if (li == 1) load_to_lds_16B_at<4096>(kbase, lm.fill_src[1], kdst_s);
-            if (li == 2) load_to_lds_16B_at<8192>(kbase, lm.fill_src[2], kdst_s);
-            if (li == 3) load_to_lds_16B_at<12288>(kbase, lm.fill_src[3], kdst_s);
-            if constexpr (BF16) {
-                if (li >= 4) vreg[li - 4] = *reinterpret_cast<const u4*>(vbase + lm.fill_src[li - 4]);
+        constexpr int OC = BF16 ? 3 * CW : 0;
+        constexpr int OM = 32 + OC, OB = OM + 64;
+        constexpr int T0 = (OM * TB + OB - 1) / OB;
+        auto op_b = [&](int n) {
+            if (n < OM) {
+                const int j = n * 32 / OM, done = (n + 1) * 32 / OM;
+                if (j != done) max_op(j & 3, j >> 2);
+                if constexpr (BF16) {
+                    const int w = n * CW / OM;
+                    if (w != (n + 1) * CW / OM) convert_word(w, f.vdst);
+                }
             } else {
-                if (li == 4) load_to_lds_16B_at<0>(vbase, lm.fill_src[0], vdst_s);
-                if (li == 5) load_to_lds_16B_at<4096>(vbase, lm.fill_src[1], vdst_s);
-                if (li == 6) load_to_lds_16B_at<8192>(vbase, lm.fill_src[2], vdst_s);
-                if (li == 7) load_to_lds_16B_at<12288>(vbase, lm.fill_src[3], vdst_s);
+                shift_score(n - OM);
             }
         };
-#pragma unroll
-        for (int idx = 0; idx < NB; ++idx) {
-            if (idx == NB / 2) {
-                // ---- everything fetched before this iteration has landed (all but its own first two loads); publish it
-                asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-                __syncthreads();
+        static_for<TB>([&](auto tc) {
+            constexpr int t = decltype(tc)::value, q = t / QT, m = q ^ 1;
+            if constexpr (t % QT == 0 && q % 2 == 0) {
+                if constexpr (q + LA < NB) { av[q + LA] = v_read(q + LA); av[q + LA + 1] = v_read(q + LA + 1); }
+                else { ak[q + LA - NB] = k_read(q + LA - NB); ak[q + LA - NB + 1] = k_read(q + LA - NB + 1); }
             }
-            if ((idx & 1) == 0) {
-                if (idx + 2 < NB) { av[idx + 2] = v_read(idx + 2); av[idx + 3] = v_read(idx + 3); }
-                else { ak[0] = k_read(0, 0); ak[1] = k_read(1, 0); }   // the first K fragments of the next iteration
-            }
-            const int f = idx ^ 1;
+            if constexpr (BF16 && t == T0) v_to_regs(f.vbase);
+            o_mfma(m, t % QT, av[m]);
+            if constexpr (t % 8 == 7) sum_mfma(t / 32, t / 8 % 4);
+            if constexpr (BF16 && t >= 2 && t < 2 + TL) load(f, t - 2);
+            static_for<(t + 1) * OB / TB - t * OB / TB>([&](auto k) {
+                constexpr int n = t * OB / TB + decltype(k)::value;
+                op_b(n);
+                if constexpr (n == OM + 8) need = __builtin_amdgcn_ballot_w64(!(mx[0] <= lim[0]) || !(mx[1] <= lim[1]) || !(mx[2] <= lim[2]) || !(mx[3] <= lim[3])) != 0;
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int t = 2 * idx + h;
-                mfma_o(st[h].o[f % DB], av[f], pf[h][f / DB]);
-                // the fetches sit in the slots with no other work: two before the barrier, six at the end
-                if (t < 2) constexpr_fetch(t);
-                if (t >= 26) constexpr_fetch(t - 24);
-                if (t >= 2 && t < 10) {
-                    // four maxima per slot, the two halves' chains alternating
+        for (int k = 0; k < 16 * QT; k += 16)
+            asm volatile("" : "+v"(x[k]), "+v"(x[k + 1]), "+v"(x[k + 2]), "+v"(x[k + 3]), "+v"(x[k + 4]), "+v"(x[k + 5]), "+v"(x[k + 6]), "+v"(x[k + 7]),
+                         "+v"(x[k + 8]), "+v"(x[k + 9]), "+v"(x[k + 10]), "+v"(x[k + 11]), "+v"(x[k + 12]), "+v"(x[k + 13]), "+v"(x[k + 14]), "+v"(x[k + 15]));
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int n = (t - 2) * 4 + q, hh = n & 1, op = n >> 1;    // op-th max3 of half hh
-                        const float u0 = S[hh][(2 * op) >> 4][(2 * op) & 15], u1 = S[hh][(2 * op) >> 4][((2 * op) & 15) + 1];
-                        mx[hh] = fmaxf(fmaxf(op == 0 ? lim[hh] : mx[hh], u0), u1);   // (starts from lim: exceeds it exactly when a score does)
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-                if (t == 10) {
-                    tmax_ahead[0] = mx[0];
-                    tmax_ahead[1] = mx[1];
-                    need = __builtin_amdgcn_ballot_w64(!(mx[0] <= lim[0]) || !(mx[1] <= lim[1])) != 0;
-                }
-                if (t >= 10 && t < 18) {            // pairs 0..3 of both halves: pf[.][0]
-                    const int hh = t & 1, u = (t - 10) / 2;
-                    if (u > 0) convert_pair(hh, u - 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    exp2_pair(hh, u);
-                }
-                if (t >= 18 && t < 26) {            // pairs 4..7: pf[.][1]
-                    const int hh = t & 1, u = 4 + (t - 18) / 2;
-                    convert_pair(hh, u - 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    exp2_pair(hh, u);
-                }
-                if (t == 26) convert_pair(0, 7);
-                if (t == 27) convert_pair(1, 7);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        // V read addresses move on to tile i+1
-        {
-            const int dv = ((i + 1) & 3) ? G::kTile : -3 * G::kTile;
-#pragma unroll
-            for (int db = 0; db < DB; ++db) { rv[db][0] += dv; rv[db][1] += dv; }
-        }
+        for (int db = 0; db < DB; ++db) rv[db] += dv;
         return need;
     };
-    // Between two iterations: the scores of the coming tile exceed the slack somewhere.  The reference maximum
-    // of that half goes up (per query row), the sum and the accumulators follow, the scores are taken relative
-    // to it and the first-block probabilities are redone.
-    auto raise_reference = [&]() {
-        mfma_settle_v(S[0][0], S[0][1], S[1][0], S[1][1]);
-        mfma_settle_a(st[0].o);
-        mfma_settle_a(st[1].o);
+    // The tiles that concern this wavefront.  In a causal scan up, the tiles of the workgroup's last rows lie wholly behind the others' rows: those
+    // wavefronts keep fetching and meeting the barriers, but compute nothing more (0 times an infinite value would be no number).
+    const int mine = CAUSAL && step > 0 && (qw0 + 63) / kTileKV + 1 < nkv ? (qw0 + 63) / kTileKV + 1 : nkv;
+    auto fetch_only = [&](int i) {       // iteration i's fetches (bfloat16: V(i+2) into LDS first)
+        const Fetch f = aim(i);
+        if constexpr (BF16) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            // (the comparison is redone on a value the compiler cannot trace back into the loop, or the loop
-            // would carry both halves' results along as lane masks)
-            float t = tmax_ahead[h];
-            asm volatile("" : "+v"(t));
-            t = pair_max(t);     // the two lanes of a query row move together
-            const bool mine = !(t <= lim[h]);   // (t is the row's maximum only where it exceeds lim)
-            if (__builtin_amdgcn_ballot_w64(mine) != 0) {
-                const float Mnew = mine ? fmaxf(st[h].M, t * c) : st[h].M;
-                const float alpha = fast_exp2(st[h].M - Mnew);
-                st[h].M = Mnew;
-                st[h].L = (st[h].L + L_hi[h]) * alpha;
-                L_hi[h] = 0.f;
+            for (int l = 0; l < NL; ++l) asm volatile("" : "+v"(vreg[l]));
 #pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) st[h].o[db][r] *= alpha;
-                set_reference(h);
-                first_block_probabilities(h);
-            }
+            for (int w = 0; w < CW; ++w) convert_word(w, f.vdst);
+            v_to_regs(f.vbase);
         }
-        mfma_guard(st[0].o);
-        mfma_guard(st[1].o);
+#pragma unroll
+        for (int li = 0; li < TL; ++li) load(f, li);
     };
+    // (The raise stands outside the inner loop: inside, the compiler copies accumulators on the common path and spills.)
     int i = 0;
-    while (i + 1 < count) {
+    while (i + 1 < mine) {
         bool need = false;
 #pragma unroll 1
-        for (; i + 1 < count; ++i) {
+        for (; i + 1 < mine; ++i) {
             need = iteration(i);
             if (need) { ++i; break; }
         }
         if (need) raise_reference();
     }
-
-    // ---------------------------------------------------------------- last tile: the rest of its probabilities, then O^T += V^T P^T
-    mfma_settle_v(S[0][0], S[0][1], S[1][0], S[1][1]);
-#pragma unroll
-    for (int u = 8; u < 16; ++u) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) { exp2_pair(h, u); convert_pair(h, u); }
+    // ---------------------------------------------------------------- last tile: probabilities, then O^T += V^T P^T
+    if constexpr (CAUSAL && !BF16) {
+        if (mine < nkv) fetch_only(mine - 1);
     }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) { sum_pair(0, u); sum_pair(1, u); }
+    static_for<OA>([&](auto n) { op_a(decltype(n)::value); });
+    convert_op(31);
+    landed_barrier<0>();
+    if constexpr (CAUSAL && BF16) {
+        if (mine < nkv) fetch_only(mine - 1);
+    }
     {
-        s8 av[NB];
+        u4 av[NB];
 #pragma unroll
-        for (int idx = 0; idx < RA; ++idx) av[idx] = v_read(idx);
-#pragma unroll
-        for (int idx = 0; idx < NB; ++idx) {
-            if (idx + RA < NB) av[idx + RA] = v_read(idx + RA);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) mfma_o(st[h].o[idx % DB], av[idx], pf[h][idx / DB]);
+        for (int m = 0; m < LA; ++m) av[m] = v_read(m);
+        static_for<TB>([&](auto tc) {
+            constexpr int t = decltype(tc)::value, m = t / QT;
+            if constexpr (t % QT == 0 && m + LA < NB) av[m + LA] = v_read(m + LA);
+            o_mfma(m, t % QT, av[m]);
+            if constexpr (t % 8 == 7) sum_mfma(t / 32, t / 8 % 4);
             __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+    if constexpr (CAUSAL) {
+#pragma unroll 1
+        for (i = mine; i < nkv; ++i) {
+            if (!BF16 && i + 1 < nkv) fetch_only(i);
+            landed_barrier<0>();
+            if (BF16 && i + 1 < nkv) fetch_only(i);
         }
     }
-    st[0].L += L_hi[0];
-    st[1].L += L_hi[1];
-    mfma_settle_a(st[0].o);   // the accumulators are complete before the caller's vector code reads them
-    mfma_settle_a(st[1].o);
-    wait_tile_landed();   // also the fetches past the end of the range
-    __syncthreads();      // all reads of the last tile are done before anything refills the buffers
+    wide_settle_o(st);
+    __syncthreads();   // all reads of the last tile are done before anything refills the buffers
 }
+
 
 // The epilogue where variant.qo_streaming asks for it: O leaves through LDS so that a store instruction writes whole
 // 128-byte lines (8 rows x 128 bytes per instruction, 16 bytes per lane), marked non-temporal: the rows of O are written
@@ -1729,22 +1714,21 @@ __device__ __forceinline__ void drain_stage(LDS_PTR(char) stage, char* dst, size
     stage_fence();
 }
 
-// One query tile (Alg. 1 body): rows [t*128*NH, (t+1)*128*NH) of head `hh`, K/V tiles j0, j0+step, ... (nkv of
-// them).  A wavefront owns NH halves of 32 query rows each (NH = 2: the wide variant).
-// HALVES (32 rows per wavefront): the tile has 64 rows; of its full, unmasked K/V tiles wavefronts
+// One query tile (Alg. 1 body) of attn_fwd_kernel: rows [t*128, (t+1)*128) of head `hh`, K/V tiles j0, j0+step, ... (nkv of
+// them).
+// HALVES: the tile has 64 rows; of its full, unmasked K/V tiles wavefronts
 // 0 and 1 take the first half and wavefronts 2 and 3, for the same rows, the second half, at once, and the two partial
 // results are merged through LDS (the merge of two softmax partials: common reference maximum, both rescaled to it).
 // What does not split evenly or needs the mask -- an odd plain tile, the diagonal tile, a ragged last tile -- is taken
 // one tile at a time by wavefronts 0 and 1 alone, after the merge in a forward scan and before the halves in a
 // backward one, where it comes first.
-template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false>
+template <int D, bool BF16, bool CAUSAL, bool HALVES = false>
 __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>& lm, int hh, int t, int j0, int step,
                                                int nkv, int wave, int lane, LDS_PTR(char) lds) {
-    static_assert(!HALVES || NH == 1, "two key ranges at once: 32-row kernel");
     using G = Geo<D>;
     constexpr int KS = D / 16;    // MFMA steps along d for S^T
     constexpr int DB = D / 32;    // 32-row blocks of O^T
-    constexpr int TQ = HALVES ? kTileQ / 2 : kTileQ * NH;
+    constexpr int TQ = HALVES ? kTileQ / 2 : kTileQ;
     const int g = lane >> 5, ln = lane & 31;
     const int N = p.N;
     const size_t head_off = (size_t)hh * N * G::kRowBytes;
@@ -1753,14 +1737,14 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
     const char* Vh = static_cast<const char*>(p.V) + head_off;
 
     const int run = HALVES ? wave >> 1 : 0;                            // which half of the scan this wavefront computes
-    const int qw0 = t * TQ + (HALVES ? wave & 1 : wave) * 32 * NH;     // first query row of this wavefront
-    const int qrow = qw0 + ln;                // this lane's query row in half 0 (column of S^T)
+    const int qw0 = t * TQ + (HALVES ? wave & 1 : wave) * 32;     // first query row of this wavefront
+    const int qrow = qw0 + ln;                // this lane's query row (column of S^T)
 
-    TileState<D> st[NH];
+    TileState<D> st;
     // With variant.qo_streaming the rows of Q come in the way K tiles do -- 64 rows at a time straight into LDS, whole
     // lines per instruction, the four wavefronts together -- but marked non-temporal, and are read from there in the
     // K operand's pattern, which is also Q's.  The buffers are free: the last range of the previous tile ended with a barrier.
-    unsigned q_at = 0;     // byte offset in LDS of this lane's first fragment of half 0
+    unsigned q_at = 0;     // byte offset in LDS of this lane's first fragment
     if (p.stream_q) {
         int l2 = lane;
         asm volatile("" : "+v"(l2));        // (a lane map of its own that does not live on: see the note on registers below)
@@ -1778,39 +1762,30 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
                 load_to_lds_16B_nt(base, (unsigned)((r - first) * G::kRowBytes + chunk), lds0 + m * G::kTile + lq.fill_dst + i * 4096);
             }
         }
-        const int mine = HALVES ? wave & 1 : wave;           // which 32 * NH rows of the tile are this wavefront's
-        q_at = (mine * NH / 2) * G::kTile + ((mine * NH) & 1) * 32 * G::kRowBytes + lq.k_rd[0];
+        const int mine = HALVES ? wave & 1 : wave;           // which 32 rows of the tile are this wavefront's
+        q_at = (mine / 2) * G::kTile + (mine & 1) * 32 * G::kRowBytes + lq.k_rd[0];
         wait_tile_landed();
         __syncthreads();
     }
     int lane_q = lane;
     asm volatile("" : "+v"(lane_q));      // (addresses used once: built from a copy of the lane index of their own)
-#pragma unroll
-    for (int h = 0; h < NH; ++h) {   // rows beyond N repeat row N-1 (computed, never stored)
-        const int qr = qw0 + (lane_q & 31) + 32 * h < N ? qw0 + (lane_q & 31) + 32 * h : N - 1;
+    {   // rows beyond N repeat row N-1 (computed, never stored)
+        const int qr = qw0 + (lane_q & 31) < N ? qw0 + (lane_q & 31) : N - 1;
         const char* qp = Qh + (size_t)qr * G::kRowBytes + (lane_q >> 5) * 16;
         const unsigned flip = p.negate_q ? 0x80008000u : 0u;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             // (chunk 2 ks + g of a row sits at chunk position (2 ks + g) ^ swz(row): k_rd[ks] = k_rd[0] ^ (32 ks))
-            u4 v = p.stream_q ? *(LDS_PTR(u4))(lds + ((q_at + h * 32 * G::kRowBytes) ^ (unsigned)(ks * 32)))
-                              : *reinterpret_cast<const u4*>(qp + ks * 32);
+            u4 v = p.stream_q ? *(LDS_PTR(u4))(lds + (q_at ^ (unsigned)(ks * 32))) : *reinterpret_cast<const u4*>(qp + ks * 32);
             v[0] ^= flip; v[1] ^= flip; v[2] ^= flip; v[3] ^= flip;
-            if constexpr (NH == 2) {
-                if constexpr (!BF16) {
-                    if (p.q_bf16) v = bf16x8_to_f16x8(v);   // K and V are binary16 copies: Q follows (exact for normal binary16 magnitudes)
-                }
-                asm volatile("" : "=a"(st[h].qf[ks]) : "0"(v));   // accumulation registers from here on
-            } else {
-                st[h].qf[ks] = v;
-            }
+            st.qf[ks] = v;
         }
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) st[h].o[db][r] = 0.f;
-        st[h].M = -INFINITY;
-        st[h].L = 0.f;
+            for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
+        st.M = -INFINITY;
+        st.L = 0.f;
     }
     if (p.stream_q) __syncthreads();      // the fragments are in registers before the first K/V fetch overwrites the rows
     const float c = p.c;
@@ -1822,34 +1797,16 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
     const int jm = CAUSAL ? (t * TQ) / kTileKV : ((N % kTileKV) ? kv_tiles - 1 : kv_tiles);
     const int n_masked = nkv > jm ? nkv - jm : 0;
     const int n_plain = nkv - n_masked;
-    // (The wide variant has no registers to spare: each of its runs builds the per-lane address tables afresh,
-    // from a lane index the compiler cannot see through, so that none of them stays live across the other run.)
-    auto plain = [&](int j_first) {
-        if constexpr (NH == 1) {
-            pipelined_range<D, BF16>(st[0], lm, Kh, Vh, c, j_first, step, n_plain, lane, lds);
-        } else {
-            int l2 = lane;
-            asm volatile("" : "+v"(l2));
-            const LaneMap<D> lm2(wave, l2);
-            pipelined_range_wide<BF16>(st, lm2, Kh, Vh, c, j_first, step, n_plain, l2, lds);
-        }
-    };
+    auto plain = [&](int j_first) { pipelined_range<D, BF16>(st, lm, Kh, Vh, c, j_first, step, n_plain, lane, lds); };
     auto masked = [&](int j_first) {
-        if constexpr (NH == 1) {
-            general_range<D, BF16, CAUSAL, true, NH>(st, lm, Kh, Vh, N, c, j_first, step, n_masked, qw0, qrow, lane, lds);
-        } else {
-            int l2 = lane;
-            asm volatile("" : "+v"(l2));
-            const LaneMap<D> lm2(wave, l2);
-            general_range<D, BF16, CAUSAL, true, NH>(st, lm2, Kh, Vh, N, c, j_first, step, n_masked, qw0, qrow, l2, lds);
-        }
+        general_range<D, BF16, CAUSAL, true>(st, lm, Kh, Vh, N, c, j_first, step, n_masked, qw0, qrow, lane, lds);
     };
     if constexpr (HALVES) {
         const int half = n_plain / 2;                       // plain tiles per run
         const int n_left = (n_plain & 1) + n_masked;        // tiles left for the tile-at-a-time code
         if (step < 0)
-            general_range<D, BF16, CAUSAL, true, NH>(st, lm, Kh, Vh, N, c, j0, step, n_left, qw0, qrow, lane, lds, run == 1);
-        pipelined_range<D, BF16, true>(st[0], lm, Kh, Vh, c, step > 0 ? j0 : j0 + n_left * step, step, half, lane, lds, run);
+            general_range<D, BF16, CAUSAL, true>(st, lm, Kh, Vh, N, c, j0, step, n_left, qw0, qrow, lane, lds, run == 1);
+        pipelined_range<D, BF16, true>(st, lm, Kh, Vh, c, step > 0 ? j0 : j0 + n_left * step, step, half, lane, lds, run);
         // ---- merge: wavefront w + 2 hands (O^T, M, L) of its half to wavefront w, lane to lane, through LDS
         //      (value k of lane l of wavefront w + 2 at float index (2k + w) * 64 + l: no bank conflicts)
         constexpr int NV = DB * 16 + 2;
@@ -1858,27 +1815,27 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) xch[(2 * (db * 16 + r) + (wave & 1)) * 64 + lane] = st[0].o[db][r];
-            xch[(2 * (NV - 2) + (wave & 1)) * 64 + lane] = st[0].M;
-            xch[(2 * (NV - 1) + (wave & 1)) * 64 + lane] = st[0].L;
+                for (int r = 0; r < 16; ++r) xch[(2 * (db * 16 + r) + (wave & 1)) * 64 + lane] = st.o[db][r];
+            xch[(2 * (NV - 2) + (wave & 1)) * 64 + lane] = st.M;
+            xch[(2 * (NV - 1) + (wave & 1)) * 64 + lane] = st.L;
         }
         __syncthreads();
         if (run == 0) {
             const float M1 = xch[(2 * (NV - 2) + wave) * 64 + lane], L1 = xch[(2 * (NV - 1) + wave) * 64 + lane];
-            const float M = fmaxf(st[0].M, M1);
-            const float a0 = st[0].M == -INFINITY ? 0.f : fast_exp2(st[0].M - M);
+            const float M = fmaxf(st.M, M1);
+            const float a0 = st.M == -INFINITY ? 0.f : fast_exp2(st.M - M);
             const float a1 = M1 == -INFINITY ? 0.f : fast_exp2(M1 - M);
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    st[0].o[db][r] = st[0].o[db][r] * a0 + xch[(2 * (db * 16 + r) + wave) * 64 + lane] * a1;
-            st[0].M = M;
-            st[0].L = st[0].L * a0 + L1 * a1;
+                    st.o[db][r] = st.o[db][r] * a0 + xch[(2 * (db * 16 + r) + wave) * 64 + lane] * a1;
+            st.M = M;
+            st.L = st.L * a0 + L1 * a1;
         }
         __syncthreads();   // the exchange area is read before the next fetches overwrite it
         if (step > 0)
-            general_range<D, BF16, CAUSAL, true, NH>(st, lm, Kh, Vh, N, c, j0 + 2 * half * step, step, n_left, qw0, qrow, lane,
+            general_range<D, BF16, CAUSAL, true>(st, lm, Kh, Vh, N, c, j0 + 2 * half * step, step, n_left, qw0, qrow, lane,
                                                      lds, run == 1);
     } else if (step > 0) {
         plain(j0);
@@ -1900,42 +1857,39 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
             asm volatile("" : "+v"(lane));     // lane-derived addresses are built here, not carried across the scan
             const int g = lane >> 5, ln = lane & 31;
             const int sw = ln & 7;
+            const float inv = 1.0f / pair_sum(st.L);
+            const int row0 = qw0;
+            const int rows_left = N - row0;      // <= 0: all rows lie beyond the sequence
+            if (p.o_dtype == SAWATTN_F32) {
+                constexpr size_t RB = (size_t)D * 4;
+                char* dst = static_cast<char*>(p.O) + ((size_t)hh * N + row0) * RB;
 #pragma unroll
-            for (int h = 0; h < NH; ++h) {
-                const float inv = 1.0f / pair_sum(st[h].L);
-                const int row0 = qw0 + 32 * h;
-                const int rows_left = N - row0;      // <= 0: the whole half lies beyond the sequence
-                if (p.o_dtype == SAWATTN_F32) {
-                    constexpr size_t RB = (size_t)D * 4;
-                    char* dst = static_cast<char*>(p.O) + ((size_t)hh * N + row0) * RB;
+                for (int db = 0; db < DB; ++db) {          // 32 columns = 128 bytes per row
+                    const f16v& o = st.o[db];
 #pragma unroll
-                    for (int db = 0; db < DB; ++db) {          // 32 columns = 128 bytes per row
-                        const f16v& o = st[h].o[db];
+                    for (int rq = 0; rq < 4; ++rq) {
+                        const f4 v = {o[4 * rq] * inv, o[4 * rq + 1] * inv, o[4 * rq + 2] * inv, o[4 * rq + 3] * inv};
+                        *(LDS_PTR(f4))(stage + ln * 128 + (((2 * rq + g) ^ sw) << 4)) = v;
+                    }
+                    drain_stage(stage, dst + db * 128, RB, rows_left, lane);
+                }
+            } else {
+                constexpr size_t RB = (size_t)D * 2;
+                char* dst = static_cast<char*>(p.O) + ((size_t)hh * N + row0) * RB;
+#pragma unroll
+                for (int pass = 0; pass < DB / 2; ++pass) {   // 64 columns = 128 bytes per row
+#pragma unroll
+                    for (int dbl = 0; dbl < 2; ++dbl) {
+                        const f16v& o = st.o[2 * pass + dbl];
 #pragma unroll
                         for (int rq = 0; rq < 4; ++rq) {
                             const f4 v = {o[4 * rq] * inv, o[4 * rq + 1] * inv, o[4 * rq + 2] * inv, o[4 * rq + 3] * inv};
-                            *(LDS_PTR(f4))(stage + ln * 128 + (((2 * rq + g) ^ sw) << 4)) = v;
+                            LDS_PTR(char) at = stage + ln * 128 + (((4 * dbl + rq) ^ sw) << 4) + 8 * g;
+                            if (p.o_dtype == SAWATTN_F16) *(LDS_PTR(h4))at = __builtin_convertvector(v, h4);
+                            else *(LDS_PTR(b4))at = __builtin_convertvector(v, b4);
                         }
-                        drain_stage(stage, dst + db * 128, RB, rows_left, lane);
                     }
-                } else {
-                    constexpr size_t RB = (size_t)D * 2;
-                    char* dst = static_cast<char*>(p.O) + ((size_t)hh * N + row0) * RB;
-#pragma unroll
-                    for (int pass = 0; pass < DB / 2; ++pass) {   // 64 columns = 128 bytes per row
-#pragma unroll
-                        for (int dbl = 0; dbl < 2; ++dbl) {
-                            const f16v& o = st[h].o[2 * pass + dbl];
-#pragma unroll
-                            for (int rq = 0; rq < 4; ++rq) {
-                                const f4 v = {o[4 * rq] * inv, o[4 * rq + 1] * inv, o[4 * rq + 2] * inv, o[4 * rq + 3] * inv};
-                                LDS_PTR(char) at = stage + ln * 128 + (((4 * dbl + rq) ^ sw) << 4) + 8 * g;
-                                if (p.o_dtype == SAWATTN_F16) *(LDS_PTR(h4))at = __builtin_convertvector(v, h4);
-                                else *(LDS_PTR(b4))at = __builtin_convertvector(v, b4);
-                            }
-                        }
-                        drain_stage(stage, dst + pass * 128, RB, rows_left, lane);
-                    }
+                    drain_stage(stage, dst + pass * 128, RB, rows_left, lane);
                 }
             }
         }
@@ -1946,48 +1900,45 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
     int lane_out = lane_in;
     asm volatile("" : "+v"(lane_out));
     const int g_out = lane_out >> 5, qrow_out = qw0 + (lane_out & 31);
+    const float inv = 1.0f / pair_sum(st.L);
+    if (qrow_out < N) {
+        const size_t orow = ((size_t)hh * N + qrow_out) * D;
 #pragma unroll
-    for (int h = 0; h < NH; ++h) {
-        const float inv = 1.0f / pair_sum(st[h].L);
-        if (qrow_out + 32 * h < N) {
-            const size_t orow = ((size_t)hh * N + qrow_out + 32 * h) * D;
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                    const f16v& o = st[h].o[db];
-                    f4 v = {o[4 * rq] * inv, o[4 * rq + 1] * inv, o[4 * rq + 2] * inv, o[4 * rq + 3] * inv};
-                    const size_t col = 32 * db + 8 * rq + 4 * g_out;
-                    if (p.o_dtype == SAWATTN_F32) {
-                        *reinterpret_cast<f4*>(static_cast<float*>(p.O) + orow + col) = v;
-                    } else if (p.o_dtype == SAWATTN_F16) {
-                        *reinterpret_cast<h4*>(static_cast<_Float16*>(p.O) + orow + col) = __builtin_convertvector(v, h4);
-                    } else {
-                        *reinterpret_cast<b4*>(static_cast<__bf16*>(p.O) + orow + col) = __builtin_convertvector(v, b4);
-                    }
+            for (int rq = 0; rq < 4; ++rq) {
+                const f16v& o = st.o[db];
+                f4 v = {o[4 * rq] * inv, o[4 * rq + 1] * inv, o[4 * rq + 2] * inv, o[4 * rq + 3] * inv};
+                const size_t col = 32 * db + 8 * rq + 4 * g_out;
+                if (p.o_dtype == SAWATTN_F32) {
+                    *reinterpret_cast<f4*>(static_cast<float*>(p.O) + orow + col) = v;
+                } else if (p.o_dtype == SAWATTN_F16) {
+                    *reinterpret_cast<h4*>(static_cast<_Float16*>(p.O) + orow + col) = __builtin_convertvector(v, h4);
+                } else {
+                    *reinterpret_cast<b4*>(static_cast<__bf16*>(p.O) + orow + col) = __builtin_convertvector(v, b4);
                 }
-        }
+            }
     }
 }
 
-// One query tile (Alg. 1 body) of attn_fwd_shared_kernel: rows [t*128, (t+1)*128) of head `hh`,
-// K/V tiles j0, j0+step, ... (nkv of them).
-template <int D, bool BF16, bool CAUSAL, bool PHASES>
+// One query tile (Alg. 1 body) on 16x16x32 MFMAs: rows [t*64*QT, (t+1)*64*QT) of head `hh`, K/V tiles j0, j0+step, ... (nkv of
+// them).  A wavefront owns QT blocks of 16 query rows: two in attn_fwd_shared_kernel, four with 256-row tiles.
+template <int D, bool BF16, bool CAUSAL, bool PHASES, int QT = 2>
 __device__ __forceinline__ void process_q_tile_narrow(const Params& p, const NarrowMap<D>& lm, int hh, int t, int j0, int step,
                                                       int nkv, int wave, int lane, LDS_PTR(char) lds) {
     using G = Geo<D>;
     constexpr int KS = D / 32;    // MFMA steps along d for S^T
     constexpr int DB = D / 16;    // column blocks of O^T
-    constexpr int TQ = kTileQ;
+    constexpr int TQ = 64 * QT;
     const int N = p.N;
     const size_t head_off = (size_t)hh * N * G::kRowBytes;
     const char* Qh = static_cast<const char*>(p.Q) + head_off;
     const char* Kh = static_cast<const char*>(p.K) + head_off;
     const char* Vh = static_cast<const char*>(p.V) + head_off;
 
-    const int qw0 = t * TQ + wave * 32;       // first query row of this wavefront
+    const int qw0 = t * TQ + wave * 16 * QT;       // first query row of this wavefront
 
-    NarrowState<D> st;
+    NarrowState<D, QT> st;
     // With variant.qo_streaming the rows of Q come in the way K tiles do -- 64 rows at a time straight into LDS, whole
     // lines per instruction, the four wavefronts together -- but marked non-temporal, and are read from there in the
     // K operand's pattern, which is also Q's.  The buffers are free: the last range of the previous tile ended with a barrier.
@@ -2010,14 +1961,14 @@ __device__ __forceinline__ void process_q_tile_narrow(const Params& p, const Nar
                 load_to_lds_16B_nt(base, (unsigned)((r - first) * G::kRowBytes + chunk), lds0 + m * G::kTile + lq.fill_dst + i * 4096);
             }
         }
-        q_at = (wave / 2) * G::kTile + (wave & 1) * 32 * G::kRowBytes + lq.k_rd[0];
+        q_at = wave * QT / 4 * G::kTile + (QT == 2 ? wave & 1 : 0) * 32 * G::kRowBytes + lq.k_rd[0];
         wait_tile_landed();
         __syncthreads();
     }
     int lane_q = lane;
     asm volatile("" : "+v"(lane_q));      // (addresses used once: built from a copy of the lane index of their own)
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt) {   // rows beyond N repeat row N-1 (computed, never stored)
+    for (int qt = 0; qt < QT; ++qt) {   // rows beyond N repeat row N-1 (computed, never stored)
         const int q0 = qw0 + (lane_q & 15) + 16 * qt;
         const int qr = q0 < N ? q0 : N - 1;
         const char* qp = Qh + (size_t)qr * G::kRowBytes + (lane_q >> 4) * 16;
@@ -2028,7 +1979,14 @@ __device__ __forceinline__ void process_q_tile_narrow(const Params& p, const Nar
             u4 v = p.stream_q ? *(LDS_PTR(u4))(lds + ((q_at + qt * 16 * G::kRowBytes) ^ (unsigned)(ks * 64)))
                               : *reinterpret_cast<const u4*>(qp + ks * 64);
             v[0] ^= flip; v[1] ^= flip; v[2] ^= flip; v[3] ^= flip;
-            st.qf[ks][qt] = v;
+            if constexpr (QT == 4) {
+                if constexpr (!BF16) {
+                    if (p.q_bf16) v = bf16x8_to_f16x8(v);   // K and V are binary16 copies: Q follows (exact for normal binary16 magnitudes)
+                }
+                asm volatile("" : "=a"(st.qf[ks][qt]) : "0"(v));   // accumulation registers from here on
+            } else {
+                st.qf[ks][qt] = v;
+            }
         }
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -2039,10 +1997,13 @@ __device__ __forceinline__ void process_q_tile_narrow(const Params& p, const Nar
     }
     if (p.stream_q) __syncthreads();      // the fragments are in registers before the first K/V fetch overwrites the rows
 
-    scan_tiles<D, BF16, CAUSAL, PHASES>(st, lm, Kh, Vh, N, p.c, j0, step, nkv, qw0, qw0 + (lane & 15), lane, lds);
+    if constexpr (QT == 4) scan_tiles_wide<BF16, CAUSAL>(st, lm, Kh, Vh, N, p.c, j0, step, nkv, qw0, lane, lds);
+    else scan_tiles<D, BF16, CAUSAL, PHASES>(st, lm, Kh, Vh, N, p.c, j0, step, nkv, qw0, qw0 + (lane & 15), lane, lds);
 
     // ---- epilogue: O_i = acc / l  (the division Alg. 1 leaves implicit; Eq. 1 fixes it)
-    const float inv[2] = {1.0f / st.L[0][0], 1.0f / st.L[1][0]};
+    float inv[QT];
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) inv[qt] = 1.0f / (QT == 4 ? quad_sum(st.L[qt][0]) : st.L[qt][0]);
     if (p.stream_o) {
         // (the scan ended with a barrier and nothing in flight: the K/V buffers serve as staging area)
         LDS_PTR(char) stage = lds + wave * 4096;
@@ -2050,36 +2011,39 @@ __device__ __forceinline__ void process_q_tile_narrow(const Params& p, const Nar
         asm volatile("" : "+v"(l2));     // lane-derived addresses are built here, not carried across the scan
         const int g = l2 >> 4, ln = l2 & 15;
         const int sw = ln & 7;
-        const int rows_left = N - qw0;      // <= 0: all rows lie beyond the sequence
-        if (p.o_dtype == SAWATTN_F32) {
-            constexpr size_t RB = (size_t)D * 4;
-            char* dst = static_cast<char*>(p.O) + ((size_t)hh * N + qw0) * RB;
 #pragma unroll
-            for (int pass = 0; pass < DB / 2; ++pass) {          // 32 columns = 128 bytes per row
+        for (int q0 = 0; q0 < QT; q0 += 2) {      // 32 rows at a time
+            const int row0 = qw0 + 16 * q0, rows_left = N - row0;      // <= 0: all rows lie beyond the sequence
+            if (p.o_dtype == SAWATTN_F32) {
+                constexpr size_t RB = (size_t)D * 4;
+                char* dst = static_cast<char*>(p.O) + ((size_t)hh * N + row0) * RB;
 #pragma unroll
-                for (int dbl = 0; dbl < 2; ++dbl)
+                for (int pass = 0; pass < DB / 2; ++pass) {          // 32 columns = 128 bytes per row
 #pragma unroll
-                    for (int qt = 0; qt < 2; ++qt) {
-                        const f4 v = st.o[2 * pass + dbl][qt] * inv[qt];
-                        *(LDS_PTR(f4))(stage + (16 * qt + ln) * 128 + (((4 * dbl + g) ^ sw) << 4)) = v;
-                    }
-                drain_stage(stage, dst + pass * 128, RB, rows_left, l2);
-            }
-        } else {
-            constexpr size_t RB = (size_t)D * 2;
-            char* dst = static_cast<char*>(p.O) + ((size_t)hh * N + qw0) * RB;
+                    for (int dbl = 0; dbl < 2; ++dbl)
 #pragma unroll
-            for (int pass = 0; pass < DB / 4; ++pass) {   // 64 columns = 128 bytes per row
+                        for (int q = 0; q < 2; ++q) {
+                            const f4 v = st.o[2 * pass + dbl][q0 + q] * inv[q0 + q];
+                            *(LDS_PTR(f4))(stage + (16 * q + ln) * 128 + (((4 * dbl + g) ^ sw) << 4)) = v;
+                        }
+                    drain_stage(stage, dst + pass * 128, RB, rows_left, l2);
+                }
+            } else {
+                constexpr size_t RB = (size_t)D * 2;
+                char* dst = static_cast<char*>(p.O) + ((size_t)hh * N + row0) * RB;
 #pragma unroll
-                for (int dbl = 0; dbl < 4; ++dbl)
+                for (int pass = 0; pass < DB / 4; ++pass) {   // 64 columns = 128 bytes per row
 #pragma unroll
-                    for (int qt = 0; qt < 2; ++qt) {
-                        const f4 v = st.o[4 * pass + dbl][qt] * inv[qt];
-                        LDS_PTR(char) at = stage + (16 * qt + ln) * 128 + (((2 * dbl + (g >> 1)) ^ sw) << 4) + 8 * (g & 1);
-                        if (p.o_dtype == SAWATTN_F16) *(LDS_PTR(h4))at = __builtin_convertvector(v, h4);
-                        else *(LDS_PTR(b4))at = __builtin_convertvector(v, b4);
-                    }
-                drain_stage(stage, dst + pass * 128, RB, rows_left, l2);
+                    for (int dbl = 0; dbl < 4; ++dbl)
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) {
+                            const f4 v = st.o[4 * pass + dbl][q0 + q] * inv[q0 + q];
+                            LDS_PTR(char) at = stage + (16 * q + ln) * 128 + (((2 * dbl + (g >> 1)) ^ sw) << 4) + 8 * (g & 1);
+                            if (p.o_dtype == SAWATTN_F16) *(LDS_PTR(h4))at = __builtin_convertvector(v, h4);
+                            else *(LDS_PTR(b4))at = __builtin_convertvector(v, b4);
+                        }
+                    drain_stage(stage, dst + pass * 128, RB, rows_left, l2);
+                }
             }
         }
         __syncthreads();          // the staging area is read before the next tile's fetches overwrite it
@@ -2089,7 +2053,7 @@ __device__ __forceinline__ void process_q_tile_narrow(const Params& p, const Nar
     asm volatile("" : "+v"(lane_out));
     const int g_out = lane_out >> 4, qrow_out = qw0 + (lane_out & 15);
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt) {
+    for (int qt = 0; qt < QT; ++qt) {
         if (qrow_out + 16 * qt < N) {
             const size_t orow = ((size_t)hh * N + qrow_out + 16 * qt) * D;
 #pragma unroll
@@ -2190,40 +2154,15 @@ __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
 template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false>
 __global__ __launch_bounds__(kThreads, HALVES ? (D == 64 ? 2 : 1) : NH == 2 ? 1 : (D == 64 ? 3 : 2)) void attn_fwd_kernel(Params p) {
     extern __shared__ __align__(16) char smem[];
-    if constexpr (NH == 2 && !BF16) {
-        // The same loop as for_each_q_tile, in the kernel's own body: from there the compiler gives the binary16 kernels with
-        // 256-row tiles other registers, which their scans run 0.3 to 0.7 % faster with (32 heads x 16384: 3663 against 3652
-        // us, causal 1919 against 1906 us).  The bfloat16 ones are 0.6 to 1.5 % faster with for_each_q_tile (128 x 32768
-        // causal: 32.30 against 32.08 ms, 32 x 16384 causal: 2050 against 2020 us).
-        const Schedule& s = p.sched;
-        const int lane0 = threadIdx.x & 63;
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        int local = 0;
-        for (int it = 0; it < s.local_iters; ++it) {
-            const Work w = decode_work(s, (int)blockIdx.x, it, CAUSAL, p.sawtooth != 0);
-            if (w.tile >= 0) {
-                const int nkv = visible_kv_tiles(s, w.tile, p.N, CAUSAL);
-                const int j0 = w.backward ? nkv - 1 : 0;
-                const int step = w.backward ? -1 : 1;
-                if (p.trace && threadIdx.x == 0) {
-                    int32_t* rec = p.trace + ((size_t)blockIdx.x * p.max_local + local) * 4;
-                    rec[0] = w.head; rec[1] = w.tile; rec[2] = j0; rec[3] = j0 + (nkv - 1) * step;
-                }
-                int lane = lane0;
-                asm volatile("" : "+v"(lane));
-                const LaneMap<D> lm(wave, lane);
-                process_q_tile<D, BF16, CAUSAL, NH, HALVES>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
-                ++local;
-            }
-            if (w.sync_after) domain_sync(p.ticket_set, (int)blockIdx.x % kDomains, s.slots);
-        }
-        if (p.trace_count && threadIdx.x == 0) p.trace_count[blockIdx.x] = local;
-    } else {
-        for_each_q_tile<CAUSAL, NH == 1>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
+    for_each_q_tile<CAUSAL, NH == 1>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
+        if constexpr (NH == 2) {
+            const NarrowMap<D> lm(wave, lane);
+            process_q_tile_narrow<D, BF16, CAUSAL, false, 4>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
+        } else {
             const LaneMap<D> lm(wave, lane);
-            process_q_tile<D, BF16, CAUSAL, NH, HALVES>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
-        });
-    }
+            process_q_tile<D, BF16, CAUSAL, HALVES>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
+        }
+    });
 }
 
 // 128-row tiles where workgroups share the compute units (see default_shared_kernel, default_phase_priority).
