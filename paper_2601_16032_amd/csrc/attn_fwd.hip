@@ -911,7 +911,11 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
     constexpr int NB = 2 * DB;            // V^T fragments of a tile (two MFMAs each)
     constexpr int NL = G::kLoadsPerWave;
     constexpr int TA = 2 * NA, TB = 2 * NB;   // MFMAs of the first and of the second product
-    constexpr int LA = D == 64 ? 2 : 3;   // fragments read ahead of their use
+    constexpr int LA = 2;                 // fragments read ahead of their use
+    // At d = 128 fragments are read two at a time and used in the order second, first, so that the one wait for the later read covers
+    // both: half as many waits in the instruction stream.  (Read one by one, three ahead: 12 heads x 5000, bfloat16: 155.7 against 152.7
+    // us with the fetches below, 32 x 8192, causal: 487 against 477 us.  At d = 64 it costs registers: 0 to +3 %.)
+    constexpr bool PAIRS = D == 128;
     const unsigned lds0 = (unsigned)(size_t)lds;
     const int g = lane >> 4;
     // Binary16 1.0, A operand of the row sums.  Made where it is used, from a scalar register: a constant that the compiler
@@ -996,8 +1000,8 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
         const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s4))(size_t)(at + 16 * G::kRowBytes));
         return __builtin_bit_cast(u4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
-    auto s_mfma = [&](int m, int qt, u4 a) {
-        A[m / KS][qt] = mfma_16x16<BF16>(a, st.qf[m % KS][qt], m % KS == 0 ? zero : A[m / KS][qt]);
+    auto s_mfma = [&](int m, int qt, u4 a, bool first) {
+        A[m / KS][qt] = mfma_16x16<BF16>(a, st.qf[m % KS][qt], first ? zero : A[m / KS][qt]);
     };
     auto o_mfma = [&](int m, int qt, u4 a) { st.o[m % DB][qt] = mfma_16x16<false>(a, pf[m / DB][qt], st.o[m % DB][qt]); };
     // The scores in A: -inf where the key is not visible.  Register r of block kb is key
@@ -1082,7 +1086,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
         for (int m = 0; m < NA; ++m) {
             if (m + LA < NA) a[m + LA] = k_read(m + LA);
 #pragma unroll
-            for (int qt = 0; qt < 2; ++qt) s_mfma(m, qt, a[m]);
+            for (int qt = 0; qt < 2; ++qt) s_mfma(m, qt, a[m], m % KS == 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -1141,12 +1145,14 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
 #pragma unroll
             for (int m = 0; m < LA; ++m) a[m] = ak[m];
 #pragma unroll
-            for (int m = 0; m < NA; ++m) {
-                if (m + LA < NA) a[m + LA] = k_read(m + LA);
+            for (int q = 0; q < NA; ++q) {
+                const int m = PAIRS ? q ^ 1 : q;
+                if (!PAIRS && q + LA < NA) a[q + LA] = k_read(q + LA);
+                if (PAIRS && q % 2 == 0 && q + LA < NA) { a[q + LA] = k_read(q + LA); a[q + LA + 1] = k_read(q + LA + 1); }
 #pragma unroll
                 for (int qt = 0; qt < 2; ++qt) {
-                    const int t = 2 * m + qt;
-                    s_mfma(m, qt, a[m]);
+                    const int t = 2 * q + qt;
+                    s_mfma(m, qt, a[m], q % KS == 0);
 #pragma unroll
                     for (int n = t * OA / TA; n < (t + 1) * OA / TA; ++n) op_a(n);
                     __builtin_amdgcn_sched_barrier(0);
@@ -1163,7 +1169,8 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
         mask();
         // ---- phase B.  Under its MFMAs, in order: the row maxima of A, the row sums of tile i, the shifted scores of tile
         //      i+1 -- if the reference maximum has to be raised (need), they are taken again behind the iteration.  The direct
-        //      loads of an iteration are spread over it too, V first because it is needed first.
+        //      loads of an iteration come along too, one behind every fourth MFMA (spread over all of it: 0 to +1 %; at d = 64 under
+        //      the mask that is 0.4 % better), V first because it is needed first.
         //      With V through registers the conversion comes along with the maxima, then the next V loads.  (The V registers
         //      have landed: the compiler is told so here, or it would wait for them where it uses them, and with them for the
         //      direct loads issued in between, which it does not know of.)
@@ -1197,13 +1204,14 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
         };
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
-            const int m = t / 2;
-            if ((t & 1) == 0 && m + LA < NB) av[m + LA] = v_read(m + LA);
+            const int q = t / 2, m = PAIRS ? q ^ 1 : q;
+            if (!PAIRS && t % 2 == 0 && q + LA < NB) av[q + LA] = v_read(q + LA);
+            if (PAIRS && t % 4 == 0 && q + LA < NB) { av[q + LA] = v_read(q + LA); av[q + LA + 1] = v_read(q + LA + 1); }
             if (BF16 && t == T0) v_to_regs();
             o_mfma(m, t & 1, av[m]);
             if (t % (TB / 4) == TB / 4 - 1) sum_mfma(t / (TB / 2), t / (TB / 4) & 1);
-#pragma unroll
-            for (int li = t * TL / TB; li < (t + 1) * TL / TB; ++li) {
+            constexpr bool EARLY = D == 128 || !CAUSAL;
+            for (int li = EARLY ? t / 4 : t * TL / TB; li < TL && (EARLY ? t % 4 == 1 && li == t / 4 : li < (t + 1) * TL / TB); ++li) {
                 if (li < NV) tile_load_to_lds(dv, lm.fill_src + li * 4096, vdst + li * 4096);
                 else tile_load_to_lds(dk, lm.fill_src + (li - NV) * 4096, kdst + (li - NV) * 4096);
             }
