@@ -20,7 +20,8 @@
 // lane: lanes l and l+32 share a query row and hold disjoint key subsets, so the running maximum is merged across the
 // pair every tile while the running sum stays a per-lane partial (it is linear) and is merged once in the epilogue.  A
 // query tile's scan is a software-pipelined run of full, unmasked K/V tiles (pipelined_range) plus, at one end, a short
-// run of masked tiles (general_range).  With 64-row tiles it walks the two halves of a scan at once (HALVES).
+// run of masked tiles (general_range).  With 64-row tiles it walks the two halves of a scan at once (HALVES), short scans
+// with everything in one pipeline (scan_halves).
 //
 // attn_fwd_shared_kernel (scan_tiles), 128-row tiles where workgroups share the compute units: both contractions on
 // v_mfma_f32_16x16x32, layouts as described there.  Four lanes share a query row, row sums are a product with ones,
@@ -1698,6 +1699,373 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
 }
 
 
+// ------------------------------------------------------------------------------------------------
+// The scan of a 64-row tile, walked as two halves at once, for small problems, where the chip has more compute units than there are query
+// tiles and the length of one wavefront's walk is what the launch takes.  Run r takes the positions r*count .. of the scan's `nkv` tiles j0,
+// j0 + step, ..., count = ceil(nkv / 2); wavefronts 0 and 1 compute on run 0, wavefronts 2 and 3, for the same rows, on run 1, and all four
+// fetch the tiles of both into a set of buffers each (K0 K1 V0 V1).  This wavefront computes on run `run`.
+//
+// 32x32x16 MFMAs, transposed like pipelined_range.  A wavefront has its SIMD to itself, so what counts is the instructions it issues per tile
+// and what it waits for in between.  The order is scan_tiles': masked tiles in the pipeline, one barrier between the two products, and
+// behind it the fetches of V(i+1) and K(i+3), which then have a whole iteration to land; fragments in pairs with one wait each; the
+// maximum per lane on raw scores, against a limit.  d = 64: 243 instructions per tile against pipelined_range's 276, of 20 and 16 MFMAs.
+// What it saves are the odd and masked tiles taken one at a time, with nothing in flight, before or after the halves, about 2 us of a
+// launch (figures at launch_halves); per tile of a long scan it is 3 to 4 % slower.  The row sums' products moved into the first product,
+// or a quarter of the exponentials into the second, were 1 to 2 % slower yet.
+template <int D, bool BF16, bool CAUSAL>
+__device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& lm, const char* Kh, const char* Vh, int N, float c, int j0,
+                                            int step, int nkv, int qw0, int qrow, int lane, LDS_PTR(char) lds, int run) {
+    using G = Geo<D>;
+    constexpr unsigned kSet = 4 * G::kTile;   // one set of buffers: K0 K1 V0 V1
+    constexpr int KS = D / 16, DB = D / 32;
+    constexpr int NA = 2 * KS;                // MFMAs (and K fragments) of one S^T tile
+    constexpr int NB = 4 * DB;                // MFMAs (and V^T fragments) of one O^T update
+    constexpr int NL = G::kLoadsPerWave, RL = 2 * NL;
+    constexpr int LA = 4;                     // fragments read ahead of their use, in pairs
+    const unsigned lds0 = (unsigned)(size_t)lds;
+    const int g = lane >> 5;
+    const int count = (nkv + 1) / 2;          // tiles of run 0; run 1 has as many or one less
+    const int mine = run == 0 ? count : nkv - count < 1 ? 1 : nkv - count;      // (a run of no tile computes on a stand-in, see the end)
+    const u4 ones = {0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u};
+    const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f16v A[2];          // S^T of the tile one ahead: block b = keys 32b..32b+31 of the tile
+    // Row sum of the rounded probabilities: at d = 64 a product with ones (in every element of L), at d = 128, where the matrix pipe
+    // is the busier one, two fused multiply-adds per pair (this lane's keys, in two partial sums).
+    constexpr bool kSumMfma = D == 64;
+    f16v L = zero;
+    float L_lo = 0.f, L_hi = 0.f;
+    const _Float16 one = opaque_one();
+    float x[32];        // score*c - M of the current tile, index 16*b + r
+    u4 pf[4];           // its probabilities as B operands
+    u4 vreg[RL];        // bfloat16 V chunks in flight (BF16 only), run r in vreg[r * NL ...]
+    float lim = -INFINITY, mx;
+
+    unsigned rk[KS], rv[DB][2];      // LDS read addresses: K of the tile one ahead, V of the current tile
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) rk[ks] = lds0 + run * kSet + lm.k_rd[ks];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+        rv[db][0] = lds0 + run * kSet + 2 * G::kTile + lm.v_rd[db][0];
+        rv[db][1] = lds0 + run * kSet + 2 * G::kTile + lm.v_rd[db][1];
+    }
+    // Position p of run r.  Fetches beyond the end of a run fetch its last tile again, into a buffer nobody reads.
+    auto tile_of = [&](int r, int p) {
+        const int at = r == 0 ? (p < count ? p : count - 1) : (count + p < nkv ? count + p : nkv - 1);
+        return j0 + at * step;
+    };
+    auto offsets = [&](int j, unsigned (&off)[NL]) {      // the rows that the last tile of the sequence lacks repeat row N-1
+        const int left = N - j * kTileKV;
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            off[l] = lm.fill_src[l];
+            const unsigned row = off[l] / G::kRowBytes;
+            if (left < kTileKV) off[l] = (row < (unsigned)left ? row : (unsigned)left - 1) * G::kRowBytes + off[l] % G::kRowBytes;
+        }
+    };
+    struct Fetch {       // the tiles of a fetch in both runs and the lanes' offsets in them
+        const char* base[2];
+        unsigned off[2][NL];
+    };
+    auto aim = [&](const char* head, int p) {
+        Fetch f;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int j = tile_of(r, p);
+            f.base[r] = head + (long long)j * G::kTile;
+            offsets(j, f.off[r]);
+        }
+        return f;
+    };
+    // From position p - 1 to p, p > 0.  (Of all of these only run 1 of a forward scan can reach the sequence's ragged last tile.)
+    const long long stride = step * (long long)G::kTile;
+    const int ragged_at = N % kTileKV && step > 0 ? nkv - 1 - count : -1;
+    auto advance = [&](Fetch& f, int p) {
+        f.base[0] += p < count ? stride : 0;
+        f.base[1] += count + p < nkv ? stride : 0;
+        if (__builtin_expect(p == ragged_at, 0)) offsets(tile_of(1, p), f.off[1]);
+    };
+    auto load = [&](const Fetch& f, int li, unsigned dst) {      // load li of the 2 NL of a K or V fetch
+        const int r = li / NL, l = li % NL;
+        load_to_lds_16B(f.base[r], f.off[r][l], dst + r * kSet + l * 4096);
+    };
+    auto fetch_burst = [&](const Fetch& f, unsigned dst) {
+#pragma unroll
+        for (int li = 0; li < RL; ++li) load(f, li, dst);
+    };
+    auto v_to_regs = [&](const Fetch& f) {
+#pragma unroll
+        for (int li = 0; li < RL; ++li) vreg[li] = *reinterpret_cast<const u4*>(f.base[li / NL] + f.off[li / NL][li % NL]);
+    };
+    auto convert_word = [&](int w, unsigned dst) {      // w-th 32-bit word of the fetched chunks; every fourth completes 16 bytes for LDS
+        f2 y;
+        const unsigned word = vreg[w / 4][w % 4];
+        y[0] = __builtin_bit_cast(float, word << 16);
+        y[1] = __builtin_bit_cast(float, word & 0xffff0000u);
+        vreg[w / 4][w % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(y, h2));
+        if (w % 4 == 3)
+            *(LDS_PTR(u4))(size_t)(dst + (w / 4 / NL) * kSet + (w / 4 % NL) * 4096 + lane * 16) = vreg[w / 4];
+    };
+    constexpr int CW = RL * 4;
+    // fragment m of K: columns 16*(m / 2).., keys 32*(m % 2)..; fragment m of V^T: keys 16*(m / DB).., columns 32*(m % DB)..
+    auto k_read = [&](int m) -> u4 { return *(LDS_PTR(u4))(size_t)(rk[m / 2] + (m & 1) * 32 * G::kRowBytes); };
+    auto v_read = [&](int m) -> s8 {
+        const int ks = m / DB, db = m % DB;
+        const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s4))(size_t)(rv[db][0] + ks * 16 * G::kRowBytes));
+        const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s4))(size_t)(rv[db][1] + ks * 16 * G::kRowBytes));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+    auto s_mfma = [&](int m, u4 a, bool first) { A[m & 1] = mfma_16bit<BF16>(a, st.qf[m / 2], first ? zero : A[m & 1]); };
+    auto o_mfma = [&](int m, s8 a) {
+        st.o[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, pf[m / DB]), st.o[m % DB], 0, 0, 0);
+    };
+    auto sum_mfma = [&](int ks) {
+        if constexpr (kSumMfma) L = mfma_16bit<false>(ones, pf[ks], L);
+    };
+    auto sum_pair = [&](int u) { add_pair(L_lo, L_hi, __builtin_bit_cast(h2, (unsigned)pf[u / 4][u % 4]), one); };
+    const int all_see = CAUSAL ? (qw0 < N - 1 ? qw0 : N - 1) : N - 1;      // last key visible to every row of the wavefront
+    int kv0 = tile_of(run, 0) * kTileKV;                                   // first key of the tile in A
+    auto mask = [&]() {
+        if (__builtin_expect(kv0 + kTileKV - 1 > all_see, 0)) {
+            const int last_key = CAUSAL ? (qrow < N - 1 ? qrow : N - 1) : N - 1;
+            int ahead = last_key - kv0 - 4 * g;
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    asm volatile("" : "+v"(ahead));     // (separate comparisons: no lane masks kept and combined)
+                    A[b][r] = 32 * b + 8 * (r >> 2) + (r & 3) > ahead ? -INFINITY : A[b][r];
+                }
+        }
+    };
+    auto shift_score = [&](int k) { x[k] = __builtin_fmaf(A[k >> 4][k & 15], c, -st.M); };
+    auto max_op = [&](int op) { mx = fmaxf(fmaxf(mx, A[op >> 3][2 * (op & 7)]), A[op >> 3][2 * (op & 7) + 1]); };
+    auto raise_reference = [&]() {      // as in scan_tiles
+        float t = mx;
+        asm volatile("" : "+v"(t));
+        t = pair_max(t);
+        const bool up = t > lim, fresh = lim == -INFINITY;
+        const float Mnew = up ? t * c : st.M;
+        const float alpha = up && !fresh ? fast_exp2(st.M - Mnew) : 1.0f;
+        st.M = Mnew;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) L[r] *= alpha;
+        L_lo *= alpha;
+        L_hi *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st.o[db][r] = fresh ? 0.f : st.o[db][r] * alpha;
+        if (up) lim = score_limit(t, Mnew, c);
+#pragma unroll
+        for (int k = 0; k < 32; ++k) shift_score(k);
+    };
+    float e[16][2];
+    auto op_a = [&](int n) {      // the two exponentials of pair n / 3, the convert of the one before
+        const int u = n / 3, k = n % 3;
+        if (k < 2) e[u][k] = fast_exp2(x[2 * u + k]);
+        else if (u > 0) pf[(u - 1) / 4][(u - 1) % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u - 1][0], e[u - 1][1]}, h2));
+    };
+    auto last_convert = [&]() { pf[3][3] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[15][0], e[15][1]}, h2)); };
+    constexpr int OA = 48;
+
+    // ---------------------------------------------------------------- prologue: K(0..1) and V(0) on their way, S(0)
+    const unsigned fill = lds0 + lm.fill_dst;
+    Fetch fv = aim(Vh, 0), fk = aim(Kh, 2);
+    fetch_burst(aim(Kh, 0), fill);
+    fetch_burst(aim(Kh, 1), fill + G::kTile);
+    __builtin_amdgcn_sched_barrier(0);    // (the counts of the waits below go by this order)
+    asm volatile("" ::: "memory");
+    if constexpr (BF16) v_to_regs(fv);
+    else fetch_burst(fv, fill + 2 * G::kTile);
+    landed_barrier<2 * RL>();
+    {
+        u4 a[NA];
+#pragma unroll
+        for (int m = 0; m < LA; ++m) a[m] = k_read(m);
+#pragma unroll
+        for (int m = 0; m < NA; ++m) {
+            if (m + LA < NA) a[m + LA] = k_read(m + LA);
+            s_mfma(m, a[m], m < 2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if constexpr (BF16) {
+#pragma unroll
+        for (int w = 0; w < CW; ++w) convert_word(w, fill + 2 * G::kTile);
+    }
+    landed_barrier<BF16 ? 0 : RL>();      // K(0) has been read, K(1) has landed
+    fetch_burst(fk, fill);
+    if constexpr (BF16) {
+        fv = aim(Vh, 1);
+        v_to_regs(fv);
+    }
+#pragma unroll
+    for (int l = 0; l < NL; ++l) { fk.off[0][l] = lm.fill_src[l]; fv.off[0][l] = lm.fill_src[l]; }
+    mask();
+    mx = lim;
+#pragma unroll
+    for (int op = 0; op < 16; ++op) max_op(op);
+    {
+        const float t = pair_max(mx);
+        st.M = t == -INFINITY ? 0.f : t * c;
+        if (t != -INFINITY) lim = score_limit(t, st.M, c);
+    }
+#pragma unroll
+    for (int k = 0; k < 32; ++k) shift_score(k);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) rk[ks] += G::kTile;   // K of tile 1 is in buffer 1
+    u4 ak[LA];
+#pragma unroll
+    for (int m = 0; m < LA; ++m) ak[m] = k_read(m);
+
+    // ---------------------------------------------------------------- steady state: iteration i
+    // reads K(i+1) from K buffer (i+1)&1 and V(i) from V buffer i&1; fetches K(i+3) and V(i+1) into the buffers (i+1)&1 (bfloat16: V(i+1) from
+    // registers, then V(i+2) into them).  Returns whether the reference maximum has to be raised before tile i+1 can be used.
+    auto iteration = [&](int i) -> bool {
+        const unsigned kdst = fill + ((i + 1) & 1) * G::kTile, vdst = kdst + 2 * G::kTile;
+        {
+            u4 a[NA];
+#pragma unroll
+            for (int m = 0; m < LA; ++m) a[m] = ak[m];
+#pragma unroll
+            for (int t = 0; t < NA; ++t) {
+                if (t % 2 == 0 && t + LA < NA) { a[t + LA] = k_read(t + LA); a[t + LA + 1] = k_read(t + LA + 1); }
+                s_mfma(t ^ 1, a[t ^ 1], t < 2);
+#pragma unroll
+                for (int n = t * OA / NA; n < (t + 1) * OA / NA; ++n) op_a(n);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            last_convert();
+        }
+        asm volatile("" : "+v"(pf[0]), "+v"(pf[1]), "+v"(pf[2]), "+v"(pf[3]));
+        landed_barrier<0>();
+        s8 av[NB];
+#pragma unroll
+        for (int m = 0; m < LA; ++m) av[m] = v_read(m);
+        __builtin_amdgcn_sched_barrier(0);
+        advance(fv, BF16 ? i + 2 : i + 1);      // (while the first fragments are on their way)
+        advance(fk, i + 3);
+        if constexpr (BF16) {
+#pragma unroll
+            for (int l = 0; l < RL; ++l) asm volatile("" : "+v"(vreg[l]));
+        }
+        kv0 += step * kTileKV;
+        mask();
+        __builtin_amdgcn_sched_barrier(0);
+        mx = lim;
+        const int flip = i & 1 ? G::kTile : -G::kTile;      // K(i+2) is in buffer i&1, V(i+1) in buffer (i+1)&1
+        bool need = false;
+        constexpr int OC = BF16 ? 3 * CW : 0;            // conversions count as three
+        constexpr int OM = 16 + OC, OB = OM + 32 + (kSumMfma ? 0 : 16);
+        constexpr int T0 = (OM * NB + OB - 1) / OB;      // first MFMA after the conversions
+        constexpr int TL = (BF16 ? 1 : 2) * RL;          // direct loads
+        auto op_b = [&](int n) {
+            if (n < OM) {
+                const int j = n * 16 / OM, done = (n + 1) * 16 / OM;
+                if (j != done) max_op(j);
+                if constexpr (BF16) {
+                    const int w = n * CW / OM;
+                    if (w != (n + 1) * CW / OM) convert_word(w, vdst);
+                }
+            } else if (n < OM + 32) {
+                shift_score(n - OM);
+            } else {
+                sum_pair(n - OM - 32);
+            }
+        };
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            if (t % 2 == 0) {
+                if (t + LA < NB) { av[t + LA] = v_read(t + LA); av[t + LA + 1] = v_read(t + LA + 1); }
+            }
+            if (BF16 && t == T0) v_to_regs(fv);
+            o_mfma(t ^ 1, av[t ^ 1]);
+            if (t % DB == DB - 1) sum_mfma(t / DB);
+#pragma unroll
+            for (int li = t * TL / NB; li < (t + 1) * TL / NB; ++li) {      // V first because it is needed first
+                if (!BF16 && li < RL) load(fv, li, vdst);
+                else load(fk, li % RL, kdst);
+            }
+#pragma unroll
+            for (int n = t * OB / NB; n < (t + 1) * OB / NB; ++n) {
+                op_b(n);
+                if (n == OM + 4) need = __builtin_amdgcn_ballot_w64(!(mx <= lim)) != 0;      // (mx starts from lim)
+            }
+            if (t == NB - 3) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) rk[ks] += flip;
+#pragma unroll
+                for (int m = 0; m < LA; ++m) ak[m] = k_read(m);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int db = 0; db < DB; ++db) { rv[db][0] -= flip; rv[db][1] -= flip; }
+        return need;
+    };
+    auto fetch_only = [&](int i) {       // iteration i's fetches (bfloat16: V(i+1) into LDS first)
+        const unsigned kdst = fill + ((i + 1) & 1) * G::kTile, vdst = kdst + 2 * G::kTile;
+        advance(fk, i + 3);
+        advance(fv, BF16 ? i + 2 : i + 1);
+        if constexpr (BF16) {
+#pragma unroll
+            for (int l = 0; l < RL; ++l) asm volatile("" : "+v"(vreg[l]));
+#pragma unroll
+            for (int w = 0; w < CW; ++w) convert_word(w, vdst);
+            v_to_regs(fv);
+        } else {
+            fetch_burst(fv, vdst);
+        }
+        fetch_burst(fk, kdst);
+    };
+    int i = 0;
+    while (i + 1 < mine) {
+        bool need = false;
+#pragma unroll 1
+        for (; i + 1 < mine; ++i) {
+            need = iteration(i);
+            if (need) { ++i; break; }
+        }
+        if (need) raise_reference();
+    }
+    // ---------------------------------------------------------------- last tile: probabilities, then O^T += V^T P^T
+#pragma unroll
+    for (int n = 0; n < OA; ++n) op_a(n);
+    last_convert();
+    if constexpr (!kSumMfma) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) sum_pair(u);
+    }
+    landed_barrier<0>();
+    if (mine < count) fetch_only(mine - 1);
+    {
+        s8 av[NB];
+#pragma unroll
+        for (int m = 0; m < LA; ++m) av[m] = v_read(m);
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+            if (t + LA < NB) av[t + LA] = v_read(t + LA);
+            o_mfma(t, av[t]);
+            if (t % DB == DB - 1) sum_mfma(t / DB);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll 1
+    for (i = mine; i < count; ++i) {      // run 1 is one tile shorter: the barriers of the other wavefronts
+        landed_barrier<0>();
+        if (i + 1 < count) fetch_only(i);
+    }
+    __syncthreads();   // all reads of the last tile are done before anything refills the buffers
+    st.L = kSumMfma ? 0.5f * L[0] : L_lo + L_hi;     // (both lanes of a pair hold L, the row's whole sum)
+    if (lim == -INFINITY) st.M = -INFINITY;      // nothing was seen: weight 0 in the merge
+    if (run == 1 && nkv == 1) {             // a run of no tile
+        st.M = -INFINITY;
+        st.L = 0.f;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) st.o[db] = zero;
+    }
+}
+
 // The epilogue where variant.qo_streaming asks for it: O leaves through LDS so that a store instruction writes whole
 // 128-byte lines (8 rows x 128 bytes per instruction, 16 bytes per lane), marked non-temporal: the rows of O are written
 // once and never read by the kernel, and written this way they do not take the place of K/V tiles in the L2.
@@ -1724,13 +2092,17 @@ __device__ __forceinline__ void drain_stage(LDS_PTR(char) stage, char* dst, size
 
 // One query tile (Alg. 1 body) of attn_fwd_kernel: rows [t*128, (t+1)*128) of head `hh`, K/V tiles j0, j0+step, ... (nkv of
 // them).
-// HALVES: the tile has 64 rows; of its full, unmasked K/V tiles wavefronts
-// 0 and 1 take the first half and wavefronts 2 and 3, for the same rows, the second half, at once, and the two partial
-// results are merged through LDS (the merge of two softmax partials: common reference maximum, both rescaled to it).
-// What does not split evenly or needs the mask -- an odd plain tile, the diagonal tile, a ragged last tile -- is taken
-// one tile at a time by wavefronts 0 and 1 alone, after the merge in a forward scan and before the halves in a
-// backward one, where it comes first.
-template <int D, bool BF16, bool CAUSAL, bool HALVES = false>
+// HALVES: the tile has 64 rows; wavefronts 0 and 1 take the first half of its K/V tiles and wavefronts 2 and 3, for the same rows, the
+// second half, at once, and the two partial results are merged through LDS (the merge of two softmax partials: common reference maximum,
+// both rescaled to it).  Which tiles those are, and what happens to the others, is the kernel's SPLIT:
+// kSplitEven   all of them, full and even in number: pipelined_range.  A kernel without the code for any others is smaller, which counts
+//              in launches of some microseconds: 256 keys, d = 64: 6.05 -> 5.7 us, 4 x 1024, d = 128: 15.2 -> 14.3, 8 x 2048: 15.8 -> 15.4.
+// kSplitShort  all of them, in the one pipeline of scan_halves.
+// kSplitLong   the full, unmasked ones, in pipelined_range.  An odd plain tile, the diagonal tile and a ragged last tile are taken one at
+//              a time by wavefronts 0 and 1 alone, after the merge in a forward scan and before the halves in a backward one.
+enum SplitKind { kSplitEven, kSplitShort, kSplitLong };
+
+template <int D, bool BF16, bool CAUSAL, bool HALVES = false, int SPLIT = kSplitLong>
 __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>& lm, int hh, int t, int j0, int step,
                                                int nkv, int wave, int lane, LDS_PTR(char) lds) {
     using G = Geo<D>;
@@ -1788,9 +2160,8 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
             if constexpr (!HALVES) { v[0] ^= flip; v[1] ^= flip; v[2] ^= flip; v[3] ^= flip; }
             st.qf[ks] = v;
         }
-        // (Behind a branch: where nothing is done to them here, the fragments are on their way while the first tiles
-        // are fetched.  One head x 256: 6.21 -> 6.05 us, 4 x 1024, d = 128: 15.6 -> 15.2, 2 x 700, d = 128: 16.2 -> 15.5;
-        // with 128-row tiles it changes times by -1 to +1 %, so the flip stays unconditional there.)
+        // (Behind a branch: where nothing is done to them here, the fragments are on their way while the first tiles are fetched.  One head
+        // x 256: 6.2 -> 6.1 us, 2 x 700, d = 128: 16.2 -> 15.5 us; with 128-row tiles it is 0 to +1 %.)
         if constexpr (HALVES) {
             if (p.negate_q) {
 #pragma unroll
@@ -1819,11 +2190,20 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
         general_range<D, BF16, CAUSAL, true>(st, lm, Kh, Vh, N, c, j_first, step, n_masked, qw0, qrow, lane, lds);
     };
     if constexpr (HALVES) {
-        const int half = n_plain / 2;                       // plain tiles per run
-        const int n_left = (n_plain & 1) + n_masked;        // tiles left for the tile-at-a-time code
-        if (step < 0)
-            general_range<D, BF16, CAUSAL, true>(st, lm, Kh, Vh, N, c, j0, step, n_left, qw0, qrow, lane, lds, run == 1);
-        pipelined_range<D, BF16, true>(st, lm, Kh, Vh, c, step > 0 ? j0 : j0 + n_left * step, step, half, lane, lds, run);
+        const int half = n_plain / 2;                       // kSplitLong: plain tiles per run
+        const int n_left = (n_plain & 1) + n_masked;        // and the tiles left for the tile-at-a-time code
+        if constexpr (SPLIT == kSplitEven) {
+            pipelined_range<D, BF16, true>(st, lm, Kh, Vh, c, j0, step, nkv / 2, lane, lds, run);
+        } else if constexpr (SPLIT == kSplitShort) {
+            if (nkv == 1)
+                general_range<D, BF16, CAUSAL, true>(st, lm, Kh, Vh, N, c, j0, step, 1, qw0, qrow, lane, lds, run == 1);
+            else
+                scan_halves<D, BF16, CAUSAL>(st, lm, Kh, Vh, N, c, j0, step, nkv, qw0, qrow, lane, lds, run);
+        } else {
+            if (step < 0)
+                general_range<D, BF16, CAUSAL, true>(st, lm, Kh, Vh, N, c, j0, step, n_left, qw0, qrow, lane, lds, run == 1);
+            pipelined_range<D, BF16, true>(st, lm, Kh, Vh, c, step > 0 ? j0 : j0 + n_left * step, step, half, lane, lds, run);
+        }
         // ---- merge: wavefront w + 2 hands (O^T, M, L) of its half to wavefront w, lane to lane, through LDS
         //      (value k of lane l of wavefront w + 2 at float index (2k + w) * 64 + l: no bank conflicts)
         constexpr int NV = DB * 16 + 2;
@@ -1850,10 +2230,12 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
             st.M = M;
             st.L = st.L * a0 + L1 * a1;
         }
-        __syncthreads();   // the exchange area is read before the next fetches overwrite it
-        if (step > 0)
-            general_range<D, BF16, CAUSAL, true>(st, lm, Kh, Vh, N, c, j0 + 2 * half * step, step, n_left, qw0, qrow, lane,
+        __syncthreads();   // the exchange area is read before anything else overwrites it
+        if constexpr (SPLIT == kSplitLong) {
+            if (step > 0)
+                general_range<D, BF16, CAUSAL, true>(st, lm, Kh, Vh, N, c, j0 + 2 * half * step, step, n_left, qw0, qrow, lane,
                                                      lds, run == 1);
+        }
     } else if (step > 0) {
         plain(j0);
         masked(j0 + n_plain * step);
@@ -2168,7 +2550,7 @@ __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
     if (p.trace_count && threadIdx.x == 0) p.trace_count[wg] = local;
 }
 
-template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false>
+template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false, int SPLIT = kSplitLong>
 __global__ __launch_bounds__(kThreads, HALVES ? (D == 64 ? 2 : 1) : NH == 2 ? 1 : (D == 64 ? 3 : 2)) void attn_fwd_kernel(Params p) {
     extern __shared__ __align__(16) char smem[];
     for_each_q_tile<CAUSAL, NH == 1>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
@@ -2177,7 +2559,7 @@ __global__ __launch_bounds__(kThreads, HALVES ? (D == 64 ? 2 : 1) : NH == 2 ? 1 
             process_q_tile_narrow<D, BF16, CAUSAL, false, 4>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
         } else {
             const LaneMap<D> lm(wave, lane);
-            process_q_tile<D, BF16, CAUSAL, HALVES>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
+            process_q_tile<D, BF16, CAUSAL, HALVES, SPLIT>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
         }
     });
 }
@@ -2266,9 +2648,9 @@ int launch_kernel(Params& p, int grid, int lds_bytes, hipStream_t stream) {
     return SAWATTN_OK;
 }
 
-template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false>
+template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false, int SPLIT = kSplitLong>
 int launch(Params& p, int grid, hipStream_t stream) {
-    return launch_kernel<attn_fwd_kernel<D, BF16, CAUSAL, NH, HALVES>>(
+    return launch_kernel<attn_fwd_kernel<D, BF16, CAUSAL, NH, HALVES, SPLIT>>(
         p, grid, NH == 2 ? kWideLdsBytes : (HALVES ? 2 : 1) * Geo<D>::kLdsBytes, stream);
 }
 
@@ -2281,6 +2663,24 @@ int launch_128(Params& p, int grid, hipStream_t stream) {
             return launch_kernel<attn_fwd_shared_kernel<D, BF16, CAUSAL, false>>(p, grid, Geo<D>::kLdsBytes, stream);
     }
     return launch_kernel<attn_fwd_shared_kernel<D, BF16, CAUSAL, true>>(p, grid, Geo<D>::kLdsBytes, stream);
+}
+
+// 64-row tiles: which of the kernels.  Without a mask a sequence of an even number of full tiles needs nothing but the pipeline (see
+// SplitKind).  Otherwise short scans go through scan_halves and long ones, where the pipeline's cheaper tiles outweigh the odd and masked ones
+// taken singly, stay with it.  Measured, pipeline -> scan_halves: 16 x 1000, d = 64: 12.1 -> 10.5 us; 8 x 2048 causal, bf16: 19.1 -> 17.2;
+// 24 x 2600 causal: 35.5 -> 34.3; 2 x 100, d = 128, causal: 9.4 -> 8.1; 5 x 1000, d = 128: 20.0 -> 18.3; 3000 causal, d = 128: 30.8 -> 28.6;
+// but 3 x 5000, d = 128, causal: 47.9 -> 49.6, 3 x 10000: 113.7 -> 115.0, 30000: 289.7 -> 297.1, and between 4096 and 16384 keys it goes either way
+// (2 x 8000, d = 128, causal: 68.9 -> 65.8).  One tile is all masked code, in the smaller kernel: 64 causal: 4.8 us against 4.9.
+template <int D, bool BF16>
+int launch_halves(Params& p, bool causal, int grid, hipStream_t stream) {
+    const bool brief = p.N > kTileKV && p.N <= 64 * kTileKV;
+    if (causal) {
+        if (brief) return launch<D, BF16, true, 1, true, kSplitShort>(p, grid, stream);
+        return launch<D, BF16, true, 1, true, kSplitLong>(p, grid, stream);
+    }
+    if (p.N % (2 * kTileKV) == 0) return launch<D, BF16, false, 1, true, kSplitEven>(p, grid, stream);
+    if (brief) return launch<D, BF16, false, 1, true, kSplitShort>(p, grid, stream);
+    return launch<D, BF16, false, 1, true, kSplitLong>(p, grid, stream);
 }
 
 // Validates a variant description (NULL = the default schedule) and builds its schedule.
@@ -2442,12 +2842,8 @@ int run(const void* Q, const void* K, const void* V, void* O, int B, int H, int 
         return ca ? launch<128, false, true, 2>(p, grid, stream) : launch<128, false, false, 2>(p, grid, stream);
     }
     if (sched.tile_q < kTileQ) {   // 64-row tiles: the two halves of the K/V scan at once
-        if (d == 128) {
-            if (bf) return ca ? launch<128, true, true, 1, true>(p, grid, stream) : launch<128, true, false, 1, true>(p, grid, stream);
-            return ca ? launch<128, false, true, 1, true>(p, grid, stream) : launch<128, false, false, 1, true>(p, grid, stream);
-        }
-        if (bf) return ca ? launch<64, true, true, 1, true>(p, grid, stream) : launch<64, true, false, 1, true>(p, grid, stream);
-        return ca ? launch<64, false, true, 1, true>(p, grid, stream) : launch<64, false, false, 1, true>(p, grid, stream);
+        if (d == 128) return bf ? launch_halves<128, true>(p, ca, grid, stream) : launch_halves<128, false>(p, ca, grid, stream);
+        return bf ? launch_halves<64, true>(p, ca, grid, stream) : launch_halves<64, false>(p, ca, grid, stream);
     }
     if (d == 128) {
         if (bf) return ca ? launch_128<128, true, true>(p, grid, stream) : launch_128<128, true, false>(p, grid, stream);
