@@ -159,7 +159,8 @@ SAW_HD float persistent_imbalance(int n, long long chunks, int resident, bool ca
 //     60: -6 to +2 %, 64: -6 to +1 %, 72 to 88: -22 to -6 %, 96: -4 to -2 %;
 //   * several rounds per chunk, by the imbalance above.  Causal, d = 64: 1.1 to 1.2: -3 to -6 %, 1.3 to 1.8: -3 to -16 %; d = 128: 1.17: -3 %,
 //     1.3 to 1.8: -1 to -17 %.  No mask, two chunks and more: 1.3 and 1.5: -6 to -9 %, 1.7 and more: -18 to -27 % (40 heads x 8320, d =
-//     128, bfloat16: 2002 -> 1466 us); one chunk, d = 64: 1.1 and 1.3: -1 to -2 %, 1.5 and more: -5 to -9 %; d = 128: 1.75 and more: -5 %, else 0.
+//     128, bfloat16: 2002 -> 1466 us); one chunk, d = 64: 1.1 and 1.3: -1 to -2 %, 1.42 to 1.47: -1 % in two rounds, +2 % in three
+//     (8 heads x 25920: 1427 -> 1449 us), 1.5 and more: -5 to -9 %; d = 128: 1.75 and more: -5 %, else 0.
 //     Below that the persistent launch stays, although at d = 64 under the mask it is 2 to 9 % slower: it has the turn-around;
 //   * 64-row tiles: causal, one round per chunk, C = 3 and more, odd: -16 to -21 %; C = 2, n = 47: -10 %, 61: +2 %.
 SAW_HD bool direct_instead(int heads, int N, int d, bool causal, int tile_q) {
@@ -178,7 +179,7 @@ SAW_HD bool direct_instead(int heads, int N, int d, bool causal, int tile_q) {
     if (tile_q < kTileQ) return false;
     const float imbalance = persistent_imbalance(n, chunks, resident, causal);
     if (causal) return d == 64 ? imbalance >= 1.1f : chunks > 1 && imbalance >= 1.15f;
-    return chunks > 1 ? imbalance >= 1.1f : d == 64 && imbalance >= 1.4f;
+    return chunks > 1 ? imbalance >= 1.1f : d == 64 && imbalance >= 1.5f;
 }
 
 struct Schedule {
