@@ -48,11 +48,10 @@ SAW_HD int ceil_div_i(long long a, long long b) { return (int)((a + b - 1) / b);
 // every resident workgroup of a domain gets at least one full-length tile of a head (nearly two under the
 // causal mask, where a tile walks half the keys on average), and only if the rounds of 32 tiles are well
 // filled: a last round with a few tiles costs this kernel a full round, while the workgroups of 128-row tiles run faster when
-// they have their compute unit to themselves.  The lines were drawn against the 32x32x16 kernel for 128-row tiles, over which
-// the wide one gains up to 12 %.  Against 128-row tiles as they run now (default_shared_kernel), by 256-row tiles per head and XCD,
-// binary16 / bfloat16, 8 heads, change of the rate: plain 32: -1 / +2 %, 36: -11 / -13, 40: -11 / -13, 48: -8 / -8, 56: +1 / +4,
-// 64: 0 / +3, 72: -6 / -9, 80: -4 / -5, 88: +1 / +4, 96: +1 / +3; causal 48: -13 / -11, 56: -3 / -1, 64: 0 / +3, 72: -5 / -4,
-// 80: -5 / -4, 88: -4 / -3, 96: -3 / -2.
+// they have their compute unit to themselves.  The lines were drawn against the 32x32x16 kernels of both tile shapes.  As both
+// run now (16x16x32 here, default_shared_kernel there), by 256-row tiles per head and XCD, binary16 / bfloat16, 8 heads, change of
+// the rate in %: plain 32: -3 / +10, 36: -15 / -7, 40: -14 / -6, 48: -9 / 0, 56: +4 / +9, 64: +6 / +9, 72: -7 / -3, 80: -3 / +4,
+// 88: +5 / +11, 96: +5 / +7; causal 48: -9 / -5, 56: +1 / +6, 64: +3 / +10, 72: -1 / +1, 80: -1 / +2, 88: 0 / +2, 96: +1 / +4.
 SAW_HD int default_rows_per_wavefront(int heads, int N, int d, bool causal, bool bf16) {
     (void)bf16;
     if (d != 128) return 32;
