@@ -27,6 +27,9 @@ Variants kept for comparison (same records, other hand-out):
     list (linear decode) or of a chunk's tile list (domain decode, workgroups of a domain
     numbered chunk after chunk); with two tiles per workgroup the second is walked backward
     under the sawtooth order (Sec. 4.3, the variant that advances the loop by two).
+  * launch "grid" with `turn_after`: one workgroup per tile in place of a persistent launch with that many workgroups per
+    domain.  Each tile is walked in the direction of the round it would belong to: backward under the sawtooth order if its
+    position in the chunk's list lies in an odd run of `turn_after` (Alg. 4; the hardware starts the workgroups in that order).
 
 The tile height `tile_q` (query rows per workgroup tile) and `resident` (how many workgroups of one domain run
 at the same time, the G of Alg. 2 per domain) are inputs: they are properties of the kernel that runs the
@@ -45,7 +48,7 @@ def ceil_div(a: int, b: int) -> int:
 
 
 def launch_geometry(B: int, H: int, N: int, *, tile_q: int, resident: int, launch: str = "persistent",
-                    decode: str = "domain", tiles_per_workgroup: int = 2):
+                    decode: str = "domain", tiles_per_workgroup: int = 2, turn_after: int = 0):
     heads = B * H
     q_tiles = ceil_div(N, tile_q)
     total = heads * q_tiles
@@ -88,7 +91,7 @@ def record(head: int, t: int, N: int, causal: bool, backward: bool, tile_q: int)
 
 
 def schedule(B: int, H: int, N: int, causal: bool, scan_order: str, *, tile_q: int, resident: int,
-             launch: str = "persistent", decode: str = "domain", tiles_per_workgroup: int = 2):
+             launch: str = "persistent", decode: str = "domain", tiles_per_workgroup: int = 2, turn_after: int = 0):
     """Return {workgroup: [(head, query tile, first K/V tile, last K/V tile), ...]} in the order
     each workgroup processes its tiles."""
     geo = launch_geometry(B, H, N, tile_q=tile_q, resident=resident, launch=launch, decode=decode,
@@ -117,7 +120,8 @@ def schedule(B: int, H: int, N: int, causal: bool, scan_order: str, *, tile_q: i
             for head, tiles in chunk_tiles:
                 for unit in range(geo["units_per_chunk"]):
                     mine = tiles[unit * tiles_per_workgroup:(unit + 1) * tiles_per_workgroup]
-                    out[m * DOMAINS + domain] = [record(head, t, N, causal, saw and i % 2 == 1, tq)
+                    turned = turn_after > 0 and unit // turn_after % 2 == 1      # (one tile per workgroup)
+                    out[m * DOMAINS + domain] = [record(head, t, N, causal, saw and (i % 2 == 1 or turned), tq)
                                                  for i, t in enumerate(mine)]
                     m += 1
             continue

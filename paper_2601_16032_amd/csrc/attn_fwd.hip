@@ -2517,8 +2517,9 @@ __device__ __forceinline__ void domain_sync(int set, int domain, int slots) {
     __syncthreads();
 }
 
-// The outer loop of a workgroup: its query tiles one after the other (Alg. 2, Alg. 3), `tile` computes one.
-template <bool CAUSAL, bool LATE, typename TILE>
+// The outer loop of a workgroup: its query tiles one after the other (Alg. 2, Alg. 3), `tile` computes one.  TURNS: 128-row tiles, the only
+// ones that schedule_for gives a launch with sched.turn (in the kernels of 64-row tiles, for small problems, the test alone costs 0.1 us).
+template <bool CAUSAL, bool LATE, bool TURNS, typename TILE>
 __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
     const Schedule& s = p.sched;
     const int lane0 = threadIdx.x & 63;
@@ -2526,7 +2527,7 @@ __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
     const int wg = CAUSAL && LATE ? workgroup_of_block(s, (int)blockIdx.x) : (int)blockIdx.x;      // (LATE: 128-row tiles and shorter)
     int local = 0;           // query tiles this workgroup has processed
     for (int it = 0; it < s.local_iters; ++it) {
-        const Work w = decode_work<LATE>(s, wg, it, CAUSAL, p.sawtooth != 0);
+        const Work w = decode_work<LATE, TURNS>(s, wg, it, CAUSAL, p.sawtooth != 0);
         if (w.tile >= 0) {
             const int nkv = visible_kv_tiles(s, w.tile, p.N, CAUSAL);
             const int j0 = w.backward ? nkv - 1 : 0;
@@ -2553,7 +2554,7 @@ __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
 template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false, int SPLIT = kSplitLong>
 __global__ __launch_bounds__(kThreads, HALVES ? (D == 64 ? 2 : 1) : NH == 2 ? 1 : (D == 64 ? 3 : 2)) void attn_fwd_kernel(Params p) {
     extern __shared__ __align__(16) char smem[];
-    for_each_q_tile<CAUSAL, NH == 1>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
+    for_each_q_tile<CAUSAL, NH == 1, NH == 1 && !HALVES>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
         if constexpr (NH == 2) {
             const NarrowMap<D> lm(wave, lane);
             process_q_tile_narrow<D, BF16, CAUSAL, false, 4>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
@@ -2568,7 +2569,7 @@ __global__ __launch_bounds__(kThreads, HALVES ? (D == 64 ? 2 : 1) : NH == 2 ? 1 
 template <int D, bool BF16, bool CAUSAL, bool PHASES>
 __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_fwd_shared_kernel(Params p) {
     extern __shared__ __align__(16) char smem[];
-    for_each_q_tile<CAUSAL, true>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
+    for_each_q_tile<CAUSAL, true, true>(p, [&](const Work& w, int j0, int step, int nkv, int wave, int lane) {
         const NarrowMap<D> lm(wave, lane);
         process_q_tile_narrow<D, BF16, CAUSAL, PHASES>(p, lm, w.head, w.tile, j0, step, nkv, wave, lane, (LDS_PTR(char))smem);
     });
@@ -2686,7 +2687,7 @@ int launch_halves(Params& p, bool causal, int grid, hipStream_t stream) {
 // Validates a variant description (NULL = the default schedule) and builds its schedule.
 int schedule_for(int B, int H, int N, int d, bool causal, bool bf16, const sawattn_variant* v, Schedule* out) {
     int launch = -1 /* chosen below */, decode = kDecodeDomain, max_slots = 0, tiles_per_wg = 0, rows = 0, halves = 0;
-    bool align_rounds = false;
+    bool align_rounds = false, instead = false;
     if (v) {
         if (v->kv_halves < 0 || v->kv_halves > 2)
             return fail(SAWATTN_ERR_INVALID_ARG, "variant.kv_halves must be 0 (default), 1 or 2");
@@ -2732,14 +2733,15 @@ int schedule_for(int B, int H, int N, int d, bool causal, bool bf16, const sawat
     if (launch < 0) {
         // the caller leaves the launch open: persistent, or for short heads and uneven rounds the direct launch with one tile each
         launch = decode == kDecodeDomain && max_slots == 0 ? default_launch(B * H, N, d, causal, tile_q) : kLaunchPersistent;
-        if (launch == kLaunchPersistent && decode == kDecodeDomain && max_slots == 0 && tiles_per_wg < 2 && !align_rounds &&
-            direct_instead(B * H, N, d, causal, tile_q))
-            launch = kLaunchGrid;
+        instead = launch == kLaunchPersistent && decode == kDecodeDomain && max_slots == 0 && tiles_per_wg < 2 && !align_rounds &&
+                  direct_instead(B * H, N, d, causal, tile_q);
+        if (instead) launch = kLaunchGrid;
         if (launch == kLaunchGrid && tiles_per_wg == 0) tiles_per_wg = 1;
     }
     if (tiles_per_wg == 0) tiles_per_wg = 2;
     if (max_slots == 0) max_slots = resident_slots(d, tile_q);
     *out = make_schedule(B * H, N, causal, launch, decode, max_slots, tiles_per_wg, tile_q, align_rounds);
+    if (instead && tile_q == kTileQ) turn_after(*out, max_slots);      // (with 64-row tiles only for a single round)
     start_longest_first(*out, d, causal);
     out->qo_streaming = v && v->qo_streaming ? v->qo_streaming : default_qo_streaming(N, d);
     return SAWATTN_OK;

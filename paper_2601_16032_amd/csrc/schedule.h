@@ -23,7 +23,9 @@
 //     causal tiles all start from key 0 together.  Taking the round index rather than a per-
 //     workgroup count keeps the whole domain walking one way when a workgroup sits a round out;
 //   * a direct launch has one workgroup per tile, numbered chunk after chunk.  Under the causal mask they start in
-//     another order than that of their numbers, the longest of several chunks first (start_longest_first).
+//     another order than that of their numbers, the longest of several chunks first (start_longest_first).  Where it stands in for
+//     a persistent launch of several rounds per chunk (direct_instead), every tile is walked in the direction it has there, so that
+//     the workgroups that follow on a domain's first ones turn around as its rounds do (turn_after).
 #pragma once
 
 #if defined(__HIPCC__)
@@ -150,8 +152,8 @@ SAW_HD float persistent_imbalance(int n, long long chunks, int resident, bool ca
 }
 
 // Whether a launch that default_launch leaves persistent is faster as a direct one (under the mask with its longest workgroups first): the
-// dispatcher evens out what a fixed hand-out leaves uneven.  What is given up is the turn-around of the sawtooth order, which
-// exists only where a chunk takes several rounds.  Change of the time from persistent to direct, n tiles per chunk on C chunks per XCD:
+// dispatcher evens out what a fixed hand-out leaves uneven.  The scan directions stay those of the rounds (turn_after), but their
+// workgroups no longer keep step.  Change of the time from persistent to direct, n tiles per chunk on C chunks per XCD:
 //   * causal, one round per chunk.  An odd number of rounds leaves somebody with an unpaired one: -6 to -38 % at C = 3, 5, -4 to
 //     -37 % at 7 and more.  With an even number all workgroups have the same, but n of them fill the compute units evenly only where
 //     n is a multiple of 32: d = 128, n = 34 to 56: -35 to -3 %, 60: -2 to -1 %, 64: +1 to +2 %; d = 64, n = 34 to 52: -22 to 0 %,
@@ -198,6 +200,8 @@ struct Schedule {
     int local_iters;        // local iterations every workgroup runs through (some may be idle)
     int sync_heads;         // persistent, domain decode: the workgroups of a domain wait for each other between heads
     int sync_rounds;        // ... and after every round as well (a study of Sec. 3.4's lockstep; costs time)
+    unsigned turn;          // direct launch, domain decode: 2^32 over the tiles of a chunk after which the scan direction turns, rounded up
+                            // (0: all walk forward)
     int chunks_abreast;     // direct launch: chunks whose workgroups start together, longest first (1: in the order of their numbers)
     int qo_streaming;       // 1: O tiles leave through LDS as whole non-temporal lines; 2: Q tiles arrive that way; 3: both; 4: neither
 };
@@ -229,6 +233,7 @@ SAW_HD Schedule make_schedule(int heads, int N, bool causal, int launch, int dec
     s.units_per_chunk = 0;
     s.sync_heads = 0;
     s.sync_rounds = 0;
+    s.turn = 0;             // turn_after
     s.chunks_abreast = 1;   // start_longest_first
     const long long total = (long long)heads * s.q_tiles;
     if (launch == kLaunchPersistent) {
@@ -258,6 +263,16 @@ SAW_HD Schedule make_schedule(int heads, int N, bool causal, int launch, int dec
     s.grid = kDomains * s.slots;
     return s;
 }
+
+// A direct launch in place of a persistent one of `tiles` workgroups per domain: tile u of a chunk, which round u / tiles would take, is walked in
+// that round's direction.  The workgroups start in the order of u, as places come free, so those of a round still follow on the one before over
+// the same K/V, and turning around finds in the L2 what that left there.  L2 misses, cyclic -> sawtooth (TCC_MISS, millions): 1 x 131072,
+// d = 64, plain 7.5 -> 7.2 (persistent 7.5 -> 7.3); 8 x 32768, d = 64, causal 1.8 -> 1.5 (1.9 -> 1.7); 2 x 131072, d = 64, causal 71 -> 42
+// (55 -> 8.7: there the workgroups drift apart, which the persistent launch's pairs of a long and a short tile prevent).  Times of the two
+// orders: alike, within 1.4 %.
+// (The quotient as a product: exact for r <= 96 up to u = 2^27, and a chunk has at most 2^24 tiles.  A division and its branch cost every
+// direct launch 0.1 to 0.2 us, this at most 0.07: 42 x 1000, d = 64, causal: 17.14 -> 17.35 against 17.21 us.)
+SAW_HD void turn_after(Schedule& s, int tiles) { s.turn = (unsigned)((0x100000000ull + tiles - 1) / tiles); }
 
 // Direct launches under the causal mask: which workgroups start first.  The hardware starts them in the order of their block numbers and
 // a new one wherever one has finished.  In the order of their own numbers, chunk after chunk, the last chunk's longest
@@ -406,8 +421,8 @@ SAW_HD T quotient(T a, T b) {
     return a / b;
 }
 
-// What workgroup `wg` does in its local iteration `it` (0 <= it < local_iters).
-template <bool LATE = false>
+// What workgroup `wg` does in its local iteration `it` (0 <= it < local_iters).  TURNS false: for kernels whose tiles no launch with `turn` has.
+template <bool LATE = false, bool TURNS = true>
 SAW_HD Work decode_work(const Schedule& s, int wg, int it, bool causal, bool sawtooth) {
     Work w;
     w.head = 0;
@@ -438,7 +453,8 @@ SAW_HD Work decode_work(const Schedule& s, int wg, int it, bool causal, bool saw
     } else {
         cs = quotient<LATE>(slot, s.units_per_chunk);
         u = (slot - cs * s.units_per_chunk) * s.tiles_per_wg + it;
-        w.backward = sawtooth && (it & 1);
+        const int run = TURNS ? (int)((unsigned long long)(unsigned)u * s.turn >> 32) : 0;
+        w.backward = sawtooth && ((it | run) & 1);
     }
     const int c = cs * kDomains + domain;
     const int part = c % s.parts;

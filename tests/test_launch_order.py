@@ -119,6 +119,41 @@ def test_which_launches_are_direct(shape, want):
     assert binding.attn_fwd_variant_launch_info(*shape, binding.variant(launch="auto", slots_per_domain=7))["launch"] == binding.LAUNCH_PERSISTENT
 
 
+SEVERAL_ROUNDS = [(1, 1, 131072, 64, False), (1, 16, 12544, 64, False), (8, 1, 32768, 64, True), (1, 2, 131072, 64, True), (1, 16, 13440, 64, True),
+                  (1, 16, 8320, 128, False), (1, 16, 8960, 128, True), (1, 20, 27000, 64, True)]
+
+
+@pytest.mark.parametrize("shape", SEVERAL_ROUNDS)
+@pytest.mark.parametrize("order", ["cyclic", "sawtooth"])
+def test_direct_launches_keep_the_scan_directions_of_the_rounds(shape, order):
+    """A launch that is direct instead of persistent walks every tile the way the persistent launch does: under the sawtooth order the odd
+    rounds go down.  A direct launch that the caller asks for has no rounds."""
+    def tiles(**kw):
+        trace, count = binding.attn_fwd_plan(*shape, scan_order=order, variant=binding.variant(kv_halves=1, **kw) if kw else None)
+        return sorted(tuple(r) for wg in range(len(count)) for r in trace[wg, : int(count[wg])].tolist())
+    assert binding.attn_fwd_launch_info(*shape)["launch"] == binding.LAUNCH_GRID
+    got = tiles()
+    assert got == tiles(launch="persistent", rows_per_wavefront=32)
+    assert any(first > last for _, _, first, last in got) == (order == "sawtooth")
+    assert all(first <= last for _, _, first, last in tiles(launch="grid", tiles_per_workgroup=1, rows_per_wavefront=32))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,N,d,dtype,causal", [(16, 12500, 64, "f16", False), (16, 13440, 64, "bf16", True), (20, 27000, 64, "f16", True)])
+def test_direct_and_persistent_launches_give_the_same_bits(H, N, d, dtype, causal):
+    """At d = 64 one kernel computes both launches, and no other order of summation may come from the launch."""
+    assert binding.attn_fwd_launch_info(1, H, N, d, causal, dtype=dtype)["launch"] == binding.LAUNCH_GRID
+    q, k, v = (t.cuda() for t in workloads.make_random(1, H, N, d, dtype, seed=900 + H))
+    scale, O = 1.0 / math.sqrt(d), {}
+    for order in ("cyclic", "sawtooth"):
+        O[order] = binding.attn_fwd(q, k, v, scale=scale, causal=causal, scan_order=order, o_dtype=torch.float32)
+        same = binding.attn_fwd_variant(q, k, v, scale=scale, causal=causal, scan_order=order, o_dtype=torch.float32,
+                                        variant=binding.variant(launch="persistent", kv_halves=1))
+        torch.cuda.synchronize()
+        assert torch.equal(O[order], same), order
+    assert not torch.equal(O["cyclic"], O["sawtooth"])
+
+
 # Causal launches of every kernel and of one and two groups of chunks, and the plain ones that are direct now.
 GPU_CASES = [
     (17, 2048, 128, "f16", True, "A"), (25, 1800, 128, "bf16", True, "S"), (35, 2100, 128, "f16", True, "P"), (97, 1100, 128, "bf16", True, "P"),

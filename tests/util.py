@@ -44,6 +44,8 @@ def oracle_inputs(info, d, variant_kw=None):
         out["tiles_per_workgroup"] = info["tiles_per_workgroup"]
     out["tile_q"] = info["tile_q"]
     out["resident"] = kw.get("slots_per_domain") or RESIDENT_PER_XCD[(d, info["tile_q"])]
+    if kw.get("launch", "auto") == "auto" and out["launch"] == "grid":     # walked as in the persistent launch it stands in for
+        out["turn_after"] = out["resident"]
     return out
 
 
