@@ -2518,7 +2518,7 @@ __device__ __forceinline__ void domain_sync(int set, int domain, int slots) {
 }
 
 // The outer loop of a workgroup: its query tiles one after the other (Alg. 2, Alg. 3), `tile` computes one.  TURNS: 128-row tiles, the only
-// ones that schedule_for gives a launch with sched.turn (in the kernels of 64-row tiles, for small problems, the test alone costs 0.1 us).
+// ones that launch_schedule gives a launch with sched.turn (in the kernels of 64-row tiles, for small problems, the test alone costs 0.1 us).
 template <bool CAUSAL, bool LATE, bool TURNS, typename TILE>
 __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
     const Schedule& s = p.sched;
@@ -2686,8 +2686,8 @@ int launch_halves(Params& p, bool causal, int grid, hipStream_t stream) {
 
 // Validates a variant description (NULL = the default schedule) and builds its schedule.
 int schedule_for(int B, int H, int N, int d, bool causal, bool bf16, const sawattn_variant* v, Schedule* out) {
-    int launch = -1 /* chosen below */, decode = kDecodeDomain, max_slots = 0, tiles_per_wg = 0, rows = 0, halves = 0;
-    bool align_rounds = false, instead = false;
+    int launch = -1 /* open */, decode = kDecodeDomain, max_slots = 0, tiles_per_wg = 0, rows = 0, halves = 0;
+    bool align_rounds = false;
     if (v) {
         if (v->kv_halves < 0 || v->kv_halves > 2)
             return fail(SAWATTN_ERR_INVALID_ARG, "variant.kv_halves must be 0 (default), 1 or 2");
@@ -2730,19 +2730,7 @@ int schedule_for(int B, int H, int N, int d, bool causal, bool bf16, const sawat
     if (halves == 2) rows = 32;
     if (rows == 0) rows = default_rows_per_wavefront(B * H, N, d, causal, bf16);
     const int tile_q = rows == 64 ? 2 * kTileQ : (halves == 2 ? kTileQ / 2 : kTileQ);
-    if (launch < 0) {
-        // the caller leaves the launch open: persistent, or for short heads and uneven rounds the direct launch with one tile each
-        launch = decode == kDecodeDomain && max_slots == 0 ? default_launch(B * H, N, d, causal, tile_q) : kLaunchPersistent;
-        instead = launch == kLaunchPersistent && decode == kDecodeDomain && max_slots == 0 && tiles_per_wg < 2 && !align_rounds &&
-                  direct_instead(B * H, N, d, causal, tile_q);
-        if (instead) launch = kLaunchGrid;
-        if (launch == kLaunchGrid && tiles_per_wg == 0) tiles_per_wg = 1;
-    }
-    if (tiles_per_wg == 0) tiles_per_wg = 2;
-    if (max_slots == 0) max_slots = resident_slots(d, tile_q);
-    *out = make_schedule(B * H, N, causal, launch, decode, max_slots, tiles_per_wg, tile_q, align_rounds);
-    if (instead && tile_q == kTileQ) turn_after(*out, max_slots);      // (with 64-row tiles only for a single round)
-    start_longest_first(*out, d, causal);
+    *out = launch_schedule(B * H, N, d, causal, tile_q, launch, decode, max_slots, tiles_per_wg, align_rounds);
     out->qo_streaming = v && v->qo_streaming ? v->qo_streaming : default_qo_streaming(N, d);
     return SAWATTN_OK;
 }

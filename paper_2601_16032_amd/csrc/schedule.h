@@ -295,6 +295,30 @@ SAW_HD void start_longest_first(Schedule& s, int d, bool causal) {
     s.chunks_abreast = groups > 1 ? (s.chunks_per_domain + groups - 1) / groups : s.chunks_per_domain;
 }
 
+// The schedule of a launch with query tiles of `tile_q` rows.  What is left open (launch -1; max_slots, tiles_per_wg 0) is chosen here: the
+// persistent launch, or for short heads and uneven rounds the direct one with a tile each.  A direct launch that the caller names is that
+// of Alg. 3: started in the order of the workgroups' numbers, every first tile walked forward.
+SAW_HD Schedule launch_schedule(int heads, int N, int d, bool causal, int tile_q, int launch = -1, int decode = kDecodeDomain, int max_slots = 0,
+                                int tiles_per_wg = 0, bool align_rounds = false) {
+    const bool open = launch < 0;
+    bool instead = false;
+    if (open) {
+        launch = kLaunchPersistent;
+        if (decode == kDecodeDomain && max_slots == 0) {
+            launch = default_launch(heads, N, d, causal, tile_q);
+            instead = launch == kLaunchPersistent && tiles_per_wg < 2 && !align_rounds && direct_instead(heads, N, d, causal, tile_q);
+            if (instead) launch = kLaunchGrid;
+        }
+        if (launch == kLaunchGrid && tiles_per_wg == 0) tiles_per_wg = 1;
+    }
+    if (tiles_per_wg == 0) tiles_per_wg = 2;
+    if (max_slots == 0) max_slots = resident_slots(d, tile_q);
+    Schedule s = make_schedule(heads, N, causal, launch, decode, max_slots, tiles_per_wg, tile_q, align_rounds);
+    if (instead && tile_q == kTileQ) turn_after(s, max_slots);      // (with 64-row tiles only for a single round)
+    if (open) start_longest_first(s, d, causal);
+    return s;
+}
+
 // The workgroup that the hardware's block `block` is.
 SAW_HD int workgroup_of_block(const Schedule& s, int block) {
     if (s.chunks_abreast <= 1) return block;

@@ -18,18 +18,18 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 @pytest.fixture(scope="module")
 def ask(tmp_path_factory):
-    """(heads, N, d, bf16, query rows per tile) -> per causal direct launch with one tile per workgroup: what computes it (A, S or P: the
-    32x32x16 kernel, the 16x16x32 one without and with precedence), chunks per XCD, workgroups per chunk, and the workgroups of
-    XCD 3 in the order in which they start."""
+    """(heads, N, d, bf16, query rows per tile) -> per causal direct launch with one tile per workgroup, longest first or (last argument) as
+    the caller's variant names it: what computes it (A, S or P: the 32x32x16 kernel, the 16x16x32 one without and with precedence), chunks
+    per XCD, workgroups per chunk, and the workgroups of XCD 3 in the order in which they start."""
     d = tmp_path_factory.mktemp("order")
     (d / "order.cpp").write_text("""#include <stdio.h>
 #include "schedule.h"
 using namespace sawattn;
 int main() {
-    int heads, N, d, bf16, tile_q;
-    while (scanf("%d %d %d %d %d", &heads, &N, &d, &bf16, &tile_q) == 5) {
-        Schedule s = make_schedule(heads, N, true, kLaunchGrid, kDecodeDomain, resident_slots(d, tile_q), 1, tile_q);
-        start_longest_first(s, d, true);
+    int heads, N, d, bf16, tile_q, named;
+    while (scanf("%d %d %d %d %d %d", &heads, &N, &d, &bf16, &tile_q, &named) == 6) {
+        Schedule s = launch_schedule(heads, N, d, true, tile_q, kLaunchGrid, kDecodeDomain, 0, 1);
+        if (!named) start_longest_first(s, d, true);
         printf("%c %d %d", !default_shared_kernel(s, d, true, bf16) ? 'A' : default_phase_priority(s, d, true) ? 'P' : 'S',
                s.chunks_per_domain, s.units_per_chunk);
         for (int block = 3; block < s.grid; block += kDomains) printf(" %d", workgroup_of_block(s, block));
@@ -40,8 +40,8 @@ int main() {
     subprocess.run(["g++", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "paper_2601_16032_amd", "csrc"), str(d / "order.cpp"),
                     "-o", str(d / "order")], check=True, capture_output=True)
 
-    def run(cases):
-        text = "\n".join(" ".join(str(int(x)) for x in c) for c in cases)
+    def run(cases, named=False):
+        text = "\n".join(" ".join(str(int(x)) for x in c + (named,)) for c in cases)
         lines = subprocess.run([str(d / "order")], input=text, check=True, capture_output=True, text=True).stdout.splitlines()
         out = []
         for line in lines:
@@ -78,6 +78,12 @@ def test_blocks_are_a_permutation_of_the_workgroups_longest_first(ask):
             seen += mine
         assert seen == list(range(chunks)), case
         assert len(groups) == 1 or all(2 * len(g) >= 3 * resident for g in groups[:-1]), case
+
+
+def test_a_direct_launch_that_is_named_starts_in_the_order_of_its_numbers(ask):
+    """Alg. 3 as printed can be measured: only what attn_fwd picks by itself starts longest first."""
+    for case, (_, chunks, units, order) in zip(ORDER_CASES, ask(ORDER_CASES, named=True)):
+        assert order == [8 * k + 3 for k in range(chunks * units)], case
 
 
 def test_what_computes_a_launch_whose_longest_workgroups_start_first(ask):
