@@ -11,7 +11,7 @@ import torch
 
 from oracle import schedule_oracle as so
 from paper_2601_16032_amd import binding, traffic_model
-from tests.util import SHARED_HEADS, SHARED_LENGTHS, oracle_inputs
+from tests.util import SHARED_EVEN, SHARED_HEADS, SHARED_LENGTHS, oracle_inputs
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -608,7 +608,7 @@ def test_score_limit_never_lies_below_the_maximum_it_comes_from(tmp_path):
 def kernel_of(tmp_path_factory):
     """(heads, N, d, causal, bf16, launch, decode, slots per domain, tiles per workgroup) -> what computes the 128-row tiles
     of that launch: "alone" (32x32x16, a workgroup to a compute unit), "shared" (16x16x32) or "shared, precedence".  The
-    schedule is built by the header the library is built from; launch -1 and 0 slots are the library's own choice."""
+    schedule is built by the header the library is built from; launch -1, 0 slots and 0 tiles are left open as attn_fwd leaves them."""
     import subprocess
     d = tmp_path_factory.mktemp("rule")
     (d / "rule.cpp").write_text("""#include <stdio.h>
@@ -617,8 +617,7 @@ using namespace sawattn;
 int main() {
     int heads, N, d, causal, bf16, launch, decode, slots, tiles;
     while (scanf("%d %d %d %d %d %d %d %d %d", &heads, &N, &d, &causal, &bf16, &launch, &decode, &slots, &tiles) == 9) {
-        if (launch < 0) launch = default_launch(heads, N, d, causal, kTileQ);
-        const Schedule s = make_schedule(heads, N, causal, launch, decode, slots ? slots : resident_slots(d), tiles);
+        const Schedule s = launch_schedule(heads, N, d, causal, kTileQ, launch, decode, slots, tiles);
         if (!default_shared_kernel(s, d, causal, bf16)) puts("alone");
         else puts(default_phase_priority(s, d, causal) ? "shared, precedence" : "shared");
     }
@@ -636,7 +635,8 @@ int main() {
 
 
 def test_which_kernel_computes_128_row_tiles(kernel_of):
-    """Launches on both sides of every line of the rule, each the faster way when measured (profiles/shared_kernel_rules.txt)."""
+    """Launches on both sides of every line of the rule, each the faster way when measured (profiles/shared_kernel_rules.txt; the
+    library's own direct launches under the mask: A, S and P timed in turn, best to 1 %)."""
     A, S, P = "alone", "shared", "shared, precedence"
     by_hand = [     # (heads, N, d, causal, bf16): what runs; the library's own launch
         ((32, 1024, 64, 0, 0), A), ((132, 256, 64, 0, 0), P), ((8, 4096, 128, 0, 0), A), ((42, 584, 128, 0, 1), P),
@@ -646,19 +646,26 @@ def test_which_kernel_computes_128_row_tiles(kernel_of):
         ((8, 12800, 128, 0, 1), P),
         # causal, one round per chunk: 1, even, odd
         ((8, 8192, 128, 1, 0), A), ((1, 40000, 128, 1, 0), A), ((8, 10000, 64, 1, 0), S), ((16, 8192, 128, 1, 1), P),
-        ((16, 4352, 128, 1, 0), P), ((6, 16667, 128, 1, 1), A), ((12, 10496, 128, 1, 0), S), ((40, 5760, 128, 1, 0), S),
-        ((104, 7808, 128, 1, 1), P), ((12, 16311, 64, 1, 0), S), ((6, 35968, 64, 1, 0), P), ((20, 12959, 64, 1, 0), P),
+        ((16, 4352, 128, 1, 0), S), ((12, 10496, 128, 1, 0), P), ((40, 5760, 128, 1, 0), S),
+        ((104, 7808, 128, 1, 1), P), ((6, 35968, 64, 1, 0), P), ((20, 12959, 64, 1, 0), P),
         # causal, several rounds per chunk
         ((4, 16677, 128, 1, 0), A), ((8, 12308, 128, 1, 0), S), ((16, 16393, 128, 1, 0), P), ((4, 25783, 64, 1, 0), S),
         ((8, 17152, 64, 1, 0), P), ((8, 32768, 64, 1, 0), P), ((1, 131072, 64, 1, 0), P),
         # causal, direct: all at once, few shared, more than fit
-        ((35, 512, 128, 1, 0), P), ((12, 2816, 128, 1, 1), A), ((3, 13440, 128, 1, 0), A), ((24, 1935, 128, 1, 0), P),
-        ((42, 1000, 64, 1, 1), P), ((64, 2048, 64, 1, 0), S), ((40, 3968, 64, 1, 0), S), ((5, 23171, 64, 1, 1), P),
-        ((36, 6841, 64, 1, 0), P), ((26, 3712, 128, 1, 0), A), ((97, 1624, 128, 1, 0), A), ((32, 4096, 128, 1, 0), S),
+        ((35, 512, 128, 1, 0), P), ((12, 2816, 128, 1, 1), A), ((3, 13440, 128, 1, 0), A),
+        ((42, 1000, 64, 1, 1), S), ((64, 2048, 64, 1, 0), S), ((40, 3968, 64, 1, 0), S), ((5, 23171, 64, 1, 1), P),
+        ((36, 6841, 64, 1, 0), P), ((26, 3712, 128, 1, 0), P), ((97, 1624, 128, 1, 0), P), ((32, 4096, 128, 1, 0), P),
         ((80, 837, 128, 1, 0), S), ((113, 750, 128, 1, 0), S), ((5, 23936, 128, 1, 0), P), ((7, 15644, 128, 1, 0), P),
     ]
-    got = kernel_of([c + (-1, 0, 0, 1) for c, _ in by_hand])
-    wrong = [(c, w, g) for (c, w), g in zip(by_hand, got) if w != g]
+    named = [       # (heads, N, d, causal, bf16, launch): what runs where a variant names the launch: persistent (0), or direct (1) with a
+                    # tile each, started in the order of the numbers
+        ((16, 4352, 128, 1, 0, 0), P), ((6, 16667, 128, 1, 1, 0), A), ((12, 10496, 128, 1, 0, 0), S), ((12, 16311, 64, 1, 0, 0), S),
+        ((24, 1935, 128, 1, 0, 1), P), ((42, 1000, 64, 1, 1, 1), P), ((26, 3712, 128, 1, 0, 1), A), ((97, 1624, 128, 1, 0, 1), A),
+        ((32, 4096, 128, 1, 0, 1), S), ((5, 23936, 128, 1, 0, 1), P),
+    ]
+    cases = [(c + (-1, 0, 0, 0), w) for c, w in by_hand] + [(c + (0, 0, 1), w) for c, w in named]
+    got = kernel_of([c for c, _ in cases])
+    wrong = [(c, w, g) for (c, w), g in zip(cases, got) if w != g]
     assert not wrong, wrong
 
 
@@ -666,13 +673,14 @@ def test_the_lengths_of_the_gpu_tests_reach_every_build_of_the_shared_kernel(ker
     two = (1, 0, 0, 2)                                    # direct launch, two tiles per workgroup
     for d in (64, 128):
         for bf16 in (0, 1):
-            for launch in ((-1, 0, 0, 1), two):
+            for launch in ((-1, 0, 0, 0), two):
                 plain = kernel_of([(SHARED_HEADS, N, d, 0, bf16) + launch for N in SHARED_LENGTHS])
                 causal = kernel_of([(SHARED_HEADS, N, d, 1, bf16) + launch for N in SHARED_LENGTHS])
-                assert plain[-1] == "shared, precedence" and causal[-1] == "shared"
+                assert plain[-1] == "shared, precedence" and causal[-1] == ("shared" if launch == two else "shared, precedence")
                 assert causal[0] == "shared, precedence" and "alone" not in causal[:5]
                 assert d == 128 or "alone" not in plain + causal
+            assert kernel_of([SHARED_EVEN + (d, 1, bf16, -1, 0, 0, 0)]) == ["shared"]
             # the lengths the single tests pick
-            for case in ((577,) + two, (300, -1, 0, 0, 1), (577, 0, 1, 0, 1)):
+            for case in ((577,) + two, (300, -1, 0, 0, 0), (577, 0, 1, 0, 1)):
                 for ca in (0, 1):
                     assert kernel_of([(SHARED_HEADS, case[0], d, ca, bf16) + case[1:]])[0].startswith("shared"), (case, d, bf16, ca)

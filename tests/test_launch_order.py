@@ -11,7 +11,7 @@ import torch
 
 from paper_2601_16032_amd import binding, workloads
 
-from .util import assert_close, oracle_inputs
+from .util import SHARED_EVEN, assert_close, oracle_inputs
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -164,7 +164,8 @@ def test_direct_and_persistent_launches_give_the_same_bits(H, N, d, dtype, causa
 GPU_CASES = [
     (17, 2048, 128, "f16", True, "A"), (25, 1800, 128, "bf16", True, "S"), (35, 2100, 128, "f16", True, "P"), (97, 1100, 128, "bf16", True, "P"),
     (17, 3100, 128, "f16", True, "S"), (17, 2040, 64, "bf16", True, "S"), (49, 1100, 64, "f16", True, "P"), (64, 2000, 64, "bf16", True, "S"),
-    (24, 2600, 64, "f16", True, None), (11, 1400, 128, "bf16", True, None), (24, 5000, 128, "f16", True, None), (16, 8300, 128, "bf16", False, None),
+    (*SHARED_EVEN, 64, "f16", True, "S"), (*SHARED_EVEN, 64, "bf16", True, "S"), (*SHARED_EVEN, 128, "f16", True, "S"),
+    (*SHARED_EVEN, 128, "bf16", True, "S"), (24, 2600, 64, "f16", True, None), (11, 1400, 128, "bf16", True, None), (24, 5000, 128, "f16", True, None), (16, 8300, 128, "bf16", False, None),
 ]
 
 

@@ -51,7 +51,10 @@ def oracle_inputs(info, d, variant_kw=None):
 
 # Short heads that make the kernel for compute units shared by workgroups run (33 workgroups and more per XCD; too many heads
 # for a halved scan), and lengths at which, launched one or two tiles per workgroup, they reach every build of it: both head
-# dimensions and input types, without a mask, and under the mask with and without precedence by phase (d = 128 with 2, 4 or
+# dimensions and input types, without a mask, and under the mask with (one tile) and without (two) precedence by phase (two tiles at d = 128 with 2, 4 or
 # 8 workgroups per head, as at 129..256 and 385..512 rows, is left to the other kernel there).
 SHARED_HEADS = 264
 SHARED_LENGTHS = [1, 63, 64, 65, 128, 129, 200, 321, 577]
+# (heads, rows) whose causal launch, left open, reaches the build without precedence at both head dimensions: all 49 workgroups of an XCD at
+# once, the last tile of a head one of 65 rows.  (With 264 heads the lengths above have it from two tiles per workgroup.)
+SHARED_EVEN = (56, 833)
