@@ -22,7 +22,8 @@ Studies
             the persistent launch, the direct launch with one tile per workgroup, and what attn_fwd picks by itself.
 
 A point without a variant runs what attn_fwd runs (launch left open); a variant pins the persistent launch unless
-it names the other.
+it names the other.  seqlen and batch are about rounds that share an L2 and pin the persistent launch, which attn_fwd
+leaves for a direct one where the rounds are uneven (1 x 131072 and 8 x 16384 at d = 64 among others).
 
 Inputs are seeded N(0,1) values rounded to fp16 (`workloads.make_random`), scale 1/sqrt(d).
 """
@@ -36,6 +37,7 @@ import time
 
 from . import traffic_model as tm
 from . import workloads
+from .binding import LAUNCH_PERSISTENT
 
 L2_BYTES_PER_XCD = 4 * 2 ** 20
 
@@ -53,7 +55,7 @@ def study_points(study: str):
                     if H == 8 and N > 65536:
                         continue
                     for order in ("cyclic", "sawtooth"):
-                        pts.append(_pt(1, H, N, d, order=order))
+                        pts.append(_pt(1, H, N, d, order=order, launch="persistent"))
     elif study == "resident":
         for (H, N, d) in ((8, 32768, 64), (32, 16384, 128)):
             for w in (1, 2, 4, 8, 16, 32, 64) + ((96,) if d == 64 else ()):
@@ -79,7 +81,7 @@ def study_points(study: str):
             for causal in (False, True):
                 for B in (1, 2, 4, 8):
                     for order in ("cyclic", "sawtooth"):
-                        pts.append(_pt(B, 1, N, 64, causal, order))
+                        pts.append(_pt(B, 1, N, 64, causal, order, launch="persistent"))
     elif study == "heads":
         for d in (64, 128):
             for (H, N) in ((128, 512), (64, 1024), (64, 2048), (16, 2048), (24, 2048), (16, 4096), (32, 4096), (32, 8192)):
@@ -101,7 +103,7 @@ def model(pt, info):
            "compulsory_bytes": tm.compulsory_bytes(B, H, N, d),
            "kv_bytes_per_head": kv_head,
            "kv_over_l2": kv_head / L2_BYTES_PER_XCD}
-    if not causal and pt["variant"].get("decode", "domain") == "domain" and pt["variant"].get("launch", "persistent") == "persistent":
+    if not causal and pt["variant"].get("decode", "domain") == "domain" and info["launch"] == LAUNCH_PERSISTENT:
         # every domain that holds a part of a head walks that head's K/V once per round
         # (a domain that holds 1/parts of a head's query tiles sees them as tiles `parts` times as tall)
         per_domain_head = tm.lru_kv_miss_bytes(N, d, info["tile_q"] * info["parts_per_head"], info["slots"],

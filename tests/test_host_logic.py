@@ -11,7 +11,7 @@ import torch
 
 from oracle import schedule_oracle as so
 from paper_2601_16032_amd import binding, traffic_model
-from tests.util import SHARED_EVEN, SHARED_HEADS, SHARED_LENGTHS, oracle_inputs
+from tests.util import RESIDENT_PER_XCD, SHARED_EVEN, SHARED_HEADS, SHARED_LENGTHS, oracle_inputs
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -475,6 +475,25 @@ def test_byte_model_and_lru_model():
 
 
 # ------------------------------------------------------------------ the benchmark's profile figures come from profiles/
+def test_sweeps_predict_lockstep_for_persistent_launches_only(sa):
+    """The LRU and lockstep figures describe workgroups that are resident together and walk a head in rounds: a point that runs as a direct
+    launch gets none, and the studies of the scan order run persistent launches."""
+    from paper_2601_16032_amd import sweeps
+    direct = 0
+    for study in ("seqlen", "resident", "decode", "launch", "batch", "heads"):
+        for pt in sweeps.study_points(study):
+            shape = (pt["B"], pt["H"], pt["N"], pt["d"], pt["causal"])
+            info = sa.attn_fwd_variant_launch_info(*shape, sa.variant(**pt["variant"]) if pt["variant"] else None)
+            assert study not in ("seqlen", "batch") or info["launch"] == sa.LAUNCH_PERSISTENT, pt
+            out = sweeps.model(pt, info)
+            if info["launch"] == sa.LAUNCH_GRID:
+                assert "lru_kv_miss_bytes" not in out and "lockstep_hit_rate" not in out, pt
+                direct += not pt["variant"]
+            elif "lockstep_hit_rate" in out:
+                assert info["slots"] <= RESIDENT_PER_XCD[(pt["d"], info["tile_q"])], pt
+    assert direct > 0
+
+
 def test_bench_reads_its_counter_figures_from_the_committed_profiles():
     """bench.py reports HBM-side bytes and L2 misses per scan order as profile figures: they are parsed from the
     rocprofv3 summary of the workload, so they cannot drift from it; every workload has a summary."""
