@@ -132,23 +132,25 @@ SAW_HD int default_launch(int heads, int N, int d, bool causal, int tile_q) {
 }
 enum { kDecodeDomain = 0, kDecodeLinear = 1 };
 
-// K/V tiles of the busiest workgroup of a persistent hand-out over what an even share would be (the longest tile of a chunk, if that
-// is more).  `n` tiles per chunk, under the causal mask of 1 .. n parts, otherwise of one; rounds as in decode_work.
-SAW_HD float persistent_imbalance(int n, long long chunks, int resident, bool causal) {
+// The imbalance of a persistent hand-out: K/V tiles of its busiest workgroup over what an even share would be (the longest tile of a chunk, if that
+// is more).  `n` tiles per chunk, under the causal mask of 1 .. n parts, otherwise of one; rounds as in decode_work.  Whether it is at least
+// num / den, in whole numbers: whole loads give simple fractions, 1 x 131072, d = 64, without a mask exactly 3/2.  (Below 2^62: n * chunks
+// is at most 2^28, n at most 2^24.)
+SAW_HD bool imbalance_at_least(int num, int den, int n, long long chunks, int resident, bool causal) {
     const int slots = n < resident ? n : resident, rounds = (n + slots - 1) / slots;
-    double most = 0;
+    long long most = 0;
     for (int slot = 0; slot < slots; ++slot) {
-        double in_chunk[2] = {0, 0};                  // the rounds of a chunk that begins with an even / odd one
+        long long in_chunk[2] = {0, 0};               // the rounds of a chunk that begins with an even / odd one
         for (int first = 0; first < 2; ++first)
             for (int r = 0; r < rounds; ++r) {
                 const int u = r * slots + ((r + first) & 1 ? slots - 1 - slot : slot);
                 if (u < n) in_chunk[first] += causal ? n - u : 1;
             }
-        const double all = rounds % 2 == 0 ? chunks * in_chunk[0] : (chunks + 1) / 2 * in_chunk[0] + chunks / 2 * in_chunk[1];
+        const long long all = rounds % 2 == 0 ? chunks * in_chunk[0] : (chunks + 1) / 2 * in_chunk[0] + chunks / 2 * in_chunk[1];
         if (all > most) most = all;
     }
-    const double longest = causal ? n : 1, share = (causal ? n * (n + 1.0) / 2 : n) * chunks / resident;
-    return (float)(most / (share > longest ? share : longest));
+    const long long longest = causal ? n : 1, total = (causal ? n * (n + 1ll) / 2 : n) * chunks;
+    return most * resident * den >= num * (total > longest * resident ? total : longest * resident);
 }
 
 // Whether a launch that default_launch leaves persistent is faster as a direct one (under the mask with its longest workgroups first): the
@@ -162,7 +164,7 @@ SAW_HD float persistent_imbalance(int n, long long chunks, int resident, bool ca
 //     1.3 to 1.8: -1 to -17 %.  No mask, two chunks and more: 1.3 and 1.5: -6 to -9 %, 1.7 and more: -18 to -27 % (40 heads x 8320, d =
 //     128, bfloat16: 2002 -> 1466 us); one chunk, d = 64: 1.1 and 1.3: -1 to -2 %, 1.42 to 1.47: -1 % in two rounds, +2 % in three
 //     (8 heads x 25920: 1427 -> 1449 us), 1.5 and more: -5 to -9 %; d = 128: 1.75 and more: -5 %, else 0.
-//     Below that the persistent launch stays, although at d = 64 under the mask it is 2 to 9 % slower: it has the turn-around;
+//     Below that the persistent launch stays, although at d = 64 under the mask it is 2 to 9 % slower: its workgroups keep step;
 //   * 64-row tiles: causal, one round per chunk, C = 3 and more, odd: -16 to -21 %; C = 2, n = 47: -10 %, 61: +2 %.
 SAW_HD bool direct_instead(int heads, int N, int d, bool causal, int tile_q) {
     if (tile_q > kTileQ) return false;
@@ -178,9 +180,9 @@ SAW_HD bool direct_instead(int heads, int N, int d, bool causal, int tile_q) {
         return chunks % 2 != 0 || n % 32 != 0;
     }
     if (tile_q < kTileQ) return false;
-    const float imbalance = persistent_imbalance(n, chunks, resident, causal);
-    if (causal) return d == 64 ? imbalance >= 1.1f : chunks > 1 && imbalance >= 1.15f;
-    return chunks > 1 ? imbalance >= 1.1f : d == 64 && imbalance >= 1.5f;
+    if (d == 128 && chunks == 1) return false;
+    if (chunks == 1 && !causal) return imbalance_at_least(3, 2, n, chunks, resident, causal);
+    return d == 128 && causal ? imbalance_at_least(23, 20, n, chunks, resident, causal) : imbalance_at_least(11, 10, n, chunks, resident, causal);
 }
 
 struct Schedule {

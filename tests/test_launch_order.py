@@ -111,6 +111,8 @@ DIRECT = [     # (B, H, N, d, causal): the launch that attn_fwd picks
     ((1, 16, 8960, 128, True), "grid"), ((1, 16, 14720, 128, True), "persistent"), ((1, 8, 17920, 128, True), "persistent"),
     ((1, 16, 8320, 128, False), "grid"), ((1, 8, 8320, 128, False), "persistent"), ((1, 16, 12544, 64, False), "grid"), ((1, 16, 24576, 64, False), "persistent"),
     ((1, 1, 131072, 64, False), "grid"), ((1, 8, 18432, 64, False), "persistent"), ((1, 8, 24576, 64, False), "persistent"),
+    # exactly on the line (128 tiles on 96 places: 3/2), and a tile to either side
+    ((1, 8, 16256, 64, False), "grid"), ((1, 8, 16384, 64, False), "grid"), ((1, 8, 16385, 64, False), "persistent"),
     # 64-row tiles
     ((1, 24, 2600, 64, True), "grid"), ((1, 16, 3000, 64, True), "grid"), ((1, 16, 3900, 64, True), "persistent"), ((1, 16, 2048, 64, True), "persistent"),
 ]
