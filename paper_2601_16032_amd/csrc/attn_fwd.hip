@@ -1712,6 +1712,11 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
 // What it saves are the odd and masked tiles taken one at a time, with nothing in flight, before or after the halves, about 2 us of a
 // launch (figures at launch_halves); per tile of a long scan it is 3 to 4 % slower.  The row sums' products moved into the first product,
 // or a quarter of the exponentials into the second, were 1 to 2 % slower yet.
+//
+// The caller sends scans of one tile elsewhere, so run 1 has a tile at least and is one shorter at most: the stand-in tile of an empty run, its
+// reset at the end and the fetch in the last loop are never reached.  They stay, because what the compiler makes of the loop without them
+// is slower: 3 x 3000, d = 128, bfloat16, causal 38.6 -> 39.1 us, 5 x 1000, d = 128 15.3 -> 15.5 us (ten forms tried: +0.4 to +1.6 % each on
+// one or more of these; the loop's instructions are the same, its place in the cache lines is not).
 template <int D, bool BF16, bool CAUSAL>
 __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& lm, const char* Kh, const char* Vh, int N, float c, int j0,
                                             int step, int nkv, int qw0, int qrow, int lane, LDS_PTR(char) lds, int run) {
