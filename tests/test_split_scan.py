@@ -1,6 +1,7 @@
 """64-row tiles, whose K/V scan is walked in two halves at once: the edges of the halves and of each kernel's range of lengths."""
 import math
 
+import numpy as np
 import pytest
 import torch
 
@@ -51,13 +52,17 @@ def test_lengths_around_the_last_short_scan(d, causal):
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_masked_infinities_stay_where_they_are(dtype):
-    """K and V of the keys from `cut` on are infinite: rows before them come out as without these keys, bit for bit."""
+    """Infinite keys from `cut` on spoil no row before them, NaN values from `cut` on no row above their own 64-row tile (behind the mask, 0 times
+    such a value is no number): those rows come out as without them, bit for bit."""
     for d in (64, 128):
         for cut in (1, 64, 100, 192, 300):
             Q, K, V = workloads.make_random(1, 8, 321, d, dtype, seed=7000 + cut)
             K2, V2 = K.clone(), V.clone()
             K2[:, :, cut:], V2[:, :, cut:] = float("inf"), float("nan")
             for order in ("cyclic", "sawtooth"):
-                a, b = run(Q, K, V, 0.1, True, order), run(Q, K2, V2, 0.1, True, order)
-                at = cut // 64 * 64       # (a query tile that holds an infinite key multiplies it by probability 0)
-                assert (a[:, :, :at] == b[:, :, :at]).all(), f"cut={cut} d={d} {dtype} {order}"
+                clean = run(Q, K, V, 0.1, True, order)
+                assert np.isfinite(clean).all()
+                for name, got, rows in (("K", run(Q, K2, V, 0.1, True, order), cut), ("V", run(Q, K, V2, 0.1, True, order), cut // 64 * 64)):
+                    assert rows > 0 or (name, cut) == ("V", 1)
+                    assert (clean[:, :, :rows] == got[:, :, :rows]).all(), f"{name} cut={cut} d={d} {dtype} {order}"
+                    assert not np.isfinite(got[:, :, cut:]).any(), f"{name} cut={cut} d={d} {dtype} {order}"
