@@ -285,13 +285,16 @@ SAW_HD void turn_after(Schedule& s, int tiles) { s.turn = (unsigned)((0x10000000
 // -2.4, -4.7, -4.7, -4.4, -3.9, -2.0 %; 48 x 4096, d = 64: -15, -20, -20, -21, -21, -21 %; 126 x 3500, d = 128: +0.9, -0.3,
 // +0.8, +7, +10, +10 %.  At 3/2 loads, over 155 launches that were direct before: -38 to +1 %, -11 % in the mean (32 x 4096, d =
 // 128: 151 -> 130 us; 64 x 2048, d = 64: 52.7 -> 43 us).  Who computes what, and the recorded schedule, stay as they are.
-// Not at d = 128 with 3, 5 or 6 workgroups to a chunk and 2.7 loads and more: the end counts for less there than what the few workgroups
-// of a chunk share when they start together (107 heads x 2880: +9 %, 127 x 5000: +5 %, 63 x 3000: +3 %, 75 x 5000: -1 %).  Chunks of
-// 2, 4 and 8 gain all the same (111 x 3097: -22 %), as workgroups of one length would meet on the compute units otherwise.
+// Not at d = 128 with 3 or 5 workgroups to a chunk and 55 chunks and more: what so few share when they start together counts for more there than the
+// end.  45 to 54 chunks: 3 to a chunk -7 to +6 % (-1 % in the mean), 5 to a chunk -4 to +1 % (-1.5 %); 55 and more: 3 to a chunk -5 to +13 %
+// (+6 %), 5 to a chunk -5 to +6 % (+1.6 %).  More to a chunk gain up to some 10 loads of the XCD and are even from there on, 6 to 10 loads: 7, 9, 11 ..
+// -6 to +5 % (-1.5 %), 6, 10, 14 .. -8 to +4 % (-3 %); 10 and more: odd -4 to +9 % (+0.6 %), 6, 10, 14 .. -8 to +3 % (-1 %).  Multiples
+// of 4 gain whatever the loads (-23 to +1 %), as workgroups of one length would meet on the compute units otherwise, and so do 2 to a chunk
+// (-21 to +2 %).  d = 64: below 6 loads -35 to +2 %, 10 and more: odd -5 to +3 % (+0.4 %), even -12 to +1 % (-2.4 %).
 SAW_HD void start_longest_first(Schedule& s, int d, bool causal) {
     if (!causal || s.launch != kLaunchGrid || s.decode != kDecodeDomain || s.tiles_per_wg != 1 || s.tile_q > kTileQ) return;
     const int n = s.units_per_chunk, resident = resident_slots(d, s.tile_q);
-    if (n < 2 || (d == 128 && (n == 3 || n == 5 || n == 6) && 10ll * s.slots >= 27 * resident)) return;
+    if (n < 2 || (d == 128 && n % 2 && n < 7 && s.chunks_per_domain >= 55)) return;
     const int least = (3 * resident + 2 * n - 1) / (2 * n);
     const int groups = s.chunks_per_domain / least;
     s.chunks_abreast = groups > 1 ? (s.chunks_per_domain + groups - 1) / groups : s.chunks_per_domain;

@@ -51,9 +51,12 @@ int main() {
     return run
 
 
-ORDER_CASES = [(32, 4096, 128, 0, 128), (97, 1100, 128, 0, 128), (9, 1000, 64, 0, 128), (5, 129, 64, 1, 128), (128, 4096, 64, 0, 128),
-               (126, 3500, 128, 1, 128), (17, 12000, 64, 0, 128), (24, 2600, 64, 0, 64), (11, 1400, 128, 0, 64), (1, 64, 64, 0, 128),
-               (107, 2880, 128, 0, 128), (40, 3968, 64, 1, 128), (8, 100, 128, 0, 128)]
+# launches that start longest first, and those that lose by it (3 or 5 workgroups to each of many chunks) or have one workgroup to a chunk
+LONGEST_FIRST = [(32, 4096, 128, 0, 128), (97, 1100, 128, 0, 128), (9, 1000, 64, 0, 128), (5, 129, 64, 1, 128), (128, 4096, 64, 0, 128),
+                 (17, 12000, 64, 0, 128), (24, 2600, 64, 0, 64), (11, 1400, 128, 0, 64), (40, 3968, 64, 1, 128), (102, 1500, 128, 1, 128),
+                 (70, 2883, 128, 0, 128), (106, 2436, 128, 0, 128), (126, 3500, 128, 1, 128), (127, 2700, 64, 0, 128), (121, 11904, 128, 0, 128)]
+IN_ORDER = [(1, 64, 64, 0, 128), (8, 100, 128, 0, 128), (107, 2880, 128, 0, 128), (103, 3000, 128, 0, 128), (110, 2176, 128, 1, 128)]
+ORDER_CASES = LONGEST_FIRST + IN_ORDER
 
 
 def test_blocks_are_a_permutation_of_the_workgroups_longest_first(ask):
@@ -63,7 +66,7 @@ def test_blocks_are_a_permutation_of_the_workgroups_longest_first(ask):
         slots = [(w // 8) // units for w in order], [(w // 8) % units for w in order]
         resident = 32 if case[2] == 128 else 64
         resident = resident if case[4] == 64 else (64 if case[2] == 128 else 96)
-        if units == 1 or (case[2] == 128 and units in (3, 5, 6) and 10 * n >= 27 * resident):
+        if case in IN_ORDER:
             assert order == sorted(order), case
             continue
         # groups of consecutive chunks, one after the other, each of 3/2 loads at least unless there is only one; in a group the position
