@@ -31,7 +31,8 @@ enum {
 /* Order in which a workgroup walks the K/V tiles of one query tile (paper Sec. 4, Alg. 4). */
 enum {
     SAWATTN_SCAN_CYCLIC = 0,       /* always ascending */
-    SAWATTN_SCAN_SAWTOOTH = 1      /* ascending on even, descending on odd rounds over one head's K/V */
+    SAWATTN_SCAN_SAWTOOTH = 1      /* ascending on even, descending on odd rounds over one head's K/V (per launch: below,
+                                      "Scan direction per variant") */
 };
 
 enum {
@@ -51,8 +52,8 @@ enum {
 /*
  * attn_fwd -- O = softmax(Q K^T * scale) V  (paper Sec. 2.2, Eq. 1), computed tile by tile with an
  * online softmax (Alg. 1) by persistent workgroups (Alg. 2) that scan K/V in `scan_order` (Alg. 4); where
- * heads are short and come several to an XCD, by one workgroup per query tile instead (Alg. 3; see
- * SAWATTN_LAUNCH_AUTO below).
+ * heads are short and come several to an XCD, or the persistent workgroups would get unequal shares, by one
+ * workgroup per query tile instead (Alg. 3; see SAWATTN_LAUNCH_AUTO below).
  *
  *   Q, K, V  device, read only.  Contiguous [B, H, N, d], d fastest, element type `in_dtype`
  *            (SAWATTN_F16 or SAWATTN_BF16), 16-byte aligned.  Query and key sequences both have
@@ -97,14 +98,24 @@ int attn_fwd(const void* Q, const void* K, const void* V, void* O,
 enum {
     SAWATTN_LAUNCH_PERSISTENT = 0, /* Alg. 2: a fixed set of workgroups loops over the query tiles */
     SAWATTN_LAUNCH_GRID = 1,       /* Alg. 3: one workgroup per `tiles_per_workgroup` consecutive query
-                                      tiles, handed to the hardware dispatcher */
-    SAWATTN_LAUNCH_AUTO = 2        /* what attn_fwd does: PERSISTENT, except where a head has fewer query tiles than
-                                      an XCD holds workgroups and an XCD has two or more heads to go through --
-                                      then GRID with one tile per workgroup, so that the tiles of several heads run
-                                      side by side (under the causal mask only for heads of at most half that many
-                                      tiles, and with two heads per XCD only if all their tiles fit the XCD's 32
-                                      compute units at once; with slots_per_domain or the linear decode given:
-                                      PERSISTENT) */
+                                      tiles, handed to the hardware dispatcher in the order of their numbers */
+    SAWATTN_LAUNCH_AUTO = 2        /* what attn_fwd does: PERSISTENT, or GRID with one tile per workgroup
+                                      - where a head has fewer query tiles than an XCD holds workgroups and an XCD has
+                                        two or more heads to go through, so that the tiles of several heads run side by
+                                        side.  Under the causal mask only for heads of at most half that many tiles (with
+                                        two heads per XCD: of at most 16), and for longer ones where the persistent
+                                        workgroups, who take a long tile of one head and a short one of the next, would
+                                        end unevenly (an odd number of heads, or tiles that fill the compute units unevenly);
+                                      - with several rounds per head (128-row tiles), where the busiest persistent
+                                        workgroup would have 1.1 times an even share and more (causal and d = 128: 1.15;
+                                        with one head, or a part of one, per XCD 1.5 without a mask, and never at d = 128).
+                                      These GRID launches differ from the named one: under the mask the workgroups of
+                                      several heads start together, longest first, and with the sawtooth order every tile is
+                                      walked in the direction of the round it would belong to.  Name PERSISTENT for
+                                      workgroups that keep step through the rounds of a head, as studies of the scan order
+                                      want them.
+                                      PERSISTENT always with slots_per_domain or the linear decode given; with align_rounds
+                                      or two tiles per workgroup given, the first rule's heads of at most half alone are GRID */
 };
 enum {
     SAWATTN_DECODE_DOMAIN = 0,     /* work is dealt out per XCD (one L2 each): the workgroups of an XCD
@@ -124,8 +135,8 @@ typedef struct sawattn_variant {
                                 0 = default (2; 1 where AUTO picks the grid launch).  Ignored by the persistent launch. */
     int rows_per_wavefront;  /* 32: a workgroup takes 128 query rows (two or three workgroups per CU);
                                 64 (d = 128 only; UNSUPPORTED otherwise): 256 rows, one workgroup per CU (at
-                                most 32 per XCD), every K/V fragment read from LDS feeds two MFMAs; same
-                                arithmetic as the 32-row kernel;
+                                most 32 per XCD), every K/V fragment read from LDS feeds four MFMAs (two
+                                with 32 rows where workgroups share a CU, one where they do not); same arithmetic;
                                 0 = default: 64 for d = 128, slots_per_domain <= 32 and sequences long enough
                                 that every workgroup of an XCD gets at least one 256-row tile of a head (nearly
                                 two under the causal mask) and the rounds of 32 tiles are well filled: with
@@ -137,12 +148,13 @@ typedef struct sawattn_variant {
                                 time.  For measuring what the scan order can save at best.  Ignored otherwise. */
     int kv_halves;           /* 1: a workgroup's wavefronts each own query rows and walk the whole scan;
                                 2 (32 rows per wavefront; UNSUPPORTED with 64): a workgroup
-                                takes 64 query rows, two wavefronts walk the first half of the full, unmasked
-                                K/V tiles of the scan and two the second half, at once, and the two partial
-                                softmax results are merged (Alg. 1's update applied to two partial results
-                                instead of one tile at a time); an odd tile and the masked ones are taken by the
-                                first two wavefronts alone -- for problems too small to occupy the chip, where
-                                the length of one wavefront's walk is the launch time;
+                                takes 64 query rows, two wavefronts walk the first half of the K/V tiles of
+                                the scan and two the second half, at once, and the two partial softmax results are
+                                merged (Alg. 1's update applied to two partial results instead of one tile at a
+                                time).  An odd tile goes with the first half; in scans of more than 64 K/V tiles
+                                only the full, unmasked tiles are halved, and an odd one and the masked ones are
+                                taken by the first two wavefronts alone -- for problems too small to occupy the
+                                chip, where the length of one wavefront's walk is the launch time;
                                 0 = default: 2 where it is supported and B*H*ceil(N/128) is at most 128 (d = 128),
                                 or, with d = 64 and N >= 2048, 384 (512 under the causal mask); else 1. */
     int qo_streaming;        /* how the rows touched once per query tile pass the L2.  3: Q tiles are brought in and O tiles
@@ -155,9 +167,11 @@ typedef struct sawattn_variant {
 } sawattn_variant;
 /*
  * Scan direction per variant with SAWATTN_SCAN_SAWTOOTH: persistent + domain decode: parity of the round
- * over the current head (the default); persistent + linear decode: parity of the workgroup's own
- * iteration count (Alg. 4 as printed); grid launch: parity of the tile's position in its workgroup.
- * A NULL variant pointer selects { PERSISTENT, DOMAIN, 0, 0, 0, 0 }, which is what attn_fwd runs.
+ * over the current head; persistent + linear decode: parity of the workgroup's own iteration count (Alg. 4
+ * as printed); grid launch: parity of the tile's position in its workgroup -- where AUTO takes it in place of
+ * a persistent launch: parity of the round that the tile belongs to there, so that AUTO and PERSISTENT walk every
+ * tile alike.
+ * A NULL variant pointer selects { AUTO, DOMAIN, 0, 0, 0, 0, 0, 0 }, which is what attn_fwd runs.
  */
 
 /*
@@ -197,8 +211,8 @@ typedef struct sawattn_launch_info {
 /*
  * attn_fwd_workspace -- attn_fwd_variant with scratch memory from the caller (paper Sec. 2.2, Alg. 1: the same
  * kernel; the scratch only changes the element type K and V are streamed in).  On bfloat16 inputs the kernels
- * convert V to binary16 on its way into LDS, in every workgroup that streams it; the 64-rows-per-wavefront kernel,
- * whose one wavefront per SIMD has no instruction slots to spare, pays for that (about 5 % on long sequences).
+ * convert V to binary16 on its way into LDS, in every workgroup that streams it.  (The 64-rows-per-wavefront kernel
+ * used to be 5 % slower for it; as it is now both ways take the same time, 32 heads x 16384 causal 1810 and 1813 us.)
  * Given a workspace, and where that kernel is chosen (d = 128, sequence long enough; or
  * variant.rows_per_wavefront = 64), the call first writes binary16 copies of K and V into the workspace with one
  * extra kernel on the same stream and then runs the 64-row kernel on them, converting Q as it is loaded.  The

@@ -367,7 +367,7 @@ SAW_HD int per_chunk(const Schedule& s) {
 //     compute unit are then equally long and make room all together.  89 of 106 of these lose, up to 10 % (2.7 % in the
 //     mean); with 16 and 32 to a chunk -9 to +4 % (-0.6 %), with 1 -7 to +3 % (-1.4 %), with others -7 to +4 % (-1.3 %).
 // Direct launches whose longest workgroups start first (start_longest_first; the last two lines hold for those in the order of their
-// numbers), d = 128: up to 47 workgroups per XCD +4 to +12 %; 48 to 64, 8 and more to a chunk: +2 to +4 %, fewer: -7 to +2 %; more than fit:
+// numbers: named by a variant, or the few that start_longest_first leaves out), d = 128: up to 47 workgroups per XCD +4 to +12 %; 48 to 64, 8 and more to a chunk: +2 to +4 %, fewer: -7 to +2 %; more than fit:
 // -14 to +2 % (the better of the two with and without precedence).
 SAW_HD bool default_shared_kernel(const Schedule& s, int d, bool causal, bool bf16) {
     if (s.slots <= 32) return false;
@@ -407,7 +407,7 @@ SAW_HD bool default_shared_kernel(const Schedule& s, int d, bool causal, bool bf
 //     %) where a head is spread over 4 or 8 XCDs, two tiles and more to a chunk, -4 to +10 % (+2.2 %) otherwise (64 heads x
 //     2048: 54 against 59 us, 40 x 3968: 104 against 114 us).  d = 128: -7 to +7 % (+0.7 %); -10 to +2 % (-2.6 %) for 4/3 to
 //     twice as many, a head over 4 or 8 XCDs and five tiles and more to a chunk (5 x 23936: 844 -> 793 us);
-//   * direct launch, longest workgroups first (the two lines above hold for the order of their numbers).  d = 64, all at once: 8 and more to
+//   * direct launch, longest workgroups first (the two lines above hold for the order of their numbers, as a variant names it).  d = 64, all at once: 8 and more to
 //     a chunk, or up to 64 per XCD: 0 to +9 %, else -5 to 0 %; more than fit: -5 to +2 %, but +2 to +8 % for up to twice as many of
 //     16 and more to a chunk, a head on one XCD.  d = 128, all at once: +1 to +5 %; up to 1.6 times as many as fit: 2 or 3 to a
 //     chunk -5 to +2 %, more 0 to +6 %; 1.6 to 2.2 times: -10 to -1 % (32 x 4096: 137 -> 130 us); more: -8 to +3 % up to 32 to a
