@@ -199,6 +199,13 @@ __device__ __forceinline__ void load_to_lds_16B_at(const char* base, unsigned vo
     asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(lds_base), "v"(voff), "s"(base), "n"(LDS_IMM) : "memory", "m0", "scc");
 }
+// The same in two steps, for several loads into neighbouring places: where the first of them goes, and a load.  The offset AT of the instruction
+// counts on both sides: 16 bytes from base + voff + AT land at lds_addr + AT + 16*l.  Nothing else in the kernels writes M0.
+__device__ __forceinline__ void aim_lds(unsigned lds_addr) { asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" :: "s"(lds_addr) : "memory", "m0"); }
+template <int AT>
+__device__ __forceinline__ void load_aimed_16B(const char* base, unsigned voff) {
+    asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" :: "v"(voff), "s"(base), "n"(AT) : "memory");
+}
 __device__ __forceinline__ void wait_tile_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Per-lane byte offsets (relative to the head's base) of this lane's chunks of tile j.  A ragged
@@ -1272,27 +1279,28 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
 // fragment read from LDS feeds four MFMAs instead of two, which halves the operand traffic from LDS and the L2 -> LDS
 // traffic per multiply-add.
 //
-// What bounds it: with live operands the power limit, then the issue of its one wavefront per SIMD.  Per tile 136 MFMAs of 16
-// cycles (128 for the products, 8 for the row sums), 64 exponentials, 128 other vector instructions of the softmax and 48 LDS
-// reads: about 3400 cycles against 2176 of MFMA time.  Its predecessor on 32x32x16 MFMAs (half as many, row sums by 64 vector
-// additions) took 3130 with all operands zero, where the clock plays no part, but with live ones the chip took more clock from it
-// than that: 16x16x32 reads and writes half as many accumulators per multiply-add.  32 heads x 16384, from 32x32x16 to this: binary16
-// 3592 -> 3403 us, causal 1874 -> 1776 us, bfloat16 3785 -> 3445 us, causal 1960 -> 1810 us; 128 heads x 32768, bfloat16, causal: 30.5
-// -> 28.7 ms.  (Left out, binary16, no mask: exponentials -8 %, fetches -8 %, row sums -3 %, maxima and shifts -4 %.)
+// What bounds it: with live operands the power limit, and the issue of its one wavefront per SIMD, which holds with zeros too: about 3050 cycles
+// per tile for 136 MFMAs of 16 cycles (128 for the products, 8 for the row sums), 64 exponentials, 150 other vector instructions, 48 LDS reads and
+// 8 direct loads.  Both count: less clock goes with less voltage, so a tile in 7 % fewer cycles takes 3.5 % less time at the power limit.  What
+// that rests on: work spread evenly over the MFMAs (WidePlan); loads that share M0, and bases that move by a tile, in place of some 40 scalar
+// instructions a tile; nothing behind the loop's branch.  32 heads x 16384, before and after: binary16 3375 -> 3257 us
+// (zeros: 2941 -> 2739), bfloat16, causal 1796 -> 1755 us.  And neighbouring MFMAs share an operand wherever they can: columns of K go
+// in the outer loop, query blocks there and back (MFMA-only loops: 1898 -> 1935 TFLOP/s; here -0.5 to -1.5 % with live operands).
+// 16x16x32 and not 32x32x16 because it reads and writes half as many accumulators per multiply-add: from 32x32x16 to this shape, 32 heads x
+// 16384, binary16 3592 -> 3403 us, bfloat16 3785 -> 3445 us.
 //
-// What is spread how: exponentials and converts of tile i under the MFMAs of S(i+1)^T, maxima and shifted scores of tile i+1 under
-// those of O^T += V(i)^T P(i)^T, one to two vector instructions per MFMA.  K(i+4) and V(i+2) are fetched at the start of iteration
-// i, one load behind every other MFMA, into four buffers each, and have until the barrier of iteration i+1 (spread over the
-// second product, with half an iteration less: +4 %).  By then V(i+1) is needed, whose first fragments are read ahead of the barrier of
-// iteration i+1 like K's first ones ahead of the loop's branch (first V fragments behind the barrier: +2 %).  Fragments are
+// What is spread how: exponentials and converts of tile i under the MFMAs of S(i+1)^T and the first of O^T += V(i)^T P(i)^T, maxima and shifted
+// scores of tile i+1 under the rest of those.  K(i+4) and V(i+2) are fetched in the first product of iteration i, one load behind every eighth MFMA,
+// into four buffers each, and have until the barrier of iteration i+1.  By then V(i+1) is needed, whose first fragments are read ahead of the
+// barrier of iteration i+1 like K's first ones ahead of the loop's branch (first V fragments behind the barrier: +2 %).  Fragments are
 // read two at a time, one pair ahead, and used in the order second, first: one wait covers both.
 //
 // MFMAs are inline assembly with the register file of every operand fixed: with more than 256 registers per wavefront the accumulation
 // registers have to hold what only the matrix pipe touches (O^T, Q^T, the row sums) and nothing the vector ALU reads, or every use
 // costs a copy.  The compiler does not see them as MFMAs and inserts no wait states; wide_settle_*() stands wherever vector
 // instructions read what the last few MFMAs may still be writing (4 passes + 3 wait states), wide_guard() where MFMAs read
-// accumulators that vector instructions have just written.  In the loop the distance is kept by the order: the first maximum reads
-// the first block of scores, 48 MFMAs old, and the last block is read 16 MFMAs after its last one.
+// accumulators that vector instructions have just written.  In the loop the distance is kept by the order: the first maximum comes
+// behind the exponentials of the second product, ten MFMAs after the last one that wrote a score.
 constexpr int kWideBuffers = 4;
 constexpr int kWideLdsBytes = 2 * kWideBuffers * Geo<128>::kTile;
 
@@ -1332,11 +1340,70 @@ __device__ __forceinline__ void wide_guard_o(NarrowState<128, 4>& st) {
     asm volatile("s_nop 7" ::: "memory");
 }
 
+// Which of N operations stand behind which of W MFMAs: first[w] .. first[w + 1] - 1 behind MFMA w.  cost[n] is what operation n takes of the
+// issue port, taken[w] what else stands behind MFMA w; the sum is spread as evenly as the order of the operations allows.
+template <int W>
+struct Windows {
+    int first[W + 1];
+};
+template <int W, int N>
+constexpr Windows<W> spread(const int (&cost)[N], const int (&taken)[W]) {
+    int total = 0, spent = 0, n = 0;
+    for (int k = 0; k < N; ++k) total += cost[k];
+    for (int w = 0; w < W; ++w) total += taken[w];
+    Windows<W> r{};
+    for (int w = 0; w < W; ++w) {
+        r.first[w] = n;
+        spent += taken[w];
+        while (n < N && (2 * spent + cost[n]) * W <= 2 * total * (w + 1)) spent += cost[n++];
+    }
+    r.first[W] = N;
+    return r;
+}
+
+// What runs under the MFMAs of an iteration of scan_tiles_wide.  One wavefront per SIMD issues an MFMA in 8 cycles, a vector instruction in 4.5, an
+// exponential in 8.5 and an LDS read in 5 to 6 (measured one wavefront at a time: an MFMA alone 16.6 cycles, with 1, 2, 3, 4 vector instructions
+// behind it 16.9, 17.2, 22, 26, with 1, 2, 3 exponentials 17, 26, 34), and an MFMA that comes late is not made up for: work has to be even from
+// one MFMA to the next.  In vector instructions an exponential counts as three here (two: 0 to +0.2 %, four: +1.5 %).  The last PAIRS
+// pairs of exponentials run in the second product, whose first half does not need them: the first would overflow and the second have room
+// (32 x 16384, binary16, all operands zero, where the power limit plays no part: none 2878 us, 4: 2738, 6: 2696, 7: 2689, 10: 2705;
+// bfloat16, causal: 3: 1760, 4: 1780, 5: 1755, 6: 1770, 7: 1787).
+template <bool BF16>
+struct WidePlan {
+    static constexpr int PAIRS = BF16 ? 5 : 7;
+    static constexpr int OX = 3 * PAIRS, OA = 96 - OX;        // steps of the exponentials in the second product, in the first
+    static constexpr int CW = BF16 ? 16 : 0;                  // words of V to convert
+    static constexpr int exponential = 3;
+    static constexpr Windows<64> first_product() {
+        int cost[OA] = {}, taken[64] = {};
+        for (int n = 0; n < OA; ++n) cost[n] = n % 3 < 2 ? exponential : 1;
+        for (int t = 0; t < 64; ++t) {
+            if (t % 8 == 0) taken[t] += t < 56 ? 2 : 4;                               // fragment reads: a pair of K, at the end of V^T
+            if (!BF16 && t % 8 == 4) taken[t] += t == 4 || t == 36 ? 3 : 1;           // a direct load, the first of a tile with M0
+            if (t >= 57 && t < 61) taken[t] += 1;                                     // K addresses
+        }
+        return spread<64>(cost, taken);
+    }
+    // OX steps of exponentials, CW conversions, 32 maxima, 4 comparisons, 64 shifted scores
+    static constexpr int OM = OX + CW, OQ = OM + 32, OS = OQ + 4, OB = OS + 64;
+    static constexpr Windows<72> second_product() {
+        int cost[OB] = {}, taken[72] = {};
+        for (int n = 0; n < OB; ++n) cost[n] = n < OX ? (n % 3 < 2 ? exponential : 1) : n < OM ? 3 : 1;
+        for (int w = 0; w < 72; ++w) {                                                // (w = 9k + 8: a row sum's)
+            if (w % 9 == 0) taken[w] += w < 63 ? 4 : 2;                               // fragment reads: a pair of V^T, at the end of K
+            if (BF16 && w < 4) taken[w] += 1;                                         // direct loads
+            if (w >= 60) taken[w] += w < 64 ? w % 2 == 0 : 1;                        // bases, V addresses
+        }
+        return spread<72>(cost, taken);
+    }
+};
+
 template <bool BF16, bool CAUSAL>
 __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const NarrowMap<128>& lm, const char* Kh, const char* Vh, int N, float c,
-                                                int j0, int step, int nkv, int qw0, int lane, LDS_PTR(char) lds) {
+                                                int j0, int step, int nkv, int qw0, int wave, int lane, LDS_PTR(char) lds) {
     constexpr int D = 128, QT = 4;
     using G = Geo<D>;
+    using P = WidePlan<BF16>;
     constexpr int KS = 4, DB = 8, NA = 16, NB = 16, NL = G::kLoadsPerWave, TA = 64, TB = 64;
     constexpr int LA = 2;                              // fragments read ahead of their use
     constexpr unsigned VB = kWideBuffers * G::kTile;   // V buffers follow the K buffers
@@ -1360,52 +1427,63 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
 #pragma unroll
     for (int db = 0; db < DB; ++db) rv[db] = lds0 + VB + lm.v_rd[db];
 
-    // Position p of the scan lives in K buffer p & 3 and V buffer p & 3.  Fetches beyond the scan re-fetch its last tile into a buffer
-    // nobody reads.  The rows that the last tile of the sequence lacks repeat row N-1: masked before use.
-    auto tile_of = [&](int p) { return j0 + (p < nkv ? p : nkv - 1) * step; };
-    auto offsets = [&](int j, unsigned (&off)[NL]) {
-        const int left = N - j * kTileKV;
-#pragma unroll
-        for (int l = 0; l < NL; ++l) off[l] = lm.fill_src + l * 4096;
-        if (left < kTileKV) {
-#pragma unroll
-            for (int l = 0; l < NL; ++l) {
-                const unsigned row = off[l] / G::kRowBytes;
-                off[l] = (row < (unsigned)left ? row : (unsigned)left - 1) * G::kRowBytes + off[l] % G::kRowBytes;
-            }
-        }
+    // Position p of the scan lives in K buffer p & 3 and V buffer p & 3.  A wavefront fetches 16 neighbouring rows of a tile with four loads of four
+    // rows each, so that one M0 and the offsets of the instructions serve all four.  The permutation repeats every eight rows: of a whole tile, loads
+    // 0 and 2, 1 and 3 have the same addresses but for those offsets.  The rows that the last tile of the sequence lacks repeat row N-1
+    // (masked before use; bases lie kBias below the tile, so that no offset is negative).  Fetches beyond the scan re-fetch its last tile into a
+    // buffer nobody reads.
+    constexpr unsigned kBias = 4096;
+    const unsigned fill_dst = wave * 4096;
+    auto base_of = [&](const char* head, int p) {
+        const unsigned long long at = (unsigned long long)(head + (size_t)(j0 + p * step) * G::kTile - kBias);
+        return (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(at >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((unsigned)at);
     };
-    unsigned off_k[NL], off_v[NL];
-    auto base_of = [&](const char* head, int j) { return head + (size_t)j * G::kTile; };
-    auto fetch = [&](const char* head, int p, unsigned buffers, unsigned (&off)[NL]) {
-        const int j = tile_of(p);
-        offsets(j, off);
-#pragma unroll
-        for (int l = 0; l < NL; ++l) load_to_lds_16B(base_of(head, j), off[l], buffers + (p & 3) * G::kTile + lm.fill_dst + l * 4096);
+    auto offset_of = [&](int l, int rows) {      // ... of load l in a tile of `rows` rows
+        const int row = 16 * wave + 4 * l + g;
+        return (unsigned)((row < rows ? row : rows - 1) * G::kRowBytes + ((lane & 15) ^ NarrowMap<D>::swz(4 * l + g)) * 16 + (int)kBias - 1024 * l);
     };
-    auto v_to_regs = [&](const char* base) {
-#pragma unroll
-        for (int l = 0; l < NL; ++l) vreg[l] = *reinterpret_cast<const u4*>(base + off_v[l]);
+    typedef const __attribute__((address_space(1))) u4* Global16B;
+    auto rows_of = [&](int p) { return N - (j0 + p * step) * kTileKV; };
+    auto fetch = [&](const char* head, int p, unsigned buffer) {
+        p = p < nkv ? p : nkv - 1;
+        const unsigned long long base = base_of(head, p);
+        aim_lds(buffer + fill_dst);
+        static_for<NL>([&](auto l) { load_aimed_16B<1024 * decltype(l)::value>((const char*)base, offset_of(l, rows_of(p))); });
     };
+    auto v_to_regs = [&](int p) {
+        p = p < nkv ? p : nkv - 1;
+        const unsigned long long base = base_of(Vh, p);
+#pragma unroll
+        for (int l = 0; l < NL; ++l) vreg[l] = *(Global16B)(base + offset_of(l, rows_of(p)) + 1024 * l);
+    };
+    // In the loop: bases that move by a tile (move_k, move_v) and the offsets of whole tiles.  From the last position ahead of `whole` on, the first
+    // one that is not a whole tile further on, the bases stand still: the tile there is fetched again, and where the scan goes on with
+    // a tile that is not whole, that one in its place afterwards (mend).
+    const unsigned long long stride = (unsigned long long)((long long)step * G::kTile);
+    const int whole = step > 0 && nkv * kTileKV > N ? nkv - 1 : nkv;
+    const unsigned off[2] = {offset_of(0, kTileKV), offset_of(1, kTileKV)};
+    unsigned long long base_k, base_v, move_k, move_v;
+    // word w of the chunks in vreg; `dst` is where this lane's first one goes
     auto convert_word = [&](int w, unsigned dst) {
         f2 y;
         const unsigned word = vreg[w / 4][w % 4];
         y[0] = __builtin_bit_cast(float, word << 16);
         y[1] = __builtin_bit_cast(float, word & 0xffff0000u);
         vreg[w / 4][w % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(y, h2));
-        if (w % 4 == 3) *(LDS_PTR(u4))(size_t)(dst + (w / 4) * 4096 + lane * 16) = vreg[w / 4];
+        if (w % 4 == 3) *(LDS_PTR(u4))(size_t)(dst + (w / 4) * 1024) = vreg[w / 4];
     };
     constexpr int CW = NL * 4;
-    auto k_read = [&](int m) -> u4 { return *(LDS_PTR(u4))(size_t)(rk[m % KS] + (m / KS) * 16 * G::kRowBytes); };
+    // fragment m of K: columns 32*(m / 4).., keys 16*(m % 4)..; fragment m of V^T: keys 32*(m / DB).., columns 16*(m % DB)..
+    auto k_read = [&](int m) -> u4 { return *(LDS_PTR(u4))(size_t)(rk[m / 4] + (m % 4) * 16 * G::kRowBytes); };
     auto v_read = [&](int m) -> u4 {
         const unsigned at = rv[m % DB] + (m / DB) * 32 * G::kRowBytes;
         const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s4))(size_t)at);
         const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s4))(size_t)(at + 16 * G::kRowBytes));
         return __builtin_bit_cast(u4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
-    auto s_mfma = [&](int m, int qt, const u4& a, bool first) {
-        if (first) wide_s_first<BF16>(A[m / KS][qt], a, st.qf[m % KS][qt]);
-        else wide_s<BF16>(A[m / KS][qt], a, st.qf[m % KS][qt]);
+    auto s_mfma = [&](int m, int qt, const u4& a) {
+        if (m < 4) wide_s_first<BF16>(A[m % 4][qt], a, st.qf[m / 4][qt]);
+        else wide_s<BF16>(A[m % 4][qt], a, st.qf[m / 4][qt]);
     };
     auto o_mfma = [&](int m, int qt, const u4& a) {
         wide_o(st.o[m % DB][qt], a, pf[m / DB][qt]);
@@ -1424,13 +1502,18 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
             for (int qt = 0; qt < QT; ++qt) {
                 const int row = qw0 + (lane & 15) + 16 * qt;
                 const int last_key = CAUSAL ? (row < N - 1 ? row : N - 1) : N - 1;
-                int ahead = last_key - kv0 - 4 * g;
+                const int ahead = last_key - kv0 - 4 * g;
+                float none = -INFINITY;
+                asm volatile("" : "+v"(none));
 #pragma unroll
                 for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        asm volatile("" : "+v"(ahead));     // (separate comparisons: no lane masks kept and combined)
-                        A[kb][qt][r] = 16 * kb + r > ahead ? -INFINITY : A[kb][qt][r];
+                        // (assembly: in place, or the compiler keeps A in two sets of registers and copies it in every iteration)
+                        float s = A[kb][qt][r];
+                        asm volatile("v_cmp_gt_i32_e32 vcc, %1, %2\n\ts_nop 1\n\tv_cndmask_b32_e32 %0, %0, %3, vcc"
+                                     : "+v"(s) : "n"(16 * kb + r), "v"(ahead), "v"(none) : "vcc");
+                        A[kb][qt][r] = s;
                     }
             }
         }
@@ -1470,7 +1553,7 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
     auto convert_op = [&](int u) {
         pf[u / 16][u / 4 % 4][u % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u][0], e[u][1]}, h2));
     };
-    constexpr int OA = 96;
+    // step n of a pair: its two exponentials, and the convert of the pair before
     auto op_a = [&](int n) {
         const int u = n / 3, k = n % 3;
         if (k < 2) exp_op(u, k);
@@ -1482,23 +1565,19 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
     wide_guard_o(st);
 
     // ---------------------------------------------------------------- prologue: K(0..3) and V(0..1) on their way, S(0)
-    fetch(Kh, 0, lds0, off_k);
-    fetch(Kh, 1, lds0, off_k);
-    if constexpr (!BF16) fetch(Vh, 0, lds0 + VB, off_v);
-    fetch(Kh, 2, lds0, off_k);
-    if constexpr (!BF16) fetch(Vh, 1, lds0 + VB, off_v);
-    fetch(Kh, 3, lds0, off_k);
+    static_for<4>([&](auto p) {
+        fetch(Kh, p, lds0 + p * G::kTile);
+        if constexpr (!BF16 && (p == 1 || p == 2)) fetch(Vh, p - 1, lds0 + VB + (p - 1) * G::kTile);
+    });
     if constexpr (BF16) {
         // V(0) and V(1) go through registers into their buffers, V(2) waits in vreg
 #pragma unroll 1
-        for (int i = 0; i < 2; ++i) {
-            offsets(tile_of(i), off_v);
-            v_to_regs(base_of(Vh, tile_of(i)));
+        for (int p = 0; p < 2; ++p) {
+            v_to_regs(p);
 #pragma unroll
-            for (int w = 0; w < CW; ++w) convert_word(w, lds0 + VB + i * G::kTile + lm.fill_dst);
+            for (int w = 0; w < CW; ++w) convert_word(w, lds0 + VB + p * G::kTile + fill_dst + lane * 16);
         }
-        offsets(tile_of(2), off_v);
-        v_to_regs(base_of(Vh, tile_of(2)));
+        v_to_regs(2);
         landed_barrier<0>();
     } else {
         landed_barrier<12>();
@@ -1510,7 +1589,7 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
         static_for<NA>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
             if constexpr (m + LA < NA) a[m + LA] = k_read(m + LA);
-            static_for<QT>([&](auto q) { s_mfma(m, decltype(q)::value, a[m], m % KS == 0); });
+            static_for<QT>([&](auto q) { s_mfma(m, decltype(q)::value, a[m]); });
             __builtin_amdgcn_sched_barrier(0);
         });
     }
@@ -1533,8 +1612,6 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
     u4 ak[LA];
 #pragma unroll
     for (int m = 0; m < LA; ++m) ak[m] = k_read(m);
-    offsets(tile_of(4), off_k);
-    offsets(tile_of(BF16 ? 3 : 2), off_v);
 
     // ---------------------------------------------------------------- steady state: iteration i
     // reads K(i+1) and V(i), fetches K(i+4) into the place of K(i), which was read before the barrier of iteration i-1, and V(i+2) into that
@@ -1542,27 +1619,17 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
     // bfloat16: V(i+2) goes from registers into its place in the second product, then V(i+3) is loaded; K(i+4) is fetched there too, as the
     // compiler waits for all loads where it uses those registers.
     // Returns whether the reference maximum has to be raised before tile i+1 can be used.
-    struct Fetch {       // what an iteration fetches, and where to
-        const char *kbase, *vbase;
-        unsigned kdst, vdst;
-    };
-    constexpr int NV = BF16 ? 0 : NL, TL = NV + NL;
-    auto aim = [&](int i) {
-        const int jk = tile_of(i + 4), jv = tile_of(BF16 ? i + 3 : i + 2);
-        if (N % kTileKV) {      // (uniform; only the last tile of a sequence that ends inside it has offsets of its own)
-            offsets(jk, off_k);
-            offsets(jv, off_v);
-        }
-        return Fetch{base_of(Kh, jk), base_of(Vh, jv), (unsigned)__builtin_amdgcn_readfirstlane(lds0 + (i & 3) * G::kTile + lm.fill_dst),
-                     (unsigned)__builtin_amdgcn_readfirstlane(lds0 + VB + ((i + 2) & 3) * G::kTile + lm.fill_dst)};
-    };
-    auto load = [&](const Fetch& f, int li) {
-        if (li < NV) load_to_lds_16B(f.vbase, off_v[li], f.vdst + li * 4096);
-        else load_to_lds_16B(f.kbase, off_k[li - NV], f.kdst + (li - NV) * 4096);
-    };
-    auto iteration = [&](int i) -> bool {
-        const Fetch f = aim(i);
-        const int dk = ((i + 2) & 3) ? G::kTile : -3 * G::kTile, dv = ((i + 1) & 3) ? G::kTile : -3 * G::kTile;
+    unsigned ring = 0;        // byte offset of buffer i & 3
+    auto k_place = [&]() { return (unsigned)__builtin_amdgcn_readfirstlane(lds0 + ring); };
+    auto v_place = [&]() { return (unsigned)__builtin_amdgcn_readfirstlane(lds0 + VB + (ring ^ 2 * G::kTile)); };
+    auto turn = [&]() { ring = (unsigned)__builtin_amdgcn_readfirstlane((ring + G::kTile) & 3 * G::kTile); };
+    static constexpr auto plan_a = P::first_product();
+    static constexpr auto plan_b = P::second_product();
+    static_assert(plan_b.first[36] > P::OX, "the second half of the second product uses the last probabilities");
+    // (assembly: left to itself the compiler collects these additions behind the loop's branch, where nothing hides them)
+    auto move = [](unsigned& at, int by) { asm volatile("v_add_u32 %0, %1, %0" : "+v"(at) : "s"(by)); };
+    auto iteration = [&]() -> unsigned long long {
+        const int dka = ring == 2 * G::kTile ? -3 * (int)G::kTile : (int)G::kTile, dva = ring == 3 * G::kTile ? -3 * (int)G::kTile : (int)G::kTile;
         u4 av[NB];
         {
             u4 a[NA];
@@ -1570,20 +1637,24 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
             for (int m = 0; m < LA; ++m) a[m] = ak[m];
             // Fragments are read two at a time and used in the order second, first: the one wait for the later read covers both.
             static_for<TA>([&](auto tc) {
-                constexpr int t = decltype(tc)::value, q = t / QT, m = q ^ 1, qt = t % QT;
-                if constexpr (qt == 0 && q % 2 == 0) {
+                constexpr int t = decltype(tc)::value, q = t / QT, m = q ^ 1, qt = q & 1 ? QT - 1 - t % QT : t % QT;
+                if constexpr (t % 8 == 0) {
                     if constexpr (q + LA < NA) { a[q + LA] = k_read(q + LA); a[q + LA + 1] = k_read(q + LA + 1); }
                     else { av[q + LA - NA] = v_read(q + LA - NA); av[q + LA - NA + 1] = v_read(q + LA - NA + 1); }
                 }
-                s_mfma(m, qt, a[m], q % KS == 0);
-                if constexpr (!BF16 && t >= 2 && t < 2 + 2 * TL && t % 2 == 0) load(f, (t - 2) / 2);
-                static_for<(t + 1) * OA / TA - t * OA / TA>([&](auto k) { op_a(t * OA / TA + decltype(k)::value); });
+                s_mfma(m, qt, a[m]);
+                if constexpr (!BF16 && t % 8 == 4) {
+                    constexpr int li = t / 8;
+                    if constexpr (li == 0) aim_lds(v_place() + fill_dst);
+                    if constexpr (li == 4) aim_lds(k_place() + fill_dst);
+                    if constexpr (li < 4) load_aimed_16B<1024 * li>((const char*)base_v, off[li & 1]);
+                    else load_aimed_16B<1024 * (li - 4)>((const char*)base_k, off[li & 1]);
+                }
+                if constexpr (t >= 57 && t < 61) move(rk[t - 57], dka);
+                static_for<plan_a.first[t + 1] - plan_a.first[t]>([&](auto k) { op_a(plan_a.first[t] + decltype(k)::value); });
                 __builtin_amdgcn_sched_barrier(0);
             });
-            convert_op(31);
         }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) rk[ks] += dk;
         // (the probabilities pass through the statement, or the compiler moves the exponentials behind the barrier)
         pin_p();
         if constexpr (BF16) landed_barrier<0>();
@@ -1597,78 +1668,108 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) mx[qt] = lim[qt];
-        bool need = false;
-        constexpr int OC = BF16 ? 3 * CW : 0;
-        constexpr int OM = 32 + OC, OB = OM + 64;
-        constexpr int T0 = (OM * TB + OB - 1) / OB;
-        auto op_b = [&](int n) {
-            if (n < OM) {
-                const int j = n * 32 / OM, done = (n + 1) * 32 / OM;
-                if (j != done) max_op(j & 3, j >> 2);
-                if constexpr (BF16) {
-                    const int w = n * CW / OM;
-                    if (w != (n + 1) * CW / OM) convert_word(w, f.vdst);
-                }
-            } else {
-                shift_score(n - OM);
-            }
+        unsigned long long need = 0;
+        unsigned vdst = v_place();      // (bfloat16: this lane's place; one address, the rest in the instructions' offsets)
+        if constexpr (BF16) asm volatile("v_lshl_add_u32 %0, %1, 4, %2" : "=v"(vdst) : "v"(lane), "s"(vdst + fill_dst));
+        auto op_b = [&](auto nc) {
+            constexpr int n = decltype(nc)::value;
+            if constexpr (n < P::OX) op_a(P::OA + n);
+            else if constexpr (n < P::OM) {
+                if constexpr (n == P::OX) convert_op(31);
+                convert_word(n - P::OX, vdst);
+            } else if constexpr (n < P::OQ) {
+                if constexpr (n == P::OM && !BF16) convert_op(31);
+                max_op((n - P::OM) & 3, (n - P::OM) >> 2);
+            } else if constexpr (n < P::OS) {
+                // (mx starts from lim: it exceeds lim exactly when a score does)
+                need |= __builtin_amdgcn_ballot_w64(!(mx[n - P::OQ] <= lim[n - P::OQ]));
+            } else shift_score(n - P::OS);
         };
-        static_for<TB>([&](auto tc) {
-            constexpr int t = decltype(tc)::value, q = t / QT, m = q ^ 1;
-            if constexpr (t % QT == 0 && q % 2 == 0) {
-                if constexpr (q + LA < NB) { av[q + LA] = v_read(q + LA); av[q + LA + 1] = v_read(q + LA + 1); }
-                else { ak[q + LA - NB] = k_read(q + LA - NB); ak[q + LA - NB + 1] = k_read(q + LA - NB + 1); }
+        static_for<72>([&](auto wc) {
+            constexpr int w = decltype(wc)::value, t = w - w / 9, q = t / QT, m = q ^ 1;
+            if constexpr (w % 9 == 8) sum_mfma((t - 1) / 32, (t - 1) / 8 % 4);
+            else {
+                if constexpr (t % 8 == 0) {
+                    if constexpr (q + LA < NB) { av[q + LA] = v_read(q + LA); av[q + LA + 1] = v_read(q + LA + 1); }
+                    else { ak[q + LA - NB] = k_read(q + LA - NB); ak[q + LA - NB + 1] = k_read(q + LA - NB + 1); }
+                }
+                o_mfma(m, q & 1 ? QT - 1 - t % QT : t % QT, av[m]);
+                if constexpr (BF16 && t == 0) aim_lds(k_place() + fill_dst);
+                if constexpr (BF16 && t < 4) load_aimed_16B<1024 * t>((const char*)base_k, off[t & 1]);
             }
-            if constexpr (BF16 && t == T0) v_to_regs(f.vbase);
-            o_mfma(m, t % QT, av[m]);
-            if constexpr (t % 8 == 7) sum_mfma(t / 32, t / 8 % 4);
-            if constexpr (BF16 && t >= 2 && t < 2 + TL) load(f, t - 2);
-            static_for<(t + 1) * OB / TB - t * OB / TB>([&](auto k) {
-                constexpr int n = t * OB / TB + decltype(k)::value;
-                op_b(n);
-                if constexpr (n == OM + 8) need = __builtin_amdgcn_ballot_w64(!(mx[0] <= lim[0]) || !(mx[1] <= lim[1]) || !(mx[2] <= lim[2]) || !(mx[3] <= lim[3])) != 0;
-            });
+            static_for<plan_b.first[w + 1] - plan_b.first[w]>([&](auto k) { op_b(std::integral_constant<int, plan_b.first[w] + decltype(k)::value>{}); });
+            if constexpr (BF16 && plan_b.first[w] < P::OM && plan_b.first[w + 1] >= P::OM) {
+#pragma unroll
+                for (int l = 0; l < NL; ++l) vreg[l] = *(Global16B)(base_v + off[l & 1] + 1024 * l);
+            }
+            if constexpr (w >= 64) move(rv[w - 64], dva);
+            if constexpr (w == 58) turn();
+            if constexpr (w == 60) base_k += move_k;
+            if constexpr (w == 62) base_v += move_v;
             __builtin_amdgcn_sched_barrier(0);
         });
 #pragma unroll
         for (int k = 0; k < 16 * QT; k += 16)
             asm volatile("" : "+v"(x[k]), "+v"(x[k + 1]), "+v"(x[k + 2]), "+v"(x[k + 3]), "+v"(x[k + 4]), "+v"(x[k + 5]), "+v"(x[k + 6]), "+v"(x[k + 7]),
                          "+v"(x[k + 8]), "+v"(x[k + 9]), "+v"(x[k + 10]), "+v"(x[k + 11]), "+v"(x[k + 12]), "+v"(x[k + 13]), "+v"(x[k + 14]), "+v"(x[k + 15]));
-#pragma unroll
-        for (int db = 0; db < DB; ++db) rv[db] += dv;
         return need;
     };
     // The tiles that concern this wavefront.  In a causal scan up, the tiles of the workgroup's last rows lie wholly behind the others' rows: those
     // wavefronts keep fetching and meeting the barriers, but compute nothing more (0 times an infinite value would be no number).
     const int mine = CAUSAL && step > 0 && (qw0 + 63) / kTileKV + 1 < nkv ? (qw0 + 63) / kTileKV + 1 : nkv;
     auto fetch_only = [&](int i) {       // iteration i's fetches (bfloat16: V(i+2) into LDS first)
-        const Fetch f = aim(i);
         if constexpr (BF16) {
 #pragma unroll
             for (int l = 0; l < NL; ++l) asm volatile("" : "+v"(vreg[l]));
 #pragma unroll
-            for (int w = 0; w < CW; ++w) convert_word(w, f.vdst);
-            v_to_regs(f.vbase);
+            for (int w = 0; w < CW; ++w) convert_word(w, v_place() + fill_dst + lane * 16);
+            v_to_regs(i + 3);
+        } else {
+            fetch(Vh, i + 2, v_place());
         }
-#pragma unroll
-        for (int li = 0; li < TL; ++li) load(f, li);
+        fetch(Kh, i + 4, k_place());
+        turn();
     };
     // (The raise stands outside the inner loop: inside, the compiler copies accumulators on the common path and spills.)
+    constexpr int AV = BF16 ? 3 : 2;      // positions by which V is fetched ahead (K: 4)
+    // Iteration i fetched the last whole tile once more in place of one that is not whole, which follows here, behind it.
+    auto mend = [&](int i) {
+        if (whole == nkv) return;
+        if (i + 4 == whole) {
+            wait_tile_landed();
+            fetch(Kh, whole, lds0 + (whole & 3) * G::kTile);
+        }
+        if (i + AV == whole) {
+            if constexpr (BF16) v_to_regs(whole);
+            else {
+                wait_tile_landed();
+                fetch(Vh, whole, lds0 + VB + (whole & 3) * G::kTile);
+            }
+        }
+    };
     int i = 0;
+    base_k = base_of(Kh, whole > 4 ? 4 : whole > 0 ? whole - 1 : 0);
+    base_v = base_of(Vh, whole > AV ? AV : whole > 0 ? whole - 1 : 0);
     while (i + 1 < mine) {
+        // up to the next iteration ahead of which something changes
+        int pause = mine - 1;
+        for (int at : {whole - 5, whole - 3, whole - AV - 1, whole - AV + 1}) pause = at > i && at < pause ? at : pause;
+        move_k = i < whole - 5 ? stride : 0;
+        move_v = i < whole - AV - 1 ? stride : 0;
         bool need = false;
 #pragma unroll 1
-        for (; i + 1 < mine; ++i) {
-            need = iteration(i);
+        for (; i < pause; ++i) {
+            need = iteration() != 0;
             if (need) { ++i; break; }
         }
         if (need) raise_reference();
+        mend(i - 1);
     }
     // ---------------------------------------------------------------- last tile: probabilities, then O^T += V^T P^T
     if constexpr (CAUSAL && !BF16) {
         if (mine < nkv) fetch_only(mine - 1);
     }
-    static_for<OA>([&](auto n) { op_a(decltype(n)::value); });
+    static_for<96>([&](auto n) { op_a(decltype(n)::value); });
     convert_op(31);
     landed_barrier<0>();
     if constexpr (CAUSAL && BF16) {
@@ -2401,7 +2502,7 @@ __device__ __forceinline__ void process_q_tile_narrow(const Params& p, const Nar
     }
     if (p.stream_q) __syncthreads();      // the fragments are in registers before the first K/V fetch overwrites the rows
 
-    if constexpr (QT == 4) scan_tiles_wide<BF16, CAUSAL>(st, lm, Kh, Vh, N, p.c, j0, step, nkv, qw0, lane, lds);
+    if constexpr (QT == 4) scan_tiles_wide<BF16, CAUSAL>(st, lm, Kh, Vh, N, p.c, j0, step, nkv, qw0, wave, lane, lds);
     else scan_tiles<D, BF16, CAUSAL, PHASES>(st, lm, Kh, Vh, N, p.c, j0, step, nkv, qw0, qw0 + (lane & 15), lane, lds);
 
     // ---- epilogue: O_i = acc / l  (the division Alg. 1 leaves implicit; Eq. 1 fixes it)
