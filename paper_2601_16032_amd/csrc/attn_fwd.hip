@@ -1335,6 +1335,10 @@ __device__ __forceinline__ void wide_settle_o(NarrowState<128, 4>& st) {
     asm volatile("s_nop 15" ::: "memory");
     wide_hold_o(st);
 }
+// Probabilities that have just been converted, ahead of the MFMAs that read them (a vector instruction's result: 2 wait states).
+__device__ __forceinline__ void wide_settle_p(u4 (&pf)[2][4]) {
+    asm volatile("s_nop 3" : "+v"(pf[0][0]), "+v"(pf[0][1]), "+v"(pf[0][2]), "+v"(pf[0][3]), "+v"(pf[1][0]), "+v"(pf[1][1]), "+v"(pf[1][2]), "+v"(pf[1][3]));
+}
 __device__ __forceinline__ void wide_guard_o(NarrowState<128, 4>& st) {
     wide_hold_o(st);
     asm volatile("s_nop 7" ::: "memory");
@@ -1771,6 +1775,7 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
     }
     static_for<96>([&](auto n) { op_a(decltype(n)::value); });
     convert_op(31);
+    wide_settle_p(pf);
     landed_barrier<0>();
     if constexpr (CAUSAL && BF16) {
         if (mine < nkv) fetch_only(mine - 1);
