@@ -61,6 +61,8 @@ typedef float f16v __attribute__((ext_vector_type(16)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef unsigned u4 __attribute__((ext_vector_type(4)));
+typedef unsigned u8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h16 __attribute__((ext_vector_type(16)));
 typedef unsigned u16v __attribute__((ext_vector_type(16)));
 typedef unsigned u2 __attribute__((ext_vector_type(2)));
 typedef short s4 __attribute__((ext_vector_type(4)));
@@ -279,19 +281,56 @@ __device__ __forceinline__ float pair_sum(float x) {
     return lo + hi;
 }
 
-// Adds the two binary16 values of `ph` to two float partial sums (one mixed-precision FMA each:
-// exact, and cheaper in the instruction stream than the two-element dot product).
-// `one` is binary16 1.0 held in a register the compiler cannot see through (opaque_one()): the widened products
-// then become v_fma_mix_f32.  Written in C and not as inline assembly because the compiler separates dependent
-// assembly statements that have nothing in between by a no-op each, one issue slot per row-sum update.
-__device__ __forceinline__ _Float16 opaque_one() {
-    _Float16 one = (_Float16)1.0f;
-    asm volatile("" : "+v"(one));
-    return one;
+// Row sums of the rounded probabilities on the matrix cores: a sparse product with ones, 64 keys x 16 columns in one v_smfmac_f32_16x16x64, which
+// takes the 16 cycles of a 16x16x32.  Of each four neighbouring halves of the second operand a row of the first takes two; even rows
+// take the first two, odd rows the last two, so a column's sum is that of an even and an odd row.  Accumulated in binary32 like the products.
+struct SparseOnes {
+    u4 one;       // the values of this lane's row of the first operand, row lane % 16
+    int pick;     // which halves they meet, two bits each
+};
+__device__ __forceinline__ SparseOnes sparse_ones(int lane, unsigned one) {
+    SparseOnes s;
+    s.one = u4{one, one, one, one};
+    asm volatile("" : "+v"(s.one));      // (or the compiler makes them anew in every iteration)
+    s.pick = lane & 1 ? (int)0xeeeeeeee : 0x44444444;
+    asm volatile("" : "+v"(s.pick));
+    return s;
 }
-__device__ __forceinline__ void add_pair(float& sum_lo, float& sum_hi, h2 ph, _Float16 one) {
-    sum_lo = __builtin_fmaf((float)ph[0], (float)one, sum_lo);
-    sum_hi = __builtin_fmaf((float)ph[1], (float)one, sum_hi);
+constexpr unsigned kOnes = 0x3c003c00u;      // binary16 1.0, twice
+__device__ __forceinline__ f4 sparse_sum(const SparseOnes& ones, const u8& p, f4 acc) {
+    return __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, ones.one), __builtin_bit_cast(h16, p), acc, ones.pick, 0, 0);
+}
+// The same with 32 columns, second operands in the layout of 32x32x16 and the sum of a column in acc[0] + acc[1] of both lanes that hold it: two per
+// tile in place of two mixed-precision additions per pair, which took a tenth of pipelined_range's issue slots (4 x 4096, d = 64 26.5 -> 25.5 us,
+// 1 x 16384, d = 64, causal 88.1 -> 83.6, 2 x 4096, d = 128 35.8 -> 34.9), or of four plain products (8 x 2048, d = 64, causal 15.1 -> 15.0).  (Half the
+// time would do with 16 columns and zeros against the others' values, but 0 times an infinity or no number is no number: query rows would mix.)
+__device__ __forceinline__ f16v sparse_sum_32(const SparseOnes& ones, const u8& p, f16v acc) {
+    return __builtin_amdgcn_smfmac_f32_32x32x32_f16(__builtin_bit_cast(h8, ones.one), __builtin_bit_cast(h16, p), acc, ones.pick, 0, 0);
+}
+// Probabilities of 64 keys x 16 N query rows as second operands: part kh, qt = keys 32kh..32kh+31 of the rows 16qt.. .  Sparse sums want the two parts of
+// some rows in eight registers in a row; for plain sums they lie apart, which is easier to find registers for.
+template <bool SPARSE, int N>
+struct Probabilities {
+    u8 v[N];
+    __device__ __forceinline__ void set(int kh, int qt, int word, unsigned x) { v[qt][4 * kh + word] = x; }
+    __device__ __forceinline__ u4 part(int kh, int qt) const { return kh ? __builtin_shufflevector(v[qt], v[qt], 4, 5, 6, 7) : __builtin_shufflevector(v[qt], v[qt], 0, 1, 2, 3); }
+    __device__ __forceinline__ void pin() {      // nothing that writes them moves behind this, nothing that reads them ahead of it
+#pragma unroll
+        for (int qt = 0; qt < N; qt += 2) asm volatile("" : "+v"(v[qt]), "+v"(v[qt + 1]));
+    }
+};
+template <int N>
+struct Probabilities<false, N> {
+    u4 v[2][N];
+    __device__ __forceinline__ void set(int kh, int qt, int word, unsigned x) { v[kh][qt][word] = x; }
+    __device__ __forceinline__ u4 part(int kh, int qt) const { return v[kh][qt]; }
+    __device__ __forceinline__ void pin() {
+#pragma unroll
+        for (int qt = 0; qt < N; qt += 2) asm volatile("" : "+v"(v[0][qt]), "+v"(v[0][qt + 1]), "+v"(v[1][qt]), "+v"(v[1][qt + 1]));
+    }
+};
+__device__ __forceinline__ u4 half_of(const u8& p, int hi) {
+    return hi ? __builtin_shufflevector(p, p, 4, 5, 6, 7) : __builtin_shufflevector(p, p, 0, 1, 2, 3);
 }
 
 // Per-wavefront state of one query tile that the K/V loop carries along.
@@ -509,12 +548,12 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
     constexpr int EU = 16 / NA;           // exp units (2 exp + convert + sum of one pair) per MFMA of phase A
     if (count <= 0) return;
     const unsigned lds0 = (unsigned)(size_t)lds;
-    float L_hi = 0.f;   // second partial of the running sum (upper halves of the probability pairs), folded into st.L
-    const _Float16 one = opaque_one();
     const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f16v sums = zero;   // running sum of the row from here on, see sparse_sum_32; folded into st.L
+    const SparseOnes ones = sparse_ones(lane, (lane & 3) < 2 ? kOnes : 0u);
     f16v A[2];          // S^T of the tile one ahead: block b = keys 32b..32b+31 of the tile
     float x[32];        // score*c - M of the current tile, index 16*b + r
-    u4 pf[4];           // its probabilities as B operands
+    u8 pf[2];           // its probabilities as B operands, two in each
     u4 vreg[(HALVES ? 2 : 1) * NL];   // bfloat16 V chunks in flight (BF16 only), run r in vreg[r * NL ...]
 
     // LDS read addresses: K of the tile one ahead, V of the current tile
@@ -547,19 +586,18 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
         return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
     auto rescale = [&](float tmax) {
-        st.L += L_hi;
-        L_hi = 0.f;
         const float Mnew = fmaxf(st.M, tmax);
         const float alpha = (Mnew == -INFINITY) ? 1.0f : fast_exp2(st.M - Mnew);
         st.M = Mnew;
         st.L *= alpha;
+        sums *= alpha;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int r = 0; r < 16; ++r) st.o[db][r] *= alpha;
     };
     float tmax_ahead = 0.f;   // row maximum (times c) of the tile in A, from the latest iteration
-    // exp unit u (0..15): the two exponentials of pair u, and the convert + sum of pair u-1
+    // exp unit u (0..15): the two exponentials of pair u, and the convert of pair u-1
     float e0[16], e1[16];
     auto exp_unit = [&](int u) {
         if (u < 16) {
@@ -568,9 +606,7 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
         }
         if (u >= 1 && u <= 16) {
             const int v = u - 1;
-            const h2 ph = __builtin_convertvector(f2{e0[v], e1[v]}, h2);
-            add_pair(st.L, L_hi, ph, one);   // sum of the rounded probabilities, the values the second product uses
-            pf[v / 4][v % 4] = __builtin_bit_cast(unsigned, ph);
+            pf[v / 8][v % 8] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e0[v], e1[v]}, h2));
         }
     };
 
@@ -674,8 +710,9 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
 #pragma unroll
         for (int idx = 0; idx < H; ++idx) {
             av[idx + 2] = v_read(idx + 2);
-            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, pf[idx / DB]),
+            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, half_of(pf[idx / DB / 2], idx / DB & 1)),
                                                                     st.o[idx % DB], 0, 0, 0);
+            if (idx % (H / 2) == H / 2 - 1) sums = sparse_sum_32(ones, pf[idx / (H / 2)], sums);
             if (idx >= MS) {
 #pragma unroll
                 for (int q = 0; q < MPS; ++q) {
@@ -699,7 +736,7 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
 #pragma unroll
         for (int idx = H; idx < NB; ++idx) {
             if (idx + 2 < NB) av[idx + 2] = v_read(idx + 2);
-            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, pf[idx / DB]),
+            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, half_of(pf[idx / DB / 2], idx / DB & 1)),
                                                                     st.o[idx % DB], 0, 0, 0);
 #pragma unroll
             for (int q = 0; q < FPS; ++q) {
@@ -766,12 +803,13 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
 #pragma unroll
         for (int idx = 0; idx < NB; ++idx) {
             if (idx + 2 < NB) av[idx + 2] = v_read(idx + 2);
-            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, pf[idx / DB]),
+            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, half_of(pf[idx / DB / 2], idx / DB & 1)),
                                                                     st.o[idx % DB], 0, 0, 0);
+            if (idx % (NB / 2) == NB / 2 - 1) sums = sparse_sum_32(ones, pf[idx / (NB / 2)], sums);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    st.L += L_hi;
+    st.L += 0.5f * (sums[0] + sums[1]);      // (both lanes of a pair hold the row's sum)
     __syncthreads();   // all reads of the last tile are done before anything refills the buffers
 }
 
@@ -926,20 +964,14 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
     constexpr bool PAIRS = D == 128;
     const unsigned lds0 = (unsigned)(size_t)lds;
     const int g = lane >> 4;
-    // Binary16 1.0, A operand of the row sums.  Made where it is used, from a scalar register: a constant that the compiler
-    // sees through is kept in vector registers over the whole kernel, and d = 64 has none to spare (20 to 32 bytes of scratch).
-    auto make_ones = []() {
-        unsigned one = 0x3c003c00u;
-        asm volatile("" : "+s"(one));
-        u4 v = {one, one, one, one};
-        asm volatile("" : "+v"(v));
-        return v;
-    };
-    u4 ones = make_ones();
+    // Row sums: sparse products (their 16 columns are the query rows), in the first two elements of L; the first operand is zero in the other rows,
+    // which switches less.  Plain products before, sparse now: 1 x 131072, d = 64 4319 -> 4230 us, 8 x 32768, d = 64, causal 1061 -> 1043,
+    // 16 x 8192, d = 128, bfloat16, causal 251.1 -> 248.1, 128 x 512, d = 128 20.2 -> 20.0.
+    const SparseOnes ones = sparse_ones(lane, (lane & 3) < 2 ? kOnes : 0u);
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
     f4 A[4][2];         // S^T of the tile one ahead: block (kb, qt) = keys 16kb.. x query rows 16qt..
     float x[32];        // score*c - M of the current tile, index 16*qt + 4*kb + r
-    u4 pf[2][2];        // its probabilities as B operands: pf[kh][qt] = keys 32kh..32kh+31
+    Probabilities<true, 2> pf;
     u4 vreg[NL];        // bfloat16 V chunks in flight (BF16 only)
     float lim[2] = {-INFINITY, -INFINITY};    // [qt]: the raw score above which the reference maximum has to be raised
 
@@ -1011,7 +1043,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
     auto s_mfma = [&](int m, int qt, u4 a, bool first) {
         A[m / KS][qt] = mfma_16x16<BF16>(a, st.qf[m % KS][qt], first ? zero : A[m / KS][qt]);
     };
-    auto o_mfma = [&](int m, int qt, u4 a) { st.o[m % DB][qt] = mfma_16x16<false>(a, pf[m / DB][qt], st.o[m % DB][qt]); };
+    auto o_mfma = [&](int m, int qt, u4 a) { st.o[m % DB][qt] = mfma_16x16<false>(a, pf.part(m / DB, qt), st.o[m % DB][qt]); };
     // The scores in A: -inf where the key is not visible.  Register r of block kb is key
     // 16kb + 4g + r of the tile: visible up to the offset `ahead`.
     const int all_see = CAUSAL ? (qw0 < N - 1 ? qw0 : N - 1) : N - 1;      // last key visible to every row of the wavefront
@@ -1049,7 +1081,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
             const float t = quad_max(mx[qt]);           // the lanes of a query row move together
             const bool up = t > lim[qt];
             const float Mnew = up ? t * c : st.M[qt];
-            const bool fresh = st.L[qt][0] == 0.f;
+            const bool fresh = st.L[qt][0] + st.L[qt][1] == 0.f;
             const float alpha = up && !fresh ? fast_exp2(st.M[qt] - Mnew) : 1.0f;
             st.M[qt] = Mnew;
             st.L[qt] *= alpha;
@@ -1067,10 +1099,12 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
     float e[16][2];
     auto exp_op = [&](int u, int h) { e[u][h] = fast_exp2(x[16 * (u / 4 % 2) + 4 * (2 * (u / 8) + u % 4 / 2) + 2 * (u % 2) + h]); };
     auto convert_op = [&](int u) {
-        pf[u / 8][u / 4 % 2][u % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u][0], e[u][1]}, h2));
+        pf.set(u / 8, u / 4 % 2, u % 4, __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u][0], e[u][1]}, h2)));
     };
     // Row sums of the rounded probabilities, the values the second product uses.
-    auto sum_mfma = [&](int kh, int qt) { st.L[qt] = mfma_16x16<false>(ones, pf[kh][qt], st.L[qt]); };
+    auto sum_mfma = [&](int k) {      // behind the k-th quarter of the second product (all probabilities are there from its start)
+        if (k < 2) st.L[k] = sparse_sum(ones, pf.v[k], st.L[k]);
+    };
     // What runs under the first product, in order: step k of pair u, the convert one pair behind its exponentials.
     constexpr int OA = 48;
     auto op_a = [&](int n) {
@@ -1170,7 +1204,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
         }
         // ---- everything fetched in the iteration before has landed; nobody reads K(i+1) and V(i-1) any more
         //      (the probabilities pass through the statement, or the compiler moves the exponentials behind it)
-        asm volatile("" : "+v"(pf[0][0]), "+v"(pf[0][1]), "+v"(pf[1][0]), "+v"(pf[1][1]));
+        pf.pin();
         landed_barrier<0>();
         if constexpr (PHASES) __builtin_amdgcn_s_setprio(2);
         kv0 += kv_step;
@@ -1217,7 +1251,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
             if (PAIRS && t % 4 == 0 && q + LA < NB) { av[q + LA] = v_read(q + LA); av[q + LA + 1] = v_read(q + LA + 1); }
             if (BF16 && t == T0) v_to_regs();
             o_mfma(m, t & 1, av[m]);
-            if (t % (TB / 4) == TB / 4 - 1) sum_mfma(t / (TB / 2), t / (TB / 4) & 1);
+            if (t % (TB / 4) == (D == 128 ? 5 : 3)) sum_mfma(t / (TB / 4));
             constexpr bool EARLY = D == 128 || !CAUSAL;
             for (int li = EARLY ? t / 4 : t * TL / TB; li < TL && (EARLY ? t % 4 == 1 && li == t / 4 : li < (t + 1) * TL / TB); ++li) {
                 if (li < NV) tile_load_to_lds(dv, lm.fill_src + li * 4096, vdst + li * 4096);
@@ -1255,7 +1289,6 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
 #pragma unroll
     for (int n = 0; n < OA; ++n) op_a(n);
     convert_op(15);
-    ones = make_ones();
     landed_barrier<0>();      // also the fetches past the end of the scan, which write zeros into buffers nobody reads
     if (!CAUSAL || kv0 <= qw0 + 31) {      // (not if every row of the wavefront lies before the tile's first key)
         u4 av[NB];
@@ -1266,7 +1299,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
             const int m = t / 2;
             if ((t & 1) == 0 && m + LA < NB) av[m + LA] = v_read(m + LA);
             o_mfma(m, t & 1, av[m]);
-            if (t % (TB / 4) == TB / 4 - 1) sum_mfma(t / (TB / 2), t / (TB / 4) & 1);
+            if (t % (TB / 4) == TB / 4 - 1) sum_mfma(t / (TB / 4));
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -1280,7 +1313,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
 // traffic per multiply-add.
 //
 // What bounds it: with live operands the power limit, and the issue of its one wavefront per SIMD, which holds with zeros too: about 3050 cycles
-// per tile for 136 MFMAs of 16 cycles (128 for the products, 8 for the row sums), 64 exponentials, 150 other vector instructions, 48 LDS reads and
+// per tile for 132 MFMAs of 16 cycles (128 for the products, 4, for bfloat16 8, for the row sums), 64 exponentials, 150 other vector instructions, 48 LDS reads and
 // 8 direct loads.  Both count: less clock goes with less voltage, so a tile in 7 % fewer cycles takes 3.5 % less time at the power limit.  What
 // that rests on: work spread evenly over the MFMAs (WidePlan); loads that share M0, and bases that move by a tile, in place of some 40 scalar
 // instructions a tile; nothing behind the loop's branch.  32 heads x 16384, before and after: binary16 3375 -> 3257 us
@@ -1320,6 +1353,9 @@ __device__ __forceinline__ void wide_o(f4& acc, const u4& v, const u4& p) {
 __device__ __forceinline__ void wide_sum(f4& acc, const u4& ones, const u4& p) {
     asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "a"(ones), "v"(p));
 }
+__device__ __forceinline__ void wide_sparse_sum(f4& acc, const SparseOnes& ones, const u8& p) {
+    asm volatile("v_smfmac_f32_16x16x64_f16 %0, %1, %2, %3" : "+a"(acc) : "a"(ones.one), "v"(p), "v"(ones.pick));
+}
 // The accumulators pass through these statements, so that no use of them can be scheduled ahead of the wait (or, wide_guard, behind it).
 __device__ __forceinline__ void wide_settle_s(f4 (&A)[4][4]) {
     asm volatile("s_nop 15" ::: "memory");
@@ -1336,8 +1372,11 @@ __device__ __forceinline__ void wide_settle_o(NarrowState<128, 4>& st) {
     wide_hold_o(st);
 }
 // Probabilities that have just been converted, ahead of the MFMAs that read them (a vector instruction's result: 2 wait states).
-__device__ __forceinline__ void wide_settle_p(u4 (&pf)[2][4]) {
-    asm volatile("s_nop 3" : "+v"(pf[0][0]), "+v"(pf[0][1]), "+v"(pf[0][2]), "+v"(pf[0][3]), "+v"(pf[1][0]), "+v"(pf[1][1]), "+v"(pf[1][2]), "+v"(pf[1][3]));
+template <bool SPARSE>
+__device__ __forceinline__ void wide_settle_p(Probabilities<SPARSE, 4>& pf) {
+    pf.pin();
+    asm volatile("s_nop 3");
+    pf.pin();
 }
 __device__ __forceinline__ void wide_guard_o(NarrowState<128, 4>& st) {
     wide_hold_o(st);
@@ -1390,15 +1429,25 @@ struct WidePlan {
     }
     // OX steps of exponentials, CW conversions, 32 maxima, 4 comparisons, 64 shifted scores
     static constexpr int OM = OX + CW, OQ = OM + 32, OS = OQ + 4, OB = OS + 64;
-    static constexpr Windows<72> second_product() {
-        int cost[OB] = {}, taken[72] = {};
+    // MFMAs of the second product: the 64 of the product in order, row sums in between.  Sparse ones (see sparse_sum) want all of a row's probabilities and
+    // stand in the second half; bfloat16 has no registers left for them (0 to +10 %) and sums every 32 keys.
+    static constexpr bool SPARSE = !BF16;
+    static constexpr int SUMS = SPARSE ? 4 : 8, W = 64 + SUMS, HALF = SPARSE ? 32 : 36;
+    static constexpr bool sum_at(int w) { return SPARSE ? w >= HALF && w % 9 == 4 : w % 9 == 8; }
+    static constexpr int product_at(int w) {
+        int t = 0;
+        for (int v = 0; v < w; ++v) t += !sum_at(v);
+        return t;
+    }
+    static constexpr Windows<W> second_product() {
+        int cost[OB] = {}, taken[W] = {};
         for (int n = 0; n < OB; ++n) cost[n] = n < OX ? (n % 3 < 2 ? exponential : 1) : n < OM ? 3 : 1;
-        for (int w = 0; w < 72; ++w) {                                                // (w = 9k + 8: a row sum's)
-            if (w % 9 == 0) taken[w] += w < 63 ? 4 : 2;                               // fragment reads: a pair of V^T, at the end of K
+        for (int w = 0; w < W; ++w) {
+            if (!sum_at(w) && product_at(w) % 8 == 0) taken[w] += product_at(w) < 56 ? 4 : 2;      // fragment reads: a pair of V^T, at the end of K
             if (BF16 && w < 4) taken[w] += 1;                                         // direct loads
-            if (w >= 60) taken[w] += w < 64 ? w % 2 == 0 : 1;                        // bases, V addresses
+            if (w >= W - 12) taken[w] += w < W - 8 ? w % 2 == 0 : 1;                 // bases, V addresses
         }
-        return spread<72>(cost, taken);
+        return spread<W>(cost, taken);
     }
 };
 
@@ -1413,13 +1462,13 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
     constexpr unsigned VB = kWideBuffers * G::kTile;   // V buffers follow the K buffers
     const unsigned lds0 = (unsigned)(size_t)lds;
     const int g = lane >> 4;
-    // A operand of the row sums: binary16 ones in its first row, zeros in the others (all ones: +0.7 %, the zeros switch nothing)
-    const unsigned one = (lane & 15) != 0 ? 0u : 0x3c003c00u;
-    u4 ones = {one, one, one, one};
-    asm volatile("" : "+a"(ones));
+    // A operand of the row sums: binary16 ones in its first row or two, zeros in the others (all ones: +0.7 %, the zeros switch nothing)
+    const unsigned one = (lane & 15) > (P::SPARSE ? 1 : 0) ? 0u : kOnes;
+    SparseOnes ones = sparse_ones(lane, one);
+    asm volatile("" : "+a"(ones.one));
     f4 A[4][QT];        // S^T of the tile one ahead: block (kb, qt) = keys 16kb.. x query rows 16qt..
     float x[16 * QT];   // score*c - M of the current tile, index 16*qt + 4*kb + r
-    u4 pf[2][QT];       // its probabilities as B operands: pf[kh][qt] = keys 32kh..32kh+31
+    Probabilities<P::SPARSE, QT> pf;
     u4 vreg[NL];        // bfloat16 V chunks in flight (BF16 only)
     float lim[QT], mx[QT];
 #pragma unroll
@@ -1490,10 +1539,11 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
         else wide_s<BF16>(A[m % 4][qt], a, st.qf[m / 4][qt]);
     };
     auto o_mfma = [&](int m, int qt, const u4& a) {
-        wide_o(st.o[m % DB][qt], a, pf[m / DB][qt]);
+        wide_o(st.o[m % DB][qt], a, pf.part(m / DB, qt));
     };
-    auto sum_mfma = [&](int kh, int qt) {
-        wide_sum(st.L[qt], ones, pf[kh][qt]);
+    auto sum_mfma = [&](int k) {      // the k-th row sum of a tile
+        if constexpr (P::SPARSE) wide_sparse_sum(st.L[k], ones, pf.v[k]);
+        else wide_sum(st.L[k % QT], ones.one, pf.part(k / QT, k % QT));
     };
     // Masks, maxima, shifted scores and raises as in scan_tiles.
     const int all_see = CAUSAL ? (qw0 < N - 1 ? qw0 : N - 1) : N - 1;
@@ -1537,7 +1587,7 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
             t = quad_max(t);
             const bool up = t > lim[qt];
             const float Mnew = up ? t * c : st.M[qt];
-            const bool fresh = quad_sum(st.L[qt][0]) == 0.f;
+            const bool fresh = quad_sum(st.L[qt][0] + st.L[qt][1]) == 0.f;
             const float alpha = up && !fresh ? fast_exp2(st.M[qt] - Mnew) : 1.0f;
             st.M[qt] = Mnew;
             st.L[qt] *= alpha;
@@ -1555,16 +1605,13 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
     float e[32][2];
     auto exp_op = [&](int u, int h) { e[u][h] = fast_exp2(x[16 * (u / 4 % 4) + 4 * (2 * (u / 16) + u % 4 / 2) + 2 * (u % 2) + h]); };
     auto convert_op = [&](int u) {
-        pf[u / 16][u / 4 % 4][u % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u][0], e[u][1]}, h2));
+        pf.set(u / 16, u / 4 % 4, u % 4, __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u][0], e[u][1]}, h2)));
     };
     // step n of a pair: its two exponentials, and the convert of the pair before
     auto op_a = [&](int n) {
         const int u = n / 3, k = n % 3;
         if (k < 2) exp_op(u, k);
         else if (u > 0) convert_op(u - 1);
-    };
-    auto pin_p = [&]() {
-        asm volatile("" : "+v"(pf[0][0]), "+v"(pf[0][1]), "+v"(pf[0][2]), "+v"(pf[0][3]), "+v"(pf[1][0]), "+v"(pf[1][1]), "+v"(pf[1][2]), "+v"(pf[1][3]));
     };
     wide_guard_o(st);
 
@@ -1629,7 +1676,7 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
     auto turn = [&]() { ring = (unsigned)__builtin_amdgcn_readfirstlane((ring + G::kTile) & 3 * G::kTile); };
     static constexpr auto plan_a = P::first_product();
     static constexpr auto plan_b = P::second_product();
-    static_assert(plan_b.first[36] > P::OX, "the second half of the second product uses the last probabilities");
+    static_assert(plan_b.first[P::HALF] > P::OX, "the second half of the second product uses the last probabilities");
     // (assembly: left to itself the compiler collects these additions behind the loop's branch, where nothing hides them)
     auto move = [](unsigned& at, int by) { asm volatile("v_add_u32 %0, %1, %0" : "+v"(at) : "s"(by)); };
     auto iteration = [&]() -> unsigned long long {
@@ -1660,10 +1707,11 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
             });
         }
         // (the probabilities pass through the statement, or the compiler moves the exponentials behind the barrier)
-        pin_p();
+        pf.pin();
         if constexpr (BF16) landed_barrier<0>();
         else landed_barrier<8>();
         kv0 += kv_step;
+        asm volatile("" : "+s"(kv0));
         mask();
         if constexpr (BF16) {      // (the V registers have landed: the compiler is told so here, see scan_tiles)
 #pragma unroll
@@ -1689,9 +1737,9 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
                 need |= __builtin_amdgcn_ballot_w64(!(mx[n - P::OQ] <= lim[n - P::OQ]));
             } else shift_score(n - P::OS);
         };
-        static_for<72>([&](auto wc) {
-            constexpr int w = decltype(wc)::value, t = w - w / 9, q = t / QT, m = q ^ 1;
-            if constexpr (w % 9 == 8) sum_mfma((t - 1) / 32, (t - 1) / 8 % 4);
+        static_for<P::W>([&](auto wc) {
+            constexpr int w = decltype(wc)::value, t = P::product_at(w), q = t / QT, m = q ^ 1;
+            if constexpr (P::sum_at(w)) sum_mfma(w - t);
             else {
                 if constexpr (t % 8 == 0) {
                     if constexpr (q + LA < NB) { av[q + LA] = v_read(q + LA); av[q + LA + 1] = v_read(q + LA + 1); }
@@ -1706,10 +1754,10 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
 #pragma unroll
                 for (int l = 0; l < NL; ++l) vreg[l] = *(Global16B)(base_v + off[l & 1] + 1024 * l);
             }
-            if constexpr (w >= 64) move(rv[w - 64], dva);
-            if constexpr (w == 58) turn();
-            if constexpr (w == 60) base_k += move_k;
-            if constexpr (w == 62) base_v += move_v;
+            if constexpr (w >= P::W - 8) move(rv[w - (P::W - 8)], dva);
+            if constexpr (w == P::W - 14) { turn(); asm volatile("" : "+s"(ring)); }
+            if constexpr (w == P::W - 12) base_k += move_k;
+            if constexpr (w == P::W - 10) base_v += move_v;
             __builtin_amdgcn_sched_barrier(0);
         });
 #pragma unroll
@@ -1788,7 +1836,7 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
             constexpr int t = decltype(tc)::value, m = t / QT;
             if constexpr (t % QT == 0 && m + LA < NB) av[m + LA] = v_read(m + LA);
             o_mfma(m, t % QT, av[m]);
-            if constexpr (t % 8 == 7) sum_mfma(t / 32, t / 8 % 4);
+            if constexpr (t % 8 == 7 && (!P::SPARSE || t >= 32)) sum_mfma((P::SPARSE ? t - 32 : t) / 8);
             __builtin_amdgcn_sched_barrier(0);
         });
     }
@@ -1814,7 +1862,7 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
 // 32x32x16 MFMAs, transposed like pipelined_range.  A wavefront has its SIMD to itself, so what counts is the instructions it issues per tile
 // and what it waits for in between.  The order is scan_tiles': masked tiles in the pipeline, one barrier between the two products, and
 // behind it the fetches of V(i+1) and K(i+3), which then have a whole iteration to land; fragments in pairs with one wait each; the
-// maximum per lane on raw scores, against a limit.  d = 64: 243 instructions per tile against pipelined_range's 276, of 20 and 16 MFMAs.
+// maximum per lane on raw scores, against a limit.  d = 64: 239 instructions per tile against pipelined_range's 246, of 18 MFMAs each.
 // What it saves are the odd and masked tiles taken one at a time, with nothing in flight, before or after the halves, about 2 us of a
 // launch (figures at launch_halves); per tile of a long scan it is 3 to 4 % slower.  The row sums' products moved into the first product,
 // or a quarter of the exponentials into the second, were 1 to 2 % slower yet.
@@ -1837,17 +1885,12 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
     const int g = lane >> 5;
     const int count = (nkv + 1) / 2;          // tiles of run 0; run 1 has as many or one less
     const int mine = run == 0 ? count : nkv - count < 1 ? 1 : nkv - count;      // (a run of no tile computes on a stand-in, see the end)
-    const u4 ones = {0x3c003c00u, 0x3c003c00u, 0x3c003c00u, 0x3c003c00u};
     const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     f16v A[2];          // S^T of the tile one ahead: block b = keys 32b..32b+31 of the tile
-    // Row sum of the rounded probabilities: at d = 64 a product with ones (in every element of L), at d = 128, where the matrix pipe
-    // is the busier one, two fused multiply-adds per pair (this lane's keys, in two partial sums).
-    constexpr bool kSumMfma = D == 64;
-    f16v L = zero;
-    float L_lo = 0.f, L_hi = 0.f;
-    const _Float16 one = opaque_one();
+    f16v sums = zero;   // row sum of the rounded probabilities, see sparse_sum_32
+    const SparseOnes ones = sparse_ones(lane, (lane & 3) < 2 ? kOnes : 0u);
     float x[32];        // score*c - M of the current tile, index 16*b + r
-    u4 pf[4];           // its probabilities as B operands
+    u8 pf[2];           // its probabilities as B operands, two in each
     u4 vreg[RL];        // bfloat16 V chunks in flight (BF16 only), run r in vreg[r * NL ...]
     float lim = -INFINITY, mx;
 
@@ -1927,12 +1970,9 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
     };
     auto s_mfma = [&](int m, u4 a, bool first) { A[m & 1] = mfma_16bit<BF16>(a, st.qf[m / 2], first ? zero : A[m & 1]); };
     auto o_mfma = [&](int m, s8 a) {
-        st.o[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, pf[m / DB]), st.o[m % DB], 0, 0, 0);
+        st.o[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, half_of(pf[m / DB / 2], m / DB & 1)), st.o[m % DB], 0, 0, 0);
     };
-    auto sum_mfma = [&](int ks) {
-        if constexpr (kSumMfma) L = mfma_16bit<false>(ones, pf[ks], L);
-    };
-    auto sum_pair = [&](int u) { add_pair(L_lo, L_hi, __builtin_bit_cast(h2, (unsigned)pf[u / 4][u % 4]), one); };
+    auto sum_mfma = [&](int k) { sums = sparse_sum_32(ones, pf[k], sums); };      // keys 32k.. of the tile
     const int all_see = CAUSAL ? (qw0 < N - 1 ? qw0 : N - 1) : N - 1;      // last key visible to every row of the wavefront
     int kv0 = tile_of(run, 0) * kTileKV;                                   // first key of the tile in A
     auto mask = [&]() {
@@ -1958,10 +1998,7 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
         const float Mnew = up ? t * c : st.M;
         const float alpha = up && !fresh ? fast_exp2(st.M - Mnew) : 1.0f;
         st.M = Mnew;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) L[r] *= alpha;
-        L_lo *= alpha;
-        L_hi *= alpha;
+        sums *= alpha;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1974,9 +2011,9 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
     auto op_a = [&](int n) {      // the two exponentials of pair n / 3, the convert of the one before
         const int u = n / 3, k = n % 3;
         if (k < 2) e[u][k] = fast_exp2(x[2 * u + k]);
-        else if (u > 0) pf[(u - 1) / 4][(u - 1) % 4] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u - 1][0], e[u - 1][1]}, h2));
+        else if (u > 0) pf[(u - 1) / 8][(u - 1) % 8] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u - 1][0], e[u - 1][1]}, h2));
     };
-    auto last_convert = [&]() { pf[3][3] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[15][0], e[15][1]}, h2)); };
+    auto last_convert = [&]() { pf[1][7] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[15][0], e[15][1]}, h2)); };
     constexpr int OA = 48;
 
     // ---------------------------------------------------------------- prologue: K(0..1) and V(0) on their way, S(0)
@@ -2048,7 +2085,7 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
             }
             last_convert();
         }
-        asm volatile("" : "+v"(pf[0]), "+v"(pf[1]), "+v"(pf[2]), "+v"(pf[3]));
+        asm volatile("" : "+v"(pf[0]), "+v"(pf[1]));
         landed_barrier<0>();
         s8 av[NB];
 #pragma unroll
@@ -2067,7 +2104,7 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
         const int flip = i & 1 ? G::kTile : -G::kTile;      // K(i+2) is in buffer i&1, V(i+1) in buffer (i+1)&1
         bool need = false;
         constexpr int OC = BF16 ? 3 * CW : 0;            // conversions count as three
-        constexpr int OM = 16 + OC, OB = OM + 32 + (kSumMfma ? 0 : 16);
+        constexpr int OM = 16 + OC, OB = OM + 32;
         constexpr int T0 = (OM * NB + OB - 1) / OB;      // first MFMA after the conversions
         constexpr int TL = (BF16 ? 1 : 2) * RL;          // direct loads
         auto op_b = [&](int n) {
@@ -2078,10 +2115,8 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
                     const int w = n * CW / OM;
                     if (w != (n + 1) * CW / OM) convert_word(w, vdst);
                 }
-            } else if (n < OM + 32) {
-                shift_score(n - OM);
             } else {
-                sum_pair(n - OM - 32);
+                shift_score(n - OM);
             }
         };
 #pragma unroll
@@ -2091,7 +2126,7 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
             }
             if (BF16 && t == T0) v_to_regs(fv);
             o_mfma(t ^ 1, av[t ^ 1]);
-            if (t % DB == DB - 1) sum_mfma(t / DB);
+            if (t % (NB / 4) == NB / 4 - 1 && t < NB / 2) sum_mfma(t / (NB / 4));
 #pragma unroll
             for (int li = t * TL / NB; li < (t + 1) * TL / NB; ++li) {      // V first because it is needed first
                 if (!BF16 && li < RL) load(fv, li, vdst);
@@ -2143,10 +2178,6 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
 #pragma unroll
     for (int n = 0; n < OA; ++n) op_a(n);
     last_convert();
-    if constexpr (!kSumMfma) {
-#pragma unroll
-        for (int u = 0; u < 16; ++u) sum_pair(u);
-    }
     landed_barrier<0>();
     if (mine < count) fetch_only(mine - 1);
     {
@@ -2157,7 +2188,7 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
         for (int t = 0; t < NB; ++t) {
             if (t + LA < NB) av[t + LA] = v_read(t + LA);
             o_mfma(t, av[t]);
-            if (t % DB == DB - 1) sum_mfma(t / DB);
+            if (t % (NB / 2) == NB / 2 - 1) sum_mfma(t / (NB / 2));
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -2167,7 +2198,7 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
         if (i + 1 < count) fetch_only(i);
     }
     __syncthreads();   // all reads of the last tile are done before anything refills the buffers
-    st.L = kSumMfma ? 0.5f * L[0] : L_lo + L_hi;     // (both lanes of a pair hold L, the row's whole sum)
+    st.L = 0.5f * (sums[0] + sums[1]);       // (both lanes of a pair hold the row's whole sum)
     if (lim == -INFINITY) st.M = -INFINITY;      // nothing was seen: weight 0 in the merge
     if (run == 1 && nkv == 1) {             // a run of no tile
         st.M = -INFINITY;
@@ -2513,7 +2544,7 @@ __device__ __forceinline__ void process_q_tile_narrow(const Params& p, const Nar
     // ---- epilogue: O_i = acc / l  (the division Alg. 1 leaves implicit; Eq. 1 fixes it)
     float inv[QT];
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) inv[qt] = 1.0f / (QT == 4 ? quad_sum(st.L[qt][0]) : st.L[qt][0]);
+    for (int qt = 0; qt < QT; ++qt) inv[qt] = 1.0f / (QT == 4 ? quad_sum(st.L[qt][0] + st.L[qt][1]) : st.L[qt][0] + st.L[qt][1]);
     if (p.stream_o) {
         // (the scan ended with a barrier and nothing in flight: the K/V buffers serve as staging area)
         LDS_PTR(char) stage = lds + wave * 4096;
@@ -2613,10 +2644,20 @@ __global__ void clear_tickets_kernel(int set) {
     if (threadIdx.x < kDomains) g_domain_tickets[set][threadIdx.x] = 0u;
 }
 
+// The lane index, made where it is used and unknown to the compiler: what derives from it is not kept in registers across the loops.
+__device__ __forceinline__ int lane_now() {
+    unsigned all = ~0u;
+    asm volatile("" : "+s"(all));
+    return (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+}
+
 // Called by every workgroup of `domain` the same number of times; `slots` workgroups take part.
-__device__ __forceinline__ void domain_sync(int set, int domain, int slots) {
+template <bool TIGHT>
+__device__ __forceinline__ void domain_sync(int set, int domain, int slots, int wave) {
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (wave == 0 && lane_now() == 0) {
+        // (TIGHT: made unknown here, or the division's reciprocal is kept in a vector register over the whole kernel, and d = 64 has none to spare)
+        if constexpr (TIGHT) asm volatile("" : "+s"(slots));
         unsigned* t = &g_domain_tickets[set][domain];
         const unsigned mine = __hip_atomic_fetch_add(t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const unsigned target = (mine / (unsigned)slots + 1u) * (unsigned)slots;
@@ -2633,7 +2674,6 @@ __device__ __forceinline__ void domain_sync(int set, int domain, int slots) {
 template <bool CAUSAL, bool LATE, bool TURNS, typename TILE>
 __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
     const Schedule& s = p.sched;
-    const int lane0 = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wg = CAUSAL && LATE ? workgroup_of_block(s, (int)blockIdx.x) : (int)blockIdx.x;      // (LATE: 128-row tiles and shorter)
     int local = 0;           // query tiles this workgroup has processed
@@ -2643,23 +2683,19 @@ __device__ __forceinline__ void for_each_q_tile(const Params& p, TILE&& tile) {
             const int nkv = visible_kv_tiles(s, w.tile, p.N, CAUSAL);
             const int j0 = w.backward ? nkv - 1 : 0;
             const int step = w.backward ? -1 : 1;
-            if (p.trace && threadIdx.x == 0) {
+            if (p.trace && wave == 0 && lane_now() == 0) {
                 int32_t* rec = p.trace + ((size_t)wg * p.max_local + local) * 4;
                 rec[0] = w.head; rec[1] = w.tile; rec[2] = j0; rec[3] = j0 + (nkv - 1) * step;
             }
-            // The per-lane address tables are rebuilt for every query tile from a lane index the
-            // compiler cannot see through, so that they are not kept in registers across the loops.
-            int lane = lane0;
-            asm volatile("" : "+v"(lane));
-            tile(w, j0, step, nkv, wave, lane);
+            tile(w, j0, step, nkv, wave, lane_now());
             ++local;
         }
         // Every workgroup of the domain comes here once per head, also those that sat rounds out.
         // (With the align_rounds variant also once per round: measured, it changes neither the L2 traffic
         // nor the time of the kernel with 64 rows per wavefront, whose workgroups stay in step by themselves.)
-        if (w.sync_after) domain_sync(p.ticket_set, (int)blockIdx.x % kDomains, s.slots);
+        if (w.sync_after) domain_sync<LATE>(p.ticket_set, (int)blockIdx.x % kDomains, s.slots, wave);
     }
-    if (p.trace_count && threadIdx.x == 0) p.trace_count[wg] = local;
+    if (p.trace_count && wave == 0 && lane_now() == 0) p.trace_count[wg] = local;
 }
 
 template <int D, bool BF16, bool CAUSAL, int NH, bool HALVES = false, int SPLIT = kSplitLong>
