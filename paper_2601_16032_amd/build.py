@@ -48,6 +48,15 @@ def check_wide_kernels(resources: dict) -> None:
         raise RuntimeError(f"kernels with 64 rows per wavefront must not use scratch memory (bytes per lane): {bad}")
 
 
+def check_scratch(resources: dict) -> None:
+    """No attention kernel uses scratch memory: what spills is stored and loaded per query tile at best, a tenth of a short launch's time.
+    Refuse a build in which one does, or in which there is nothing to look at."""
+    kernels = {k: v for k, v in resources.items() if "attn_fwd_" in k}
+    bad = {k: v.get("ScratchSize", -1) for k, v in kernels.items() if v.get("ScratchSize", -1) != 0}
+    if bad or not kernels:
+        raise RuntimeError(f"attention kernels must not use scratch memory (bytes per lane): {bad or 'no kernels found'}")
+
+
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     for source, target in (("attn_fwd.hip", LIB_PATH), ("mfma_probe.hip", PROBE_LIB_PATH)):
@@ -58,7 +67,9 @@ def build(verbose: bool = False) -> str:
             raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
         if source == "attn_fwd.hip":
             try:
-                check_wide_kernels(kernel_resources(res.stderr))
+                resources = kernel_resources(res.stderr)
+                check_wide_kernels(resources)
+                check_scratch(resources)
             except RuntimeError:
                 os.remove(target)      # never leave a library behind that must not be used
                 raise

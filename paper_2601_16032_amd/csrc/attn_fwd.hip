@@ -333,6 +333,48 @@ __device__ __forceinline__ u4 half_of(const u8& p, int hi) {
     return hi ? __builtin_shufflevector(p, p, 4, 5, 6, 7) : __builtin_shufflevector(p, p, 0, 1, 2, 3);
 }
 
+// Adds the two binary16 values of `ph` to two float partial sums (one mixed-precision FMA each: exact, and cheaper in
+// the instruction stream than the two-element dot product).  `one` is binary16 1.0 held in a register the compiler
+// cannot see through (opaque_one()): the widened products then become v_fma_mix_f32.  Written in C and not as inline
+// assembly because the compiler separates dependent assembly statements that have nothing in between by a no-op each.
+__device__ __forceinline__ _Float16 opaque_one() {
+    _Float16 one = (_Float16)1.0f;
+    asm volatile("" : "+v"(one));
+    return one;
+}
+__device__ __forceinline__ void add_pair(float& sum_lo, float& sum_hi, h2 ph, _Float16 one) {
+    sum_lo = __builtin_fmaf((float)ph[0], (float)one, sum_lo);
+    sum_hi = __builtin_fmaf((float)ph[1], (float)one, sum_hi);
+}
+
+// A wavefront's running row sums in pipelined_range.  of_lane(): a lane's part of its row's sum, which the lanes that share the row add up to.
+// Sparse products take 21 registers and two places among the MFMAs of a tile, additions three registers and 32 places of the vector unit's.  Products
+// on 64-row tiles (see sparse_sum_32); on 128-row tiles where they gain and fit: d = 128, binary16, causal, from additions -0.3 to -1.2 % (1 x 20000
+// 240.7 -> 237.7 us).  Additions elsewhere: d = 128 without a mask, where the matrix pipe is the busier one, products take up to 1.6 % more (1 x 32768
+// 534 -> 543 us), and with bfloat16 they spill; d = 64 has 168 registers, and 40 to 60 bytes of scratch per lane cost short scans 1 to 11 % (128 x 256
+// 7.6 -> 8.5 us, 64 x 512 9.9 -> 10.6).  (With 256 registers products take up to 5 % less there, 16 x 2000 25.9 -> 25.0 us, but two workgroups
+// to a compute unit in place of three slow down launches on three streams: 16 x 2000 18.7 -> 20.0 us each, bfloat16 19.6 -> 21.4.)
+template <bool SPARSE>
+struct RowSums {
+    SparseOnes ones;
+    f16v sum;
+    __device__ __forceinline__ explicit RowSums(int lane) : ones(sparse_ones(lane, (lane & 3) < 2 ? kOnes : 0u)) {
+        sum = f16v{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void add(const u8& p) { sum = sparse_sum_32(ones, p, sum); }
+    __device__ __forceinline__ void scale(float alpha) { sum *= alpha; }
+    __device__ __forceinline__ float of_lane() const { return 0.5f * (sum[0] + sum[1]); }      // (both lanes of a pair hold the row's sum)
+};
+template <>
+struct RowSums<false> {
+    _Float16 one = opaque_one();
+    float lo = 0.f, hi = 0.f;
+    __device__ __forceinline__ explicit RowSums(int) {}
+    __device__ __forceinline__ void add(h2 p) { add_pair(lo, hi, p, one); }
+    __device__ __forceinline__ void scale(float alpha) { lo *= alpha; hi *= alpha; }
+    __device__ __forceinline__ float of_lane() const { return lo + hi; }
+};
+
 // Per-wavefront state of one query tile that the K/V loop carries along.
 template <int D>
 struct TileState {
@@ -534,7 +576,9 @@ __device__ __forceinline__ void general_range(TileState<D>& st, const LaneMap<D>
 // the length of one wavefront's walk is what the launch takes.  All four wavefronts fetch the tiles of both
 // runs (a second set of K/V buffers behind the first; for bfloat16 inputs a second set of V registers);
 // this wavefront computes on run `run`.
-template <int D, bool BF16, bool HALVES = false>
+//
+// SPARSE: row sums as sparse products instead of additions, see RowSums.
+template <int D, bool BF16, bool HALVES = false, bool SPARSE = HALVES>
 __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<D>& lm, const char* Kh, const char* Vh,
                                                 float c, int j_first, int step, int count, int lane, LDS_PTR(char) lds,
                                                 int run = 0) {
@@ -549,11 +593,10 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
     if (count <= 0) return;
     const unsigned lds0 = (unsigned)(size_t)lds;
     const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    f16v sums = zero;   // running sum of the row from here on, see sparse_sum_32; folded into st.L
-    const SparseOnes ones = sparse_ones(lane, (lane & 3) < 2 ? kOnes : 0u);
+    RowSums<SPARSE> sums(lane);      // of the rounded probabilities, the values the second product uses
     f16v A[2];          // S^T of the tile one ahead: block b = keys 32b..32b+31 of the tile
     float x[32];        // score*c - M of the current tile, index 16*b + r
-    u8 pf[2];           // its probabilities as B operands, two in each
+    Probabilities<SPARSE, 2> pf;      // its probabilities as B operands, 16 keys each: part(ks & 1, ks / 2)
     u4 vreg[(HALVES ? 2 : 1) * NL];   // bfloat16 V chunks in flight (BF16 only), run r in vreg[r * NL ...]
 
     // LDS read addresses: K of the tile one ahead, V of the current tile
@@ -590,7 +633,7 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
         const float alpha = (Mnew == -INFINITY) ? 1.0f : fast_exp2(st.M - Mnew);
         st.M = Mnew;
         st.L *= alpha;
-        sums *= alpha;
+        sums.scale(alpha);
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -606,7 +649,9 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
         }
         if (u >= 1 && u <= 16) {
             const int v = u - 1;
-            pf[v / 8][v % 8] = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e0[v], e1[v]}, h2));
+            const h2 ph = __builtin_convertvector(f2{e0[v], e1[v]}, h2);
+            if constexpr (!SPARSE) sums.add(ph);
+            pf.set(v / 4 & 1, v / 8, v % 4, __builtin_bit_cast(unsigned, ph));
         }
     };
 
@@ -710,9 +755,9 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
 #pragma unroll
         for (int idx = 0; idx < H; ++idx) {
             av[idx + 2] = v_read(idx + 2);
-            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, half_of(pf[idx / DB / 2], idx / DB & 1)),
+            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, pf.part(idx / DB & 1, idx / DB / 2)),
                                                                     st.o[idx % DB], 0, 0, 0);
-            if (idx % (H / 2) == H / 2 - 1) sums = sparse_sum_32(ones, pf[idx / (H / 2)], sums);
+            if constexpr (SPARSE) { if (idx % (H / 2) == H / 2 - 1) sums.add(pf.v[idx / (H / 2)]); }
             if (idx >= MS) {
 #pragma unroll
                 for (int q = 0; q < MPS; ++q) {
@@ -736,7 +781,7 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
 #pragma unroll
         for (int idx = H; idx < NB; ++idx) {
             if (idx + 2 < NB) av[idx + 2] = v_read(idx + 2);
-            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, half_of(pf[idx / DB / 2], idx / DB & 1)),
+            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, pf.part(idx / DB & 1, idx / DB / 2)),
                                                                     st.o[idx % DB], 0, 0, 0);
 #pragma unroll
             for (int q = 0; q < FPS; ++q) {
@@ -803,13 +848,13 @@ __device__ __forceinline__ void pipelined_range(TileState<D>& st, const LaneMap<
 #pragma unroll
         for (int idx = 0; idx < NB; ++idx) {
             if (idx + 2 < NB) av[idx + 2] = v_read(idx + 2);
-            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, half_of(pf[idx / DB / 2], idx / DB & 1)),
+            st.o[idx % DB] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, av[idx]), __builtin_bit_cast(h8, pf.part(idx / DB & 1, idx / DB / 2)),
                                                                     st.o[idx % DB], 0, 0, 0);
-            if (idx % (NB / 2) == NB / 2 - 1) sums = sparse_sum_32(ones, pf[idx / (NB / 2)], sums);
+            if constexpr (SPARSE) { if (idx % (NB / 2) == NB / 2 - 1) sums.add(pf.v[idx / (NB / 2)]); }
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    st.L += 0.5f * (sums[0] + sums[1]);      // (both lanes of a pair hold the row's sum)
+    st.L += sums.of_lane();
     __syncthreads();   // all reads of the last tile are done before anything refills the buffers
 }
 
@@ -2327,7 +2372,9 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
     const int jm = CAUSAL ? (t * TQ) / kTileKV : ((N % kTileKV) ? kv_tiles - 1 : kv_tiles);
     const int n_masked = nkv > jm ? nkv - jm : 0;
     const int n_plain = nkv - n_masked;
-    auto plain = [&](int j_first) { pipelined_range<D, BF16>(st, lm, Kh, Vh, c, j_first, step, n_plain, lane, lds); };
+    auto plain = [&](int j_first) {
+        pipelined_range<D, BF16, false, D == 128 && CAUSAL && !BF16>(st, lm, Kh, Vh, c, j_first, step, n_plain, lane, lds);      // see RowSums
+    };
     auto masked = [&](int j_first) {
         general_range<D, BF16, CAUSAL, true>(st, lm, Kh, Vh, N, c, j_first, step, n_masked, qw0, qrow, lane, lds);
     };

@@ -1,4 +1,9 @@
 """Shared helpers for the tests (comparison metrics and launch facts only; no attention arithmetic)."""
+import glob
+import os
+import shutil
+import subprocess
+
 import numpy as np
 
 MAX_ABS_TOL = 2e-3     # stated tolerance of the benchmark definition, fp16/bf16 inputs
@@ -58,3 +63,19 @@ SHARED_LENGTHS = [1, 63, 64, 65, 128, 129, 200, 321, 577]
 # (heads, rows) whose causal launch, left open, reaches the build without precedence at both head dimensions: all 49 workgroups of an XCD at
 # once, the last tile of a head one of 65 rows.  (With 264 heads the lengths above have it from two tiles per workgroup.)
 SHARED_EVEN = (56, 833)
+
+
+def llvm_tool(name, *args):
+    """What one of the LLVM tools that come with the compiler of the library prints."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    tool = subprocess.run([hipcc, f"-print-prog-name={name}"], check=True, capture_output=True, text=True).stdout.strip()
+    return subprocess.run([tool, *args], check=True, capture_output=True, text=True).stdout
+
+
+def device_code(into):
+    """The code object inside the built library, unpacked into the directory `into`."""
+    from paper_2601_16032_amd import build as hip_build
+    lib = shutil.copy(hip_build.LIB_PATH, os.path.join(into, "lib.so"))
+    llvm_tool("llvm-objdump", "--offloading", lib)
+    path, = glob.glob(lib + "*gfx950")
+    return path
