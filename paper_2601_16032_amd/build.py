@@ -39,13 +39,16 @@ def check_wide_kernels(resources: dict) -> None:
     """The kernels with 64 rows per wavefront (fourth template argument 2) issue their MFMAs as inline assembly with
     hand-placed wait states.  That is only sound while the compiler keeps every accumulator where the source puts
     it: a spill would copy registers that an MFMA in flight is still writing.  Refuse a build in which one of them
-    needs scratch memory."""
+    needs scratch memory, or spills into accumulation registers, which takes none."""
     wide = {k: v for k, v in resources.items() if "attn_fwd_kernel" in k and "ELi2ELb" in k}
     if len(wide) != 4:
         raise RuntimeError(f"expected the resource usage of 4 kernels with 64 rows per wavefront, found {sorted(wide)}")
     bad = {k: v["ScratchSize"] for k, v in wide.items() if v.get("ScratchSize", -1) != 0}
     if bad:
         raise RuntimeError(f"kernels with 64 rows per wavefront must not use scratch memory (bytes per lane): {bad}")
+    bad = {k: v["VGPRs Spill"] for k, v in wide.items() if v.get("VGPRs Spill", 0) != 0}
+    if bad:
+        raise RuntimeError(f"kernels with 64 rows per wavefront must not spill vector registers: {bad}")
 
 
 def check_scratch(resources: dict) -> None:

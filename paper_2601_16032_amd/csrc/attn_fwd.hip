@@ -1478,6 +1478,9 @@ struct WidePlan {
     // stand in the second half; bfloat16 has no registers left for them (0 to +10 %) and sums every 32 keys.
     static constexpr bool SPARSE = !BF16;
     static constexpr int SUMS = SPARSE ? 4 : 8, W = 64 + SUMS, HALF = SPARSE ? 32 : 36;
+    // The sum of this lane's row from its accumulators: sparse products leave it in two, plain ones in the first alone (with the second, a zero, added
+    // there too the bfloat16 kernels needed three registers more than they have).
+    static __device__ __forceinline__ float row_sum(const f4& L) { return quad_sum(SPARSE ? L[0] + L[1] : L[0]); }
     static constexpr bool sum_at(int w) { return SPARSE ? w >= HALF && w % 9 == 4 : w % 9 == 8; }
     static constexpr int product_at(int w) {
         int t = 0;
@@ -1632,7 +1635,7 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
             t = quad_max(t);
             const bool up = t > lim[qt];
             const float Mnew = up ? t * c : st.M[qt];
-            const bool fresh = quad_sum(st.L[qt][0] + st.L[qt][1]) == 0.f;
+            const bool fresh = P::row_sum(st.L[qt]) == 0.f;
             const float alpha = up && !fresh ? fast_exp2(st.M[qt] - Mnew) : 1.0f;
             st.M[qt] = Mnew;
             st.L[qt] *= alpha;
@@ -2591,7 +2594,7 @@ __device__ __forceinline__ void process_q_tile_narrow(const Params& p, const Nar
     // ---- epilogue: O_i = acc / l  (the division Alg. 1 leaves implicit; Eq. 1 fixes it)
     float inv[QT];
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) inv[qt] = 1.0f / (QT == 4 ? quad_sum(st.L[qt][0] + st.L[qt][1]) : st.L[qt][0] + st.L[qt][1]);
+    for (int qt = 0; qt < QT; ++qt) inv[qt] = 1.0f / (QT == 4 ? WidePlan<BF16>::row_sum(st.L[qt]) : st.L[qt][0] + st.L[qt][1]);
     if (p.stream_o) {
         // (the scan ended with a barrier and nothing in flight: the K/V buffers serve as staging area)
         LDS_PTR(char) stage = lds + wave * 4096;
