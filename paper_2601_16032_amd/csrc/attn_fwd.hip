@@ -1378,7 +1378,8 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
 // costs a copy.  The compiler does not see them as MFMAs and inserts no wait states; wide_settle_*() stands wherever vector
 // instructions read what the last few MFMAs may still be writing (4 passes + 3 wait states), wide_guard() where MFMAs read
 // accumulators that vector instructions have just written.  In the loop the distance is kept by the order: the first maximum comes
-// behind the exponentials of the second product, ten MFMAs after the last one that wrote a score.
+// behind the exponentials of the second product, 23 MFMAs (bfloat16: 33) after the last one that wrote a score.  static_asserts beside the
+// plan and a test that walks the built code hold that.
 constexpr int kWideBuffers = 4;
 constexpr int kWideLdsBytes = 2 * kWideBuffers * Geo<128>::kTile;
 
@@ -1486,6 +1487,12 @@ struct WidePlan {
         int t = 0;
         for (int v = 0; v < w; ++v) t += !sum_at(v);
         return t;
+    }
+    // Sparse sums read all of a row's probabilities, sum k of the others those of 32 keys: the second 32 from k = 4 on.
+    static constexpr bool sums_in_time() {
+        for (int w = 0, k = 0; w < W; ++w)
+            if (sum_at(w) && (SPARSE || k++ >= 4) && w < HALF) return false;
+        return true;
     }
     static constexpr Windows<W> second_product() {
         int cost[OB] = {}, taken[W] = {};
@@ -1724,7 +1731,11 @@ __device__ __forceinline__ void scan_tiles_wide(NarrowState<128, 4>& st, const N
     auto turn = [&]() { ring = (unsigned)__builtin_amdgcn_readfirstlane((ring + G::kTile) & 3 * G::kTile); };
     static constexpr auto plan_a = P::first_product();
     static constexpr auto plan_b = P::second_product();
-    static_assert(plan_b.first[P::HALF] > P::OX, "the second half of the second product uses the last probabilities");
+    // What the order has to keep apart, as the compiler adds no wait states.  (Operation n stands behind MFMA w where first[w] <= n < first[w + 1].)
+    static_assert(plan_b.first[8] <= P::OM, "no score is read within eight MFMAs after the one that wrote the last");
+    static_assert(P::OA / 3 > 16, "the first half of the probabilities is complete ahead of the barrier");
+    static_assert(plan_b.first[P::HALF - 1] > P::OX, "an MFMA and more between the last conversion, ahead of operation OX, and the first that reads it");
+    static_assert(P::product_at(P::HALF) == 32 && P::sums_in_time(), "the second half of the probabilities is read from MFMA HALF on");
     // (assembly: left to itself the compiler collects these additions behind the loop's branch, where nothing hides them)
     auto move = [](unsigned& at, int by) { asm volatile("v_add_u32 %0, %1, %0" : "+v"(at) : "s"(by)); };
     auto iteration = [&]() -> unsigned long long {

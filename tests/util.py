@@ -1,6 +1,7 @@
 """Shared helpers for the tests (comparison metrics and launch facts only; no attention arithmetic)."""
 import glob
 import os
+import re
 import shutil
 import subprocess
 
@@ -79,3 +80,28 @@ def device_code(into):
     llvm_tool("llvm-objdump", "--offloading", lib)
     path, = glob.glob(lib + "*gfx950")
     return path
+
+
+def device_listing(into):
+    """The assembly of the built library's kernels."""
+    return llvm_tool("llvm-objdump", "-d", "--mcpu=gfx950", device_code(into)).splitlines()
+
+
+def kernel_bodies(listing):
+    """{kernel: [(instruction, index of the instruction it may branch to, or None)]}, names as in the source."""
+    mangled, kernels = None, {}
+    for line in listing:
+        head = re.match(r"[0-9a-f]+ <(\w+)>:", line)
+        if head:
+            mangled = head.group(1)
+            kernels[mangled] = []
+            continue
+        code = re.match(r"\t(\S.*?)\s*// ([0-9A-F]+): [0-9A-F ]+(?:<\w+\+0x([0-9a-f]+)>)?", line)
+        if code and mangled:
+            kernels[mangled].append((code.group(1), int(code.group(2), 16), code.group(3)))
+    names = subprocess.run(["c++filt", *kernels], check=True, capture_output=True, text=True).stdout.splitlines()
+    out = {}
+    for name, body in zip(names, kernels.values()):
+        at = {address: i for i, (_, address, _) in enumerate(body)}
+        out[name] = [(text, at[body[0][1] + int(to, 16)] if to else None) for text, _, to in body]
+    return out
