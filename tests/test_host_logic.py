@@ -11,7 +11,7 @@ import torch
 
 from oracle import schedule_oracle as so
 from paper_2601_16032_amd import binding, traffic_model
-from tests.util import RESIDENT_PER_XCD, SHARED_EVEN, SHARED_HEADS, SHARED_LENGTHS, oracle_inputs
+from tests.util import RESIDENT_PER_XCD, SHARED_EVEN, SHARED_HEADS, SHARED_LENGTHS, SHARED_ROW_SUMS, oracle_inputs
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -703,3 +703,14 @@ def test_the_lengths_of_the_gpu_tests_reach_every_build_of_the_shared_kernel(ker
             for case in ((577,) + two, (300, -1, 0, 0, 0), (577, 0, 1, 0, 1)):
                 for ca in (0, 1):
                     assert kernel_of([(SHARED_HEADS, case[0], d, ca, bf16) + case[1:]])[0].startswith("shared"), (case, d, bf16, ca)
+
+
+def test_the_row_sums_of_the_shared_kernel_are_those_tested(kernel_of):
+    """test_row_sums.py names its 128-row launches by what runs there: "rows32" (8 heads, persistent) one workgroup to a compute unit, "shared"
+    the other kernel."""
+    for d in (64, 128):
+        for bf16 in (0, 1):
+            for causal in (0, 1):
+                assert set(kernel_of([(8, N, d, causal, bf16, 0, 0, 0, 0) for N in (1, 640)])) == {"alone"}
+                shared = kernel_of([(SHARED_HEADS, N, d, causal, bf16, -1, 0, 0, 0) for N in SHARED_ROW_SUMS])
+                assert all(k.startswith("shared") for k in shared), (d, bf16, causal, shared)

@@ -64,6 +64,8 @@ SHARED_LENGTHS = [1, 63, 64, 65, 128, 129, 200, 321, 577]
 # (heads, rows) whose causal launch, left open, reaches the build without precedence at both head dimensions: all 49 workgroups of an XCD at
 # once, the last tile of a head one of 65 rows.  (With 264 heads the lengths above have it from two tiles per workgroup.)
 SHARED_EVEN = (56, 833)
+# Lengths at which SHARED_HEADS run on that kernel without exception, launched as the library chooses, for its row sums.
+SHARED_ROW_SUMS = [1, 63, 64, 65, 128, 321, 577]
 
 
 def llvm_tool(name, *args):
