@@ -2185,7 +2185,10 @@ __device__ __forceinline__ void scan_halves(TileState<D>& st, const LaneMap<D>& 
             }
             if (BF16 && t == T0) v_to_regs(fv);
             o_mfma(t ^ 1, av[t ^ 1]);
-            if (t % (NB / 4) == NB / 4 - 1 && t < NB / 2) sum_mfma(t / (NB / 4));
+            // Row sums behind the first and the second half: bfloat16 converts in the first, whose places a sum among them lengthens.  d = 64, bfloat16, causal,
+            // plain products for sums / after the first and the second quarter / here: 4 x 3904 27.8, 30.2, 27.2 us, 3 x 2159 17.8, 18.9, 17.4, binary16 23.3,
+            // 23.5, 22.9 and 15.3, 15.4, 15.1; d = 128, 4 x 3000 37.7, 37.3, 37.2.
+            if (t == NB / 2 - 1 || t == 3 * NB / 4 - 1) sum_mfma(t / (NB / 4) - 1);
 #pragma unroll
             for (int li = t * TL / NB; li < (t + 1) * TL / NB; ++li) {      // V first because it is needed first
                 if (!BF16 && li < RL) load(fv, li, vdst);
