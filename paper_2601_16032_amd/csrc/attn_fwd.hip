@@ -1147,9 +1147,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
         pf.set(u / 8, u / 4 % 2, u % 4, __builtin_bit_cast(unsigned, __builtin_convertvector(f2{e[u][0], e[u][1]}, h2)));
     };
     // Row sums of the rounded probabilities, the values the second product uses.
-    auto sum_mfma = [&](int k) {      // behind the k-th quarter of the second product (all probabilities are there from its start)
-        if (k < 2) st.L[k] = sparse_sum(ones, pf.v[k], st.L[k]);
-    };
+    auto sum_mfma = [&](int qt) { st.L[qt] = sparse_sum(ones, pf.v[qt], st.L[qt]); };      // (all probabilities are there from the start of the second product)
     // What runs under the first product, in order: step k of pair u, the convert one pair behind its exponentials.
     constexpr int OA = 48;
     auto op_a = [&](int n) {
@@ -1296,7 +1294,11 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
             if (PAIRS && t % 4 == 0 && q + LA < NB) { av[q + LA] = v_read(q + LA); av[q + LA + 1] = v_read(q + LA + 1); }
             if (BF16 && t == T0) v_to_regs();
             o_mfma(m, t & 1, av[m]);
-            if (t % (TB / 4) == (D == 128 ? 5 : 3)) sum_mfma(t / (TB / 4));
+            // Row sums: behind the first MFMA of each half at d = 64 without a mask (4 x 14836 259.1 us, behind the 4th of the first two quarters 269.9, with
+            // plain products 260.6; 18 x 3260 63.9, 65.5, 64.4; in the mean of 87 bfloat16 launches -1.3 and -1.0 % from plain products), elsewhere early in
+            // the first two quarters (under the mask at d = 64 the compiler spills with later ones).
+            constexpr int S0 = D == 128 ? 5 : CAUSAL ? TB / 4 - 1 : 1, S1 = D == 128 ? TB / 4 + 5 : CAUSAL ? TB / 2 - 1 : TB / 2 + 1;
+            if (t == S0 || t == S1) sum_mfma(t == S1);
             constexpr bool EARLY = D == 128 || !CAUSAL;
             for (int li = EARLY ? t / 4 : t * TL / TB; li < TL && (EARLY ? t % 4 == 1 && li == t / 4 : li < (t + 1) * TL / TB); ++li) {
                 if (li < NV) tile_load_to_lds(dv, lm.fill_src + li * 4096, vdst + li * 4096);
@@ -1344,7 +1346,7 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
             const int m = t / 2;
             if ((t & 1) == 0 && m + LA < NB) av[m + LA] = v_read(m + LA);
             o_mfma(m, t & 1, av[m]);
-            if (t % (TB / 4) == TB / 4 - 1) sum_mfma(t / (TB / 4));
+            if (t == TB / 4 - 1 || t == TB / 2 - 1) sum_mfma(t == TB / 2 - 1);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
