@@ -349,7 +349,8 @@ __device__ __forceinline__ void add_pair(float& sum_lo, float& sum_hi, h2 ph, _F
 
 // A wavefront's running row sums in pipelined_range.  of_lane(): a lane's part of its row's sum, which the lanes that share the row add up to.
 // Sparse products take 21 registers and two places among the MFMAs of a tile, additions three registers and 32 places of the vector unit's.  Products
-// on 64-row tiles (see sparse_sum_32); on 128-row tiles where they gain and fit: d = 128, binary16, causal, from additions -0.3 to -1.2 % (1 x 20000
+// on 64-row tiles (see sparse_sum_32), but for d = 128, bfloat16 in the kernel of full even scans, whose start took 0.25 us more (2 x 128 8.0 -> 8.2, 5 x 256
+// 9.4 -> 9.7 us) and whose tiles only 0 to 1 % less; on 128-row tiles where they gain and fit: d = 128, binary16, causal, from additions -0.3 to -1.2 % (1 x 20000
 // 240.7 -> 237.7 us).  Additions elsewhere: d = 128 without a mask, where the matrix pipe is the busier one, products take up to 1.6 % more (1 x 32768
 // 534 -> 543 us), and with bfloat16 they spill; d = 64 has 168 registers, and 40 to 60 bytes of scratch per lane cost short scans 1 to 11 % (128 x 256
 // 7.6 -> 8.5 us, 64 x 512 9.9 -> 10.6).  (With 256 registers products take up to 5 % less there, 16 x 2000 25.9 -> 25.0 us, but two workgroups
@@ -2401,7 +2402,7 @@ __device__ __forceinline__ void process_q_tile(const Params& p, const LaneMap<D>
         const int half = n_plain / 2;                       // kSplitLong: plain tiles per run
         const int n_left = (n_plain & 1) + n_masked;        // and the tiles left for the tile-at-a-time code
         if constexpr (SPLIT == kSplitEven) {
-            pipelined_range<D, BF16, true>(st, lm, Kh, Vh, c, j0, step, nkv / 2, lane, lds, run);
+            pipelined_range<D, BF16, true, !(BF16 && D == 128)>(st, lm, Kh, Vh, c, j0, step, nkv / 2, lane, lds, run);      // see RowSums
         } else if constexpr (SPLIT == kSplitShort) {
             if (nkv == 1)
                 general_range<D, BF16, CAUSAL, true>(st, lm, Kh, Vh, N, c, j0, step, 1, qw0, qrow, lane, lds, run == 1);
