@@ -2885,10 +2885,11 @@ int launch_128(Params& p, int grid, hipStream_t stream) {
 // taken singly, stay with it.  Measured, pipeline -> scan_halves: 16 x 1000, d = 64: 12.1 -> 10.5 us; 8 x 2048 causal, bf16: 19.1 -> 17.2;
 // 24 x 2600 causal: 35.5 -> 34.3; 2 x 100, d = 128, causal: 9.4 -> 8.1; 5 x 1000, d = 128: 20.0 -> 18.3; 3000 causal, d = 128: 30.8 -> 28.6;
 // but 3 x 5000, d = 128, causal: 47.9 -> 49.6, 3 x 10000: 113.7 -> 115.0, 30000: 289.7 -> 297.1, and between 4096 and 16384 keys it goes either way
-// (2 x 8000, d = 128, causal: 68.9 -> 65.8).  One tile is all masked code, in the smaller kernel: 64 causal: 4.8 us against 4.9.
+// (2 x 8000, d = 128, causal: 68.9 -> 65.8).  One tile is all masked code, in the kernel that starts sooner, long / short: 8 x 64, d
+// = 64 5.6, 5.3 us, bfloat16, causal 5.4, 5.3; d = 128 8.1, 7.7 and 7.9, 7.5.
 template <int D, bool BF16>
 int launch_halves(Params& p, bool causal, int grid, hipStream_t stream) {
-    const bool brief = p.N > kTileKV && p.N <= 64 * kTileKV;
+    const bool brief = p.N <= 64 * kTileKV;
     if (causal) {
         if (brief) return launch<D, BF16, true, 1, true, kSplitShort>(p, grid, stream);
         return launch<D, BF16, true, 1, true, kSplitLong>(p, grid, stream);
