@@ -301,8 +301,8 @@ __device__ __forceinline__ f4 sparse_sum(const SparseOnes& ones, const u8& p, f4
     return __builtin_amdgcn_smfmac_f32_16x16x64_f16(__builtin_bit_cast(h8, ones.one), __builtin_bit_cast(h16, p), acc, ones.pick, 0, 0);
 }
 // The same with 32 columns, second operands in the layout of 32x32x16 and the sum of a column in acc[0] + acc[1] of both lanes that hold it: two per
-// tile in place of two mixed-precision additions per pair, which took a tenth of pipelined_range's issue slots (4 x 4096, d = 64 26.5 -> 25.5 us,
-// 1 x 16384, d = 64, causal 88.1 -> 83.6, 2 x 4096, d = 128 35.8 -> 34.9), or of four plain products (8 x 2048, d = 64, causal 15.1 -> 15.0).  (Half the
+// tile in place of two mixed-precision additions per pair, which took a tenth of pipelined_range's issue slots (4 x 4096, d = 64 26.5 -> 25.4 us,
+// 1 x 16384, d = 64, causal 88.0 -> 83.8, 2 x 4096, d = 128 35.8 -> 35.0), or of four plain products (8 x 2048, d = 64, causal 14.9 -> 14.6).  (Half the
 // time would do with 16 columns and zeros against the others' values, but 0 times an infinity or no number is no number: query rows would mix.)
 __device__ __forceinline__ f16v sparse_sum_32(const SparseOnes& ones, const u8& p, f16v acc) {
     return __builtin_amdgcn_smfmac_f32_32x32x32_f16(__builtin_bit_cast(h8, ones.one), __builtin_bit_cast(h16, p), acc, ones.pick, 0, 0);
@@ -350,8 +350,8 @@ __device__ __forceinline__ void add_pair(float& sum_lo, float& sum_hi, h2 ph, _F
 // A wavefront's running row sums in pipelined_range.  of_lane(): a lane's part of its row's sum, which the lanes that share the row add up to.
 // Sparse products take 21 registers and two places among the MFMAs of a tile, additions three registers and 32 places of the vector unit's.  Products
 // on 64-row tiles (see sparse_sum_32), but for d = 128, bfloat16 in the kernel of full even scans, whose start took 0.25 us more (2 x 128 8.0 -> 8.2, 5 x 256
-// 9.4 -> 9.7 us) and whose tiles only 0 to 1 % less; on 128-row tiles where they gain and fit: d = 128, binary16, causal, from additions -0.3 to -1.2 % (1 x 20000
-// 240.7 -> 237.7 us).  Additions elsewhere: d = 128 without a mask, where the matrix pipe is the busier one, products take up to 1.6 % more (1 x 32768
+// 9.4 -> 9.7 us) and whose tiles only 0 to 1 % less; on 128-row tiles where they gain and fit: d = 128, binary16, causal, from additions -0.3 % in the mean of
+// 51 launches (-1.6 to +1.4 %; 1 x 20000 240.7 -> 237.7 us).  Additions elsewhere: d = 128 without a mask, where the matrix pipe is the busier one, products take up to 1.6 % more (1 x 32768
 // 534 -> 543 us), and with bfloat16 they spill; d = 64 has 168 registers, and 40 to 60 bytes of scratch per lane cost short scans 1 to 11 % (128 x 256
 // 7.6 -> 8.5 us, 64 x 512 9.9 -> 10.6).  (With 256 registers products take up to 5 % less there, 16 x 2000 25.9 -> 25.0 us, but two workgroups
 // to a compute unit in place of three slow down launches on three streams: 16 x 2000 18.7 -> 20.0 us each, bfloat16 19.6 -> 21.4.)
@@ -1011,8 +1011,10 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
     const unsigned lds0 = (unsigned)(size_t)lds;
     const int g = lane >> 4;
     // Row sums: sparse products (their 16 columns are the query rows), in the first two elements of L; the first operand is zero in the other rows,
-    // which switches less.  Plain products before, sparse now: 1 x 131072, d = 64 4319 -> 4230 us, 8 x 32768, d = 64, causal 1061 -> 1043,
-    // 16 x 8192, d = 128, bfloat16, causal 251.1 -> 248.1, 128 x 512, d = 128 20.2 -> 20.0.
+    // which switches less.  From plain products, in the mean of 15 to 73 launches: d = 64 without a mask -0.5 % (bfloat16 -1.2 %), causal -1.0 % (-0.5 %); d =
+    // 128 -1.0 % (0), causal -0.1 % (0); single launches -3 to +6 %, where workgroups come to end together or apart (22 x 7168, d = 64, bfloat16,
+    // causal 172 -> 178 us, 77 x 493, d = 128, bfloat16 37.7 -> 40.3).  8 x 32768, d = 64, causal 1030 -> 1013 us, 1 x 131072 4196 -> 4154, 12 x 5000, bfloat16
+    // 146.4 -> 144.2, 16 x 8192, bfloat16, causal 248.1 -> 249.2, 128 x 512 21.1 both.
     const SparseOnes ones = sparse_ones(lane, (lane & 3) < 2 ? kOnes : 0u);
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
     f4 A[4][2];         // S^T of the tile one ahead: block (kb, qt) = keys 16kb.. x query rows 16qt..
@@ -1360,9 +1362,10 @@ __device__ __forceinline__ void scan_tiles(NarrowState<D>& st, const NarrowMap<D
 // fragment read from LDS feeds four MFMAs instead of two, which halves the operand traffic from LDS and the L2 -> LDS
 // traffic per multiply-add.
 //
-// What bounds it: with live operands the power limit, and the issue of its one wavefront per SIMD, which holds with zeros too: about 3050 cycles
-// per tile for 132 MFMAs of 16 cycles (128 for the products, 4, for bfloat16 8, for the row sums), 64 exponentials, 150 other vector instructions, 48 LDS reads and
-// 8 direct loads.  Both count: less clock goes with less voltage, so a tile in 7 % fewer cycles takes 3.5 % less time at the power limit.  What
+// What bounds it: with live operands the power limit, and the issue of its one wavefront per SIMD, which holds with zeros too.  A launch takes 3170
+// cycles per tile at 1.93 GHz (zeros: 3100 at 2.36) for 132 MFMAs of 16 cycles (128 for the products, 4 for the row sums), 64 exponentials, 149 other
+// vector, 48 LDS and 33 scalar instructions and 8 loads; bfloat16 3450 at 2.06 GHz (3380 at 2.39) for 136 MFMAs, 8 of them for the row sums, 201 other
+// vector and 52 LDS instructions (profiles/wide_kernel_cycles.txt).  Both count: less clock goes with less voltage, so a tile in 7 % fewer cycles takes 3.5 % less time at the power limit.  What
 // that rests on: work spread evenly over the MFMAs (WidePlan); loads that share M0, and bases that move by a tile, in place of some 40 scalar
 // instructions a tile; nothing behind the loop's branch.  32 heads x 16384, before and after: binary16 3375 -> 3257 us
 // (zeros: 2941 -> 2739), bfloat16, causal 1796 -> 1755 us.  And neighbouring MFMAs share an operand wherever they can: columns of K go

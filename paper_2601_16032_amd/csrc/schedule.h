@@ -52,8 +52,8 @@ SAW_HD int ceil_div_i(long long a, long long b) { return (int)((a + b - 1) / b);
 // filled: a last round with a few tiles costs this kernel a full round, while the workgroups of 128-row tiles run faster when
 // they have their compute unit to themselves.  The lines were drawn against the 32x32x16 kernels of both tile shapes.  As both
 // run now (16x16x32 here, default_shared_kernel there), by 256-row tiles per head and XCD, binary16 / bfloat16, 8 heads, change of
-// the rate in %: plain 32: -3 / +10, 36: -15 / -7, 40: -14 / -6, 48: -9 / 0, 56: +4 / +9, 64: +6 / +9, 72: -7 / -3, 80: -3 / +4,
-// 88: +5 / +11, 96: +5 / +7; causal 48: -9 / -5, 56: +1 / +6, 64: +3 / +10, 72: -1 / +1, 80: -1 / +2, 88: 0 / +2, 96: +1 / +4.
+// the rate in %: plain 32: +8 / +14, 36: -9 / -1, 40: -9 / 0, 48: -4 / +5, 56: +9 / +14, 64: +10 / +15, 72: -2 / +3, 80: +2 / +10,
+// 88: +10 / +14, 96: +10 / +16; causal 48: -4 / -1, 56: +7 / +10, 64: +10 / +14, 72: +4 / +7, 80: +4 / +7, 88: +5 / +9, 96: +6 / +10.
 SAW_HD int default_rows_per_wavefront(int heads, int N, int d, bool causal, bool bf16) {
     (void)bf16;
     if (d != 128) return 32;
@@ -84,9 +84,9 @@ SAW_HD int resident_slots(int d, int tile_q = kTileQ) {
 // d = 128: 128 (beyond, the 64-row workgroups, one per compute unit, no longer run all at once: up to 1.5x slower at 256);
 // d = 64: 384 plain, 512 causal, and beyond 128 only for N >= 2048: a scan of 16 tiles or fewer is too short for its halves to
 // pay for the merge (N = 512: 25 % slower).  They were drawn against the 32x32x16 kernel (gains of 3-10 % there, none at 768).
-// Time against 128-row tiles as they run now (default_shared_kernel), binary16 and bfloat16: d = 128, 128 tiles: -4 to -32 %;
-// d = 64, plain, 128 tiles: -29 to -40 %, 256: -7 to 0 %, 384: +8 to +11 %; causal, 128: -27 to -43 %, 256: -14 to -36 %, 384:
-// -6 to -16 %, 512: 0 to +4 %.
+// Time against 128-row tiles as they run now (default_shared_kernel), binary16 and bfloat16, 1 to 16 heads: d = 128, 128 tiles: -9 to -33 %;
+// d = 64, plain, 128 tiles: -28 to -42 %, 256: -11 to -2 %, 384: +1 to +12 %; causal, 128: -30 to -46 %, 256: -20 to -37 %, 384:
+// -15 to -27 %, 512: -11 to -3 %.
 // 1 = one scan per workgroup, 2 = two halves.
 SAW_HD int default_kv_halves(int heads, int N, int d, bool causal, bool bf16) {
     (void)bf16;
